@@ -204,7 +204,8 @@ int rexi_step_adjoint(rexi_plan *plan, const void *g1, void *g0, int S, int nste
  *   builds them (and allocates); otherwise REXI_EINVAL.  A step whose
  *   workspace exceeds 64 MiB returns REXI_EUNSUPPORTED (a schedule with fewer
  *   work items, rexi_plan_set_schedule, needs less; T256 with 4 states fits
- *   with about 2048 items).  Persistent schedules (a resident grid taking
+ *   with about 2048 items).  A pole-per-lane schedule whose workspace for a
+ *   full chip exceeds it is replaced by the default tiled schedule for S.  Persistent schedules (a resident grid taking
  *   items from a counter) return REXI_EUNSUPPORTED.
  *   The array is per GPU and lives until the process ends; every call on a
  *   GPU uses it, so calls that overlap on one GPU (on different streams or
@@ -246,12 +247,15 @@ int rexi_solve_variants(int per_term, int capacity, int *se, int *kind, int *sta
 /* The solve launches of one schedule candidate for S states (index as for
  * rexi_plan_set_schedule; -1 = the per-term schedule, which the first
  * rexi_step_per_term call with S builds): per launch the variant's (se,
- * kind, states_per_item), as rexi_solve_variants reports them. */
+ * kind, states_per_item), as rexi_solve_variants reports them.  kind 3 is the
+ * solve with one pole per lane and whole chains in a lane, which is not a
+ * tiling: se is then the elements of a block of its backward pass, and
+ * states_per_item the most states of an item. */
 int rexi_plan_schedule_classes(rexi_plan *plan, int S, int index, int capacity, int *se, int *kind,
                                int *states_per_item, int *count);
 
 /* The name of schedule candidate `index` for S states (-1 = the per-term
- * schedule, once built): tile policy, work-item count, "persistent_" for a
+ * schedule, once built): tile policy ("sweep" for one pole per lane), work-item count, "persistent_" for a
  * grid of resident workgroups pulling items from a counter, and "_shared" /
  * "_mixed" where states share each pole's factorisation in every / some of
  * its tile classes (no suffix: in none).  Written NUL-terminated into buf (host, capacity bytes, truncated

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <complex>
 #include <string>
 #include <vector>
@@ -104,6 +105,35 @@ struct Launch {
     int rot;   // states per work item
 };
 
+// The pole-per-lane solve (sweep_kernels.hip).  Chains are stored as pairs of a
+// vorticity and a divergence element, every chain padded to whole groups of two
+// pairs; kSweepBlock pairs form a block of its backward pass.
+constexpr int kSweepBlock = 6;
+constexpr int kSweepCst = 5;      // doubles of operator constants per pair
+constexpr int kSweepRec = 6;      // doubles of data per pair and state
+constexpr int kSweepPad = 2 * kSweepBlock * kSweepRec;  // doubles past the end of constants and data that a block may read
+constexpr int kSweepStates = 4;   // most states per work item
+constexpr int kSweepWaves = 4;    // waves of a workgroup
+constexpr int kSweepKind = 3;     // its kind in a schedule's classes (no moves between lanes)
+struct SweepItem {                // one chain, states [s0, s0 + nst), poles [k0, k1): a wave's work
+    int pair0, npair, s0, nst, k0, k1;
+    long long part_off;           // doubles; layout [nst][npair][kSweepRec]
+};
+struct SweepChain { int pair0, npair; };
+struct SweepTile { int tile, pos, nst; };               // of a state: its tile, place there, states of the tile
+struct SweepGroup { long long part_off; int nr, pad; };  // of a (chain, tile): its nr consecutive items' partials
+struct SweepTables {
+    bool built = false, usable = false;
+    int npairs = 0;
+    std::vector<SweepChain> chains;  // index 2 m + p
+    double* d_cst = nullptr;         // [pair][kSweepCst]
+    int2* d_idx = nullptr;           // [pair] spectral index of its vorticity and divergence (-1: a dummy)
+    double *d_fin[2] = {nullptr, nullptr}, *d_fout[2] = {nullptr, nullptr};  // [pair][3]
+    double2* d_poles[2] = {nullptr, nullptr};                                // [N][6]
+    SweepChain* d_chains = nullptr;
+    int* d_pair_chain = nullptr;
+};
+
 constexpr int kMaxLaunches = 8;  // solve launches per step (tile classes)
 
 // Device workspace of a step: the states in chain layout (double buffered
@@ -115,6 +145,9 @@ struct Workspace {
     double2* ch_phi[2];  // [S][nspec]
     double2* part;       // partial sums, the schedule's part_size entries
     int* counters;       // kMaxLaunches
+    double* rec[2];          // pole-per-lane solve: [S][pairs + 1][kSweepRec] and kSweepPad
+    double2* sweep_scratch;  // its block-boundary values, one slot per workgroup
+    int sweep_groups;        // slots there
 };
 
 struct Schedule {
@@ -131,6 +164,15 @@ struct Schedule {
     MInfo* d_minfo = nullptr;
     Item* d_items = nullptr;
     Group* d_groups = nullptr;
+    // pole-per-lane schedules (then the members above hold one launch for the
+    // queries and nothing else)
+    bool sweep = false;
+    int sweep_nst = 0, sweep_ntiles = 0;  // most states of an item, state tiles
+    long long sweep_stride = 0;           // scratch of one workgroup (double2)
+    std::vector<SweepItem> sweep_items;
+    SweepItem* d_sweep_items = nullptr;
+    SweepTile* d_sweep_tiles = nullptr;
+    SweepGroup* d_sweep_groups = nullptr;
     std::string name;
 };
 
@@ -163,6 +205,7 @@ struct rexi_plan {
     // schedules: candidates per S, chosen index per S; per-term form per S
     std::vector<std::vector<rexi::Schedule>> sched;  // [S] -> candidates
     std::vector<int> chosen;
+    std::vector<int> tiled;  // the default among the tiled schedules, [S]
     std::vector<rexi::Schedule> per_term;             // [S]
     long long acc_capacity = 0;
 
@@ -186,6 +229,11 @@ struct rexi_plan {
 
     // persistent launches: one work counter per solve launch
     int* d_counters = nullptr;
+    // pole-per-lane solve: tables, records of two buffers, scratch
+    rexi::SweepTables sweep;
+    double* d_rec[2] = {nullptr, nullptr};
+    double2* d_sweep_scratch = nullptr;
+    long long rec_capacity = 0, sweep_scratch_capacity = 0;
     // captured step graphs: key (S, adjoint, input buffer), valid for `graph_gen`
     struct StepGraph {
         const rexi::Schedule* sched;
@@ -233,6 +281,16 @@ hipError_t enqueue_finish(rexi_plan* pl, const Workspace& ws, int buf, void* u, 
                           const MInfo* d_layout, hipStream_t s);
 hipError_t enqueue_per_term_pole(rexi_plan* pl, const Workspace& ws, const Schedule& sc, int k, int buf, int S,
                                  hipStream_t s);
+hipError_t enqueue_reset_counters(int* c, int n, hipStream_t s);
+hipError_t enqueue_sweep_prep(rexi_plan* pl, const Workspace& ws, const void* u, int buf, int S, int adjoint,
+                              hipStream_t s);
+hipError_t enqueue_sweep_solve(rexi_plan* pl, const Workspace& ws, const Schedule& sc, int buf, int S, int adjoint,
+                               hipStream_t s);
+hipError_t enqueue_sweep_reduce(rexi_plan* pl, const Workspace& ws, const Schedule& sc, int buf_in, int buf_out,
+                                void* u_out, int S, int adjoint, hipStream_t s);
+// nsteps steps of a pole-per-lane schedule, launched one by one (plan.cpp).
+int run_sweep_steps(rexi_plan* pl, const Workspace& ws, const Schedule& sc, const void* u0, void* u1, int S,
+                    int nsteps, int adjoint, hipStream_t s);
 int sh_setup(rexi_plan* pl);
 void sh_release(rexi_plan* pl);
 int sh_run(rexi_plan* pl, const void* in, void* out, int B, bool forward, hipStream_t s);
@@ -243,9 +301,11 @@ int check_state_call(rexi_plan* pl, const void* in, const void* out, int S, int 
 int scratch_setup(void** ptr, size_t* bytes);
 
 // The plan's own workspace.
-inline Workspace plan_workspace(const rexi_plan* pl) {
+inline Workspace plan_workspace(const rexi_plan* pl, const Schedule& sc) {
+    const int groups = sc.sweep_stride > 0 ? (int)std::min<long long>(pl->sweep_scratch_capacity / (kSweepWaves * sc.sweep_stride), 1 << 20)
+                                           : 1 << 20;
     return Workspace{{pl->d_ch_var[0], pl->d_ch_var[1]}, {pl->d_ch_phi[0], pl->d_ch_phi[1]}, pl->d_part,
-                     pl->d_counters};
+                     pl->d_counters, {pl->d_rec[0], pl->d_rec[1]}, pl->d_sweep_scratch, groups};
 }
 // Record an event before / after a timed launch when timing is on.
 hipError_t timed_begin(rexi_plan* pl, int kind, hipStream_t s);

@@ -12,6 +12,7 @@
 // share that copy and race.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <mutex>
 #include <string>
 
@@ -64,10 +65,10 @@ extern "C" int rexi_step_noalloc(rexi_plan* plan, const void* u0, void* u1, int 
         return fail(REXI_EINVAL,
                     "no schedule for this S yet: one call of rexi_step, rexi_plan_set_schedule or "
                     "rexi_plan_autotune with S builds them (and allocates); call it before the no-allocation step");
-    const Schedule& sc = plan->sched[S][plan->chosen[S]];
+    const Schedule* psc = &plan->sched[S][plan->chosen[S]];
     // switched off: persistent schedules launched outside a graph (a first
     // run of this step over every T256 candidate went silent there)
-    if (sc.persistent)
+    if (psc->persistent)
         return fail(REXI_EUNSUPPORTED, "the no-allocation step does not run persistent schedules; select a "
                                        "one-workgroup-per-item schedule with rexi_plan_set_schedule");
     // carve the workspace out of the array, every piece 256-byte aligned
@@ -77,6 +78,39 @@ extern "C" int rexi_step_noalloc(rexi_plan* plan, const void* u0, void* u1, int 
         off += (bytes + 255) & ~size_t(255);
         return o;
     };
+    if (psc->sweep) {
+        // records, partial sums and counters, then the workgroups' slots
+        const Schedule& sc = *psc;
+        const size_t rec_bytes =
+            ((size_t)(plan->sweep.npairs + 1) * S * kSweepRec + kSweepPad) * sizeof(double);
+        const size_t o_r0 = take(rec_bytes), o_r1 = take(rec_bytes);
+        const size_t o_part = take((size_t)sc.part_size * 16), o_cnt = take(kMaxLaunches * sizeof(int));
+        const size_t slot = (size_t)sc.sweep_stride * 16 * kSweepWaves;
+        const long long wgs = ((long long)sc.sweep_items.size() + kSweepWaves - 1) / kSweepWaves;
+        const long long fit = off < plan->scratch_bytes ? (long long)((plan->scratch_bytes - off) / slot) : 0;
+        // fewer workgroups than fill the chip (two per CU) would run much slower
+        // than the tiled schedule, which then takes the call
+        if (fit >= std::min(wgs, 512LL)) {
+            char* base = static_cast<char*>(plan->scratch);
+            Workspace ws{};
+            ws.part = reinterpret_cast<double2*>(base + o_part);
+            ws.counters = reinterpret_cast<int*>(base + o_cnt);
+            ws.rec[0] = reinterpret_cast<double*>(base + o_r0);
+            ws.rec[1] = reinterpret_cast<double*>(base + o_r1);
+            ws.sweep_scratch = reinterpret_cast<double2*>(base + off);
+            ws.sweep_groups = (int)std::min(fit, 1LL << 20);
+            if (nsteps == 0) {
+                REXI_HIP(hipMemcpyAsync(u1, u0, (size_t)S * 3 * plan->nspec * 16, hipMemcpyDeviceToDevice,
+                                        (hipStream_t)stream));
+                return REXI_OK;
+            }
+            return run_sweep_steps(plan, ws, sc, u0, u1, S, nsteps, 0, (hipStream_t)stream);
+        }
+        if (plan->tiled[S] < 0) return fail(REXI_EUNSUPPORTED, "no schedule fits the no-allocation limit");
+        psc = &plan->sched[S][plan->tiled[S]];
+        off = 0;
+    }
+    const Schedule& sc = *psc;
     const size_t var_bytes = (size_t)S * (plan->nslots + 2) * 16, phi_bytes = (size_t)S * plan->nspec * 16;
     const size_t o_v0 = take(var_bytes), o_v1 = take(var_bytes), o_p0 = take(phi_bytes), o_p1 = take(phi_bytes);
     const size_t o_part = take((size_t)sc.part_size * 16), o_cnt = take(kMaxLaunches * sizeof(int));
@@ -87,7 +121,7 @@ extern "C" int rexi_step_noalloc(rexi_plan* plan, const void* u0, void* u1, int 
     char* base = static_cast<char*>(plan->scratch);
     const Workspace ws{{reinterpret_cast<double2*>(base + o_v0), reinterpret_cast<double2*>(base + o_v1)},
                        {reinterpret_cast<double2*>(base + o_p0), reinterpret_cast<double2*>(base + o_p1)},
-                       reinterpret_cast<double2*>(base + o_part), reinterpret_cast<int*>(base + o_cnt)};
+                       reinterpret_cast<double2*>(base + o_part), reinterpret_cast<int*>(base + o_cnt), {nullptr, nullptr}, nullptr, 0};
     hipStream_t s = (hipStream_t)stream;
     if (nsteps == 0) {
         REXI_HIP(hipMemcpyAsync(u1, u0, (size_t)S * 3 * plan->nspec * 16, hipMemcpyDeviceToDevice, s));

@@ -282,7 +282,168 @@ int build_schedule(rexi_plan* pl, int S, int policy, long long target_items, boo
     return rc;
 }
 
+// Tables of the pole-per-lane solve (see sweep_kernels.hip), built with the
+// first schedules.  Not usable without a Coriolis force (the scaling divides by
+// the couplings) or where the scaled constants leave a comfortable FP64 range.
+int build_sweep_tables(rexi_plan* pl) {
+    SweepTables& t = pl->sweep;
+    if (t.built) return REXI_OK;
+    const int T = pl->T, N = pl->N;
+    const long double a = pl->prm.radius, Om = pl->prm.omega, pb = pl->phibar, dt = pl->prm.dt;
+    const double kDummy = 1e100;
+    std::vector<double> cst, fin[2], fout[2];
+    std::vector<int2> idx;
+    std::vector<int> chain_of;
+    bool ok = true;
+    auto in_range = [](long double x) { return fabsl(x) > 1e-40L && fabsl(x) < 1e40L; };
+    for (int m = 0; m <= T; ++m)
+        for (int p = 0; p < 2; ++p) {
+            const int n0 = std::max(m, 1), L = T + 1 - n0, pre = (n0 + p) & 1;
+            const int np = 2 * ((pre + L + 3) / 4);
+            t.chains.push_back({(int)idx.size(), np});
+            const size_t q0 = idx.size();
+            cst.resize((q0 + np) * kSweepCst, 0.0);
+            idx.resize(q0 + np, make_int2(-1, -1));
+            chain_of.resize(q0 + np, 2 * m + p);
+            for (int d = 0; d < 2; ++d) {
+                fin[d].resize((q0 + np) * 3, 0.0);
+                fout[d].resize((q0 + np) * 3, 0.0);
+            }
+            for (int q = 0; q < np; ++q) cst[(q0 + q) * kSweepCst] = cst[(q0 + q) * kSweepCst + 2] = kDummy;
+            long double D = 1.0L;
+            for (int j = 0; j < L; ++j) {
+                const int n = n0 + j;
+                const long double nn = (long double)n * (n + 1);
+                auto couple = [&](int k) { return 2 * Om * dt * eps_nm(k, m) * sqrtl((long double)k * k - 1) / k; };
+                if (j == 0 && L > 1) D = 1.0L / sqrtl(fabsl(couple(n0 + 1)));
+                if (j > 0) D = 1.0L / (couple(n) * D);
+                const long double om = sqrtl(pb * nn) / a * dt, s = a * sqrtl(pb / nn), th = 2 * Om * m / nn * dt;
+                ok = ok && in_range(D) && in_range(om) && in_range(s);
+                const size_t q = q0 + (pre + j) / 2;
+                double* c = &cst[q * kSweepCst];
+                const int i = (int)(spec_offset(T, m) + (n - m));
+                const bool div = ((pre + j) & 1) != 0;
+                if (div) {
+                    idx[q].y = i;
+                    c[2] = (double)(D * D);
+                    c[3] = (double)(D * D * th);
+                    c[4] = (double)(D * D * om * om);
+                } else {
+                    idx[q].x = i;
+                    c[0] = (double)(D * D);
+                    c[1] = (double)(D * D * th);
+                }
+                for (int d = 0; d < 2; ++d) {
+                    fin[d][3 * q + div] = (double)(d ? D / s : D * s);
+                    fout[d][3 * q + div] = (double)(d ? D * s : D / s);
+                    if (div) {
+                        fin[d][3 * q + 2] = (double)(D * om);
+                        fout[d][3 * q + 2] = (double)(1 / (D * om));
+                    }
+                }
+            }
+        }
+    t.npairs = (int)idx.size();
+    cst.resize(cst.size() + kSweepPad, 0.0);
+    t.usable = ok;
+    t.built = true;
+    if (!ok) return REXI_OK;
+    int rc = upload(&t.d_cst, cst);
+    if (!rc) rc = upload(&t.d_idx, idx);
+    if (!rc) rc = upload(&t.d_chains, t.chains);
+    if (!rc) rc = upload(&t.d_pair_chain, chain_of);
+    for (int d = 0; d < 2 && !rc; ++d) {
+        rc = upload(&t.d_fin[d], fin[d]);
+        if (!rc) rc = upload(&t.d_fout[d], fout[d]);
+        std::vector<double2> pd;
+        pd.reserve(6 * (size_t)N);
+        auto put = [&](const cld& z) { pd.push_back(make_double2((double)z.real(), (double)z.imag())); };
+        for (int k = 0; k < N; ++k) {
+            const std::complex<double> bp = pl->poles.beta_plus[k], bm = std::conj(pl->poles.beta_minus[N - 1 - k]);
+            const cld al(pl->poles.alpha[k]), wx(d ? bm : bp), wy(d ? bp : bm);
+            const cld ai = cld(1) / al, mi = cld(0, -1) * ai;
+            for (const cld& z : {al, ai, wx + wy, wx - wy, mi * (wx + wy), mi * (wx - wy)}) put(z);
+        }
+        if (!rc) rc = upload(&t.d_poles[d], pd);
+    }
+    return rc;
+}
+
+void free_sweep_tables(SweepTables& t) {
+    dev_free(t.d_cst);
+    dev_free(t.d_idx);
+    dev_free(t.d_chains);
+    dev_free(t.d_pair_chain);
+    for (int d = 0; d < 2; ++d) {
+        dev_free(t.d_fin[d]);
+        dev_free(t.d_fout[d]);
+        dev_free(t.d_poles[d]);
+    }
+}
+
+// A pole-per-lane schedule: the states in tiles of up to kSweepStates, split
+// evenly; items are (chain, tile, range of 64-pole batches), as many per
+// (chain, tile) as its share of target_items, longest first.
+int build_sweep_schedule(rexi_plan* pl, int S, long long target_items, Schedule& out) {
+    const SweepTables& t = pl->sweep;
+    out = Schedule();
+    out.sweep = true;
+    out.S = S;
+    const int nt = (S + kSweepStates - 1) / kSweepStates, nb = (pl->N + 63) / 64;
+    out.sweep_ntiles = nt;
+    std::vector<SweepTile> tiles(S);
+    std::vector<int> s0(nt + 1);
+    for (int k = 0; k <= nt; ++k) s0[k] = S * k / nt;
+    for (int k = 0; k < nt; ++k)
+        for (int s = s0[k]; s < s0[k + 1]; ++s) tiles[s] = {k, s - s0[k], s0[k + 1] - s0[k]};
+    // relative cost of a pair's batch: pivots of both passes, then each state
+    auto cost = [&](int npair, int nst) { return (npair + 1) * (30.0 + 50.0 * nst); };
+    double total = 0;
+    for (const SweepChain& c : t.chains)
+        for (int k = 0; k < nt; ++k) total += cost(c.npair, s0[k + 1] - s0[k]) * nb;
+    const double target = total / (double)std::max<long long>(1, target_items);
+    std::vector<SweepGroup> groups(t.chains.size() * nt);
+    std::vector<std::pair<double, SweepItem>> items;
+    long long off = 0;
+    int npmax = 0;
+    for (size_t ch = 0; ch < t.chains.size(); ++ch) {
+        const SweepChain& c = t.chains[ch];
+        npmax = std::max(npmax, c.npair);
+        for (int k = 0; k < nt; ++k) {
+            const int nst = s0[k + 1] - s0[k];
+            out.sweep_nst = std::max(out.sweep_nst, nst);
+            const double u = cost(c.npair, nst);
+            const int per = std::max(1, std::min((int)std::lround(target / u), nb));  // batches per item
+            SweepGroup& gr = groups[ch * nt + k];
+            gr = {off, 0, 0};
+            for (int b = 0; b < nb; b += per) {
+                const int b1 = std::min(nb, b + per);
+                items.push_back({u * (b1 - b), {c.pair0, c.npair, s0[k], nst, 64 * b, std::min(pl->N, 64 * b1), off}});
+                off += (long long)nst * c.npair * kSweepRec;
+                ++gr.nr;
+            }
+        }
+    }
+    std::stable_sort(items.begin(), items.end(), [](const std::pair<double, SweepItem>& x,
+                                                    const std::pair<double, SweepItem>& y) { return x.first > y.first; });
+    for (const auto& x : items) out.sweep_items.push_back(x.second);
+    out.part_size = (off + 1) / 2;
+    out.sweep_stride = (long long)std::max((npmax + kSweepBlock - 1) / kSweepBlock - 1, 1) * (1 + 2 * out.sweep_nst) * 64;
+    out.rot_max = out.sweep_nst;
+    out.launches.push_back({2 * kSweepBlock, kSweepKind, 0, (int)items.size(), 1, out.sweep_nst});
+    char buf[96];
+    std::snprintf(buf, sizeof buf, "sweep_items%lld%s", (long long)items.size(), out.sweep_nst > 1 ? "_shared" : "");
+    out.name = buf;
+    int rc = upload(&out.d_sweep_items, out.sweep_items);
+    if (!rc) rc = upload(&out.d_sweep_tiles, tiles);
+    if (!rc) rc = upload(&out.d_sweep_groups, groups);
+    return rc;
+}
+
 void free_schedule(Schedule& s) {
+    dev_free(s.d_sweep_items);
+    dev_free(s.d_sweep_tiles);
+    dev_free(s.d_sweep_groups);
     dev_free(s.d_minfo);
     dev_free(s.d_items);
     dev_free(s.d_groups);
@@ -314,11 +475,42 @@ int ensure_part(rexi_plan* pl, long long n) {
     return REXI_OK;
 }
 
+// Records of S states and the scratch of a pole-per-lane schedule: one slot per
+// workgroup, at most kSweepScratch bytes of them (workgroups beyond take several
+// items in turn).
+constexpr long long kSweepScratch = 1LL << 30;
+int ensure_sweep(rexi_plan* pl, const Schedule& sc) {
+    const long long rec = (long long)(pl->sweep.npairs + 1) * sc.S * kSweepRec + kSweepPad;
+    if (rec > pl->rec_capacity) {
+        drop_graphs(pl);
+        pl->rec_capacity = 0;
+        for (int d = 0; d < 2; ++d) {
+            dev_free(pl->d_rec[d]);
+            int rc = dev_alloc(&pl->d_rec[d], (size_t)rec);
+            if (rc) return rc;
+        }
+        pl->rec_capacity = rec;
+    }
+    const long long most = std::max(1LL, kSweepScratch / 16 / kSweepWaves / std::max(1LL, sc.sweep_stride));
+    const long long wgs = ((long long)sc.sweep_items.size() + kSweepWaves - 1) / kSweepWaves;
+    const long long need = std::min(wgs, most) * kSweepWaves * sc.sweep_stride;
+    if (need > pl->sweep_scratch_capacity) {
+        drop_graphs(pl);
+        dev_free(pl->d_sweep_scratch);
+        pl->sweep_scratch_capacity = 0;
+        int rc = dev_alloc(&pl->d_sweep_scratch, (size_t)need);
+        if (rc) return rc;
+        pl->sweep_scratch_capacity = need;
+    }
+    return REXI_OK;
+}
+
 // Candidate schedules for S states (built on first use).
 int schedules_for(rexi_plan* pl, int S, std::vector<Schedule>** out) {
     if ((int)pl->sched.size() <= S) {
         pl->sched.resize(S + 1);
         pl->chosen.resize(S + 1, -1);
+        pl->tiled.resize(S + 1, -1);
     }
     std::vector<Schedule>& c = pl->sched[S];
     if (c.empty()) {
@@ -353,6 +545,27 @@ int schedules_for(rexi_plan* pl, int S, std::vector<Schedule>** out) {
                     if (!persistent && policy == 5 && t == 2816 && rot == rots.back()) dflt = (int)c.size();
                     c.push_back(sc);
                 }
+        pl->tiled[S] = dflt;
+        int rc = build_sweep_tables(pl);
+        if (rc) return rc;
+        // one pole per lane wherever the operator allows it: at every size and
+        // state count measured (T63 to T301, 1 to 8 states) it beats the tiled
+        // schedules (see sweep_kernels.hip).  ~8192 items (four per wave slot of
+        // the chip) against ~4096 at T256 with four states: 1527 / 1570 us per
+        // step; within 1% of each other elsewhere.
+        for (int persistent = 0; pl->sweep.usable && persistent < 2; ++persistent)
+            for (long long t : {4096LL, 8192LL}) {
+                Schedule sc;
+                rc = build_sweep_schedule(pl, S, t, sc);
+                if (rc) { free_schedule(sc); return rc; }
+                sc.persistent = persistent != 0;
+                if (sc.persistent) sc.name = "persistent_" + sc.name;
+                rc = ensure_part(pl, sc.part_size);
+                if (!rc) rc = ensure_sweep(pl, sc);
+                if (rc) { free_schedule(sc); return rc; }
+                if (!persistent && t == 8192) dflt = (int)c.size();
+                c.push_back(sc);
+            }
         if (c.empty()) return fail(REXI_EUNSUPPORTED, "no schedule fits this truncation");
         pl->chosen[S] = dflt >= 0 ? dflt : 0;
     }
@@ -379,7 +592,7 @@ int step_graph(rexi_plan* pl, const Schedule& sc, int S, int adjoint, int buf, h
         }
     hipGraph_t graph = nullptr;
     REXI_HIP(hipStreamBeginCapture(pl->cap_stream, hipStreamCaptureModeThreadLocal));
-    const Workspace ws = plan_workspace(pl);
+    const Workspace ws = plan_workspace(pl, sc);
     hipError_t e1 = enqueue_solve(pl, ws, sc, buf, S, adjoint, pl->cap_stream);
     hipError_t e2 = hipSuccess;
     if (e1 == hipSuccess)
@@ -404,6 +617,26 @@ int step_graph(rexi_plan* pl, const Schedule& sc, int S, int adjoint, int buf, h
     return REXI_OK;
 }
 
+}  // namespace
+
+int run_sweep_steps(rexi_plan* pl, const Workspace& ws, const Schedule& sc, const void* u0, void* u1, int S,
+                    int nsteps, int adjoint, hipStream_t s) {
+    REXI_HIP(enqueue_sweep_prep(pl, ws, u0, 0, S, adjoint, s));
+    int cur = 0;
+    for (int k = 0; k < nsteps; ++k) {
+        const bool last = (k == nsteps - 1);
+        REXI_HIP(timed_begin(pl, REXI_KERNEL_SOLVE, s));
+        REXI_HIP(enqueue_sweep_solve(pl, ws, sc, cur, S, adjoint, s));
+        if (!pl->use_graphs) REXI_HIP(timed_end(pl, REXI_KERNEL_SOLVE, s));
+        REXI_HIP(enqueue_sweep_reduce(pl, ws, sc, cur, cur ^ 1, last ? u1 : nullptr, S, adjoint, s));
+        if (pl->use_graphs) REXI_HIP(timed_end(pl, REXI_KERNEL_SOLVE, s));
+        cur ^= 1;
+    }
+    return REXI_OK;
+}
+
+namespace {
+
 int run_steps(rexi_plan* pl, const Schedule& sc, const void* u0, void* u1, int S, int nsteps, int adjoint,
               hipStream_t s) {
     const size_t bytes = (size_t)S * 3 * pl->nspec * 16;
@@ -411,7 +644,8 @@ int run_steps(rexi_plan* pl, const Schedule& sc, const void* u0, void* u1, int S
         REXI_HIP(hipMemcpyAsync(u1, u0, bytes, hipMemcpyDeviceToDevice, s));
         return REXI_OK;
     }
-    const Workspace ws = plan_workspace(pl);
+    const Workspace ws = plan_workspace(pl, sc);
+    if (sc.sweep) return run_sweep_steps(pl, ws, sc, u0, u1, S, nsteps, adjoint, s);
     REXI_HIP(enqueue_prep(pl, ws, u0, 0, S, adjoint, pl->sched_layout, s));
     int cur = 0;
     if (pl->use_graphs) {
@@ -532,6 +766,10 @@ void release(rexi_plan* pl) {
     dev_free(pl->d_fs_work);
     dev_free(pl->sched_layout);
     dev_free(pl->d_slot_m);
+    free_sweep_tables(pl->sweep);
+    dev_free(pl->d_rec[0]);
+    dev_free(pl->d_rec[1]);
+    dev_free(pl->d_sweep_scratch);
     sh_release(pl);
 }
 
@@ -790,7 +1028,7 @@ int rexi_step_per_term(rexi_plan* plan, const void* u0, void* u1, int S, void* s
             plan->acc_capacity = sc.part_size;
         }
         hipStream_t s = (hipStream_t)stream;
-        const Workspace ws = plan_workspace(plan);
+        const Workspace ws = plan_workspace(plan, sc);
         REXI_HIP(enqueue_prep(plan, ws, u0, 0, S, 0, plan->sched_layout, s));
         REXI_HIP(enqueue_zero(plan->d_acc, sc.part_size, s));
         for (int k = 0; k < plan->N; ++k) REXI_HIP(enqueue_per_term_pole(plan, ws, sc, k, 0, S, s));

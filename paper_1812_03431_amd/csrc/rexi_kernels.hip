@@ -1155,10 +1155,7 @@ hipError_t enqueue_solve(rexi_plan* pl, const Workspace& ws, const Schedule& sc,
     a.var_stride = pl->nslots + 2;
     a.nspec = pl->nspec;
     if (sc.persistent) {
-        const int n = (int)sc.launches.size();
-        if (n > kMaxLaunches) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k_reset_counters, dim3(1), dim3(64), 0, s, ws.counters, n);
-        hipError_t e = hipGetLastError();
+        hipError_t e = enqueue_reset_counters(ws.counters, (int)sc.launches.size(), s);
         if (e != hipSuccess) return e;
     }
     const int nl = (int)sc.launches.size();
@@ -1227,6 +1224,12 @@ hipError_t enqueue_fsphere_step(rexi_plan* pl, const void* in, void* out, int S,
     hipLaunchKernelGGL(k_fsphere_step, dim3((unsigned)((n + bs - 1) / bs)), dim3(bs), 0, s, (const double2*)in,
                        (double2*)out, pl->d_fs_poles, pl->N, pl->d_om, pl->d_sc, pl->d_idx_n, pl->f0dt, S,
                        pl->nspec, adjoint);
+    return hipGetLastError();
+}
+
+hipError_t enqueue_reset_counters(int* c, int n, hipStream_t s) {
+    if (n > kMaxLaunches) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_reset_counters, dim3(1), dim3(64), 0, s, c, n);
     return hipGetLastError();
 }
 

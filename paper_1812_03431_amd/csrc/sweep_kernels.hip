@@ -1,0 +1,708 @@
+// The fused T-REXI step with one pole per lane (gfx950).
+//
+// Same sum over poles as rexi_kernels.hip, for problems with enough (pole
+// batch, chain) pairs to fill the chip: a lane solves a whole tridiagonal
+// chain for its pole by plain elimination (no partitioning, no cross-lane
+// reduction of interface unknowns), 64 poles per wave.
+//
+// Real form.  With zeta = i zeta', Phi = i Phi' the shifted operator of a chain
+// is alpha + i dt H with H real symmetric: off-diagonals i c_t, diagonal
+// alpha + i th (vorticity) and alpha + i th + om^2/alpha (divergence, Phi'
+// eliminated: Phi' = (r_Phi' - i om delta)/alpha).  A complex right-hand side
+// splits into two real ones (a, b), and the minus-sign solves are conjugates of
+// the plus-sign solves of real data at the conjugate pole, which is again in
+// the list.  With X_a, X_b the solutions at pole k and wx, wy the weight pair
+// of the pole (see rexi_kernels.hip), W1 = wx + wy, W2 = wx - wy:
+//   Re y = sum_k Re(W1 X_a) - Im(W2 X_b),  Im y = sum_k Im(W2 X_a) + Re(W1 X_b),
+// and the same with V = -i W / alpha for the Phi' sums.
+//
+// Scaling.  x = D x~ with D_t D_{t+1} = 1/c_{t+1} makes every off-diagonal i:
+//   pivots   b_t = D2 alpha + i th' (+ om2' / alpha) + q_{t-1},  q_t = 1/b_t
+//   forward  F_t = g_t - i q_{t-1} F_{t-1}
+//   backward x_t = q_t (F_t - i x_{t+1})
+// Chains alternate vorticity and divergence; a chain that would start with a
+// divergence gets a dummy vorticity in front, and its end is padded to whole
+// groups of two pairs, with D2 = kDummy: a pivot so large that the dummy's
+// contribution to its neighbour rounds away.
+//
+// Uniform data.  All lanes of a wave are at the same chain position, so the
+// operator constants and the right-hand sides are scalar loads and every FMA
+// takes them from scalar registers.
+//
+// Memory.  Elimination needs every forward value again in the backward sweep,
+// 16 bytes per right-hand side, element and pole: too much for registers, and
+// tens of GB for HBM.  So the chain is cut into blocks of kBlk pairs: pass 1 runs
+// forward and keeps only the pivot and the forward values at the block
+// boundaries (global scratch, 16 (1 + 2 states) bytes per lane and block), pass 2
+// takes the blocks in reverse, repeats the forward sweep of one block into
+// registers and substitutes back.  Pass 1 needs the block-end values alone, a sum
+// of products of the (real, uniform) right-hand sides with per-pole coefficients
+// that all states share.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "internal.hpp"
+
+namespace rexi {
+namespace {
+
+struct cd {
+    double r, i;
+};
+
+__device__ __forceinline__ cd mk(double r, double i) { return cd{r, i}; }
+__device__ __forceinline__ cd cmul(cd a, cd b) {
+    return cd{fma(a.r, b.r, -a.i * b.i), fma(a.r, b.i, a.i * b.r)};
+}
+// 1 / a: v_rcp_f64 of |a|^2 refined by one third-order step
+__device__ __forceinline__ cd crcp(cd a) {
+    const double d = fma(a.r, a.r, a.i * a.i);
+    const double r0 = __builtin_amdgcn_rcp(d);
+    const double e = fma(-d, r0, 1.0);
+    const double r = fma(r0, fma(e, e, e), r0);
+    return cd{a.r * r, -a.i * r};
+}
+// -i q v
+__device__ __forceinline__ cd miqv(cd q, cd v) { return cd{fma(q.i, v.r, q.r * v.i), fma(q.i, v.i, -q.r * v.r)}; }
+
+// wave-uniform read-only data: scalar loads
+typedef const double __attribute__((address_space(4)))* sptr;
+__device__ __forceinline__ sptr uniform(const double* p) { return (sptr)(unsigned long long)p; }
+
+// A scalar value of its own: without this the compiler keeps whole groups of
+// kernel arguments together in scalar registers and spills them together.
+template <class T>
+__device__ __forceinline__ T detach(T x) {
+    asm volatile("" : "+s"(x));
+    return x;
+}
+// a b + s, s scalar: the compiler would copy s to vector registers first (to use
+// the two-address form)
+__device__ __forceinline__ double fma_s(double a, double b, double s) {
+    double r;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(s));
+    return r;
+}
+
+struct SweepPole {
+    double2 al, ai, w1, w2, v1, v2;
+};
+
+struct SweepArgs {
+    const SweepItem* items;
+    const double* cst;       // [pair][kSweepCst]: D2, th' of the vorticity; D2, th', om2' of the divergence
+    const double* rec;       // [S][npairs + 1][kSweepRec]: a, b of the vorticity; a, b, psi_a, psi_b of the divergence
+    const SweepPole* poles;
+    unsigned state_stride;  // doubles between two states' data
+    double* part;            // [item][state][pair][kSweepRec]
+    double2* scratch;        // per wave: [max(block - 1, 1)][1 + 2 states][64]
+    long long scratch_stride;
+    int nitems, nst;         // nst: most states of an item
+};
+
+constexpr int kGroup = 2;                      // pairs per reduction group
+constexpr int kBlk = kSweepBlock;              // pairs per block
+constexpr int kVals = kGroup * kSweepRec;      // sums per reduction group
+
+// Pivots of one pair after the pivot qp of the element before it.
+__device__ __forceinline__ void pivots(const double* c, cd al, cd ai, cd qp, cd& qz, cd& qd) {
+    qz = crcp(mk(fma(c[0], al.r, qp.r), fma(c[0], al.i, qp.i + c[1])));
+    qd = crcp(mk(fma(c[2], al.r, fma(c[4], ai.r, qz.r)), fma(c[2], al.i, fma(c[4], ai.i, qz.i + c[3]))));
+}
+
+__device__ __forceinline__ double dpp_quad_xor(double x, const int ctrl_is_2) {
+    const long long v = __double_as_longlong(x);
+    int lo, hi;
+    if (ctrl_is_2) {
+        lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)v, 0x4E, 0xF, 0xF, true);  // quad_perm [2,3,0,1]
+        hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), 0x4E, 0xF, 0xF, true);
+    } else {
+        lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)v, 0xB1, 0xF, 0xF, true);  // quad_perm [1,0,3,2]
+        hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), 0xB1, 0xF, 0xF, true);
+    }
+    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+
+// weighted sums of one element (see the top): 2 values
+__device__ __forceinline__ void weigh(cd w1, cd w2, cd xa, cd xb, double& re, double& im) {
+    re = fma(w1.r, xa.r, fma(-w1.i, xa.i, fma(-w2.r, xb.i, -w2.i * xb.r)));
+    im = fma(w2.r, xa.i, fma(w2.i, xa.r, fma(w1.r, xb.r, -w1.i * xb.i)));
+}
+
+// orders LDS accesses of the wave's lanes (the hardware keeps a wave's LDS
+// operations in order; this keeps the compiler from moving them)
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Wave-uniform loads of N doubles into scalar registers, kept where the source
+// has them (the compiler would sink them to their first use and wait there).
+template <int N>
+__device__ __forceinline__ void fetch(double (&h)[N], sptr p) {
+#pragma unroll
+    for (int k = 0; k < N; ++k) h[k] = p[k];
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// Brings the data of a block's states and the constants of the block after it
+// into the scalar cache: one load per 64-byte line, waited for only at warm_wait,
+// after work that needs no LDS or scalar data.
+constexpr int kLines = (kBlk * kSweepRec * 8 + 63) / 64 + 1, kCstLines = (kBlk * kSweepCst * 8 + 63) / 64 + 1;
+struct Warm {
+    int x[kSweepStates][kLines], c[kCstLines];
+};
+__device__ __forceinline__ void warm(Warm& w, sptr p, unsigned sstep, int nst, sptr cst) {
+    typedef const int __attribute__((address_space(4)))* iptr;
+#pragma unroll
+    for (int s = 0; s < kSweepStates; ++s) {
+        const iptr q = (iptr)(p + (s < nst ? s : 0) * sstep);
+#pragma unroll
+        for (int k = 0; k < kLines; ++k) w.x[s][k] = q[k + 1 < kLines ? 16 * k : 2 * kBlk * kSweepRec - 1];
+    }
+#pragma unroll
+    for (int k = 0; k < kCstLines; ++k) w.c[k] = ((iptr)cst)[k + 1 < kCstLines ? 16 * k : 2 * kBlk * kSweepCst - 1];
+    __builtin_amdgcn_sched_barrier(0);
+}
+__device__ __forceinline__ void warm_wait(const Warm& w) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < kSweepStates; ++s)
+#pragma unroll
+        for (int k = 0; k < kLines; ++k) asm volatile("" ::"s"(w.x[s][k]));
+#pragma unroll
+    for (int k = 0; k < kCstLines; ++k) asm volatile("" ::"s"(w.c[k]));
+}
+
+constexpr int kPitch = 68;                  // row pitch of the reduction buffer: 4 mod 32 banks of 8 bytes
+constexpr int kRedDoubles = kVals * kPitch;
+constexpr int kPart = kGroup * kSweepRec;   // data of a group of pairs and one state
+
+// Sums over the wave's lanes.  A reduction group leaves kVals values per lane
+// in LDS rows; lane 4 v + r then reads every fourth term of row v from r (lanes
+// past the rows do what lanes 0..3 do).  The reads are issued at once and added
+// only after the next group's work, so that their latency is not waited for.
+struct Pending {
+    double term[16];
+};
+__device__ __forceinline__ void pend_read(Pending& P, const double* src) {
+    wave_sync();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) P.term[i] = src[4 * i];
+    __builtin_amdgcn_sched_barrier(0);
+}
+// the sum of row rv, in all four lanes of the row
+__device__ __forceinline__ double pend_add(const Pending& P) {
+    double s[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        s[i] = (P.term[4 * i] + P.term[4 * i + 1]) + (P.term[4 * i + 2] + P.term[4 * i + 3]);
+    double sum = (s[0] + s[1]) + (s[2] + s[3]);
+    sum += dpp_quad_xor(sum, 0);
+    sum += dpp_quad_xor(sum, 1);
+    return sum;
+}
+
+// What the backward pass of one batch keeps.
+struct Back {
+    cd al, ai, w1, w2, v1, v2;
+    const double* rsrc;   // this lane's terms in the reduction buffer
+    double* red;          // this lane's column there
+    double2* car;         // [state][2][64]: x of the element above the block, this lane
+    int rp;               // this lane stores the sums of group rp (of group 0 for rp = 3)
+    bool add;             // the sums are added to those of earlier batches
+    int nst;
+    unsigned sstep, pstep;  // between states: data, partial sums
+};
+
+// What a block needs first of the boundary values before it (this lane's),
+// loaded one block ahead.
+struct Boundary {
+    double2 q, fa, fb;
+};
+__device__ __forceinline__ Boundary load_boundary(const double2* ckpt) { return Boundary{ckpt[0], ckpt[64], ckpt[128]}; }
+
+// One block of the backward pass (pass 2) for all states of an item: the block's
+// pivots from the one before it (qin), then per state the forward values into
+// registers, the back substitution, and the weighted sums over the wave's poles.
+// FULL: the block has all kBlk pairs, else ng groups of kGroup pairs.  head: the
+// chain's first block (no boundary values before it).  h0 holds the first state's
+// data of the block's first group on entry and those of rec_next on return (a
+// whole block's do not fit in the scalar registers beside the rest).
+//
+// All global loads and stores are unconditional and issued at the start of a
+// state (the store of a state's sums: after the next state's forward sweep), so
+// that every wait for one finds it, and what was issued before it, a state's work
+// old; where there is nothing to load, the address is any valid one and the value
+// is dropped.
+template <bool FULL>
+__device__ __forceinline__ void back_block(const Back& B, int ng, bool head, sptr cst, sptr cst_next, sptr rec,
+                                           sptr rec_next, const double2* ckpt, const double2* ckpt_next, Boundary& bd,
+                                           double* out, double (&h0)[kPart]) {
+    constexpr int kGroups = kBlk / kGroup;
+    const cd ai = B.ai;
+    cd qin = cd{bd.q.x, bd.q.y};
+    if (head) qin = mk(0, 0);
+    double2 fan = bd.fa, fbn = bd.fb;
+    bd = load_boundary(ckpt_next);
+    cd q[2 * kBlk];
+    Warm wm;
+    {
+        double c[kBlk * kSweepCst];
+        fetch(c, cst);
+        warm(wm, rec, B.sstep, B.nst, cst_next);
+        cd qq = qin;
+#pragma unroll
+        for (int g = 0; g < kGroups; ++g)
+            if (FULL || g < ng) {
+#pragma unroll
+                for (int t = g * kGroup; t < (g + 1) * kGroup; ++t) {
+                    pivots(c + t * kSweepCst, B.al, ai, qq, q[2 * t], q[2 * t + 1]);
+                    qq = q[2 * t + 1];
+                }
+            }
+    }
+    warm_wait(wm);
+    Pending P;
+    double2* cr = B.car;
+    double sum0 = 0.0, sum1 = 0.0, old = 0.0;   // this lane's group's sum (groups 0 and others), what it is added to
+    double* prev = out;                         // the previous state's place
+#pragma unroll 1
+    for (int s = 0; s < B.nst; ++s, cr += 128) {
+        cd fa = cd{fan.x, fan.y}, fb = cd{fbn.x, fbn.y};
+        if (head) fa = fb = mk(0, 0);
+        const double before = old;
+        old = *out;
+        {
+            const double2* n = ckpt + (s + 1 < B.nst ? 3 + 2 * s : 1) * 64;
+            fan = n[0];
+            fbn = n[64];
+        }
+        cd xa = cd{cr[0].x, cr[0].y}, xb = cd{cr[64].x, cr[64].y};
+        cd Fa[2 * kBlk], Fb[2 * kBlk];
+        const sptr rs = rec + s * B.sstep;
+        double hg[kGroups][kPart];
+#pragma unroll
+        for (int k = 0; k < kPart; ++k) hg[0][k] = h0[k];
+        fetch(hg[1], rs + kPart);
+#pragma unroll
+        for (int g = 0; g < kGroups; ++g) {
+            if (FULL || g < ng) {
+#pragma unroll
+                for (int t = g * kGroup; t < (g + 1) * kGroup; ++t) {
+                    const double* rt = hg[g] + (t - g * kGroup) * kSweepRec;
+                    const cd qz = t > 0 ? q[2 * t - 1] : qin, qd = q[2 * t];
+                    fa = mk(fma(qz.i, fa.r, fma_s(qz.r, fa.i, rt[0])), fma(qz.i, fa.i, -qz.r * fa.r));
+                    fb = mk(fma(qz.i, fb.r, fma_s(qz.r, fb.i, rt[1])), fma(qz.i, fb.i, -qz.r * fb.r));
+                    Fa[2 * t] = fa;
+                    Fb[2 * t] = fb;
+                    fa = mk(fma(qd.i, fa.r, fma(ai.i, rt[4], fma_s(qd.r, fa.i, rt[2]))),
+                            fma(qd.i, fa.i, fma(-qd.r, fa.r, -ai.r * rt[4])));
+                    fb = mk(fma(qd.i, fb.r, fma(ai.i, rt[5], fma_s(qd.r, fb.i, rt[3]))),
+                            fma(qd.i, fb.i, fma(-qd.r, fb.r, -ai.r * rt[5])));
+                    Fa[2 * t + 1] = fa;
+                    Fb[2 * t + 1] = fb;
+                }
+            }
+            if (g + 2 < kGroups) fetch(hg[g + 2], rs + (g + 2) * kPart);
+        }
+        // The previous state's last group before the scalar loads: while scalar
+        // loads are in flight, any wait for LDS waits for them too.
+        if (FULL && s > 0) {
+            const double v = pend_add(P);
+            *prev = (B.rp == 0 || B.rp == 3 ? v : sum1) + (B.add ? before : 0.0);
+        }
+        fetch(h0, s + 1 < B.nst ? rec + (s + 1) * B.sstep : rec_next);
+#pragma unroll
+        for (int g = kGroups - 1; g >= 0; --g)
+            if (FULL || g < ng) {
+#pragma unroll
+                for (int t = (g + 1) * kGroup - 1; t >= g * kGroup; --t) {
+                    double* v = B.red + (t - g * kGroup) * kSweepRec * kPitch;
+                    double re, im;
+                    cd qq = q[2 * t + 1];
+                    xa = cmul(qq, mk(Fa[2 * t + 1].r + xa.i, Fa[2 * t + 1].i - xa.r));
+                    xb = cmul(qq, mk(Fb[2 * t + 1].r + xb.i, Fb[2 * t + 1].i - xb.r));
+                    weigh(B.w1, B.w2, xa, xb, re, im);
+                    v[2 * kPitch] = re;
+                    v[3 * kPitch] = im;
+                    weigh(B.v1, B.v2, xa, xb, re, im);
+                    v[4 * kPitch] = re;
+                    v[5 * kPitch] = im;
+                    qq = q[2 * t];
+                    xa = cmul(qq, mk(Fa[2 * t].r + xa.i, Fa[2 * t].i - xa.r));
+                    xb = cmul(qq, mk(Fb[2 * t].r + xb.i, Fb[2 * t].i - xb.r));
+                    weigh(B.w1, B.w2, xa, xb, re, im);
+                    v[0] = re;
+                    v[kPitch] = im;
+                }
+                if (FULL && g < kGroups - 1) {
+                    const double v = pend_add(P);
+                    sum1 = (g == kGroups - 2 || B.rp == g + 1) ? v : sum1;
+                }
+                pend_read(P, B.rsrc);
+                if (!FULL) {
+                    const double v = pend_add(P);
+                    if (g == 0) sum0 = v;
+                    else sum1 = B.rp == g ? v : sum1;
+                }
+            }
+        if (!FULL) {
+            // groups past the block's end have no place: their lanes repeat group 0
+            *out = (B.rp == 0 || B.rp >= ng ? sum0 : sum1) + (B.add ? old : 0.0);
+        }
+        cr[0] = make_double2(xa.r, xa.i);
+        cr[64] = make_double2(xb.r, xb.i);
+        prev = out;
+        out += B.pstep;
+    }
+    if (FULL) {
+        const double v = pend_add(P);
+        *prev = (B.rp == 0 || B.rp == 3 ? v : sum1) + (B.add ? old : 0.0);
+    }
+}
+
+// One group of a block in pass 1: adds the products of one state's data and the
+// coefficients of the block-end values.
+__device__ __forceinline__ void forward_group(const cd* c, const cd* cpsi, const double (&h)[kPart], cd& fa, cd& fb) {
+#pragma unroll
+    for (int t = 0; t < kGroup; ++t) {
+        const double* rt = h + t * kSweepRec;
+        fa = mk(fma(c[2 * t].r, rt[0], fa.r), fma(c[2 * t].i, rt[0], fa.i));
+        fb = mk(fma(c[2 * t].r, rt[1], fb.r), fma(c[2 * t].i, rt[1], fb.i));
+        fa = mk(fma(c[2 * t + 1].r, rt[2], fa.r), fma(c[2 * t + 1].i, rt[2], fa.i));
+        fb = mk(fma(c[2 * t + 1].r, rt[3], fb.r), fma(c[2 * t + 1].i, rt[3], fb.i));
+        fa = mk(fma(cpsi[t].r, rt[4], fa.r), fma(cpsi[t].i, rt[4], fa.i));
+        fb = mk(fma(cpsi[t].r, rt[5], fb.r), fma(cpsi[t].i, rt[5], fb.i));
+    }
+}
+
+// One wave's work item.
+__device__ __forceinline__ void sweep_wave(const SweepArgs& A, const SweepItem& it, double2* scr, double* red,
+                                           double2* car, int lane) {
+        const int nst = detach(it.nst), npair = detach(it.npair), k0 = detach(it.k0), k1 = detach(it.k1);
+    const int ckpt = (1 + 2 * nst) * 64;  // scratch entries per block
+    const sptr cst = detach(uniform(A.cst + (long long)it.pair0 * kSweepCst));
+    const unsigned sstep = detach(A.state_stride);
+    const sptr rec = detach(uniform(A.rec + (long long)it.s0 * sstep + (long long)it.pair0 * kSweepRec));
+    // this lane sums row rv from term rp, and stores that row of group rp
+    const int rv = (lane >> 2) < kVals ? lane >> 2 : 0, rp = lane & 3;
+    double* part = A.part + it.part_off + rv;
+    const int nblk = (npair + kBlk - 1) / kBlk;
+    const SweepPole* poles = detach(A.poles);
+    scr += lane;
+    car += lane;
+
+    for (int kb = k0; kb < k1; kb += 64) {
+        const bool act = kb + lane < k1;
+        const SweepPole& pd = poles[act ? kb + lane : k1 - 1];
+        const cd al = cd{pd.al.x, pd.al.y}, ai = cd{pd.ai.x, pd.ai.y};
+
+        // ---- pass 1: pivots and forward values at the block boundaries
+        for (int s = 0; s < 2 * nst; ++s) car[s * 64] = make_double2(0.0, 0.0);
+        cd qp = mk(0, 0);
+        double h0[kPart];
+        for (int b = 0; b + 1 < nblk; ++b) {
+            const sptr c = cst + b * kBlk * kSweepCst;
+            const sptr rb = rec + b * kBlk * kSweepRec;
+            cd q[2 * kBlk];
+            cd qin = qp;
+            Warm wm;
+            {
+                double cc[kBlk * kSweepCst];
+                fetch(cc, c);
+                warm(wm, rb, sstep, nst, c + kBlk * kSweepCst);
+#pragma unroll
+                for (int t = 0; t < kBlk; ++t) {
+                    pivots(cc + t * kSweepCst, al, ai, qp, q[2 * t], q[2 * t + 1]);
+                    qp = q[2 * t + 1];
+                }
+            }
+            warm_wait(wm);
+            fetch(h0, rb);
+            // q[t] -> coefficient of g_t in F at the block's end; the last is 1
+            cd cpsi[kBlk];
+            cd cc = mk(1, 0);
+#pragma unroll
+            for (int t = 2 * kBlk - 1; t >= 0; --t) {
+                const cd below = t > 0 ? q[t - 1] : qin;
+                q[t] = cc;
+                if (t & 1) cpsi[t >> 1] = (t == 2 * kBlk - 1) ? mk(ai.i, -ai.r) : miqv(ai, cc);
+                cc = (t == 2 * kBlk - 1) ? mk(below.i, -below.r) : miqv(below, cc);
+            }
+            double2* o = scr + (long long)b * ckpt;  // start of block b + 1
+            o[0] = make_double2(qp.r, qp.i);
+            double2 f0 = car[0], f1 = car[64];
+#pragma unroll 1
+            for (int s = 0; s < nst; ++s) {
+                const cd ga = cmul(cc, cd{f0.x, f0.y}), gb = cmul(cc, cd{f1.x, f1.y});
+                const sptr rs = rb + s * sstep;
+                cd fa = mk(0, 0), fb = mk(0, 0);
+                double hg[kBlk / kGroup][kPart];
+#pragma unroll
+                for (int k = 0; k < kPart; ++k) hg[0][k] = h0[k];
+                fetch(hg[1], rs + kPart);
+                const int sn = s + 1 < nst ? s + 1 : s;
+#pragma unroll
+                for (int g = 0; g < kBlk / kGroup; ++g) {
+                    forward_group(q + g * 2 * kGroup, cpsi + g * kGroup, hg[g], fa, fb);
+                    if (g + 2 < kBlk / kGroup) fetch(hg[g + 2], rs + (g + 2) * kPart);
+                    if (g + 2 == kBlk / kGroup) {
+                        f0 = car[(2 * sn) * 64];
+                        f1 = car[(2 * sn + 1) * 64];
+                        fetch(h0, rb + sn * sstep);
+                    }
+                }
+                const double2 g0 = make_double2(fa.r + ga.r, fa.i + ga.i);
+                const double2 g1 = make_double2(fb.r + gb.r, fb.i + gb.i);
+                car[(2 * s) * 64] = g0;
+                car[(2 * s + 1) * 64] = g1;
+                o[(1 + 2 * s) * 64] = g0;
+                o[(2 + 2 * s) * 64] = g1;
+            }
+        }
+
+        // ---- pass 2: blocks in reverse
+        const double keep = act ? 1.0 : 0.0;
+        Back B;
+        B.al = al;
+        B.ai = ai;
+        B.w1 = cd{keep * pd.w1.x, keep * pd.w1.y};
+        B.w2 = cd{keep * pd.w2.x, keep * pd.w2.y};
+        B.v1 = cd{keep * pd.v1.x, keep * pd.v1.y};
+        B.v2 = cd{keep * pd.v2.x, keep * pd.v2.y};
+        B.rsrc = red + rv * kPitch + rp;
+        B.red = red + lane;
+        B.car = car;
+        B.rp = rp;
+        B.add = kb != k0;
+        B.nst = nst;
+        B.sstep = sstep;
+        B.pstep = detach((unsigned)npair * kSweepRec);
+        for (int s = 0; s < 2 * nst; ++s) car[s * 64] = make_double2(0.0, 0.0);
+        fetch(h0, rec + (nblk - 1) * kBlk * kSweepRec);
+        // boundary values before block b >= 1 are at scr + (b - 1) ckpt
+        Boundary bd = load_boundary(scr + (long long)max(nblk - 2, 0) * ckpt);
+        for (int b = nblk - 1; b >= 0; --b) {
+            const int ng = min(kBlk, npair - b * kBlk) / kGroup;  // groups of this block
+            const int bn = max(b - 1, 0);
+            const sptr c = cst + b * kBlk * kSweepCst, cn = cst + bn * kBlk * kSweepCst;
+            const sptr rb = rec + b * kBlk * kSweepRec, rn = rec + bn * kBlk * kSweepRec;
+            const double2* ck = scr + (long long)bn * ckpt;
+            const double2* cx = scr + (long long)max(b - 2, 0) * ckpt;
+            double* out = part + b * kBlk * kSweepRec + (rp < ng ? rp : 0) * kVals;
+            if (ng == kBlk / kGroup) back_block<true>(B, ng, b == 0, c, cn, rb, rn, ck, cx, bd, out, h0);
+            else back_block<false>(B, ng, b == 0, c, cn, rb, rn, ck, cx, bd, out, h0);
+        }
+    }
+}
+
+// Workgroups of kSweepWaves waves, one work item each: the schedule gives the
+// waves of a workgroup items of one chain where it can, so that they read its
+// scalar data at about the same time from the scalar cache that they share.
+// counter == null: workgroup w takes groups w, w + grid, ... of kSweepWaves
+// items; else the groups come from the atomic counter (starting at zero).
+__global__ void __launch_bounds__(64 * kSweepWaves) __attribute__((amdgpu_waves_per_eu(2)))
+k_sweep(const SweepArgs A, int* counter) {
+    extern __shared__ double2 lds[];  // per wave: [2 states][64], then the reduction buffer
+    __shared__ int next;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    double2* scr = A.scratch + ((long long)blockIdx.x * kSweepWaves + wave) * A.scratch_stride;
+    double2* car = lds + wave * (A.nst * 128 + kRedDoubles / 2);
+    double* red = reinterpret_cast<double*>(car + A.nst * 128);
+    int i = blockIdx.x;
+    for (;;) {
+        if (counter) {
+            if (threadIdx.x == 0) next = atomicAdd(counter, 1);
+            __syncthreads();
+            i = __builtin_amdgcn_readfirstlane(next);
+            __syncthreads();
+        }
+        if (i < 0 || i * kSweepWaves >= A.nitems) break;
+        if (i * kSweepWaves + wave < A.nitems) {
+            typedef const SweepItem __attribute__((address_space(4)))* iptr;
+            const iptr p = (iptr)(unsigned long long)(A.items + (i * kSweepWaves + wave));
+            const SweepItem it{p->pair0, p->npair, p->s0, p->nst, p->k0, p->k1, p->part_off};
+            sweep_wave(A, it, scr, red, car, lane);
+        }
+        i += gridDim.x;
+    }
+}
+
+// Physical state [S][3][nspec] -> records; fin[pair][3]: factors into scaled
+// energy variables of vorticity, divergence and Phi.
+__global__ void k_sweep_prep(const double2* __restrict__ u, double* __restrict__ rec, const int2* __restrict__ idx,
+                             const double* __restrict__ fin, int npairs, int S, long long nspec) {
+    const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const int s = (int)(gid / (npairs + 1)), q = (int)(gid - (long long)s * (npairs + 1));
+    if (s >= S) return;
+    const double2* us = u + (long long)s * 3 * nspec;
+    double* r = rec + gid * kSweepRec;
+    if (q == npairs) {  // (n, m) = (0, 0)
+        for (int v = 0; v < 3; ++v) {
+            r[2 * v] = us[v * nspec].x;
+            r[2 * v + 1] = us[v * nspec].y;
+        }
+        return;
+    }
+    const int2 ix = idx[q];
+    const double* f = fin + 3 * q;
+    double v[kSweepRec] = {0, 0, 0, 0, 0, 0};
+    if (ix.x >= 0) {  // zeta' = -i zeta
+        const double2 z = us[nspec + ix.x];
+        v[0] = z.y * f[0];
+        v[1] = -z.x * f[0];
+    }
+    if (ix.y >= 0) {  // delta, psi = om Phi', Phi' = -i Phi
+        const double2 d = us[2 * nspec + ix.y], p = us[ix.y];
+        v[2] = d.x * f[1];
+        v[3] = d.y * f[1];
+        v[4] = p.y * f[2];
+        v[5] = -p.x * f[2];
+    }
+    for (int k = 0; k < kSweepRec; ++k) r[k] = v[k];
+}
+
+struct SweepReduceArgs {
+    const SweepChain* chains;
+    const int* pair_chain;
+    const SweepTile* tiles;      // per state
+    const SweepGroup* groups;    // [chain][tiles]
+    const int2* idx;
+    const double* cst;
+    const double* fout;          // [pair][3]: factors back to physical variables
+    const double* part;
+    const double* rec_in;
+    double* rec_out;             // next records, or null
+    double2* u_out;              // physical state, or null
+    int npairs, S, ntiles;
+    long long nspec;
+    cd g00, gphi;
+};
+
+// Sum an item group's partials in order and finish Phi; write the next records
+// or the physical state.  One thread per (pair, state).
+__global__ void k_sweep_reduce(const SweepReduceArgs R) {
+    const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const int s = (int)(gid / (R.npairs + 1)), q = (int)(gid - (long long)s * (R.npairs + 1));
+    if (s >= R.S) return;
+    const double* ri = R.rec_in + gid * kSweepRec;
+    if (q == R.npairs) {  // the operator is zero at (0, 0)
+        for (int v = 0; v < 3; ++v) {
+            const cd y = cmul(R.g00, mk(ri[2 * v], ri[2 * v + 1]));
+            if (R.u_out) R.u_out[((long long)s * 3 + v) * R.nspec] = make_double2(y.r, y.i);
+            else {
+                R.rec_out[gid * kSweepRec + 2 * v] = y.r;
+                R.rec_out[gid * kSweepRec + 2 * v + 1] = y.i;
+            }
+        }
+        return;
+    }
+    const int ch = R.pair_chain[q];
+    const SweepChain c = R.chains[ch];
+    const SweepTile tl = R.tiles[s];
+    const SweepGroup gr = R.groups[(long long)ch * R.ntiles + tl.tile];
+    const long long step = (long long)tl.nst * c.npair * kSweepRec;
+    const double* p = R.part + gr.part_off + ((long long)tl.pos * c.npair + (q - c.pair0)) * kSweepRec;
+    double v[kSweepRec] = {0, 0, 0, 0, 0, 0};
+    for (int r = 0; r < gr.nr; ++r, p += step)
+        for (int k = 0; k < kSweepRec; ++k) v[k] += p[k];
+    const double* cs = R.cst + (long long)q * kSweepCst;
+    const cd psi = cmul(R.gphi, mk(ri[4], ri[5]));
+    const double pr = fma(cs[4], v[4], psi.r), pi = fma(cs[4], v[5], psi.i);
+    const int2 ix = R.idx[q];
+    if (R.u_out) {
+        double2* us = R.u_out + (long long)s * 3 * R.nspec;
+        const double* f = R.fout + 3 * q;
+        if (ix.x >= 0) us[R.nspec + ix.x] = make_double2(-v[1] * f[0], v[0] * f[0]);
+        if (ix.y >= 0) {
+            us[2 * R.nspec + ix.y] = make_double2(v[2] * f[1], v[3] * f[1]);
+            us[ix.y] = make_double2(-pi * f[2], pr * f[2]);
+        }
+    } else {
+        double* o = R.rec_out + gid * kSweepRec;
+        const bool z = ix.x >= 0, d = ix.y >= 0;
+        o[0] = z ? cs[0] * v[0] : 0.0;
+        o[1] = z ? cs[0] * v[1] : 0.0;
+        o[2] = d ? cs[2] * v[2] : 0.0;
+        o[3] = d ? cs[2] * v[3] : 0.0;
+        o[4] = d ? pr : 0.0;
+        o[5] = d ? pi : 0.0;
+    }
+}
+
+}  // namespace
+
+hipError_t enqueue_sweep_prep(rexi_plan* pl, const Workspace& ws, const void* u, int buf, int S, int adjoint,
+                              hipStream_t s) {
+    const SweepTables& t = pl->sweep;
+    const long long n = (long long)S * (t.npairs + 1);
+    hipLaunchKernelGGL(k_sweep_prep, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, (const double2*)u,
+                       ws.rec[buf], t.d_idx, t.d_fin[adjoint], t.npairs, S, pl->nspec);
+    return hipGetLastError();
+}
+
+hipError_t enqueue_sweep_solve(rexi_plan* pl, const Workspace& ws, const Schedule& sc, int buf, int S, int adjoint,
+                               hipStream_t s) {
+    const SweepTables& t = pl->sweep;
+    SweepArgs a;
+    a.items = sc.d_sweep_items;
+    a.cst = t.d_cst;
+    a.rec = ws.rec[buf];
+    a.poles = reinterpret_cast<const SweepPole*>(t.d_poles[adjoint]);
+    a.part = reinterpret_cast<double*>(ws.part);
+    a.scratch = ws.sweep_scratch;
+    a.scratch_stride = sc.sweep_stride;
+    a.state_stride = (unsigned)(t.npairs + 1) * kSweepRec;
+    a.nitems = (int)sc.sweep_items.size();
+    int grid = std::min((a.nitems + kSweepWaves - 1) / kSweepWaves, ws.sweep_groups);
+    if (grid < 1) return hipErrorInvalidValue;
+    a.nst = sc.sweep_nst;
+    const size_t lds = sizeof(double2) * kSweepWaves * (128 * (size_t)sc.sweep_nst + kRedDoubles / 2);
+    int* counter = nullptr;
+    if (sc.persistent) {
+        int dev = 0, ncu = 0, per_cu = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+        if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_sweep, 64 * kSweepWaves, lds);
+        if (e != hipSuccess) return e;
+        grid = std::max(1, std::min(grid, std::max(1, per_cu) * ncu));
+        counter = ws.counters;
+        e = enqueue_reset_counters(counter, 1, s);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k_sweep, dim3(grid), dim3(64 * kSweepWaves), lds, s, a, counter);
+    return hipGetLastError();
+}
+
+hipError_t enqueue_sweep_reduce(rexi_plan* pl, const Workspace& ws, const Schedule& sc, int buf_in, int buf_out,
+                                void* u_out, int S, int adjoint, hipStream_t s) {
+    const SweepTables& t = pl->sweep;
+    SweepReduceArgs r;
+    r.chains = t.d_chains;
+    r.pair_chain = t.d_pair_chain;
+    r.tiles = sc.d_sweep_tiles;
+    r.groups = sc.d_sweep_groups;
+    r.idx = t.d_idx;
+    r.cst = t.d_cst;
+    r.fout = t.d_fout[adjoint];
+    r.part = reinterpret_cast<const double*>(ws.part);
+    r.rec_in = ws.rec[buf_in];
+    r.rec_out = u_out ? nullptr : ws.rec[buf_out];
+    r.u_out = (double2*)u_out;
+    r.npairs = t.npairs;
+    r.S = S;
+    r.ntiles = sc.sweep_ntiles;
+    r.nspec = pl->nspec;
+    const std::complex<double> g00 = adjoint ? pl->g00_adj : pl->g00_fwd;
+    const std::complex<double> gp = adjoint ? pl->gphi_adj : pl->gphi_fwd;
+    r.g00 = cd{g00.real(), g00.imag()};
+    r.gphi = cd{gp.real(), gp.imag()};
+    const long long n = (long long)S * (t.npairs + 1);
+    hipLaunchKernelGGL(k_sweep_reduce, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, r);
+    return hipGetLastError();
+}
+
+}  // namespace rexi
