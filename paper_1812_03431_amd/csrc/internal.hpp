@@ -114,10 +114,16 @@ constexpr int kSweepRec = 6;      // doubles of data per pair and state
 constexpr int kSweepPad = 2 * kSweepBlock * kSweepRec;  // doubles past the end of constants and data that a block may read
 constexpr int kSweepStates = 4;   // most states per work item
 constexpr int kSweepWaves = 4;    // waves of a workgroup
+constexpr int kSweepSplit = 24;   // shortest chain that is split between two waves
+constexpr int kSweepShort = 16;   // most pairs of a chain (or half) that a wave holds in registers
 constexpr int kSweepKind = 3;     // its kind in a schedule's classes (no moves between lanes)
-struct SweepItem {                // one chain, states [s0, s0 + nst), poles [k0, k1): a wave's work
-    int pair0, npair, s0, nst, k0, k1;
-    long long part_off;           // doubles; layout [nst][npair][kSweepRec]
+struct SweepItem {                // a wave's work: pairs of one chain, states [s0, s0 + nst), poles [k0, k1)
+    int pair0, npair;
+    int pstride;                  // pairs of the whole chain (a split chain: both halves and the middle)
+    int s0, nst, k0, k1;
+    int mid, half, pad;           // a half of a split chain: its middle pair and which half, else mid = -1
+    long long part_off;           // doubles; layout [nst][pstride][kSweepRec], from this item's first pair
+    long long mid_off;            // the same from the middle pair
 };
 struct SweepChain { int pair0, npair; };
 struct SweepTile { int tile, pos, nst; };               // of a state: its tile, place there, states of the tile
@@ -126,6 +132,10 @@ struct SweepTables {
     bool built = false, usable = false;
     int npairs = 0;
     std::vector<SweepChain> chains;  // index 2 m + p
+    // split tables: chains of at least kSweepSplit elements are laid out as the
+    // part before their middle vorticity element, that element, and the part after
+    // it in reverse; pairs of the two parts (0, 0: not split)
+    std::vector<int2> halves;
     double* d_cst = nullptr;         // [pair][kSweepCst]
     int2* d_idx = nullptr;           // [pair] spectral index of its vorticity and divergence (-1: a dummy)
     double *d_fin[2] = {nullptr, nullptr}, *d_fout[2] = {nullptr, nullptr};  // [pair][3]
@@ -167,6 +177,8 @@ struct Schedule {
     // pole-per-lane schedules (then the members above hold one launch for the
     // queries and nothing else)
     bool sweep = false;
+    bool split = false;                   // long chains split between two waves
+    bool short_chains = false;            // every part of a chain in registers
     int sweep_nst = 0, sweep_ntiles = 0;  // most states of an item, state tiles
     long long sweep_stride = 0;           // scratch of one workgroup (double2)
     std::vector<SweepItem> sweep_items;
@@ -230,7 +242,7 @@ struct rexi_plan {
     // persistent launches: one work counter per solve launch
     int* d_counters = nullptr;
     // pole-per-lane solve: tables, records of two buffers, scratch
-    rexi::SweepTables sweep;
+    rexi::SweepTables sweep[2];  // whole chains, split chains
     double* d_rec[2] = {nullptr, nullptr};
     double2* d_sweep_scratch = nullptr;
     long long rec_capacity = 0, sweep_scratch_capacity = 0;
@@ -282,8 +294,8 @@ hipError_t enqueue_finish(rexi_plan* pl, const Workspace& ws, int buf, void* u, 
 hipError_t enqueue_per_term_pole(rexi_plan* pl, const Workspace& ws, const Schedule& sc, int k, int buf, int S,
                                  hipStream_t s);
 hipError_t enqueue_reset_counters(int* c, int n, hipStream_t s);
-hipError_t enqueue_sweep_prep(rexi_plan* pl, const Workspace& ws, const void* u, int buf, int S, int adjoint,
-                              hipStream_t s);
+hipError_t enqueue_sweep_prep(rexi_plan* pl, const Workspace& ws, const Schedule& sc, const void* u, int buf, int S,
+                              int adjoint, hipStream_t s);
 hipError_t enqueue_sweep_solve(rexi_plan* pl, const Workspace& ws, const Schedule& sc, int buf, int S, int adjoint,
                                hipStream_t s);
 hipError_t enqueue_sweep_reduce(rexi_plan* pl, const Workspace& ws, const Schedule& sc, int buf_in, int buf_out,

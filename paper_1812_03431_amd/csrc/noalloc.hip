@@ -82,12 +82,12 @@ extern "C" int rexi_step_noalloc(rexi_plan* plan, const void* u0, void* u1, int 
         // records, partial sums and counters, then the workgroups' slots
         const Schedule& sc = *psc;
         const size_t rec_bytes =
-            ((size_t)(plan->sweep.npairs + 1) * S * kSweepRec + kSweepPad) * sizeof(double);
+            ((size_t)(plan->sweep[sc.split].npairs + 1) * S * kSweepRec + kSweepPad) * sizeof(double);
         const size_t o_r0 = take(rec_bytes), o_r1 = take(rec_bytes);
         const size_t o_part = take((size_t)sc.part_size * 16), o_cnt = take(kMaxLaunches * sizeof(int));
         const size_t slot = (size_t)sc.sweep_stride * 16 * kSweepWaves;
         const long long wgs = ((long long)sc.sweep_items.size() + kSweepWaves - 1) / kSweepWaves;
-        const long long fit = off < plan->scratch_bytes ? (long long)((plan->scratch_bytes - off) / slot) : 0;
+        const long long fit = off > plan->scratch_bytes ? 0 : slot ? (long long)((plan->scratch_bytes - off) / slot) : wgs;
         // fewer workgroups than fill the chip (two per CU) would run much slower
         // than the tiled schedule, which then takes the call
         if (fit >= std::min(wgs, 512LL)) {

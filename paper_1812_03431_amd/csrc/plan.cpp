@@ -285,8 +285,8 @@ int build_schedule(rexi_plan* pl, int S, int policy, long long target_items, boo
 // Tables of the pole-per-lane solve (see sweep_kernels.hip), built with the
 // first schedules.  Not usable without a Coriolis force (the scaling divides by
 // the couplings) or where the scaled constants leave a comfortable FP64 range.
-int build_sweep_tables(rexi_plan* pl) {
-    SweepTables& t = pl->sweep;
+int build_sweep_tables(rexi_plan* pl, bool split) {
+    SweepTables& t = pl->sweep[split];
     if (t.built) return REXI_OK;
     const int T = pl->T, N = pl->N;
     const long double a = pl->prm.radius, Om = pl->prm.omega, pb = pl->phibar, dt = pl->prm.dt;
@@ -299,8 +299,26 @@ int build_sweep_tables(rexi_plan* pl) {
     for (int m = 0; m <= T; ++m)
         for (int p = 0; p < 2; ++p) {
             const int n0 = std::max(m, 1), L = T + 1 - n0, pre = (n0 + p) & 1;
-            const int np = 2 * ((pre + L + 3) / 4);
+            // slots of the chain (an element or -1), even ones vorticity, odd ones
+            // divergence; element j is a vorticity iff pre + j is even
+            std::vector<int> slot;
+            int2 half = make_int2(0, 0);
+            auto whole_groups = [](int n) { return 4 * ((n + 3) / 4); };
+            if (split && L >= kSweepSplit) {
+                const int h = L / 2 + ((pre + L / 2) & 1);  // the middle vorticity element
+                const int na = whole_groups(h), nb = whole_groups(L - 1 - h);
+                slot.assign(na + 2 + nb, -1);
+                for (int j = 0; j < h; ++j) slot[na - h + j] = j;
+                slot[na] = h;
+                for (int j = L - 1; j > h; --j) slot[na + 2 + nb - (j - h)] = j;
+                half = make_int2(na / 2, nb / 2);
+            } else {
+                slot.assign(whole_groups(pre + L), -1);
+                for (int j = 0; j < L; ++j) slot[pre + j] = j;
+            }
+            const int np = (int)slot.size() / 2;
             t.chains.push_back({(int)idx.size(), np});
+            t.halves.push_back(half);
             const size_t q0 = idx.size();
             cst.resize((q0 + np) * kSweepCst, 0.0);
             idx.resize(q0 + np, make_int2(-1, -1));
@@ -309,36 +327,40 @@ int build_sweep_tables(rexi_plan* pl) {
                 fin[d].resize((q0 + np) * 3, 0.0);
                 fout[d].resize((q0 + np) * 3, 0.0);
             }
-            for (int q = 0; q < np; ++q) cst[(q0 + q) * kSweepCst] = cst[(q0 + q) * kSweepCst + 2] = kDummy;
-            long double D = 1.0L;
-            for (int j = 0; j < L; ++j) {
-                const int n = n0 + j;
-                const long double nn = (long double)n * (n + 1);
-                auto couple = [&](int k) { return 2 * Om * dt * eps_nm(k, m) * sqrtl((long double)k * k - 1) / k; };
-                if (j == 0 && L > 1) D = 1.0L / sqrtl(fabsl(couple(n0 + 1)));
-                if (j > 0) D = 1.0L / (couple(n) * D);
-                const long double om = sqrtl(pb * nn) / a * dt, s = a * sqrtl(pb / nn), th = 2 * Om * m / nn * dt;
-                ok = ok && in_range(D) && in_range(om) && in_range(s);
-                const size_t q = q0 + (pre + j) / 2;
+            // D_j D_{j+1} = 1 / c_{j+1}, the couplings of consecutive elements
+            std::vector<long double> D(L, 1.0L);
+            auto couple = [&](int k) { return 2 * Om * dt * eps_nm(k, m) * sqrtl((long double)k * k - 1) / k; };
+            if (L > 1) D[0] = 1.0L / sqrtl(fabsl(couple(n0 + 1)));
+            for (int j = 1; j < L; ++j) D[j] = 1.0L / (couple(n0 + j) * D[j - 1]);
+            for (int k = 0; k < 2 * np; ++k) {
+                const size_t q = q0 + k / 2;
+                const bool div = (k & 1) != 0;
                 double* c = &cst[q * kSweepCst];
+                if (slot[k] < 0) {
+                    c[div ? 2 : 0] = kDummy;
+                    continue;
+                }
+                const int j = slot[k], n = n0 + j;
+                const long double nn = (long double)n * (n + 1), Dj = D[j];
+                const long double om = sqrtl(pb * nn) / a * dt, s = a * sqrtl(pb / nn), th = 2 * Om * m / nn * dt;
+                ok = ok && in_range(Dj) && in_range(om) && in_range(s);
                 const int i = (int)(spec_offset(T, m) + (n - m));
-                const bool div = ((pre + j) & 1) != 0;
                 if (div) {
                     idx[q].y = i;
-                    c[2] = (double)(D * D);
-                    c[3] = (double)(D * D * th);
-                    c[4] = (double)(D * D * om * om);
+                    c[2] = (double)(Dj * Dj);
+                    c[3] = (double)(Dj * Dj * th);
+                    c[4] = (double)(Dj * Dj * om * om);
                 } else {
                     idx[q].x = i;
-                    c[0] = (double)(D * D);
-                    c[1] = (double)(D * D * th);
+                    c[0] = (double)(Dj * Dj);
+                    c[1] = (double)(Dj * Dj * th);
                 }
                 for (int d = 0; d < 2; ++d) {
-                    fin[d][3 * q + div] = (double)(d ? D / s : D * s);
-                    fout[d][3 * q + div] = (double)(d ? D * s : D / s);
+                    fin[d][3 * q + div] = (double)(d ? Dj / s : Dj * s);
+                    fout[d][3 * q + div] = (double)(d ? Dj * s : Dj / s);
                     if (div) {
-                        fin[d][3 * q + 2] = (double)(D * om);
-                        fout[d][3 * q + 2] = (double)(1 / (D * om));
+                        fin[d][3 * q + 2] = (double)(Dj * om);
+                        fout[d][3 * q + 2] = (double)(1 / (Dj * om));
                     }
                 }
             }
@@ -383,11 +405,15 @@ void free_sweep_tables(SweepTables& t) {
 
 // A pole-per-lane schedule: the states in tiles of up to kSweepStates, split
 // evenly; items are (chain, tile, range of 64-pole batches), as many per
-// (chain, tile) as its share of target_items, longest first.
-int build_sweep_schedule(rexi_plan* pl, int S, long long target_items, Schedule& out) {
-    const SweepTables& t = pl->sweep;
+// (chain, tile) as its share of target_items, longest first.  split: one batch per
+// item, and the two halves of a split chain are consecutive items from an even
+// index on (waves of one workgroup).
+int build_sweep_schedule(rexi_plan* pl, int S, long long target_items, bool split, bool short_chains, Schedule& out) {
+    const SweepTables& t = pl->sweep[split];
     out = Schedule();
     out.sweep = true;
+    out.split = split;
+    out.short_chains = short_chains;
     out.S = S;
     const int nt = (S + kSweepStates - 1) / kSweepStates, nb = (pl->N + 63) / 64;
     out.sweep_ntiles = nt;
@@ -403,36 +429,60 @@ int build_sweep_schedule(rexi_plan* pl, int S, long long target_items, Schedule&
         for (int k = 0; k < nt; ++k) total += cost(c.npair, s0[k + 1] - s0[k]) * nb;
     const double target = total / (double)std::max<long long>(1, target_items);
     std::vector<SweepGroup> groups(t.chains.size() * nt);
-    std::vector<std::pair<double, SweepItem>> items;
+    struct Unit { double cost; SweepItem a, b; bool two; };
+    std::vector<Unit> units;
     long long off = 0;
     int npmax = 0;
     for (size_t ch = 0; ch < t.chains.size(); ++ch) {
         const SweepChain& c = t.chains[ch];
-        npmax = std::max(npmax, c.npair);
+        const int2 half = t.halves[ch];
+        const bool two = half.x > 0;
+        npmax = std::max(npmax, two ? std::max(half.x, half.y) : c.npair);
         for (int k = 0; k < nt; ++k) {
             const int nst = s0[k + 1] - s0[k];
             out.sweep_nst = std::max(out.sweep_nst, nst);
-            const double u = cost(c.npair, nst);
-            const int per = std::max(1, std::min((int)std::lround(target / u), nb));  // batches per item
+            const double u = cost(two ? half.x : c.npair, nst);
+            const int per = split ? 1 : std::max(1, std::min((int)std::lround(target / u), nb));  // batches per item
             SweepGroup& gr = groups[ch * nt + k];
             gr = {off, 0, 0};
             for (int b = 0; b < nb; b += per) {
-                const int b1 = std::min(nb, b + per);
-                items.push_back({u * (b1 - b), {c.pair0, c.npair, s0[k], nst, 64 * b, std::min(pl->N, 64 * b1), off}});
+                const int b1 = std::min(nb, b + per), k0 = 64 * b, k1 = std::min(pl->N, 64 * b1);
+                Unit x{u * (b1 - b), {c.pair0, c.npair, c.npair, s0[k], nst, k0, k1, -1, 0, 0, off, 0}, {}, two};
+                if (two) {
+                    x.a.npair = half.x;
+                    x.a.mid = c.pair0 + half.x;
+                    x.a.mid_off = off + (long long)half.x * kSweepRec;
+                    x.b = x.a;
+                    x.b.pair0 = x.a.mid + 1;
+                    x.b.npair = half.y;
+                    x.b.half = 1;
+                    x.b.part_off = x.a.mid_off + kSweepRec;
+                }
+                units.push_back(x);
                 off += (long long)nst * c.npair * kSweepRec;
                 ++gr.nr;
             }
         }
     }
-    std::stable_sort(items.begin(), items.end(), [](const std::pair<double, SweepItem>& x,
-                                                    const std::pair<double, SweepItem>& y) { return x.first > y.first; });
-    for (const auto& x : items) out.sweep_items.push_back(x.second);
+    // pairs of halves first (they start at even indices), each kind longest first
+    std::stable_sort(units.begin(), units.end(), [](const Unit& x, const Unit& y) {
+        return x.two != y.two ? x.two : x.cost > y.cost;
+    });
+    for (const Unit& x : units) {
+        out.sweep_items.push_back(x.a);
+        if (x.two) out.sweep_items.push_back(x.b);
+    }
     out.part_size = (off + 1) / 2;
-    out.sweep_stride = (long long)std::max((npmax + kSweepBlock - 1) / kSweepBlock - 1, 1) * (1 + 2 * out.sweep_nst) * 64;
+    out.sweep_stride = (long long)((npmax + kSweepBlock - 1) / kSweepBlock) * (1 + 2 * out.sweep_nst) * 64;
     out.rot_max = out.sweep_nst;
-    out.launches.push_back({2 * kSweepBlock, kSweepKind, 0, (int)items.size(), 1, out.sweep_nst});
+    if (short_chains) {
+        if (npmax > kSweepShort) return fail(REXI_EUNSUPPORTED, "chains too long for registers");
+        out.sweep_stride = 0;
+    }
+    out.launches.push_back({2 * kSweepBlock, kSweepKind, 0, (int)out.sweep_items.size(), 1, out.sweep_nst});
     char buf[96];
-    std::snprintf(buf, sizeof buf, "sweep_items%lld%s", (long long)items.size(), out.sweep_nst > 1 ? "_shared" : "");
+    std::snprintf(buf, sizeof buf, "%s_items%lld%s", short_chains ? "sweep_short" : split ? "sweep2" : "sweep", (long long)out.sweep_items.size(),
+                  out.sweep_nst > 1 ? "_shared" : "");
     out.name = buf;
     int rc = upload(&out.d_sweep_items, out.sweep_items);
     if (!rc) rc = upload(&out.d_sweep_tiles, tiles);
@@ -479,8 +529,17 @@ int ensure_part(rexi_plan* pl, long long n) {
 // workgroup, at most kSweepScratch bytes of them (workgroups beyond take several
 // items in turn).
 constexpr long long kSweepScratch = 1LL << 30;
+// Where the chip is not filled, a long chain's time is what counts: with at most
+// kSplitWaves waves of one batch and a whole chain each, chains are split between
+// two waves (measured, whole / split: 258 chains x 7 batches, four states 130 / 116
+// us, T110 x 5 batches 108 / 79, T200 x 3 batches 192 / 128; but 1992 waves 74 / 81,
+// 2548 waves 44 / 50).  The register-resident form runs one wave per SIMD, so it is
+// taken while its waves are few enough for that (1050 waves, four states 48 -> 36 us,
+// one state 24 -> 17 us; 3360 waves, four states 81 -> 87), for one state up to two
+// rounds (2100 waves 28 -> 26 us).
+constexpr long long kSplitWaves = 1900, kShortWaves = 1100;
 int ensure_sweep(rexi_plan* pl, const Schedule& sc) {
-    const long long rec = (long long)(pl->sweep.npairs + 1) * sc.S * kSweepRec + kSweepPad;
+    const long long rec = (long long)(pl->sweep[sc.split].npairs + 1) * sc.S * kSweepRec + kSweepPad;
     if (rec > pl->rec_capacity) {
         drop_graphs(pl);
         pl->rec_capacity = 0;
@@ -491,7 +550,8 @@ int ensure_sweep(rexi_plan* pl, const Schedule& sc) {
         }
         pl->rec_capacity = rec;
     }
-    const long long most = std::max(1LL, kSweepScratch / 16 / kSweepWaves / std::max(1LL, sc.sweep_stride));
+    if (sc.sweep_stride == 0) return REXI_OK;
+    const long long most = std::max(1LL, kSweepScratch / 16 / kSweepWaves / sc.sweep_stride);
     const long long wgs = ((long long)sc.sweep_items.size() + kSweepWaves - 1) / kSweepWaves;
     const long long need = std::min(wgs, most) * kSweepWaves * sc.sweep_stride;
     if (need > pl->sweep_scratch_capacity) {
@@ -546,24 +606,34 @@ int schedules_for(rexi_plan* pl, int S, std::vector<Schedule>** out) {
                     c.push_back(sc);
                 }
         pl->tiled[S] = dflt;
-        int rc = build_sweep_tables(pl);
+        int rc = build_sweep_tables(pl, false);
+        if (!rc) rc = build_sweep_tables(pl, true);
         if (rc) return rc;
         // one pole per lane wherever the operator allows it: at every size and
         // state count measured (T63 to T301, 1 to 8 states) it beats the tiled
         // schedules (see sweep_kernels.hip).  ~8192 items (four per wave slot of
         // the chip) against ~4096 at T256 with four states: 1527 / 1570 us per
         // step; within 1% of each other elsewhere.
-        for (int persistent = 0; pl->sweep.usable && persistent < 2; ++persistent)
-            for (long long t : {4096LL, 8192LL}) {
+        const long long waves = (long long)pl->sweep[0].chains.size() * ((S + kSweepStates - 1) / kSweepStates) *
+                                ((pl->N + 63) / 64);
+        for (int persistent = 0; pl->sweep[0].usable && persistent < 2; ++persistent)
+            for (long long t : {4096LL, 8192LL, 0LL, -1LL}) {  // 0: split chains, -1: split and in registers
                 Schedule sc;
-                rc = build_sweep_schedule(pl, S, t, sc);
+                if (t <= 0 && waves > kSplitWaves) continue;
+                rc = build_sweep_schedule(pl, S, t, t <= 0, t < 0, sc);
+                if (t < 0 && (rc == REXI_EUNSUPPORTED ||
+                              (!rc && (long long)sc.sweep_items.size() > kShortWaves * (sc.sweep_nst == 1 ? 2 : 1)))) {
+                    free_schedule(sc);
+                    rc = 0;
+                    continue;
+                }
                 if (rc) { free_schedule(sc); return rc; }
                 sc.persistent = persistent != 0;
                 if (sc.persistent) sc.name = "persistent_" + sc.name;
                 rc = ensure_part(pl, sc.part_size);
                 if (!rc) rc = ensure_sweep(pl, sc);
                 if (rc) { free_schedule(sc); return rc; }
-                if (!persistent && t == 8192) dflt = (int)c.size();
+                if (!persistent && (t == 8192 || t <= 0)) dflt = (int)c.size();
                 c.push_back(sc);
             }
         if (c.empty()) return fail(REXI_EUNSUPPORTED, "no schedule fits this truncation");
@@ -621,7 +691,7 @@ int step_graph(rexi_plan* pl, const Schedule& sc, int S, int adjoint, int buf, h
 
 int run_sweep_steps(rexi_plan* pl, const Workspace& ws, const Schedule& sc, const void* u0, void* u1, int S,
                     int nsteps, int adjoint, hipStream_t s) {
-    REXI_HIP(enqueue_sweep_prep(pl, ws, u0, 0, S, adjoint, s));
+    REXI_HIP(enqueue_sweep_prep(pl, ws, sc, u0, 0, S, adjoint, s));
     int cur = 0;
     for (int k = 0; k < nsteps; ++k) {
         const bool last = (k == nsteps - 1);
@@ -766,7 +836,7 @@ void release(rexi_plan* pl) {
     dev_free(pl->d_fs_work);
     dev_free(pl->sched_layout);
     dev_free(pl->d_slot_m);
-    free_sweep_tables(pl->sweep);
+    for (auto& t : pl->sweep) free_sweep_tables(t);
     dev_free(pl->d_rec[0]);
     dev_free(pl->d_rec[1]);
     dev_free(pl->d_sweep_scratch);

@@ -24,8 +24,10 @@ def _gpu(x):
 
 
 # (T, S, M): chains up to T elements (+ a dummy) around 1, 2, 4, 12, 24 and 36; N = 2 (M + 11) + 1 poles just below and
-# above 64 and 128; 1 to 9 states (tiles 1, 2, 3, 4, 2+3, 3+3, 3+3+3)
-@pytest.mark.parametrize("T,S,M", [(1, 1, 8), (2, 3, 20), (3, 2, 21), (4, 5, 20), (11, 4, 52), (12, 1, 53), (13, 9, 21),
+# above 64 and 128; 1 to 9 states (tiles 1, 2, 3, 4, 2+3, 3+3, 3+3+3).  From 24 elements on chains are split between
+# two waves; up to 16 pairs a half it stays in registers (T = 63 .. 65 on both sides of that).
+@pytest.mark.parametrize("T,S,M", [(26, 5, 20), (31, 1, 52), (48, 2, 20), (49, 3, 21), (63, 2, 20), (64, 1, 52), (65, 4, 20),
+                                   (1, 1, 8), (2, 3, 20), (3, 2, 21), (4, 5, 20), (11, 4, 52), (12, 1, 53), (13, 9, 21),
                                    (23, 2, 52), (24, 6, 53), (25, 1, 21), (37, 3, 52)])
 def test_sweep_edges(T, S, M):
     import paper_1812_03431_amd as rexi
