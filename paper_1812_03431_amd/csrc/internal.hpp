@@ -182,9 +182,12 @@ struct Schedule {
     int sweep_nst = 0, sweep_ntiles = 0;  // most states of an item, state tiles
     long long sweep_stride = 0;           // scratch of one workgroup (double2)
     std::vector<SweepItem> sweep_items;
+    std::vector<SweepTile> sweep_tiles;
+    std::vector<SweepGroup> sweep_groups;
     SweepItem* d_sweep_items = nullptr;
     SweepTile* d_sweep_tiles = nullptr;
     SweepGroup* d_sweep_groups = nullptr;
+    bool on_device = false;  // the device copies are there
     std::string name;
 };
 
@@ -218,6 +221,10 @@ struct rexi_plan {
     std::vector<std::vector<rexi::Schedule>> sched;  // [S] -> candidates
     std::vector<int> chosen;
     std::vector<int> tiled;  // the default among the tiled schedules, [S]
+    // until the candidates of S are asked for: the default alone, and the tiled one
+    // that takes its no-allocation steps (see schedules_for)
+    std::vector<rexi::Schedule> first, first_tiled;
+    std::vector<void*> retired;  // workspace that a caller's graph may still hold
     std::vector<rexi::Schedule> per_term;             // [S]
     long long acc_capacity = 0;
 
@@ -245,7 +252,7 @@ struct rexi_plan {
     rexi::SweepTables sweep[2];  // whole chains, split chains
     double* d_rec[2] = {nullptr, nullptr};
     double2* d_sweep_scratch = nullptr;
-    long long rec_capacity = 0, sweep_scratch_capacity = 0;
+    long long rec_capacity[2] = {0, 0}, sweep_scratch_capacity = 0;
     // captured step graphs: key (S, adjoint, input buffer), valid for `graph_gen`
     struct StepGraph {
         const rexi::Schedule* sched;
@@ -307,6 +314,9 @@ int sh_setup(rexi_plan* pl);
 void sh_release(rexi_plan* pl);
 int sh_run(rexi_plan* pl, const void* in, void* out, int B, bool forward, hipStream_t s);
 int sh_vec_run(rexi_plan* pl, const void* in, void* out, long long stride, int B, bool to_uv, hipStream_t s);
+// Whether the no-allocation step's array holds the workspace of a pole-per-lane
+// schedule (noalloc.hip; true for the others, which it carves or refuses).
+bool noalloc_takes(const rexi_plan* pl, const Schedule& sc);
 int check_state_call(rexi_plan* pl, const void* in, const void* out, int S, int nsteps);
 // The no-allocation step's fixed device array: its address on the current
 // device, looked up once per device (noalloc.hip).

@@ -52,6 +52,41 @@ int scratch_setup(void** ptr, size_t* bytes) {
     return REXI_OK;
 }
 
+namespace {
+// Pieces of the array, every one 256-byte aligned.
+struct Carver {
+    size_t off = 0;
+    size_t take(size_t bytes) {
+        const size_t o = off;
+        off += (bytes + 255) & ~size_t(255);
+        return o;
+    }
+};
+
+// Of a pole-per-lane schedule: records, partial sums and counters, then the
+// workgroups' slots.  Fewer workgroups than fill the chip (two per CU) would run
+// much slower than the tiled schedule, which then takes the call.
+struct SweepPieces { size_t rec[2], part, counters, slots; long long groups; };
+
+bool carve(const rexi_plan* pl, const Schedule& sc, SweepPieces& w) {
+    Carver c;
+    const size_t rec = ((size_t)(pl->sweep[sc.split].npairs + 1) * sc.S * kSweepRec + kSweepPad) * sizeof(double);
+    for (size_t& o : w.rec) o = c.take(rec);
+    w.part = c.take((size_t)sc.part_size * 16);
+    w.counters = c.take(kMaxLaunches * sizeof(int));
+    w.slots = c.off;
+    const size_t slot = (size_t)sc.sweep_stride * 16 * kSweepWaves;
+    const long long wgs = ((long long)sc.sweep_items.size() + kSweepWaves - 1) / kSweepWaves;
+    w.groups = c.off > pl->scratch_bytes ? 0 : slot ? (long long)((pl->scratch_bytes - c.off) / slot) : wgs;
+    return w.groups >= std::min(wgs, 512LL);
+}
+}  // namespace
+
+bool noalloc_takes(const rexi_plan* pl, const Schedule& sc) {
+    SweepPieces w;
+    return !sc.sweep || carve(pl, sc, w);
+}
+
 }  // namespace rexi
 
 using namespace rexi;
@@ -61,61 +96,46 @@ extern "C" int rexi_step_noalloc(rexi_plan* plan, const void* u0, void* u1, int 
     if (rc) return rc;
     if (plan->prm.fsphere) return fail(REXI_EUNSUPPORTED, "the no-allocation step is built for the rotating sphere only");
     if (!plan->scratch) return fail(REXI_EUNSUPPORTED, "no workspace on the plan's device");
-    if ((int)plan->sched.size() <= S || plan->sched[S].empty() || plan->chosen[S] < 0)
+    const bool listed = (int)plan->sched.size() > S && !plan->sched[S].empty();
+    const Schedule* psc = listed ? &plan->sched[S][plan->chosen[S]] : (int)plan->first.size() > S ? &plan->first[S] : nullptr;
+    if (!psc || !psc->on_device)
         return fail(REXI_EINVAL,
                     "no schedule for this S yet: one call of rexi_step, rexi_plan_set_schedule or "
                     "rexi_plan_autotune with S builds them (and allocates); call it before the no-allocation step");
-    const Schedule* psc = &plan->sched[S][plan->chosen[S]];
     // switched off: persistent schedules launched outside a graph (a first
     // run of this step over every T256 candidate went silent there)
     if (psc->persistent)
         return fail(REXI_EUNSUPPORTED, "the no-allocation step does not run persistent schedules; select a "
                                        "one-workgroup-per-item schedule with rexi_plan_set_schedule");
-    // carve the workspace out of the array, every piece 256-byte aligned
-    size_t off = 0;
-    auto take = [&off](size_t bytes) {
-        const size_t o = off;
-        off += (bytes + 255) & ~size_t(255);
-        return o;
-    };
     if (psc->sweep) {
-        // records, partial sums and counters, then the workgroups' slots
-        const Schedule& sc = *psc;
-        const size_t rec_bytes =
-            ((size_t)(plan->sweep[sc.split].npairs + 1) * S * kSweepRec + kSweepPad) * sizeof(double);
-        const size_t o_r0 = take(rec_bytes), o_r1 = take(rec_bytes);
-        const size_t o_part = take((size_t)sc.part_size * 16), o_cnt = take(kMaxLaunches * sizeof(int));
-        const size_t slot = (size_t)sc.sweep_stride * 16 * kSweepWaves;
-        const long long wgs = ((long long)sc.sweep_items.size() + kSweepWaves - 1) / kSweepWaves;
-        const long long fit = off > plan->scratch_bytes ? 0 : slot ? (long long)((plan->scratch_bytes - off) / slot) : wgs;
-        // fewer workgroups than fill the chip (two per CU) would run much slower
-        // than the tiled schedule, which then takes the call
-        if (fit >= std::min(wgs, 512LL)) {
+        SweepPieces w;
+        if (carve(plan, *psc, w)) {
             char* base = static_cast<char*>(plan->scratch);
             Workspace ws{};
-            ws.part = reinterpret_cast<double2*>(base + o_part);
-            ws.counters = reinterpret_cast<int*>(base + o_cnt);
-            ws.rec[0] = reinterpret_cast<double*>(base + o_r0);
-            ws.rec[1] = reinterpret_cast<double*>(base + o_r1);
-            ws.sweep_scratch = reinterpret_cast<double2*>(base + off);
-            ws.sweep_groups = (int)std::min(fit, 1LL << 20);
+            ws.part = reinterpret_cast<double2*>(base + w.part);
+            ws.counters = reinterpret_cast<int*>(base + w.counters);
+            for (int d = 0; d < 2; ++d) ws.rec[d] = reinterpret_cast<double*>(base + w.rec[d]);
+            ws.sweep_scratch = reinterpret_cast<double2*>(base + w.slots);
+            ws.sweep_groups = (int)std::min(w.groups, 1LL << 20);
             if (nsteps == 0) {
                 REXI_HIP(hipMemcpyAsync(u1, u0, (size_t)S * 3 * plan->nspec * 16, hipMemcpyDeviceToDevice,
                                         (hipStream_t)stream));
                 return REXI_OK;
             }
-            return run_sweep_steps(plan, ws, sc, u0, u1, S, nsteps, 0, (hipStream_t)stream);
+            return run_sweep_steps(plan, ws, *psc, u0, u1, S, nsteps, 0, (hipStream_t)stream);
         }
-        if (plan->tiled[S] < 0) return fail(REXI_EUNSUPPORTED, "no schedule fits the no-allocation limit");
-        psc = &plan->sched[S][plan->tiled[S]];
-        off = 0;
+        psc = !listed ? &plan->first_tiled[S] : plan->tiled[S] >= 0 ? &plan->sched[S][plan->tiled[S]] : nullptr;
+        if (!psc || !psc->on_device) return fail(REXI_EUNSUPPORTED, "no schedule fits the no-allocation limit");
     }
+    // carve the workspace out of the array
+    Carver pieces;
+    auto take = [&pieces](size_t bytes) { return pieces.take(bytes); };
     const Schedule& sc = *psc;
     const size_t var_bytes = (size_t)S * (plan->nslots + 2) * 16, phi_bytes = (size_t)S * plan->nspec * 16;
     const size_t o_v0 = take(var_bytes), o_v1 = take(var_bytes), o_p0 = take(phi_bytes), o_p1 = take(phi_bytes);
     const size_t o_part = take((size_t)sc.part_size * 16), o_cnt = take(kMaxLaunches * sizeof(int));
-    if (off > plan->scratch_bytes)
-        return fail(REXI_EUNSUPPORTED, "this step needs " + std::to_string(off) + " bytes of workspace, above the "
+    if (pieces.off > plan->scratch_bytes)
+        return fail(REXI_EUNSUPPORTED, "this step needs " + std::to_string(pieces.off) + " bytes of workspace, above the "
                                        "no-allocation limit of " + std::to_string(plan->scratch_bytes) +
                                        " bytes (a schedule with fewer work items needs less)");
     char* base = static_cast<char*>(plan->scratch);

@@ -276,96 +276,126 @@ int build_schedule(rexi_plan* pl, int S, int policy, long long target_items, boo
     std::snprintf(buf, sizeof buf, "%s_items%lld%s%s", kPolicyName[policy], (long long)out.items.size(), share_tag,
                   per_term ? "_perterm" : "");
     out.name = buf;
-    int rc = upload(&out.d_minfo, out.minfo);
-    if (!rc) rc = upload(&out.d_items, out.items);
-    if (!rc) rc = upload(&out.d_groups, out.groups);
-    return rc;
+    return REXI_OK;
+}
+
+// Slots of chain (m, p) in pairs (an element or -1): even ones vorticity, odd ones
+// divergence; element j (degree max(m, 1) + j) is a vorticity iff pre + j is even.
+// half: pairs of the two halves of a chain split around its middle pair, or 0.
+std::vector<int> sweep_slots(int T, int m, int p, bool split, int2* half) {
+    const int n0 = std::max(m, 1), L = T + 1 - n0, pre = (n0 + p) & 1;
+    std::vector<int> slot;
+    *half = make_int2(0, 0);
+    auto whole_groups = [](int n) { return 4 * ((n + 3) / 4); };
+    if (split && L >= kSweepSplit) {
+        const int h = L / 2 + ((pre + L / 2) & 1);  // the middle vorticity element
+        const int na = whole_groups(h), nb = whole_groups(L - 1 - h);
+        slot.assign(na + 2 + nb, -1);
+        for (int j = 0; j < h; ++j) slot[na - h + j] = j;
+        slot[na] = h;
+        for (int j = L - 1; j > h; --j) slot[na + 2 + nb - (j - h)] = j;
+        *half = make_int2(na / 2, nb / 2);
+    } else {
+        slot.assign(whole_groups(pre + L), -1);
+        for (int j = 0; j < L; ++j) slot[pre + j] = j;
+    }
+    return slot;
+}
+
+// The chains' places in the tables (host only).
+void sweep_layout(rexi_plan* pl, bool split) {
+    SweepTables& t = pl->sweep[split];
+    if (!t.chains.empty()) return;
+    for (int m = 0; m <= pl->T; ++m)
+        for (int p = 0; p < 2; ++p) {
+            int2 half;
+            const int np = (int)sweep_slots(pl->T, m, p, split, &half).size() / 2;
+            t.chains.push_back({t.npairs, np});
+            t.halves.push_back(half);
+            t.npairs += np;
+        }
 }
 
 // Tables of the pole-per-lane solve (see sweep_kernels.hip), built with the
-// first schedules.  Not usable without a Coriolis force (the scaling divides by
-// the couplings) or where the scaled constants leave a comfortable FP64 range.
+// first schedule that reads them.  Not usable without a Coriolis force (the scaling
+// divides by the couplings) or where the scaled constants leave a comfortable FP64
+// range.  The couplings are c_n^m = g_n sqrt(n^2 - m^2), so that an element costs
+// one square root and one division in long double (x87: about 20 ns each, and
+// T301 has 45 thousand elements); the rest depends on n alone.
 int build_sweep_tables(rexi_plan* pl, bool split) {
     SweepTables& t = pl->sweep[split];
     if (t.built) return REXI_OK;
+    sweep_layout(pl, split);
     const int T = pl->T, N = pl->N;
     const long double a = pl->prm.radius, Om = pl->prm.omega, pb = pl->phibar, dt = pl->prm.dt;
     const double kDummy = 1e100;
-    std::vector<double> cst, fin[2], fout[2];
-    std::vector<int2> idx;
-    std::vector<int> chain_of;
+    const size_t np = t.npairs;
+    std::vector<double> cst(np * kSweepCst, 0.0), fin[2], fout[2];
+    std::vector<int2> idx(np, make_int2(-1, -1));
+    std::vector<int> chain_of(np);
+    for (int d = 0; d < 2; ++d) {
+        fin[d].assign(np * 3, 0.0);
+        fout[d].assign(np * 3, 0.0);
+    }
     bool ok = true;
     auto in_range = [](long double x) { return fabsl(x) > 1e-40L && fabsl(x) < 1e40L; };
-    for (int m = 0; m <= T; ++m)
+    struct PerDegree { long double g, th, om, iom, s, is; };
+    std::vector<PerDegree> deg(T + 1);
+    for (int n = 1; n <= T; ++n) {
+        const long double nn = (long double)n * (n + 1), n2 = (long double)n * n;
+        PerDegree& d = deg[n];
+        d.g = 2 * Om * dt * sqrtl((n2 - 1) / (4 * n2 - 1)) / n;
+        d.th = 2 * Om / nn * dt;
+        d.om = sqrtl(pb * nn) / a * dt;
+        d.iom = 1 / d.om;
+        d.s = a * sqrtl(pb / nn);
+        d.is = 1 / d.s;
+        ok = ok && in_range(d.om) && in_range(d.s);
+    }
+    std::vector<long double> D(T + 1), iD(T + 1);
+    for (int m = 0; m <= T && ok; ++m) {
+        const int n0 = std::max(m, 1), L = T + 1 - n0;
+        // D_j D_{j+1} = 1 / c_{j+1}, the couplings of consecutive elements
+        auto couple = [&](int n) { return deg[n].g * sqrtl((long double)((long long)n * n - (long long)m * m)); };
+        iD[0] = L > 1 ? sqrtl(fabsl(couple(n0 + 1))) : 1.0L;
+        D[0] = 1 / iD[0];
+        for (int j = 1; j < L; ++j) {
+            iD[j] = couple(n0 + j) * D[j - 1];
+            D[j] = 1 / iD[j];
+        }
+        for (int j = 0; j < L; ++j) ok = ok && in_range(D[j]);
         for (int p = 0; p < 2; ++p) {
-            const int n0 = std::max(m, 1), L = T + 1 - n0, pre = (n0 + p) & 1;
-            // slots of the chain (an element or -1), even ones vorticity, odd ones
-            // divergence; element j is a vorticity iff pre + j is even
-            std::vector<int> slot;
-            int2 half = make_int2(0, 0);
-            auto whole_groups = [](int n) { return 4 * ((n + 3) / 4); };
-            if (split && L >= kSweepSplit) {
-                const int h = L / 2 + ((pre + L / 2) & 1);  // the middle vorticity element
-                const int na = whole_groups(h), nb = whole_groups(L - 1 - h);
-                slot.assign(na + 2 + nb, -1);
-                for (int j = 0; j < h; ++j) slot[na - h + j] = j;
-                slot[na] = h;
-                for (int j = L - 1; j > h; --j) slot[na + 2 + nb - (j - h)] = j;
-                half = make_int2(na / 2, nb / 2);
-            } else {
-                slot.assign(whole_groups(pre + L), -1);
-                for (int j = 0; j < L; ++j) slot[pre + j] = j;
-            }
-            const int np = (int)slot.size() / 2;
-            t.chains.push_back({(int)idx.size(), np});
-            t.halves.push_back(half);
-            const size_t q0 = idx.size();
-            cst.resize((q0 + np) * kSweepCst, 0.0);
-            idx.resize(q0 + np, make_int2(-1, -1));
-            chain_of.resize(q0 + np, 2 * m + p);
-            for (int d = 0; d < 2; ++d) {
-                fin[d].resize((q0 + np) * 3, 0.0);
-                fout[d].resize((q0 + np) * 3, 0.0);
-            }
-            // D_j D_{j+1} = 1 / c_{j+1}, the couplings of consecutive elements
-            std::vector<long double> D(L, 1.0L);
-            auto couple = [&](int k) { return 2 * Om * dt * eps_nm(k, m) * sqrtl((long double)k * k - 1) / k; };
-            if (L > 1) D[0] = 1.0L / sqrtl(fabsl(couple(n0 + 1)));
-            for (int j = 1; j < L; ++j) D[j] = 1.0L / (couple(n0 + j) * D[j - 1]);
-            for (int k = 0; k < 2 * np; ++k) {
+            int2 half;
+            const std::vector<int> slot = sweep_slots(T, m, p, split, &half);
+            const size_t q0 = t.chains[2 * m + p].pair0;
+            for (size_t k = 0; k < slot.size(); ++k) {
                 const size_t q = q0 + k / 2;
                 const bool div = (k & 1) != 0;
                 double* c = &cst[q * kSweepCst];
+                chain_of[q] = 2 * m + p;
                 if (slot[k] < 0) {
                     c[div ? 2 : 0] = kDummy;
                     continue;
                 }
                 const int j = slot[k], n = n0 + j;
-                const long double nn = (long double)n * (n + 1), Dj = D[j];
-                const long double om = sqrtl(pb * nn) / a * dt, s = a * sqrtl(pb / nn), th = 2 * Om * m / nn * dt;
-                ok = ok && in_range(Dj) && in_range(om) && in_range(s);
+                const PerDegree& e = deg[n];
+                const long double Dj = D[j], D2 = Dj * Dj;
                 const int i = (int)(spec_offset(T, m) + (n - m));
-                if (div) {
-                    idx[q].y = i;
-                    c[2] = (double)(Dj * Dj);
-                    c[3] = (double)(Dj * Dj * th);
-                    c[4] = (double)(Dj * Dj * om * om);
-                } else {
-                    idx[q].x = i;
-                    c[0] = (double)(Dj * Dj);
-                    c[1] = (double)(Dj * Dj * th);
-                }
+                c[div ? 2 : 0] = (double)D2;
+                c[div ? 3 : 1] = (double)(D2 * e.th * m);
+                if (div) c[4] = (double)(D2 * e.om * e.om);
+                (div ? idx[q].y : idx[q].x) = i;
                 for (int d = 0; d < 2; ++d) {
-                    fin[d][3 * q + div] = (double)(d ? Dj / s : Dj * s);
-                    fout[d][3 * q + div] = (double)(d ? Dj * s : Dj / s);
+                    fin[d][3 * q + div] = (double)(Dj * (d ? e.is : e.s));
+                    fout[d][3 * q + div] = (double)(Dj * (d ? e.s : e.is));
                     if (div) {
-                        fin[d][3 * q + 2] = (double)(Dj * om);
-                        fout[d][3 * q + 2] = (double)(1 / (Dj * om));
+                        fin[d][3 * q + 2] = (double)(Dj * e.om);
+                        fout[d][3 * q + 2] = (double)(iD[j] * e.iom);
                     }
                 }
             }
         }
-    t.npairs = (int)idx.size();
+    }
     cst.resize(cst.size() + kSweepPad, 0.0);
     t.usable = ok;
     t.built = true;
@@ -403,12 +433,23 @@ void free_sweep_tables(SweepTables& t) {
     }
 }
 
+// Where the chip is not filled, a long chain's time is what counts: with at most
+// kSplitWaves waves of one batch and a whole chain each, chains are split between
+// two waves (measured, whole / split: 258 chains x 7 batches, four states 130 / 116
+// us, T110 x 5 batches 108 / 79, T200 x 3 batches 192 / 128; but 1992 waves 74 / 81,
+// 2548 waves 44 / 50).  The register-resident form runs one wave per SIMD, so it is
+// taken while its waves are few enough for that (1050 waves, four states 48 -> 36 us,
+// one state 24 -> 17 us; 3360 waves, four states 81 -> 87), for one state up to two
+// rounds (2100 waves 28 -> 26 us).
+constexpr long long kSplitWaves = 1900, kShortWaves = 1100;
+
 // A pole-per-lane schedule: the states in tiles of up to kSweepStates, split
 // evenly; items are (chain, tile, range of 64-pole batches), as many per
 // (chain, tile) as its share of target_items, longest first.  split: one batch per
 // item, and the two halves of a split chain are consecutive items from an even
 // index on (waves of one workgroup).
 int build_sweep_schedule(rexi_plan* pl, int S, long long target_items, bool split, bool short_chains, Schedule& out) {
+    sweep_layout(pl, split);
     const SweepTables& t = pl->sweep[split];
     out = Schedule();
     out.sweep = true;
@@ -417,7 +458,8 @@ int build_sweep_schedule(rexi_plan* pl, int S, long long target_items, bool spli
     out.S = S;
     const int nt = (S + kSweepStates - 1) / kSweepStates, nb = (pl->N + 63) / 64;
     out.sweep_ntiles = nt;
-    std::vector<SweepTile> tiles(S);
+    std::vector<SweepTile>& tiles = out.sweep_tiles;
+    tiles.resize(S);
     std::vector<int> s0(nt + 1);
     for (int k = 0; k <= nt; ++k) s0[k] = S * k / nt;
     for (int k = 0; k < nt; ++k)
@@ -428,7 +470,8 @@ int build_sweep_schedule(rexi_plan* pl, int S, long long target_items, bool spli
     for (const SweepChain& c : t.chains)
         for (int k = 0; k < nt; ++k) total += cost(c.npair, s0[k + 1] - s0[k]) * nb;
     const double target = total / (double)std::max<long long>(1, target_items);
-    std::vector<SweepGroup> groups(t.chains.size() * nt);
+    std::vector<SweepGroup>& groups = out.sweep_groups;
+    groups.resize(t.chains.size() * nt);
     struct Unit { double cost; SweepItem a, b; bool two; };
     std::vector<Unit> units;
     long long off = 0;
@@ -476,7 +519,8 @@ int build_sweep_schedule(rexi_plan* pl, int S, long long target_items, bool spli
     out.sweep_stride = (long long)((npmax + kSweepBlock - 1) / kSweepBlock) * (1 + 2 * out.sweep_nst) * 64;
     out.rot_max = out.sweep_nst;
     if (short_chains) {
-        if (npmax > kSweepShort) return fail(REXI_EUNSUPPORTED, "chains too long for registers");
+        if (npmax > kSweepShort || (long long)out.sweep_items.size() > kShortWaves * (out.sweep_nst == 1 ? 2 : 1))
+            return fail(REXI_EUNSUPPORTED, "chains too long or too many for registers");
         out.sweep_stride = 0;
     }
     out.launches.push_back({2 * kSweepBlock, kSweepKind, 0, (int)out.sweep_items.size(), 1, out.sweep_nst});
@@ -484,13 +528,11 @@ int build_sweep_schedule(rexi_plan* pl, int S, long long target_items, bool spli
     std::snprintf(buf, sizeof buf, "%s_items%lld%s", short_chains ? "sweep_short" : split ? "sweep2" : "sweep", (long long)out.sweep_items.size(),
                   out.sweep_nst > 1 ? "_shared" : "");
     out.name = buf;
-    int rc = upload(&out.d_sweep_items, out.sweep_items);
-    if (!rc) rc = upload(&out.d_sweep_tiles, tiles);
-    if (!rc) rc = upload(&out.d_sweep_groups, groups);
-    return rc;
+    return REXI_OK;
 }
 
 void free_schedule(Schedule& s) {
+    s.on_device = false;
     dev_free(s.d_sweep_items);
     dev_free(s.d_sweep_tiles);
     dev_free(s.d_sweep_groups);
@@ -514,70 +556,142 @@ void drop_graphs(rexi_plan* pl) {
     ++pl->graph_gen;
 }
 
-int ensure_part(rexi_plan* pl, long long n) {
-    if (n <= pl->part_capacity) return REXI_OK;
+// A buffer of at least n entries.  The smaller one is kept until the plan is
+// destroyed where `keep` says that a caller's captured graph may hold it, else
+// freed.
+template <class T>
+int grow(rexi_plan* pl, T** p, long long* capacity, long long n, bool keep) {
+    if (n <= *capacity) return REXI_OK;
     drop_graphs(pl);
-    dev_free(pl->d_part);
-    pl->part_capacity = 0;
-    int rc = dev_alloc(&pl->d_part, (size_t)n);
-    if (rc) return rc;
-    pl->part_capacity = n;
+    T* q = nullptr;
+    if (!keep) dev_free(*p);
+    int rc = dev_alloc(&q, (size_t)n);
+    if (rc) {
+        if (!keep) *capacity = 0;
+        return rc;
+    }
+    if (*p) pl->retired.push_back(*p);
+    *p = q;
+    *capacity = n;
     return REXI_OK;
 }
 
-// Records of S states and the scratch of a pole-per-lane schedule: one slot per
-// workgroup, at most kSweepScratch bytes of them (workgroups beyond take several
-// items in turn).
+// Workspace of a schedule: partial sums; for a pole-per-lane schedule the
+// records of S states and its scratch, one slot per workgroup, at most
+// kSweepScratch bytes of them (workgroups beyond take several items in turn).
 constexpr long long kSweepScratch = 1LL << 30;
-// Where the chip is not filled, a long chain's time is what counts: with at most
-// kSplitWaves waves of one batch and a whole chain each, chains are split between
-// two waves (measured, whole / split: 258 chains x 7 batches, four states 130 / 116
-// us, T110 x 5 batches 108 / 79, T200 x 3 batches 192 / 128; but 1992 waves 74 / 81,
-// 2548 waves 44 / 50).  The register-resident form runs one wave per SIMD, so it is
-// taken while its waves are few enough for that (1050 waves, four states 48 -> 36 us,
-// one state 24 -> 17 us; 3360 waves, four states 81 -> 87), for one state up to two
-// rounds (2100 waves 28 -> 26 us).
-constexpr long long kSplitWaves = 1900, kShortWaves = 1100;
-int ensure_sweep(rexi_plan* pl, const Schedule& sc) {
-    const long long rec = (long long)(pl->sweep[sc.split].npairs + 1) * sc.S * kSweepRec + kSweepPad;
-    if (rec > pl->rec_capacity) {
-        drop_graphs(pl);
-        pl->rec_capacity = 0;
-        for (int d = 0; d < 2; ++d) {
-            dev_free(pl->d_rec[d]);
-            int rc = dev_alloc(&pl->d_rec[d], (size_t)rec);
-            if (rc) return rc;
-        }
-        pl->rec_capacity = rec;
-    }
-    if (sc.sweep_stride == 0) return REXI_OK;
+struct Sizes { long long part = 0, rec = 0, scratch = 0; };
+
+void add_sizes(const rexi_plan* pl, const Schedule& sc, Sizes& z) {
+    z.part = std::max(z.part, sc.part_size);
+    if (!sc.sweep) return;
+    z.rec = std::max(z.rec, (long long)(pl->sweep[sc.split].npairs + 1) * sc.S * kSweepRec + kSweepPad);
+    if (sc.sweep_stride == 0) return;
     const long long most = std::max(1LL, kSweepScratch / 16 / kSweepWaves / sc.sweep_stride);
     const long long wgs = ((long long)sc.sweep_items.size() + kSweepWaves - 1) / kSweepWaves;
-    const long long need = std::min(wgs, most) * kSweepWaves * sc.sweep_stride;
-    if (need > pl->sweep_scratch_capacity) {
-        drop_graphs(pl);
-        dev_free(pl->d_sweep_scratch);
-        pl->sweep_scratch_capacity = 0;
-        int rc = dev_alloc(&pl->d_sweep_scratch, (size_t)need);
-        if (rc) return rc;
-        pl->sweep_scratch_capacity = need;
+    z.scratch = std::max(z.scratch, std::min(wgs, most) * kSweepWaves * sc.sweep_stride);
+}
+
+int ensure_sizes(rexi_plan* pl, const Sizes& z, bool keep) {
+    int rc = grow(pl, &pl->d_part, &pl->part_capacity, z.part, keep);
+    for (int d = 0; d < 2 && !rc; ++d) rc = grow(pl, &pl->d_rec[d], &pl->rec_capacity[d], z.rec, keep);
+    if (!rc) rc = grow(pl, &pl->d_sweep_scratch, &pl->sweep_scratch_capacity, z.scratch, keep);
+    return rc;
+}
+
+// The device side of a schedule, once: its lists and the tables that it reads.
+int upload_schedule(rexi_plan* pl, Schedule& sc) {
+    if (sc.on_device) return REXI_OK;
+    int rc = REXI_OK;
+    if (sc.sweep) {
+        rc = build_sweep_tables(pl, sc.split);
+        if (!rc) rc = upload(&sc.d_sweep_items, sc.sweep_items);
+        if (!rc) rc = upload(&sc.d_sweep_tiles, sc.sweep_tiles);
+        if (!rc) rc = upload(&sc.d_sweep_groups, sc.sweep_groups);
+    } else {
+        rc = upload(&sc.d_minfo, sc.minfo);
+        if (!rc) rc = upload(&sc.d_items, sc.items);
+        if (!rc) rc = upload(&sc.d_groups, sc.groups);
     }
+    if (rc) {
+        free_schedule(sc);
+        return rc;
+    }
+    sc.on_device = true;
     return REXI_OK;
 }
 
-// Candidate schedules for S states (built on first use).
-int schedules_for(rexi_plan* pl, int S, std::vector<Schedule>** out) {
+// The tiled schedules' default for S states: "fine", ~2816 items, one launch per
+// item, states sharing factorisations where that measured faster.  (Item targets:
+// ~2816 measured fastest at T256, four states per item and concurrent classes, by
+// 3% over ~4096, with ~2048 and ~3072 on either side slower.)
+constexpr int kTiledPolicy = 5;
+constexpr long long kTiledTarget = 2816;
+int tiled_rot(int S) { return S % 2 == 0 ? 2 : 0; }
+
+// The pole-per-lane solve's default: one pole per lane wherever the operator
+// allows it, which at every size and state count measured (T63 to T301, 1 to 8
+// states) beats the tiled schedules (see sweep_kernels.hip).  ~8192 items (four per
+// wave slot of the chip) against ~4096 at T256 with four states: 1527 / 1570 us per
+// step; within 1% of each other elsewhere.
+long long sweep_waves(const rexi_plan* pl, int S) {
+    return 2LL * (pl->T + 1) * ((S + kSweepStates - 1) / kSweepStates) * ((pl->N + 63) / 64);
+}
+constexpr long long kSweepTarget = 8192;
+
+// Uploads schedule `sc` and, where the no-allocation step's array does not hold
+// it, the tiled schedule that takes that step in its place.
+int upload_with_tiled(rexi_plan* pl, Schedule& sc, Schedule* tiled) {
+    int rc = upload_schedule(pl, sc);
+    if (!rc && tiled && !noalloc_takes(pl, sc)) rc = upload_schedule(pl, *tiled);
+    return rc;
+}
+
+// The default schedule of S states alone, for the first step; the candidate list,
+// of which it is a part, is built by the first call that asks for it.  A new
+// plan's first step, with all of the list built and uploaded in it / the default
+// alone: T301, three states, 21 / 4 ms; T256, four states, 39 / 5 ms; T15, two
+// states, 7.9 / 0.4 ms.  REXI_EUNSUPPORTED: the default is a tiled schedule.
+int first_schedule(rexi_plan* pl, int S) {
+    if ((int)pl->first.size() <= S) {
+        pl->first.resize(S + 1);
+        pl->first_tiled.resize(S + 1);
+    }
+    Schedule &sc = pl->first[S], &t = pl->first_tiled[S];
+    if (sc.on_device) return REXI_OK;
+    const bool split = sweep_waves(pl, S) <= kSplitWaves;
+    int rc = build_sweep_tables(pl, split);
+    if (rc) return rc;
+    if (!pl->sweep[split].usable) return REXI_EUNSUPPORTED;
+    rc = split ? build_sweep_schedule(pl, S, 0, true, true, sc) : REXI_EUNSUPPORTED;
+    if (rc == REXI_EUNSUPPORTED) rc = build_sweep_schedule(pl, S, split ? 0 : kSweepTarget, split, false, sc);
+    if (rc) return rc;
+    bool tiled = !t.on_device && !noalloc_takes(pl, sc);
+    if (tiled && (build_schedule(pl, S, kTiledPolicy, kTiledTarget, false, tiled_rot(S), t) != REXI_OK ||
+                  (int)t.launches.size() > kMaxLaunches)) {
+        t = Schedule();  // the no-allocation step refuses then
+        tiled = false;
+    }
+    Sizes z;
+    add_sizes(pl, sc, z);
+    rc = ensure_sizes(pl, z, false);
+    if (!rc) rc = upload_with_tiled(pl, sc, tiled ? &t : nullptr);
+    return rc;
+}
+
+// Candidate schedules for S states (built on first use, on the host only; those
+// that run are uploaded).  all: the workspace holds any of them afterwards.
+int schedules_for(rexi_plan* pl, int S, bool all, std::vector<Schedule>** out) {
     if ((int)pl->sched.size() <= S) {
         pl->sched.resize(S + 1);
         pl->chosen.resize(S + 1, -1);
         pl->tiled.resize(S + 1, -1);
     }
     std::vector<Schedule>& c = pl->sched[S];
+    // buffers that an earlier step of S states used outlive a growth here
+    const bool stepped = !c.empty() || ((int)pl->first.size() > S && pl->first[S].on_device);
     if (c.empty()) {
-        // item targets: ~2816 measured fastest at T256 (four states per
-        // item, concurrent classes), by 3% over ~4096, with ~2048 and ~3072
-        // on either side slower
-        const long long tg[] = {2048, 2816, 4096, 8192};
+        const long long tg[] = {2048, kTiledTarget, 4096, 8192};
         // states per item (see build_schedule): one (each state factorises
         // its own poles), and for an even number of states up to four sharing
         // each factorisation, in every tile class or in some
@@ -586,61 +700,62 @@ int schedules_for(rexi_plan* pl, int S, std::vector<Schedule>** out) {
             rots.push_back(1);
             rots.push_back(2);
         }
-        int dflt = -1;
+        const bool few = sweep_waves(pl, S) <= kSplitWaves;
+        int rc = build_sweep_tables(pl, few);
+        if (rc) return rc;
+        if ((int)pl->first.size() <= S) {
+            pl->first.resize(S + 1);
+            pl->first_tiled.resize(S + 1);
+        }
+        std::vector<Schedule> list;
+        int tiled = -1, dflt = -1, from_first = -1, from_tiled = -1;
         for (int rot : rots)
         for (int persistent = 0; persistent < 2; ++persistent)
             for (int policy = 0; policy < kPolicies; ++policy)
                 for (long long t : tg) {
                     Schedule sc;
-                    int rc = build_schedule(pl, S, policy, t, false, rot, sc);
-                    if (rc == REXI_EUNSUPPORTED) { free_schedule(sc); continue; }
-                    if (rc) { free_schedule(sc); return rc; }
-                    if ((int)sc.launches.size() > kMaxLaunches) { free_schedule(sc); continue; }
+                    rc = build_schedule(pl, S, policy, t, false, rot, sc);
+                    if (rc == REXI_EUNSUPPORTED) continue;
+                    if (rc) return rc;
+                    if ((int)sc.launches.size() > kMaxLaunches) continue;
                     sc.persistent = persistent != 0;
                     if (sc.persistent) sc.name = "persistent_" + sc.name;
-                    rc = ensure_part(pl, sc.part_size);
-                    if (rc) { free_schedule(sc); return rc; }
-                    // until autotuned: "fine", ~2816 items, one launch per item,
-                    // states sharing factorisations where that measured faster
-                    if (!persistent && policy == 5 && t == 2816 && rot == rots.back()) dflt = (int)c.size();
-                    c.push_back(sc);
+                    if (!persistent && policy == kTiledPolicy && t == kTiledTarget && rot == tiled_rot(S)) {
+                        tiled = (int)list.size();
+                        if (pl->first_tiled[S].on_device) from_tiled = tiled;
+                    }
+                    list.push_back(std::move(sc));
                 }
-        pl->tiled[S] = dflt;
-        int rc = build_sweep_tables(pl, false);
-        if (!rc) rc = build_sweep_tables(pl, true);
-        if (rc) return rc;
-        // one pole per lane wherever the operator allows it: at every size and
-        // state count measured (T63 to T301, 1 to 8 states) it beats the tiled
-        // schedules (see sweep_kernels.hip).  ~8192 items (four per wave slot of
-        // the chip) against ~4096 at T256 with four states: 1527 / 1570 us per
-        // step; within 1% of each other elsewhere.
-        const long long waves = (long long)pl->sweep[0].chains.size() * ((S + kSweepStates - 1) / kSweepStates) *
-                                ((pl->N + 63) / 64);
-        for (int persistent = 0; pl->sweep[0].usable && persistent < 2; ++persistent)
-            for (long long t : {4096LL, 8192LL, 0LL, -1LL}) {  // 0: split chains, -1: split and in registers
+        dflt = tiled;
+        for (int persistent = 0; pl->sweep[few].usable && persistent < 2; ++persistent)
+            for (long long t : {4096LL, kSweepTarget, 0LL, -1LL}) {  // 0: split chains, -1: split and in registers
                 Schedule sc;
-                if (t <= 0 && waves > kSplitWaves) continue;
+                if (t <= 0 && !few) continue;
                 rc = build_sweep_schedule(pl, S, t, t <= 0, t < 0, sc);
-                if (t < 0 && (rc == REXI_EUNSUPPORTED ||
-                              (!rc && (long long)sc.sweep_items.size() > kShortWaves * (sc.sweep_nst == 1 ? 2 : 1)))) {
-                    free_schedule(sc);
-                    rc = 0;
-                    continue;
-                }
-                if (rc) { free_schedule(sc); return rc; }
+                if (rc == REXI_EUNSUPPORTED) continue;
+                if (rc) return rc;
                 sc.persistent = persistent != 0;
                 if (sc.persistent) sc.name = "persistent_" + sc.name;
-                rc = ensure_part(pl, sc.part_size);
-                if (!rc) rc = ensure_sweep(pl, sc);
-                if (rc) { free_schedule(sc); return rc; }
-                if (!persistent && (t == 8192 || t <= 0)) dflt = (int)c.size();
-                c.push_back(sc);
+                if (!persistent && t != 4096) {
+                    dflt = (int)list.size();
+                    if (pl->first[S].on_device && pl->first[S].name == sc.name) from_first = dflt;
+                }
+                list.push_back(std::move(sc));
             }
-        if (c.empty()) return fail(REXI_EUNSUPPORTED, "no schedule fits this truncation");
+        if (list.empty()) return fail(REXI_EUNSUPPORTED, "no schedule fits this truncation");
+        // the device copies of the first step's schedules move with them
+        if (from_first >= 0) list[from_first] = std::exchange(pl->first[S], Schedule());
+        if (from_tiled >= 0) list[from_tiled] = std::exchange(pl->first_tiled[S], Schedule());
+        c = std::move(list);
+        pl->tiled[S] = tiled;
         pl->chosen[S] = dflt >= 0 ? dflt : 0;
     }
     *out = &c;
-    return REXI_OK;
+    Sizes z;
+    for (int i = 0; i < (int)c.size(); ++i)
+        if (all || i == pl->chosen[S]) add_sizes(pl, c[i], z);
+    const int rc = ensure_sizes(pl, z, stepped);
+    return rc ? rc : upload_with_tiled(pl, c[pl->chosen[S]], pl->tiled[S] >= 0 ? &c[pl->tiled[S]] : nullptr);
 }
 
 bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
@@ -786,10 +901,19 @@ int do_step(rexi_plan* pl, const void* u0, void* u1, int S, int nsteps, int adjo
     int rc = check_state_call(pl, u0, u1, S, nsteps);
     if (rc) return rc;
     if (pl->prm.fsphere) return run_fsphere(pl, u0, u1, S, nsteps, adjoint, (hipStream_t)stream);
-    std::vector<Schedule>* c = nullptr;
-    rc = schedules_for(pl, S, &c);
-    if (rc) return rc;
-    return run_steps(pl, (*c)[pl->chosen[S]], u0, u1, S, nsteps, adjoint, (hipStream_t)stream);
+    const Schedule* sc = nullptr;
+    if ((int)pl->sched.size() <= S || pl->sched[S].empty()) {
+        rc = first_schedule(pl, S);
+        if (rc && rc != REXI_EUNSUPPORTED) return rc;
+        if (!rc) sc = &pl->first[S];
+    }
+    if (!sc) {
+        std::vector<Schedule>* c = nullptr;
+        rc = schedules_for(pl, S, false, &c);
+        if (rc) return rc;
+        sc = &(*c)[pl->chosen[S]];
+    }
+    return run_steps(pl, *sc, u0, u1, S, nsteps, adjoint, (hipStream_t)stream);
 }
 
 void drop_events(rexi_plan* pl) {
@@ -819,6 +943,10 @@ void release(rexi_plan* pl) {
     for (auto& c : pl->sched)
         for (auto& s : c) free_schedule(s);
     for (auto& s : pl->per_term) free_schedule(s);
+    for (auto& s : pl->first) free_schedule(s);
+    for (auto& s : pl->first_tiled) free_schedule(s);
+    for (void* p : pl->retired) (void)hipFree(p);
+    pl->retired.clear();
     dev_free(pl->d_th);
     dev_free(pl->d_om);
     dev_free(pl->d_cc);
@@ -1088,6 +1216,7 @@ int rexi_step_per_term(rexi_plan* plan, const void* u0, void* u1, int S, void* s
         Schedule& sc = plan->per_term[S];
         if (sc.items.empty()) {
             rc = build_schedule(plan, S, 0, 0, true, 0, sc);  // 8 elements per lane, one wave per chain
+            if (!rc) rc = upload_schedule(plan, sc);
             if (rc) { free_schedule(sc); sc = Schedule(); return rc; }
         }
         if (sc.part_size > plan->acc_capacity) {
@@ -1114,14 +1243,17 @@ int rexi_plan_set_schedule(rexi_plan* plan, int S, int index, int* count) {
     if (plan->prm.fsphere) return fail(REXI_EUNSUPPORTED, "f-sphere plans have no schedules");
     if (S < 1 || S > plan->prm.max_states) return fail(REXI_EINVAL, "S out of range");
     std::vector<Schedule>* c = nullptr;
-    int rc = schedules_for(plan, S, &c);
+    int rc = schedules_for(plan, S, index >= 0, &c);
     if (rc) return rc;
     if (count) *count = (int)c->size();
     if (index < 0) return REXI_OK;
     if (index >= (int)c->size()) return fail(REXI_EINVAL, "schedule index out of range");
-    if (plan->chosen[S] != index) drop_graphs(plan);
+    const int was = plan->chosen[S];
+    if (was != index) drop_graphs(plan);
     plan->chosen[S] = index;
-    return REXI_OK;
+    rc = schedules_for(plan, S, true, &c);
+    if (rc) plan->chosen[S] = was;
+    return rc;
 }
 
 int rexi_plan_get_schedule(rexi_plan* plan, int S, int* index) {
@@ -1129,7 +1261,7 @@ int rexi_plan_get_schedule(rexi_plan* plan, int S, int* index) {
     if (plan->prm.fsphere) return fail(REXI_EUNSUPPORTED, "f-sphere plans have no schedules");
     if (S < 1 || S > plan->prm.max_states) return fail(REXI_EINVAL, "S out of range");
     std::vector<Schedule>* c = nullptr;
-    int rc = schedules_for(plan, S, &c);
+    int rc = schedules_for(plan, S, false, &c);
     if (rc) return rc;
     *index = plan->chosen[S];
     return REXI_OK;
@@ -1140,7 +1272,7 @@ int rexi_plan_autotune(rexi_plan* plan, int S, void* stream, int* chosen) {
     if (plan->prm.fsphere) return fail(REXI_EUNSUPPORTED, "f-sphere plans have no schedules");
     if (S < 1 || S > plan->prm.max_states) return fail(REXI_EINVAL, "S out of range");
     std::vector<Schedule>* c = nullptr;
-    int rc = schedules_for(plan, S, &c);
+    int rc = schedules_for(plan, S, true, &c);
     if (rc) return rc;
     hipStream_t s = (hipStream_t)stream;
     const size_t bytes = (size_t)S * 3 * plan->nspec * 16;
@@ -1159,8 +1291,9 @@ int rexi_plan_autotune(rexi_plan* plan, int S, void* stream, int* chosen) {
             break;
         }
         for (int i = 0; i < (int)c->size() && !rc; ++i) {
-            const Schedule& sc = (*c)[i];
-            rc = run_steps(plan, sc, u0, u1, S, 1, 0, s);
+            Schedule& sc = (*c)[i];
+            rc = upload_schedule(plan, sc);
+            if (!rc) rc = run_steps(plan, sc, u0, u1, S, 1, 0, s);
             if (rc) break;
             if ((e = hipEventRecord(a, s)) != hipSuccess) { rc = hip_fail(e, "hipEventRecord"); break; }
             rc = run_steps(plan, sc, u0, u1, S, 3, 0, s);
@@ -1181,7 +1314,7 @@ int rexi_plan_autotune(rexi_plan* plan, int S, void* stream, int* chosen) {
     if (plan->chosen[S] != best) drop_graphs(plan);
     plan->chosen[S] = best;
     if (chosen) *chosen = best;
-    return REXI_OK;
+    return schedules_for(plan, S, true, &c);  // what the no-allocation step needs with it
 }
 
 int rexi_solve_variants(int per_term, int capacity, int* se, int* kind, int* states_per_item, int* count) {
@@ -1204,7 +1337,7 @@ int rexi_plan_schedule_classes(rexi_plan* plan, int S, int index, int capacity, 
         sc = &plan->per_term[S];
     } else {
         std::vector<Schedule>* c = nullptr;
-        int rc = schedules_for(plan, S, &c);
+        int rc = schedules_for(plan, S, false, &c);
         if (rc) return rc;
         if (index < -1 || index >= (int)c->size()) return fail(REXI_EINVAL, "schedule index out of range");
         sc = &(*c)[index];
@@ -1232,7 +1365,7 @@ int rexi_plan_schedule_name(rexi_plan* plan, int S, int index, char* buf, int ca
         sc = &plan->per_term[S];
     } else {
         std::vector<Schedule>* c = nullptr;
-        int rc = schedules_for(plan, S, &c);
+        int rc = schedules_for(plan, S, false, &c);
         if (rc) return rc;
         if (index < -1 || index >= (int)c->size()) return fail(REXI_EINVAL, "schedule index out of range");
         sc = &(*c)[index];
