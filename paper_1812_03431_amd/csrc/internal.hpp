@@ -241,10 +241,9 @@ struct rexi_plan {
     double2* d_vspec = nullptr;   // vector transforms: [max_fields][nspec(T+1)]
 
     // f-sphere variant: constant Coriolis parameter times dt, poles
-    // [N][3] (alpha, beta+, beta-), one state-sized work buffer
+    // [N][3] (alpha, beta+, beta-)
     double f0dt = 0.0;
     double2* d_fs_poles = nullptr;
-    double2* d_fs_work = nullptr;
 
     // persistent launches: one work counter per solve launch
     int* d_counters = nullptr;
@@ -295,7 +294,8 @@ hipError_t enqueue_solve(rexi_plan* pl, const Workspace& ws, const Schedule& sc,
 hipError_t enqueue_reduce(rexi_plan* pl, const Workspace& ws, const Schedule& sc, const double2* part, int buf_in,
                           int buf_out, void* u_out, int S, int adjoint, const int* d_slot_m, hipStream_t s);
 hipError_t enqueue_zero(double2* p, long long n, hipStream_t s);
-hipError_t enqueue_fsphere_step(rexi_plan* pl, const void* in, void* out, int S, int adjoint, hipStream_t s);
+hipError_t enqueue_fsphere_steps(rexi_plan* pl, const void* in, void* out, int S, int nsteps, int adjoint,
+                                 hipStream_t s);
 hipError_t enqueue_finish(rexi_plan* pl, const Workspace& ws, int buf, void* u, int S, int adjoint,
                           const MInfo* d_layout, hipStream_t s);
 hipError_t enqueue_per_term_pole(rexi_plan* pl, const Workspace& ws, const Schedule& sc, int k, int buf, int S,

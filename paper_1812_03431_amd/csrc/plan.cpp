@@ -880,20 +880,13 @@ using namespace rexi;
 
 namespace {
 
-// f-sphere steps: the closed-form kernel, alternating between u1 and the work
-// buffer so that the last step lands in u1.
+// f-sphere steps: the closed-form kernel takes all of them at once.
 int run_fsphere(rexi_plan* pl, const void* u0, void* u1, int S, int nsteps, int adjoint, hipStream_t s) {
-    const size_t bytes = (size_t)S * 3 * pl->nspec * 16;
     if (nsteps == 0) {
-        REXI_HIP(hipMemcpyAsync(u1, u0, bytes, hipMemcpyDeviceToDevice, s));
+        REXI_HIP(hipMemcpyAsync(u1, u0, (size_t)S * 3 * pl->nspec * 16, hipMemcpyDeviceToDevice, s));
         return REXI_OK;
     }
-    const void* src = u0;
-    for (int k = 0; k < nsteps; ++k) {
-        void* dst = ((nsteps - 1 - k) % 2 == 0) ? u1 : (void*)pl->d_fs_work;
-        REXI_HIP(enqueue_fsphere_step(pl, src, dst, S, adjoint, s));
-        src = dst;
-    }
+    REXI_HIP(enqueue_fsphere_steps(pl, u0, u1, S, nsteps, adjoint, s));
     return REXI_OK;
 }
 
@@ -961,7 +954,6 @@ void release(rexi_plan* pl) {
     dev_free(pl->d_part);
     dev_free(pl->d_acc);
     dev_free(pl->d_fs_poles);
-    dev_free(pl->d_fs_work);
     dev_free(pl->sched_layout);
     dev_free(pl->d_slot_m);
     for (auto& t : pl->sweep) free_sweep_tables(t);
@@ -1083,7 +1075,6 @@ int create(const rexi_params* p, rexi_plan** out) {
             fp.push_back(pl->poles.beta_minus[k]);
         }
         rc = upload(&pl->d_fs_poles, to_d2(fp));
-        if (!rc) rc = dev_alloc(&pl->d_fs_work, (size_t)p->max_states * 3 * pl->nspec);
     }
     if (!rc) rc = dev_alloc(&pl->d_counters, kMaxLaunches);
     if (!rc) {

@@ -965,59 +965,103 @@ __global__ void k_zero(double2* p, long long n) {
 // variables Phi_t = -w delta, zeta_t = -f0 delta, delta_t = f0 zeta + w Phi, so
 // with p = dt w_n and q = dt f0 the shifted system (a + dt L^) x = r has the
 // closed-form solution
-//   delta = (a r_d - q r_z - p r_P) / (a^2 + p^2 + q^2),
+//   delta = (a r_d - q r_z - p r_P) / D,  D = a^2 + p^2 + q^2,
 //   Phi = (r_P + p delta) / a,  zeta = (r_z + q delta) / a,
-// and (a - dt L^) flips the signs of p and q.  One thread per (state, n, m)
-// sums over the poles; the adjoint uses conj(beta), conj(alpha) and
-// L^H = -L^ with the inverse scaling.  (n, m) = (0, 0): the operator is zero.
-__device__ __forceinline__ cd cdiv(cd a, cd b) {
-    const double d = fma(b.r, b.r, b.i * b.i);
-    return cd{fma(a.r, b.r, a.i * b.i) / d, fma(a.i, b.r, -a.r * b.i) / d};
-}
-__device__ __forceinline__ void fsphere_solve(cd a, double p, double q, cd rP, cd rz, cd rd, cd& xP, cd& xz,
-                                              cd& xd) {
-    const cd den = cd{fma(a.r, a.r, -a.i * a.i) + p * p + q * q, 2.0 * a.r * a.i};
-    const cd num = cd{a.r * rd.r - a.i * rd.i - q * rz.r - p * rP.r, a.r * rd.i + a.i * rd.r - q * rz.i - p * rP.i};
-    xd = cdiv(num, den);
-    xP = cdiv(cd{rP.r + p * xd.r, rP.i + p * xd.i}, a);
-    xz = cdiv(cd{rz.r + q * xd.r, rz.i + q * xd.i}, a);
-}
+// and (a - dt L^) flips the signs of p and q.  It depends on the degree alone, so
+// that the sum over the poles, with weights b+ and b-, is one 3x3 matrix per
+// degree, of three sums:
+//   s0 = sum (b+ + b-) / (a D),  s1 = sum (b+ + b-) a / D,  s2 = sum (b+ - b-) / D,
+//   Phi' = (s1 + q^2 s0) Phi - p q s0 zeta + p s2 delta,
+//   zeta' = -p q s0 Phi + (s1 + p^2 s0) zeta + q s2 delta,
+//   delta' = s1 delta - s2 (p Phi + q zeta).
+// The adjoint uses conj(beta), conj(alpha), L^H = -L^ and the inverse scaling:
+// the conjugate sums and the opposite signs of p and q.  (n, m) = (0, 0): the
+// operator is zero.
+//
+// A workgroup takes kFsDeg consecutive degrees: wave w sums the poles of degree
+// n0 + w, a lane every 64th, and then the workgroup's share of the (state, order)
+// pairs takes all steps of the call in registers; the degrees of a pair are
+// consecutive in memory (128 bytes).  Bound by the latency of its one pass (loads,
+// pole sums, barrier, stores); summing all poles in the thread of every (state,
+// n, m), with six complex divisions each, took 54 us a call at T16 with 64 states
+// and 87 poles, this 10.1.
+constexpr int kFsDeg = 8;
 
-__global__ void k_fsphere_step(const double2* __restrict__ in, double2* __restrict__ out,
-                               const double2* __restrict__ poles, int N, const double* __restrict__ om,
-                               const double* __restrict__ sc, const int* __restrict__ idx_n, double qf, int S,
-                               long long nspec, int adjoint) {
-    const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= (long long)S * nspec) return;
-    const int st = (int)(gid / nspec);
-    const long long i = gid - (long long)st * nspec;
-    const long long base = (long long)st * 3 * nspec + i;
-    const int n = idx_n[i];
-    const double p = n > 0 ? om[i] : 0.0, q = n > 0 ? qf : 0.0;
-    const double f = adjoint ? 1.0 / sc[i] : sc[i];  // into energy variables
-    const cd rP = ld2(in, base), rz = cscale(ld2(in, base + nspec), f), rd = cscale(ld2(in, base + 2 * nspec), f);
-    const double sg = adjoint ? -1.0 : 1.0;  // L^H = -L^
-    cd aP = mk(0, 0), az = mk(0, 0), ad = mk(0, 0);
-    for (int k = 0; k < N; ++k) {
-        cd a = ld2(poles, 3LL * k), bp = ld2(poles, 3LL * k + 1), bm = ld2(poles, 3LL * k + 2);
-        if (adjoint) {
-            a = cconj(a);
-            bp = cconj(bp);
-            bm = cconj(bm);
+__global__ void __launch_bounds__(64 * kFsDeg) k_fsphere_steps(const double2* __restrict__ in,
+                                                              double2* __restrict__ out,
+                                                              const double2* __restrict__ poles, int N,
+                                                              const double* __restrict__ om,
+                                                              const double* __restrict__ sc, double qf, int T, int S,
+                                                              long long nspec, int nsteps, int adjoint, int per) {
+    __shared__ double2 sums[kFsDeg][3];
+    const int n0 = blockIdx.x * kFsDeg, nm = min(n0 + kFsDeg, T + 1);  // orders of these degrees
+    const int pr0 = blockIdx.y * per, pr1 = min(S * nm, pr0 + per);
+    if (pr0 >= pr1) return;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (n0 + wave <= T) {
+        const int n = n0 + wave;
+        const double p = n > 0 ? om[n] : 0.0, q = n > 0 ? qf : 0.0;  // order 0 is stored first
+        const double pq = fma(p, p, q * q);
+        cd s0 = mk(0, 0), s1 = mk(0, 0), s2 = mk(0, 0);
+        for (int k = lane; k < N; k += 64) {
+            const cd a = ld2(poles, 3LL * k), bp = ld2(poles, 3LL * k + 1), bm = ld2(poles, 3LL * k + 2);
+            const cd a2 = cd{fma(a.r, a.r, -a.i * a.i), 2.0 * a.r * a.i};
+            const cd D = cd{a2.r + pq, a2.i};
+            const cd aD = cd{fma(a.r, D.r, -a.i * D.i), fma(a.r, D.i, a.i * D.r)};
+            const double f = 1.0 / fma(aD.r, aD.r, aD.i * aD.i);
+            const cd inv = cd{aD.r * f, -aD.i * f};
+            const cd w = cmul(cadd(bp, bm), inv);
+            s0 = cadd(s0, w);
+            s1 = cfma(s1, w, a2);
+            s2 = cfma(s2, cmul(csub(bp, bm), inv), a);
         }
-        cd xP, xz, xd;
-        fsphere_solve(a, sg * p, sg * q, rP, rz, rd, xP, xz, xd);
-        aP = cfma(aP, bp, xP);
-        az = cfma(az, bp, xz);
-        ad = cfma(ad, bp, xd);
-        fsphere_solve(a, -sg * p, -sg * q, rP, rz, rd, xP, xz, xd);
-        aP = cfma(aP, bm, xP);
-        az = cfma(az, bm, xz);
-        ad = cfma(ad, bm, xd);
+#pragma unroll
+        for (int x = 32; x > 0; x >>= 1) {
+            s0 = cadd(s0, cd{__shfl_xor(s0.r, x), __shfl_xor(s0.i, x)});
+            s1 = cadd(s1, cd{__shfl_xor(s1.r, x), __shfl_xor(s1.i, x)});
+            s2 = cadd(s2, cd{__shfl_xor(s2.r, x), __shfl_xor(s2.i, x)});
+        }
+        if (lane == 0) {
+            st2(sums[wave], 0, s0);
+            st2(sums[wave], 1, s1);
+            st2(sums[wave], 2, s2);
+        }
     }
-    st2(out, base, aP);
-    st2(out, base + nspec, cscale(az, 1.0 / f));
-    st2(out, base + 2 * nspec, cscale(ad, 1.0 / f));
+    __syncthreads();
+    const int n = n0 + (threadIdx.x & (kFsDeg - 1));
+    if (n > T) return;
+    cd s0 = ld2(sums[n - n0], 0), s1 = ld2(sums[n - n0], 1), s2 = ld2(sums[n - n0], 2);
+    double p = n > 0 ? om[n] : 0.0, q = n > 0 ? qf : 0.0;
+    if (adjoint) {
+        s0 = cconj(s0);
+        s1 = cconj(s1);
+        s2 = cconj(s2);
+        p = -p;
+        q = -q;
+    }
+    const double f = adjoint ? 1.0 / sc[n] : sc[n], fi = 1.0 / f;  // into energy variables and back
+    const cd mPP = cadd(s1, cscale(s0, q * q)), mzz = cadd(s1, cscale(s0, p * p)), mPz = cscale(s0, -p * q);
+    for (int pr = pr0 + (int)(threadIdx.x / kFsDeg); pr < pr1; pr += 64) {
+        const int st = pr / nm, m = pr - st * nm;
+        if (m > n) continue;
+        const long long base = (long long)st * 3 * nspec + spec_offset(T, m) + (n - m);
+        cd P = ld2(in, base), z = ld2(in, base + nspec), d = ld2(in, base + 2 * nspec);
+        for (int k = 0; k < nsteps; ++k) {
+            z = cscale(z, f);
+            d = cscale(d, f);
+            const cd od = cmul(s2, d);
+            const cd c = cd{fma(p, P.r, q * z.r), fma(p, P.i, q * z.i)};
+            const cd nP = cadd(cfma(cmul(mPP, P), mPz, z), cscale(od, p));
+            const cd nz = cadd(cfma(cmul(mPz, P), mzz, z), cscale(od, q));
+            const cd nd = csub(cmul(s1, d), cmul(s2, c));
+            P = nP;
+            z = cscale(nz, fi);
+            d = cscale(nd, fi);
+        }
+        st2(out, base, P);
+        st2(out, base + nspec, z);
+        st2(out, base + 2 * nspec, d);
+    }
 }
 
 // LDS of one workgroup: the staged positions of the largest chain group.
@@ -1218,12 +1262,15 @@ hipError_t enqueue_finish(rexi_plan* pl, const Workspace& ws, int buf, void* u, 
     return hipGetLastError();
 }
 
-hipError_t enqueue_fsphere_step(rexi_plan* pl, const void* in, void* out, int S, int adjoint, hipStream_t s) {
-    const long long n = (long long)S * pl->nspec;
-    const int bs = 256;
-    hipLaunchKernelGGL(k_fsphere_step, dim3((unsigned)((n + bs - 1) / bs)), dim3(bs), 0, s, (const double2*)in,
-                       (double2*)out, pl->d_fs_poles, pl->N, pl->d_om, pl->d_sc, pl->d_idx_n, pl->f0dt, S,
-                       pl->nspec, adjoint);
+// About 1024 workgroups where there is that much: each repeats the pole sums of its
+// degrees, for one (state, order) pair per eight threads or more.
+hipError_t enqueue_fsphere_steps(rexi_plan* pl, const void* in, void* out, int S, int nsteps, int adjoint,
+                                 hipStream_t s) {
+    const int tiles = pl->T / kFsDeg + 1, passes = (S * (pl->T + 1) + 63) / 64;
+    const int chunks = std::min(passes, std::max(1, 1024 / tiles)), per = (passes + chunks - 1) / chunks * 64;
+    hipLaunchKernelGGL(k_fsphere_steps, dim3(tiles, chunks), dim3(64 * kFsDeg), 0, s, (const double2*)in,
+                       (double2*)out, pl->d_fs_poles, pl->N, pl->d_om, pl->d_sc, pl->f0dt, pl->T, S, pl->nspec,
+                       nsteps, adjoint, per);
     return hipGetLastError();
 }
 
