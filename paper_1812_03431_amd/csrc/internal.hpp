@@ -45,19 +45,20 @@ void gauss_legendre(int nlat, std::vector<double>& mu, std::vector<double>& w);
 // exact restart rows (P_{n0-1}, P_{n0}) at n0 = m + run r, [row][2][nmu] with
 // row = run_base[m] + r (run_base has T + 2 entries).
 std::vector<double> legendre_coefs(int T);
-std::vector<double> legendre_restarts(int T, int run, const std::vector<double>& mu, std::vector<int>& run_base);
+std::vector<double> legendre_restarts(int T, int run, int seg, const std::vector<double>& mu,
+                                      std::vector<int>& run_base, std::vector<double>& tail);
 
 // Device tables of the Legendre kernels for degrees 0..T (orders m <= the
 // plan's truncation): restart rows, recurrence coefficients and work lists.
 struct LegTables {
     int T = 0;
     double* d_restart = nullptr;  // [row][2][nhalf], rows every 32 degrees
-    double* d_restart8 = nullptr; // [row][2][nhalf], rows every 8 degrees (grids of <= 128 northern latitudes; inverse)
+    double* d_tail = nullptr;     // [m][4][2][nhalf], the four parts of an order's last inverse segment
     double* d_lcoef = nullptr;    // [nspec(T)][2]
     void* d_tiles_f = nullptr;    // forward runs
     void* d_tiles_i = nullptr;    // inverse work
-    int* d_seg = nullptr;         // inverse partial slots of order m: d_seg[m] .. d_seg[m+1]-1
-    int ntiles_f = 0, ntiles_i = 0, nslots = 0;
+    int ntiles_f = 0, ntiles_i = 0;
+    int inv_r = 1;                // latitude tiles per wave of the inverse
 };
 
 __host__ __device__ inline long long spec_offset(int T, int m) {
@@ -236,7 +237,7 @@ struct rexi_plan {
     double* d_mu = nullptr;       // northern Gauss nodes [nhalf]
     double* d_wts = nullptr;      // Gauss weights
     double* d_rcos = nullptr;     // 1 / cos(lat_j) [nlat]
-    double* d_four = nullptr;     // Fourier workspace [slots][nlat][2B] + padding per plane (slots >= T+1)
+    double* d_four = nullptr;     // Fourier workspace [T+1][nlat][2B] + padding per plane
     double2* d_twiddle = nullptr; // FFT twiddles
     double2* d_vspec = nullptr;   // vector transforms: [max_fields][nspec(T+1)]
 

@@ -16,8 +16,8 @@
 //
 // Fourier workspace (c = 2b + {0: re, 1: im}): the analysis writes the
 // weighted even/odd parts EO[m][0|1][j][c], j < nlat/2; the synthesis writes
-// partial sums Fw[slot][j][c] of degree segments, which the inverse FFT adds.
-// Each (m, parity) plane and each slot is padded by kFourPad doubles.
+// the coefficients Fw[m][j][c].  Each (m, parity) plane and each order's plane is
+// padded by kFourPad doubles.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -34,11 +34,11 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ int bitrev(int x, int bits) { return (int)(__brev((unsigned)x) >> (32 - bits)); }
 
 // Plane strides of the Fourier workspace, in doubles: an EO plane [j][c] of one
-// (order, parity) and a partial slot [row][c] are padded by kFourPad so that
+// (order, parity) and an order's plane [row][c] are padded by kFourPad so that
 // the lines of consecutive planes are not a power of two apart.
 constexpr int kFourPad = 32;
 __host__ __device__ __forceinline__ long long eo_plane(int H, int C) { return (long long)H * C + kFourPad; }
-__host__ __device__ __forceinline__ long long slot_plane(int nlat, int C) { return (long long)nlat * C + kFourPad; }
+__host__ __device__ __forceinline__ long long fw_plane(int nlat, int C) { return (long long)nlat * C + kFourPad; }
 
 __device__ __forceinline__ double2 cmul(double2 w, double2 v) {
     return make_double2(fma(w.x, v.x, -w.y * v.y), fma(w.x, v.y, w.y * v.x));
@@ -178,11 +178,8 @@ __global__ void __launch_bounds__(256) k_fft_forward(const double* __restrict__ 
 }
 
 // Fw -> rows j and j' = nlat-1-j (j < nlat/2) of fields b0 .. b0+nbr-1 of the
-// grid [B][nlat][nlon], scaled by rs[j] (rs may be NULL).  The Fourier
-// coefficient of order m <= T (T < 1024) is the sum of the partial slots
-// seg[m] .. seg[m+1]-1 of Fw[slot][row][c] (one per degree segment).
-__global__ void __launch_bounds__(256) k_fft_inverse(const double* __restrict__ Fw, const int* __restrict__ seg,
-                                                     double* __restrict__ grid, const double2* __restrict__ tw,
+// grid [B][nlat][nlon], scaled by rs[j] (rs may be NULL); orders m <= T < 1024.
+__global__ void __launch_bounds__(256) k_fft_inverse(const double* __restrict__ Fw, double* __restrict__ grid, const double2* __restrict__ tw,
                                                      const double* __restrict__ rs, int nlat, int nlon, int bits,
                                                      int T, int C, int nb) {
     extern __shared__ double2 X[];  // [nb][nlon] data, then [nlon/2] twiddles
@@ -205,14 +202,9 @@ __global__ void __launch_bounds__(256) k_fft_inverse(const double* __restrict__ 
             const int m = threadIdx.x + 256 * k;
             double2 v = make_double2(0.0, 0.0), w = v;
             if (m <= T) {
-                for (int sl = seg[m]; sl < seg[m + 1]; ++sl) {
-                    const double* p = Fw + sl * slot_plane(nlat, C) + (long long)j * C + cb;
-                    const double* q = Fw + sl * slot_plane(nlat, C) + (long long)j2 * C + cb;
-                    v.x += p[0];
-                    v.y += p[1];
-                    w.x += q[0];
-                    w.y += q[1];
-                }
+                const double* p = Fw + m * fw_plane(nlat, C) + cb;
+                v = make_double2(p[(long long)j * C], p[(long long)j * C + 1]);
+                w = make_double2(p[(long long)j2 * C], p[(long long)j2 * C + 1]);
                 if (m == 0) v.y = w.y = 0.0;  // real fields: Re F_0
             }
             fv[k] = v;
@@ -263,27 +255,24 @@ __global__ void __launch_bounds__(256) k_fft_inverse(const double* __restrict__ 
 // Legendre contractions with P_n^m generated on the device.  The table
 // itself (34 MB at T256) is never stored: P follows from the three-term
 // recurrence P_n = a_n mu P_{n-1} - b_n P_{n-2}, restarted from exact host
-// values every kRun degrees (and, on grids of at most 128 northern latitudes,
-// also every 8 degrees for the inverse), which keeps the FP64 recurrence
-// error at a few ulp.
+// values every kRun degrees (and, for the inverse, at the quarters of an order's
+// last, shorter segment), which keeps the FP64 recurrence error at a few ulp.
 constexpr int kRun = 32;         // degrees per restart row of the table
-constexpr int kInvSeg = 4 * kRun;  // degrees per inverse work item (at most; four parts)
+constexpr int kInvSeg = 4 * kRun;  // degrees per inverse segment (at most; four parts)
+constexpr int kInvPad = 8;       // doubles between the parts of a staged segment
 constexpr int kFwdDeg = 32;      // degrees per forward run: two 16-row parity tiles
 constexpr int kFwdLat = 128;     // latitudes per generated forward block
 constexpr int kPtPitch = kFwdLat + 1;  // LDS row pitch of the generated tile (odd: spreads banks)
 constexpr int kFwdGroup = 2;     // runs of one order per forward workgroup
 
 // Forward work: nrun consecutive 32-degree runs of order m from degree n0,
-// first restart row `row` (m = -1: an empty slot).  Inverse work: latitude
-// tiles [t0, t1) of order m (one wave each) over the degree segment
-// m + n0 .. m + n0 + kInvSeg - 1, written to partial slot `slot`.
+// first restart row `row` (m = -1: an empty slot).  Inverse work: the latitude
+// tiles from t0 on of order m, R per wave; row0 is the order's first restart row.
 struct LegRun {
     int m, n0, row, nrun;
 };
 struct LegWork {
-    int m, t0, t1, run0;  // order, latitude tiles [t0, t1), restart row of degree m + n0 (the 8-degree table
-                          // on grids of at most 128 northern latitudes, else the 32-degree one)
-    int n0, slot;         // first degree (offset from m) of the segment, output slot
+    int m, t0, row0;
 };
 
 // value of v in lane l of the wave (l uniform)
@@ -428,219 +417,166 @@ __global__ void __launch_bounds__(256) k_legendre_forward(const LegRun* __restri
     }
 }
 
-// Inverse: over one degree segment of order m, Fw[slot][j] = Fe + Fo,
-// Fw[slot][j'] = Fe - Fo with Fe / Fo the sums of P_n^m(mu_j) S_n over the
-// segment's n with n - m even / odd (the inverse FFT adds the segments of an
-// order).  A segment is four parts (the shortest multiple of 8 degrees that
-// covers it in four; restart rows every 8 degrees, grids of at most 128
-// northern latitudes); a workgroup takes up to four
-// 16-latitude tiles (one wave each) and stages in LDS the segment's spectral
-// block Sm [Ls][C], its coefficient column and the exact restart values of
-// its 64 latitudes at the start of each part.  The parts are the k index of
-// the four-block MFMA: lane 16 kq + i (i < 16) runs the recurrence of
-// latitude i over part kq from its own restart values, so no two lanes repeat
-// a recurrence and no lane selects values, and per k-step s it holds
+// Inverse: Fw[m][j] = Fe + Fo, Fw[m][j'] = Fe - Fo with Fe / Fo the sums of
+// P_n^m(mu_j) S_n over the order's n with n - m even / odd.  A workgroup takes 4 R
+// 16-latitude tiles of one order, R per wave, and all its degrees, in segments of
+// kInvSeg staged in LDS.  A segment is four parts (kRun degrees each, in an order's
+// last segment the shortest multiple of 8 that covers it in four), and the parts
+// are the k index of the four-block MFMA: lane 16 kq + i (i < 16) runs the
+// recurrence of latitude i over part kq from exact restart values, so no two lanes
+// repeat a recurrence and no lane selects values, and per step s it holds
 // A_even = P at part degree 2 s and A_odd = P at 2 s + 1 (parts start an even
-// number of degrees from m, so the parity of n - m is that of the part
-// degree).
+// number of degrees from m, so the parity of n - m is that of the part degree).
 // In the MFMA that lane is A[i & 3][kq] of block i >> 2: latitude i of the
-// tile.  The blocks share B, the segment's coefficients
-// S[Lp kq + 2 s (+1)][4 g + (lane & 3)] of column group g, and the result
-// D[q][p] of lane 16 q + 4 b + p is latitude 4 b + q, column 4 g + p.
-// Degrees past the segment need no checks: their coefficients are zero, so P
-// is zero there, and the B reads are clamped into the block; parts that start
-// past the segment have zero restart values.
-
-// Stage the spectral block of degrees m + n0 .. m + n0 + Ls - 1 ([Ls][C],
-// columns c_off..) and its coefficient column ([kInvSeg + 16], cf[k] for
-// degree m + n0 + k, zero outside 1 <= k < Ls, so that every run's recurrence
-// reads staged values up to its end).  The coefficients of one field form
-// a contiguous run of 2 Ls <= 256 doubles: thread k takes double k of every
-// field (coalesced), all loads before the stores.
-__device__ __forceinline__ void stage_segment(long long so, long long ns, int Ls, int C, int c_off,
-                                              const double* __restrict__ spec, const double2* __restrict__ coef,
-                                              double* Sm, double2* cf) {
-    const int k = threadIdx.x;
-    const int nb = C >> 1;  // fields of this column chunk (C even, c_off even), <= 16
-    const bool ok = k < 2 * Ls;
-    double v[16];
-#pragma unroll
-    for (int f = 0; f < 16; ++f)
-        v[f] = (ok && f < nb) ? spec[((long long)((c_off >> 1) + f) * ns + so) * 2 + k] : 0.0;
-#pragma unroll
-    for (int f = 0; f < 16; ++f)
-        if (ok && f < nb) Sm[(k >> 1) * C + 2 * f + (k & 1)] = v[f];  // degree k/2, column 2f + re/im
-    for (int q = threadIdx.x; q < kInvSeg + 16; q += blockDim.x)
-        cf[q] = (q >= 1 && q < Ls) ? coef[so + q] : make_double2(0.0, 0.0);
-}
-
-template <int NG>
+// tile.  The blocks share B, the coefficients of part kq, degree 2 s (+1) and one
+// column per p = lane & 3: columns 8 h + 2 p and 8 h + 2 p + 1 of a group pair
+// (one 16-byte LDS read), 8 (NG / 2) + p of a last single group.  Result D[q][p] of
+// lane 16 q + 4 b + p is latitude 4 b + q and that column.
+// The parts are staged kInvPad doubles (and one coefficient) apart, so that the
+// four a wave reads at once lie in different banks.  Degrees past the segment need
+// no checks: their recurrence coefficients, restart values and staged columns are
+// zero.
+//
+// Bound by the FP64 rate, which matrix and vector instructions share (the 4x4x4
+// shape reaches 70 of the card's 71.5 TFLOP/s, the 16x16x4 shape 48), plus three
+// recurrence instructions per two to sixteen MFMAs.  Legendre kernel / whole
+// inverse transform, against one workgroup per segment with the partial sums added
+// by the FFT (and the 16x16x4 shape above 128 northern latitudes): T1023 on 2048 x
+// 1024, 16 fields 599 -> 377 / 1093 -> 582 us; T511 on 1024 x 512, 6 fields 51 -> 28
+// / 88 -> 49; T256 on 512 x 256, 12 fields 19.1 -> 15.2 / 36.3 -> 28.4.
+template <int NG, int R>
 __global__ void __launch_bounds__(256) k_legendre_inverse(const LegWork* __restrict__ work,
-                                                          const double* __restrict__ restart8,
-                                                          const double2* __restrict__ coef,
-                                                          const double* __restrict__ mu,
-                                                          const double* __restrict__ spec,
-                                                          double* __restrict__ Fw, int T, int nlat, int H, int Cs,
-                                                          int c_off, int C) {
-    extern __shared__ double lds[];
-    const LegWork wk = work[blockIdx.x];
-    if (wk.m < 0) return;  // padding slot of the XCD-ordered list
-    const int m = wk.m;
-    const int Ls = min(kInvSeg, T + 1 - m - wk.n0);  // degrees of this segment
-    // part length: the shortest multiple of 8 (the restart rows' spacing)
-    // that covers the segment in four parts, so short segments idle few MFMA
-    // k slots
-    const int Lp = 8 * ((Ls + 31) / 32);
-    double* Sm = lds;                                        // [Ls][C]
-    double2* cf = reinterpret_cast<double2*>(lds + Ls * C);  // [kInvSeg + 16] (Ls * C is even: C is)
-    double* Rs = lds + Ls * C + 2 * (kInvSeg + 16);          // [4][2][64]
-    stage_segment(spec_offset(T, m) + wk.n0, nspec_of(T), Ls, C, c_off, spec, coef, Sm, cf);
-    const int jw = wk.t0 * 16;  // first latitude of the workgroup
-    for (int k = threadIdx.x; k < 4 * 128; k += blockDim.x) {
-        const int r = k >> 7, w = (k >> 6) & 1, j = min(jw + (k & 63), H - 1);
-        Rs[k] = (r * Lp < Ls) ? restart8[((long long)(wk.run0 + r * (Lp / 8)) * 2 + w) * H + j] : 0.0;
-    }
-    __syncthreads();
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int t = wk.t0 + wave;
-    if (t >= wk.t1) return;  // no latitude tile for this wave (no barrier follows)
-    const int i = lane & 15, kq = lane >> 4, p = lane & 3;
-    const int j = t * 16 + i;
-    const double x = (j < H) ? mu[j] : 0.0;
-    const int rb = kq * Lp;  // first segment degree of this lane's part
-    double pv = Rs[(kq * 2) * 64 + wave * 16 + i];
-    double cu = Rs[(kq * 2 + 1) * 64 + wave * 16 + i];
-    double ae[NG], ao[NG];
-#pragma unroll
-    for (int g = 0; g < NG; ++g) ae[g] = ao[g] = 0.0;
-#pragma unroll 4
-    for (int s = 0; s < Lp / 2; ++s) {
-        const int d = rb + 2 * s;                          // even part degree (segment-relative)
-        const double2 c1 = cf[d + 1], c2 = cf[d + 2];      // d + 2 <= 4 Lp <= kInvSeg
-        const double* be = Sm + min(d, Ls - 1) * C + p;
-        const double* bo = Sm + min(d + 1, Ls - 1) * C + p;
-        const double a_e = cu;
-        const double a_o = fma(c1.x * x, cu, -c1.y * pv);
-        cu = fma(c2.x * x, a_o, -c2.y * a_e);
-        pv = a_o;
-#pragma unroll
-        for (int g = 0; g < NG; ++g) {
-            const int cg = min(4 * g, C - 1 - p);  // column 4 g + p, clamped into the block
-            ae[g] = mfma4(a_e, be[cg], ae[g]);
-            ao[g] = mfma4(a_o, bo[cg], ao[g]);
-        }
-    }
-    // lane 16 q + 4 b + p holds latitude 4 b + q of the tile, column 4 g + p
-    const int jj = t * 16 + 4 * ((lane >> 2) & 3) + kq;
-    if (jj < H) {
-        double* fn = Fw + wk.slot * slot_plane(nlat, Cs) + (long long)jj * Cs + c_off;
-        double* fs = Fw + wk.slot * slot_plane(nlat, Cs) + (long long)(nlat - 1 - jj) * Cs + c_off;
-#pragma unroll
-        for (int g = 0; g < NG; ++g) {
-            const int col = 4 * g + p;
-            if (col < C) {
-                // streaming stores: the partials go out while the kernel runs
-                // instead of as dirty L2 lines written back at its end
-                __builtin_nontemporal_store(ae[g] + ao[g], fn + col);
-                __builtin_nontemporal_store(ae[g] - ao[g], fs + col);
-            }
-        }
-    }
-}
-
-// Inverse for grids of more than 128 northern latitudes, on the 16x16x4
-// shape (measured faster there: 674 against 1124 us at T1023 on 2048 x 1024
-// with 16 fields; the four-block kernel's replicated operand reads, NG per
-// parity per k-step, load the LDS more where the column groups are many).  The
-// k index is four consecutive degrees: lanes (i = lane & 15, kq = lane >> 4)
-// run the recurrence of latitude i in registers (the four kq lanes alike,
-// restarted every kSeqRun degrees) and keep what their MFMA fragment needs:
-// per k-step of 8 degrees base .. base + 7, A_even = P_{base + 2 kq},
-// A_odd = P_{base + 2 kq + 1}; B is the spectral block of column tile
-// (16 columns) and k; accumulator register q of lane l holds latitude row
-// 4 q + l/16 of the tile and column l % 16.  Same segments, staging, slots and
-// streaming stores as k_legendre_inverse.
-constexpr int kSeqRun = 64;  // degrees between the sequential inverse's restarts (a multiple of kRun)
-
-template <int NCT>
-__global__ void __launch_bounds__(256) k_legendre_inverse_seq(const LegWork* __restrict__ work,
                                                           const double* __restrict__ restart,
+                                                          const double* __restrict__ tail,
                                                           const double2* __restrict__ coef,
                                                           const double* __restrict__ mu,
                                                           const double* __restrict__ spec,
                                                           double* __restrict__ Fw, int T, int nlat, int H, int Cs,
                                                           int c_off, int C) {
-    extern __shared__ double lds[];
+    constexpr int kCp = 4 * NG, kPart = kRun * kCp + kInvPad;  // pitches of a degree and of a part
+    extern __shared__ double Sm[];                             // [4][kPart]
+    double2* cf = reinterpret_cast<double2*>(Sm + 4 * kPart);  // [4][kRun + 1]
     const LegWork wk = work[blockIdx.x];
     if (wk.m < 0) return;  // padding slot of the XCD-ordered list
-    const int m = wk.m;
-    const int Ls = min(kInvSeg, T + 1 - m - wk.n0);  // degrees of this segment
-    const int nr = (Ls + kSeqRun - 1) / kSeqRun;       // restarts of this segment
-    double* Sm = lds;                                        // [Ls][C]
-    double2* cf = reinterpret_cast<double2*>(lds + Ls * C);  // [kInvSeg + 16] (Ls * C is even: C is)
-    double* Rs = lds + Ls * C + 2 * (kInvSeg + 16);          // [nr][2][64]
-    stage_segment(spec_offset(T, m) + wk.n0, nspec_of(T), Ls, C, c_off, spec, coef, Sm, cf);
-    const int jw = wk.t0 * 16;  // first latitude of the workgroup
-    for (int k = threadIdx.x; k < nr * 128; k += blockDim.x) {
-        const int r = k >> 7, w = (k >> 6) & 1, j = min(jw + (k & 63), H - 1);
-        Rs[k] = restart[((long long)(wk.run0 + r * (kSeqRun / kRun)) * 2 + w) * H + j];
-    }
-    __syncthreads();
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int t = wk.t0 + wave;
-    if (t >= wk.t1) return;  // no latitude tile for this wave (no barrier follows)
-    const int i = lane & 15, kq = lane >> 4;
-    const int j = t * 16 + i;
-    const double x = (j < H) ? mu[j] : 0.0;
-    const int c0 = min(i, C - 1), c1 = min(16 + i, C - 1);
-    v4d ae0 = {0.0, 0.0, 0.0, 0.0}, ao0 = ae0, ae1 = ae0, ao1 = ae0;
-    for (int r = 0; r < nr; ++r) {
-        double pv = Rs[(r * 2) * 64 + wave * 16 + i];
-        double cu = Rs[(r * 2 + 1) * 64 + wave * 16 + i];
-        const int kr = r * kSeqRun;
+    const int m = wk.m, L = T + 1 - m, tid = threadIdx.x;
+    const int lane = tid & 63, wave = tid >> 6;
+    const int i = lane & 15, kq = lane >> 4, p = lane & 3;
+    const int t = wk.t0 + wave * R;  // first latitude tile of the wave (past the last one: nothing is stored)
+    const long long so = spec_offset(T, m), ns = nspec_of(T);
+    const int nb = C >> 1;  // fields of this column chunk (C even, c_off even)
+    const double* sp = spec + 2 * ((c_off >> 1) * ns + so) + tid;
+
+    // one segment's inputs: double `tid` of every field's run of coefficients (all
+    // coalesced), a recurrence coefficient, the lane's restart values
+    double v[2 * NG], pv[R], cu[R], x[R];
+    double2 cv;
+    const int cpart = tid / (kRun + 1), cdeg = tid - cpart * (kRun + 1);
+    auto fetch = [&](int n0) {
+        const int Ls = min(kInvSeg, L - n0), Lp = 8 * ((Ls + 31) / 32);
 #pragma unroll
-        for (int ks = 0; ks < kSeqRun; ks += 8) {
-            const int kb = kr + ks;
-            if (kb >= Ls) break;
-            double2 cv[8];
+        for (int f = 0; f < 2 * NG; ++f) v[f] = (tid < 2 * Ls && f < nb) ? sp[2 * (f * ns + n0)] : 0.0;
+        const int d = cpart * Lp + cdeg;
+        cv = (cpart < 4 && d >= 1 && d < Ls) ? coef[so + n0 + d] : make_double2(0.0, 0.0);
+        const double* rs = Ls == kInvSeg ? restart + (long long)(wk.row0 + n0 / kRun + kq) * 2 * H
+                                         : tail + (long long)(m * 4 + kq) * 2 * H;
 #pragma unroll
-            for (int d = 0; d < 8; ++d) cv[d] = cf[kb + d + 1];  // < Ls + 8 <= kInvSeg + 16
-            const int de = min(kb + 2 * kq, Ls - 1), dd = min(kb + 2 * kq + 1, Ls - 1);
-            const double b0 = Sm[de * C + c0], b1 = Sm[dd * C + c0];
-            const double b2 = Sm[de * C + c1], b3 = Sm[dd * C + c1];
-            double a_e = 0.0, a_o = 0.0;
+        for (int r = 0; r < R; ++r) {
+            const int j = min((t + r) * 16 + i, H - 1);
+            pv[r] = rs[j];
+            cu[r] = rs[H + j];
+        }
+    };
 #pragma unroll
-            for (int d = 0; d < 8; ++d) {
-                if ((d & 1) == 0) a_e = (kq == (d >> 1)) ? cu : a_e;
-                else a_o = (kq == (d >> 1)) ? cu : a_o;
-                const double nx = fma(cv[d].x * x, cu, -cv[d].y * pv);
-                pv = cu;
-                cu = nx;
+    for (int r = 0; r < R; ++r) x[r] = mu[min((t + r) * 16 + i, H - 1)];
+    double ae[R][NG], ao[R][NG];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int g = 0; g < NG; ++g) ae[r][g] = ao[r][g] = 0.0;
+    fetch(0);
+    for (int n0 = 0; n0 < L; n0 += kInvSeg) {
+        const int Ls = min(kInvSeg, L - n0), Lp = 8 * ((Ls + 31) / 32);
+        if (n0 > 0) __syncthreads();  // the previous segment is consumed
+        {
+            const int d = tid >> 1, part = d / Lp;  // degree d of the segment, re / im
+            double* to = Sm + part * kPart + (d - part * Lp) * kCp + (tid & 1);
+            if (part < 4) {
+#pragma unroll
+                for (int f = 0; f < 2 * NG; ++f) to[2 * f] = v[f];
             }
-            ae0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a_e, b0, ae0, 0, 0, 0);
-            ao0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a_o, b1, ao0, 0, 0, 0);
-            if constexpr (NCT > 1) {
-                ae1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a_e, b2, ae1, 0, 0, 0);
-                ao1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a_o, b3, ao1, 0, 0, 0);
+            if (cpart < 4) cf[tid] = cv;
+        }
+        double pa[R], ca[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            pa[r] = pv[r];
+            ca[r] = cu[r];
+        }
+        if (n0 + kInvSeg < L) fetch(n0 + kInvSeg);
+        __syncthreads();
+        const double* B = Sm + kq * kPart;
+        const double2* c = cf + kq * (kRun + 1);
+        for (int s0 = 0; s0 < Lp; s0 += 8) {
+#pragma unroll
+            for (int u = 0; u < 8; u += 2) {
+                const int s = s0 + u;
+                const double2 c1 = c[s + 1], c2 = c[s + 2];
+                double a_e[R], a_o[R];
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    a_e[r] = ca[r];
+                    a_o[r] = fma(c1.x * x[r], ca[r], -c1.y * pa[r]);
+                    ca[r] = fma(c2.x * x[r], a_o[r], -c2.y * a_e[r]);
+                    pa[r] = a_o[r];
+                }
+                const double* be = B + s * kCp;
+                const double* bo = be + kCp;
+#pragma unroll
+                for (int h = 0; h < NG / 2; ++h) {
+                    const double2 e = *reinterpret_cast<const double2*>(be + 8 * h + 2 * p);
+                    const double2 o = *reinterpret_cast<const double2*>(bo + 8 * h + 2 * p);
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        ae[r][2 * h] = mfma4(a_e[r], e.x, ae[r][2 * h]);
+                        ae[r][2 * h + 1] = mfma4(a_e[r], e.y, ae[r][2 * h + 1]);
+                        ao[r][2 * h] = mfma4(a_o[r], o.x, ao[r][2 * h]);
+                        ao[r][2 * h + 1] = mfma4(a_o[r], o.y, ao[r][2 * h + 1]);
+                    }
+                }
+                if constexpr (NG & 1) {
+                    const double e = be[8 * (NG / 2) + p], o = bo[8 * (NG / 2) + p];
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        ae[r][NG - 1] = mfma4(a_e[r], e, ae[r][NG - 1]);
+                        ao[r][NG - 1] = mfma4(a_o[r], o, ao[r][NG - 1]);
+                    }
+                }
             }
         }
     }
-    // accumulator register q of lane l holds D[4 q + l/16][l % 16]: latitude
-    // row 4 q + kq of the tile, column l % 16 of the column tile
+    // streaming stores: they go out while the kernel runs instead of as dirty L2
+    // lines written back at its end
+    typedef double v2d __attribute__((ext_vector_type(2)));
 #pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
-        const int col = hh * 16 + i;
-        if (hh >= NCT || col >= C) continue;
-        const v4d ae = hh ? ae1 : ae0, ao = hh ? ao1 : ao0;
+    for (int r = 0; r < R; ++r) {
+        const int jj = (t + r) * 16 + 4 * ((lane >> 2) & 3) + kq;
+        if (jj >= H) continue;
+        double* fn = Fw + m * fw_plane(nlat, Cs) + (long long)jj * Cs + c_off;
+        double* fs = Fw + m * fw_plane(nlat, Cs) + (long long)(nlat - 1 - jj) * Cs + c_off;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int jj = t * 16 + 4 * q + kq;
-            if (jj < H) {
-                // streaming stores: the partials go out while the kernel runs
-                // instead of as dirty L2 lines written back at its end
-                __builtin_nontemporal_store(ae[q] + ao[q], Fw + wk.slot * slot_plane(nlat, Cs) + (long long)jj * Cs + c_off + col);
-                __builtin_nontemporal_store(ae[q] - ao[q],
-                                            Fw + wk.slot * slot_plane(nlat, Cs) + (long long)(nlat - 1 - jj) * Cs + c_off + col);
+        for (int h = 0; h < NG / 2; ++h) {
+            const int col = 8 * h + 2 * p;
+            if (col < C) {
+                const double *e = &ae[r][2 * h], *o = &ao[r][2 * h];
+                __builtin_nontemporal_store(v2d{e[0] + o[0], e[1] + o[1]}, reinterpret_cast<v2d*>(fn + col));
+                __builtin_nontemporal_store(v2d{e[0] - o[0], e[1] - o[1]}, reinterpret_cast<v2d*>(fs + col));
+            }
+        }
+        if constexpr (NG & 1) {
+            const int col = 8 * (NG / 2) + p;
+            if (col < C) {
+                __builtin_nontemporal_store(ae[r][NG - 1] + ao[r][NG - 1], fn + col);
+                __builtin_nontemporal_store(ae[r][NG - 1] - ao[r][NG - 1], fs + col);
             }
         }
     }
@@ -728,15 +664,8 @@ __global__ void __launch_bounds__(256) k_uv_spec_to_vd(const double2* __restrict
 }
 
 
-// Inverse LDS: a segment's block [kInvSeg][w], coefficient column and restart
-// values (2 x 64 latitudes per run).
-// Restart rows every 8 degrees (besides every kRun) for grids of at most 128
-// northern latitudes, where the table stays small (9 MB at T256): the
-// inverse's four parts then shrink with short segments.
-bool restart8_rows(int H) { return H <= 128; }
-
-size_t inverse_lds(int w) {
-    return sizeof(double) * ((size_t)kInvSeg * w + 2 * (size_t)(kInvSeg + 16) + (size_t)(kInvSeg / kRun) * 128);
+size_t inverse_lds(int ng) {
+    return sizeof(double) * (4 * (size_t)(kRun * 4 * ng + kInvPad) + 2 * 4 * (size_t)(kRun + 1));
 }
 
 }  // namespace
@@ -753,12 +682,10 @@ int device_alloc(void** p, size_t bytes) {
 // degrees 0..Tt over orders m <= the plan's T.
 int leg_build(rexi_plan* pl, LegTables& t, int Tt, const std::vector<double>& north) {
     const int T = pl->T, H = pl->nhalf;
-    std::vector<int> run_base, run_base8;
-    std::vector<double> restart = legendre_restarts(Tt, kRun, north, run_base);
+    std::vector<int> run_base;
+    std::vector<double> tail;
+    std::vector<double> restart = legendre_restarts(Tt, kRun, kInvSeg, north, run_base, tail);
     std::vector<double> lcoef = legendre_coefs(Tt);
-    const bool reg = restart8_rows(H);
-    std::vector<double> restart8;
-    if (reg) restart8 = legendre_restarts(Tt, 8, north, run_base8);
     // forward: one workgroup per kFwdGroup consecutive 32-degree runs of an
     // order.  Workgroups go to the eight
     // XCDs round-robin by index, so slot s is filled from the queue of XCD
@@ -766,10 +693,6 @@ int leg_build(rexi_plan* pl, LegTables& t, int Tt, const std::vector<double>& no
     // first: all runs of an order share one XCD and its L2, where the order's
     // Fourier block is read from HBM once.  Queues that run out early are
     // padded with empty slots (m = -1).
-    // inverse: four latitude tiles (one per wave) of one degree segment of one
-    // order.  One order per workgroup: pairing m with T - m evens the work per
-    // wave but halves the waves in flight, which measured slower (30 vs 26 us
-    // at T256)
     constexpr int kXcd = 8;
     std::vector<std::vector<LegRun>> q(kXcd);
     for (int m = 0; m <= T; ++m) {
@@ -788,57 +711,35 @@ int leg_build(rexi_plan* pl, LegTables& t, int Tt, const std::vector<double>& no
     for (size_t k = 0; k < qmax; ++k)
         for (int x = 0; x < kXcd; ++x) tf.push_back(k < q[x].size() ? q[x][k] : LegRun{-1, 0, 0, 0});
     while (!tf.empty() && tf.back().m < 0) tf.pop_back();
+    // inverse: 4 R latitude tiles of one order per workgroup; the groups of an order
+    // read the same spectral coefficients and go to one XCD, longest orders first.
+    // R = 2 reads each staged value for two tiles (the LDS then serves the matrix
+    // cores' operands in half their time) where that leaves four workgroups per CU
     std::vector<LegWork> ti;
     const int nl = (H + 15) / 16;
-    // inverse: degree segments of kInvSeg, partial slot seg[m] + s; full
-    // segments first (the longest work), each with its latitude tile groups.
-    // All tile groups of a segment stage the same spectral block, so they go
-    // to one XCD: the k-th segment in this order to the queue of XCD k % 8,
-    // and the queues are interleaved like the forward list (padding m = -1).
-    // Spread over the XCDs, each group read the block from HBM again (9x the
-    // spectral bytes at T1023 on 1024 latitudes).
-    std::vector<int> seg(T + 2, 0);
-    for (int m = 0; m <= T; ++m) seg[m + 1] = seg[m] + (Tt - m) / kInvSeg + 1;
-    std::vector<std::vector<LegWork>> qi(kXcd);
-    int kseg = 0;
-    for (int full = 1; full >= 0; --full)
-        for (int m = 0; m <= T; ++m)
-            for (int n0 = 0; m + n0 <= Tt; n0 += kInvSeg) {
-                if ((m + n0 + kInvSeg - 1 <= Tt) != (full == 1)) continue;
-                std::vector<LegWork>& dst = qi[kseg++ % kXcd];
-                for (int t0 = 0; t0 < nl; t0 += 4)
-                    dst.push_back(LegWork{m, t0, std::min(nl, t0 + 4),
-                                          reg ? run_base8[m] + n0 / 8 : run_base[m] + n0 / kRun, n0,
-                                          seg[m] + n0 / kInvSeg});
-            }
-    size_t qimax = 0;
-    for (auto& v : qi) qimax = std::max(qimax, v.size());
-    for (size_t k = 0; k < qimax; ++k)
-        for (int x = 0; x < kXcd; ++x) ti.push_back(k < qi[x].size() ? qi[x][k] : LegWork{-1, 0, 0, 0, 0, 0});
-    while (!ti.empty() && ti.back().m < 0) ti.pop_back();
-    t.nslots = seg[T + 1];
+    t.inv_r = (long long)(T + 1) * ((nl + 7) / 8) >= 1024 ? 2 : 1;
+    for (int m8 = 0; m8 <= T; m8 += kXcd)
+        for (int t0 = 0; t0 < nl; t0 += 4 * t.inv_r)
+            for (int m = m8; m < m8 + kXcd; ++m) ti.push_back(m <= T ? LegWork{m, t0, run_base[m]} : LegWork{-1, 0, 0});
     t.T = Tt;
     int rc = device_alloc((void**)&t.d_restart, restart.size() * sizeof(double));
-    if (!rc && reg) rc = device_alloc((void**)&t.d_restart8, restart8.size() * sizeof(double));
+    if (!rc) rc = device_alloc((void**)&t.d_tail, tail.size() * sizeof(double));
     if (!rc) rc = device_alloc((void**)&t.d_lcoef, lcoef.size() * sizeof(double));
     if (!rc) rc = device_alloc((void**)&t.d_tiles_f, tf.size() * sizeof(LegRun));
     if (!rc) rc = device_alloc((void**)&t.d_tiles_i, ti.size() * sizeof(LegWork));
-    if (!rc) rc = device_alloc((void**)&t.d_seg, seg.size() * sizeof(int));
     if (rc) return rc;
     REXI_HIP(hipMemcpy(t.d_restart, restart.data(), restart.size() * sizeof(double), hipMemcpyHostToDevice));
-    if (reg)
-        REXI_HIP(hipMemcpy(t.d_restart8, restart8.data(), restart8.size() * sizeof(double), hipMemcpyHostToDevice));
+    REXI_HIP(hipMemcpy(t.d_tail, tail.data(), tail.size() * sizeof(double), hipMemcpyHostToDevice));
     REXI_HIP(hipMemcpy(t.d_lcoef, lcoef.data(), lcoef.size() * sizeof(double), hipMemcpyHostToDevice));
     REXI_HIP(hipMemcpy(t.d_tiles_f, tf.data(), tf.size() * sizeof(LegRun), hipMemcpyHostToDevice));
     REXI_HIP(hipMemcpy(t.d_tiles_i, ti.data(), ti.size() * sizeof(LegWork), hipMemcpyHostToDevice));
-    REXI_HIP(hipMemcpy(t.d_seg, seg.data(), seg.size() * sizeof(int), hipMemcpyHostToDevice));
     t.ntiles_f = (int)tf.size();
     t.ntiles_i = (int)ti.size();
     return REXI_OK;
 }
 
 void leg_release(LegTables& t) {
-    void* ptrs[] = {t.d_restart, t.d_restart8, t.d_lcoef, t.d_tiles_f, t.d_tiles_i, t.d_seg};
+    void* ptrs[] = {t.d_restart, t.d_tail, t.d_lcoef, t.d_tiles_f, t.d_tiles_i};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     t = LegTables{};
@@ -868,10 +769,10 @@ int fft_forward(rexi_plan* pl, const double* grid, int nf, const double* rs, hip
     return REXI_OK;
 }
 
-int fft_inverse(rexi_plan* pl, const LegTables& t, double* grid, int nf, const double* rs, hipStream_t s) {
+int fft_inverse(rexi_plan* pl, double* grid, int nf, const double* rs, hipStream_t s) {
     const int nb = fft_group(pl, nf);
     const size_t lds = (size_t)(nb * pl->nlon + pl->nlon / 2) * sizeof(double2);
-    hipLaunchKernelGGL(k_fft_inverse, dim3(((nf + nb - 1) / nb) * pl->nhalf), dim3(256), lds, s, pl->d_four, t.d_seg,
+    hipLaunchKernelGGL(k_fft_inverse, dim3(((nf + nb - 1) / nb) * pl->nhalf), dim3(256), lds, s, pl->d_four,
                        grid, pl->d_twiddle, rs, pl->nlat, pl->nlon, fft_bits(pl->nlon), pl->T, 2 * nf, nb);
     REXI_HIP(hipGetLastError());
     return REXI_OK;
@@ -900,42 +801,23 @@ int leg_forward(rexi_plan* pl, const LegTables& t, double* spec, int C, hipStrea
     return REXI_OK;
 }
 
-// spec [C/2][nspec(t.T)] -> partial slots of Fw (C columns), in launches of
-// at most 32 columns (up to eight four-column groups)
+template <int NG>
+void launch_inverse(rexi_plan* pl, const LegTables& t, const double* spec, int C, int c0, int w, hipStream_t s) {
+    const auto k = t.inv_r == 2 ? k_legendre_inverse<NG, 2> : k_legendre_inverse<NG, 1>;
+    hipLaunchKernelGGL(k, dim3(t.ntiles_i), dim3(256), inverse_lds(NG), s, (const LegWork*)t.d_tiles_i, t.d_restart,
+                       t.d_tail, reinterpret_cast<const double2*>(t.d_lcoef), pl->d_mu, spec, pl->d_four, t.T,
+                       pl->nlat, pl->nhalf, C, c0, w);
+}
+
+// spec [C/2][nspec(t.T)] -> Fw (C columns), in launches of at most 32 columns
+// (up to eight four-column groups)
 int leg_inverse(rexi_plan* pl, const LegTables& t, const double* spec, int C, hipStream_t s) {
-    const int H = pl->nhalf;
-    const double2* coef = reinterpret_cast<const double2*>(t.d_lcoef);
+    using Launcher = void (*)(rexi_plan*, const LegTables&, const double*, int, int, int, hipStream_t);
+    static constexpr Launcher of[8] = {launch_inverse<1>, launch_inverse<2>, launch_inverse<3>, launch_inverse<4>,
+                                       launch_inverse<5>, launch_inverse<6>, launch_inverse<7>, launch_inverse<8>};
     for (int c0 = 0; c0 < C; c0 += 32) {
         const int w = std::min(32, C - c0);
-        const int ng = (w + 3) / 4;
-        const size_t li = inverse_lds(w);
-        const LegWork* wl = (const LegWork*)t.d_tiles_i;
-        const dim3 g(t.ntiles_i), b(256);
-        const bool reg = restart8_rows(H);  // the plan holds restart rows every 8 degrees
-        if (!reg) {
-            if (w > 16)
-                hipLaunchKernelGGL(k_legendre_inverse_seq<2>, g, b, li, s, wl, t.d_restart, coef, pl->d_mu, spec,
-                                   pl->d_four, t.T, pl->nlat, H, C, c0, w);
-            else
-                hipLaunchKernelGGL(k_legendre_inverse_seq<1>, g, b, li, s, wl, t.d_restart, coef, pl->d_mu, spec,
-                                   pl->d_four, t.T, pl->nlat, H, C, c0, w);
-            REXI_HIP(hipGetLastError());
-            continue;
-        }
-
-#define REXI_INV(NG_)                                                                                        \
-    if (ng == NG_)                                                                                           \
-    hipLaunchKernelGGL(k_legendre_inverse<NG_>, g, b, li, s, wl, t.d_restart8, coef, pl->d_mu, spec, pl->d_four, \
-                       t.T, pl->nlat, H, C, c0, w)
-        REXI_INV(1);
-        REXI_INV(2);
-        REXI_INV(3);
-        REXI_INV(4);
-        REXI_INV(5);
-        REXI_INV(6);
-        REXI_INV(7);
-        REXI_INV(8);
-#undef REXI_INV
+        of[(w + 3) / 4 - 1](pl, t, spec, C, c0, w, s);
         REXI_HIP(hipGetLastError());
     }
     return REXI_OK;
@@ -971,11 +853,10 @@ int sh_setup(rexi_plan* pl) {
     if (!rc) rc = device_alloc((void**)&pl->d_wts, wn.size() * sizeof(double));
     if (!rc) rc = device_alloc((void**)&pl->d_rcos, rcos.size() * sizeof(double));
     if (!rc) rc = device_alloc((void**)&pl->d_twiddle, tw.size() * sizeof(double2));
-    // Fourier workspace: the forward's even/odd parts of T + 1 orders, or the
-    // inverse's partial slots
-    const size_t nsl = std::max<size_t>(T + 1, std::max(pl->leg.nslots, pl->legv.nslots));
-    // (T + 1) x 2 EO planes or nslots slots, each padded by kFourPad
-    if (!rc) rc = device_alloc((void**)&pl->d_four, nsl * (nlat * 2 * pl->prm.max_fields + 2 * kFourPad) * sizeof(double));
+    // Fourier workspace: (T + 1) x 2 EO planes or T + 1 order planes, each padded by kFourPad
+    if (!rc)
+        rc = device_alloc((void**)&pl->d_four,
+                          (size_t)(T + 1) * (nlat * 2 * pl->prm.max_fields + 2 * kFourPad) * sizeof(double));
     if (!rc && pl->prm.max_fields >= 2)
         rc = device_alloc((void**)&pl->d_vspec, (size_t)pl->prm.max_fields * nspec_of(T + 1) * sizeof(double2));
     if (rc) return rc;
@@ -1030,7 +911,7 @@ int sh_run(rexi_plan* pl, const void* in, void* out, int B, bool forward, hipStr
         REXI_HIP(timed_begin(pl, REXI_KERNEL_LEGENDRE_INV, s));
         if ((rc = leg_inverse(pl, pl->leg, (const double*)in, C, s))) return rc;
         REXI_HIP(timed_end(pl, REXI_KERNEL_LEGENDRE_INV, s));
-        if ((rc = fft_inverse(pl, pl->leg, (double*)out, B, nullptr, s))) return rc;
+        if ((rc = fft_inverse(pl, (double*)out, B, nullptr, s))) return rc;
     }
     return REXI_OK;
 }
@@ -1058,7 +939,7 @@ int sh_vec_run(rexi_plan* pl, const void* in, void* out, long long stride, int B
                            pl->prm.radius);
         REXI_HIP(hipGetLastError());
         if ((rc = leg_inverse(pl, pl->legv, (const double*)pl->d_vspec, C, s))) return rc;
-        if ((rc = fft_inverse(pl, pl->legv, (double*)out, 2 * B, pl->d_rcos, s))) return rc;
+        if ((rc = fft_inverse(pl, (double*)out, 2 * B, pl->d_rcos, s))) return rc;
     } else {
         if ((rc = fft_forward(pl, (const double*)in, 2 * B, pl->d_rcos, s))) return rc;
         if ((rc = leg_forward(pl, pl->legv, (double*)pl->d_vspec, C, s))) return rc;

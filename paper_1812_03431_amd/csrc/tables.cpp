@@ -71,16 +71,21 @@ std::vector<double> legendre_coefs(int T) {
 // n0 = m + run r <= T, row (run_base[m] + r) holds P_{n0-1}(mu_j) (0 at n0 = m)
 // and P_{n0}(mu_j), layout [row][2][nmu].  Long double (its exponent range
 // holds the seeds down to the Gaussian latitude nearest a pole at T = 1023);
-// values below 1e-300 are stored as 0.
-std::vector<double> legendre_restarts(int T, int run, const std::vector<double>& mu, std::vector<int>& run_base) {
+// values below 1e-300 are stored as 0.  tail: the same at the four parts of an
+// order's last segment of `seg` degrees where that one is not whole, layout
+// [m][4][2][nmu]: a part has 8 ceil(Ls / 32) degrees (Ls those of the segment), and
+// parts past its end hold 0.
+std::vector<double> legendre_restarts(int T, int run, int seg, const std::vector<double>& mu,
+                                      std::vector<int>& run_base, std::vector<double>& tail) {
     const int nmu = (int)mu.size();
+    tail.assign((size_t)(T + 1) * 8 * nmu, 0.0);
     run_base.assign(T + 2, 0);
     for (int m = 0; m <= T; ++m) run_base[m + 1] = run_base[m] + (T + 1 - m + run - 1) / run;
     std::vector<double> out((size_t)run_base[T + 1] * 2 * nmu, 0.0);
-    auto put = [&](int row, int which, int j, long double v) {
+    auto put = [&](std::vector<double>& to, int row, int which, int j, long double v) {
         double d = (double)v;
         if (fabs(d) < 1e-300) d = 0.0;
-        out[((size_t)row * 2 + which) * nmu + j] = d;
+        to[((size_t)row * 2 + which) * nmu + j] = d;
     };
     for (int j = 0; j < nmu; ++j) {
         const long double x = mu[j];
@@ -88,12 +93,18 @@ std::vector<double> legendre_restarts(int T, int run, const std::vector<double>&
         long double pmm = 1.0L / sqrtl(2.0L);
         for (int m = 0; m <= T; ++m) {
             if (m > 0) pmm *= sqrtl((2.0L * m + 1) / (2.0L * m)) * s;
+            const int L = T + 1 - m, t0 = L / seg * seg, part = 8 * ((L - t0 + 31) / 32);  // tail from m + t0
             long double pm2 = 0, pm1 = pmm;  // P_{n-1}, P_n at n = m
             for (int n = m;; ++n) {
                 if ((n - m) % run == 0) {
                     const int row = run_base[m] + (n - m) / run;
-                    put(row, 0, j, pm2);
-                    put(row, 1, j, pm1);
+                    put(out, row, 0, j, pm2);
+                    put(out, row, 1, j, pm1);
+                }
+                if (n - m >= t0 && (n - m - t0) % part == 0) {
+                    const int row = m * 4 + (n - m - t0) / part;
+                    put(tail, row, 0, j, pm2);
+                    put(tail, row, 1, j, pm1);
                 }
                 if (n == T) break;
                 const int n1 = n + 1;
