@@ -44,7 +44,7 @@ void gauss_legendre(int nlat, std::vector<double>& mu, std::vector<double>& w);
 // Recurrence coefficients (a_n, b_n) of the orthonormal P_n^m, [nspec][2], and
 // exact restart rows (P_{n0-1}, P_{n0}) at n0 = m + run r, [row][2][nmu] with
 // row = run_base[m] + r (run_base has T + 2 entries).
-std::vector<double> legendre_coefs(int T);
+void legendre_coefs(int T, std::vector<double>& coef, std::vector<double>& scale);
 std::vector<double> legendre_restarts(int T, int run, int seg, const std::vector<double>& mu,
                                       std::vector<int>& run_base, std::vector<double>& tail);
 
@@ -54,10 +54,12 @@ struct LegTables {
     int T = 0;
     double* d_restart = nullptr;  // [row][2][nhalf], rows every 32 degrees
     double* d_tail = nullptr;     // [m][4][2][nhalf], the four parts of an order's last inverse segment
-    double* d_lcoef = nullptr;    // [nspec(T)][2]
+    double* d_lcoef = nullptr;    // [nspec(T)] and padding
+    double* d_lscale = nullptr;   // [nspec(T)]
     void* d_tiles_f = nullptr;    // forward runs
     void* d_tiles_i = nullptr;    // inverse work
     int ntiles_f = 0, ntiles_i = 0;
+    int fwd_g = 2;                // runs per workgroup of the forward
     int inv_r = 1;                // latitude tiles per wave of the inverse
 };
 

@@ -254,16 +254,15 @@ __global__ void __launch_bounds__(256) k_fft_inverse(const double* __restrict__ 
 
 // Legendre contractions with P_n^m generated on the device.  The table
 // itself (34 MB at T256) is never stored: P follows from the three-term
-// recurrence P_n = a_n mu P_{n-1} - b_n P_{n-2}, restarted from exact host
+// recurrence P_n = s_n Q_n, Q_n = c_n mu Q_{n-1} - Q_{n-2} (the factors s_n are
+// applied to the spectral coefficients), restarted from exact host
 // values every kRun degrees (and, for the inverse, at the quarters of an order's
 // last, shorter segment), which keeps the FP64 recurrence error at a few ulp.
 constexpr int kRun = 32;         // degrees per restart row of the table
 constexpr int kInvSeg = 4 * kRun;  // degrees per inverse segment (at most; four parts)
 constexpr int kInvPad = 8;       // doubles between the parts of a staged segment
 constexpr int kFwdDeg = 32;      // degrees per forward run: two 16-row parity tiles
-constexpr int kFwdLat = 128;     // latitudes per generated forward block
-constexpr int kPtPitch = kFwdLat + 1;  // LDS row pitch of the generated tile (odd: spreads banks)
-constexpr int kFwdGroup = 2;     // runs of one order per forward workgroup
+constexpr int kFwdLat = 64;      // latitudes per generated forward block
 
 // Forward work: nrun consecutive 32-degree runs of order m from degree n0,
 // first restart row `row` (m = -1: an empty slot).  Inverse work: the latitude
@@ -274,14 +273,6 @@ struct LegRun {
 struct LegWork {
     int m, t0, row0;
 };
-
-// value of v in lane l of the wave (l uniform)
-__device__ __forceinline__ double readlane_f64(double v, int l) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)b, l);
-    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
-    return __hiloint2double(hi, lo);
-}
 
 // FP64 MFMA of four independent 4x4x4 blocks (v_mfma_f64_4x4x4f64): with
 // lane = 16 q + 4 b + p, block b takes A[i = p][k = q], B[k = q][j = p] and
@@ -295,29 +286,39 @@ __device__ __forceinline__ double mfma4(double a, double b, double c) {
 
 // Forward: out[b][idx(m, n)] = sum_{j<H} P_n^m(mu_j) EO[m][r][j][c], r the
 // parity of n - m (EO holds the Gauss-weighted even / odd Fourier parts),
-// over the runs of one work item.  Per run the first kFwdLat threads generate
-// the 32 degrees of their latitude into Pt[d][lat] (pitch kPtPitch), one
-// barrier, then every wave contracts.  Wave w = 2 h + r owns degree parity r
-// (16 degrees per run, four groups of 4) and the column groups [h NH,
-// h NH + NH) of 4 columns.  Its MFMA blocks split the latitude sum: block b
-// of k-step s takes latitudes 16 s + 4 b + q, so a lane's B operands are
-// EO[16 s + 4 b + q][4 g + p], 8 x NH values per 128 latitudes, held in
-// registers for the whole work item (larger grids reload them per block); the
-// four blocks' partial sums are added across the row at the end of a run.
-// The next run's restart values and recurrence coefficients (lane d holds
-// degree n0 + d + 1, broadcast by readlane) are loaded before the MFMAs.
+// over the up to G runs of one work item.  Per block of kFwdLat latitudes, wave g
+// generates the 32 degrees of run g, a lane per latitude, into Pt[g][d][lat], one
+// barrier, then every wave contracts all runs.
+// Wave w = 2 h + r owns degree parity r (16 degrees per run, four groups of 4) and
+// the column groups [h NH, h NH + NH) of 4 columns.  Its MFMA blocks split the
+// latitude sum: block b of k-step s takes latitudes 16 s + 4 b + q, so a lane's B
+// operands are EO[16 s + 4 b + q][column], 4 x NH values per 64 latitudes, held in
+// registers for all runs; columns 8 k + 2 p and 8 k + 2 p + 1 of a wave's group pair
+// (one 16-byte load), 8 (NH / 2) + p of its last single group.  The four blocks'
+// partial sums are added across the row at the end.  The recurrence coefficients
+// of a wave's run are uniform and stay in scalar registers.
+//
+// Bound by the FP64 rate, with the generation (two instructions per value, each
+// for up to 32 columns) and the loads of B beside it.  Legendre kernel / whole
+// analysis, against one run after the other over blocks of 128 latitudes, with two
+// waves generating three-operation recurrences behind readlanes, B reloaded for
+// each run by eight-byte loads, and bank conflicts in the operand reads: T1023 on
+// 2048 x 1024, 16 fields 579 -> 385 / 761 -> 569 us; T511 on 1024 x 512, 6 fields 46
+// -> 39 / 66 -> 59; T256 on 512 x 256, 12 fields 16.9 -> 16.0 / 30.8 -> 29.4.
 // Columns [c_off, c_off + C) of EO (row stride Cs), C <= 32.
-template <int NH>
+template <int NH, int G>
 __global__ void __launch_bounds__(256) k_legendre_forward(const LegRun* __restrict__ runs,
                                                           const double* __restrict__ restart,
-                                                          const double2* __restrict__ coef,
+                                                          const double* __restrict__ coef,
+                                                          const double* __restrict__ scale,
                                                           const double* __restrict__ mu,
                                                           const double* __restrict__ EO, double* __restrict__ spec,
                                                           int T, int H, int Cs, int c_off, int C) {
-    __shared__ double Pt[kFwdDeg * kPtPitch];
+    constexpr int kTile = kFwdDeg * kFwdLat, kSteps = kFwdLat / 16;
+    __shared__ double Pt[G * kTile];
     const LegRun rn = runs[blockIdx.x];
     if (rn.m < 0) return;  // padding slot of the XCD-ordered list
-    const int m = rn.m;
+    const int m = rn.m, nrun = rn.nrun;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int p = lane & 3, bq = (lane >> 2) & 3, q = lane >> 4;
@@ -326,93 +327,116 @@ __global__ void __launch_bounds__(256) k_legendre_forward(const LegRun* __restri
     const long long so = spec_offset(T, m);
     const long long ns = nspec_of(T);
     const double* Bsrc = EO + (long long)(m * 2 + r) * eo_plane(H, Cs) + c_off;
-    int bcol[NH];
+    // column of operand g: pairs of groups interleaved, then a single one
+    auto column = [&](int g) { return 4 * h * NH + (g < (NH & ~1) ? 8 * (g / 2) + 2 * p + (g & 1) : 4 * g + p); };
+    int bcol[(NH + 1) / 2];
 #pragma unroll
-    for (int g = 0; g < NH; ++g) bcol[g] = min(4 * (h * NH + g) + p, C - 1);
-    const int nblk = (H + kFwdLat - 1) / kFwdLat;
-    const int nit = rn.nrun * nblk;  // (run, latitude block) iterations
-    const bool gen = tid < kFwdLat;
-    // prefetched inputs of the next iteration's generation
-    auto fetch = [&](int it, double& pm, double& pc, double& x, double2& ab) {
-        const int g = it / nblk, lb = (it - g * nblk) * kFwdLat;
-        const int j = lb + tid;
-        const bool ok = gen && j < H;
-        const long long row = rn.row + g;
-        pm = ok ? restart[(row * 2) * H + j] : 0.0;
-        pc = ok ? restart[(row * 2 + 1) * H + j] : 0.0;
-        x = ok ? mu[j] : 0.0;
-        const int nc = rn.n0 + kFwdDeg * g + (lane & 31) + 1;
-        ab = (nc <= T) ? coef[so + (nc - m)] : make_double2(0.0, 0.0);
+    for (int k = 0; k < (NH + 1) / 2; ++k) bcol[k] = min(column(2 * k), 2 * k + 1 < NH ? C - 2 : C - 1);
+    // generation: run and latitude of this thread
+    const int gg = tid / kFwdLat, gl = tid - gg * kFwdLat;
+    const bool gen = gg < nrun;  // uniform over a wave
+    // recurrence coefficients of the run's degrees, kept in scalar registers (the table
+    // is padded: past degree T they are another order's, for rows that nothing stores)
+    const int gu = __builtin_amdgcn_readfirstlane(min(gg, nrun - 1));
+    const auto cs = (const __attribute__((address_space(4))) double*)(coef + so + (rn.n0 + kFwdDeg * gu + 1 - m));
+    double cn[kFwdDeg];
+#pragma unroll
+    for (int d = 0; d < kFwdDeg; ++d) cn[d] = cs[d];
+    const double* rs = restart + (long long)(rn.row + min(gg, nrun - 1)) * 2 * H;
+    double pm = 0.0, pc = 0.0, x = 0.0;
+    auto fetch = [&](int lb) {
+        const int j = min(lb + gl, H - 1);
+        const bool ok = gen && lb + gl < H;
+        const double a = rs[j], c = rs[H + j];
+        pm = ok ? a : 0.0;
+        pc = ok ? c : 0.0;
+        x = mu[j];
     };
-    double pm_n, pc_n, x_n;
-    double2 ab_n;
-    fetch(0, pm_n, pc_n, x_n, ab_n);
-    double bf[kFwdLat / 16][NH];
-    double acc[4][NH];
+    fetch(0);
+    double acc[G][4][NH];
 #pragma unroll
-    for (int d = 0; d < 4; ++d)
+    for (int g = 0; g < G; ++g)
 #pragma unroll
-        for (int g = 0; g < NH; ++g) acc[d][g] = 0.0;
-    // A operand of degree group d, k-step s: Pt row 2 (4 d + p) + r, latitude 16 s + 4 bq + q
-    const double* Ap = Pt + (2 * p + r) * kPtPitch + 4 * bq + q;
-    for (int it = 0; it < nit; ++it) {
-        const int g = it / nblk, blk = it - g * nblk;
-        const int lb = blk * kFwdLat;
-        if (it == 0 || nblk > 1) {
+        for (int d = 0; d < 4; ++d)
 #pragma unroll
-            for (int s = 0; s < kFwdLat / 16; ++s) {
-                const int j = lb + 16 * s + 4 * bq + q;
+            for (int c = 0; c < NH; ++c) acc[g][d][c] = 0.0;
+    // Degree d = 2 (4 k + p) + r keeps latitude l at Pt[g][d][l ^ swz(p)], so that the
+    // 32 values which half a wave reads at once (p, two q, bq) lie in different banks.
+    // A operand of run g, degree group d, k-step s: row 2 (4 d + p) + r, latitude 16 s + 4 bq + q
+    auto swz = [](int pp) { return 2 * (pp & 1) + 16 * (pp >> 1); };
+    const double* Ap = Pt + (2 * p + r) * kFwdLat + ((4 * bq + q) ^ (2 * (p & 1)));
+    const double *A0 = Ap + 16 * (p >> 1), *A1 = Ap - 16 * (p >> 1);  // even and odd s
+    for (int lb = 0; lb < H; lb += kFwdLat) {
+        // latitudes past the last one: any value, the generated ones are zero there
+        double bf[kSteps][NH];
 #pragma unroll
-                for (int c = 0; c < NH; ++c) bf[s][c] = (j < H) ? Bsrc[(long long)j * Cs + bcol[c]] : 0.0;
+        for (int s = 0; s < kSteps; ++s) {
+            const int row = min(lb + 16 * s + 4 * bq + q, H - 1) * Cs;
+#pragma unroll
+            for (int k = 0; k < (NH + 1) / 2; ++k) {
+                if (2 * k + 1 < NH) {
+                    const double2 v = *reinterpret_cast<const double2*>(Bsrc + (row + bcol[k]));
+                    bf[s][2 * k] = v.x;
+                    bf[s][2 * k + 1] = v.y;
+                } else {
+                    bf[s][2 * k] = Bsrc[row + bcol[k]];
+                }
             }
         }
-        if (it > 0) __syncthreads();  // the previous tile is consumed
+        __syncthreads();  // the previous tiles are consumed
         if (gen) {
-            double pm = pm_n, pc = pc_n;
-            const double x = x_n;
-            const double2 ab = ab_n;
+            double* to = Pt + gg * kTile;
 #pragma unroll
             for (int d = 0; d < kFwdDeg; ++d) {
-                Pt[d * kPtPitch + tid] = pc;  // zero beyond T (zero coefficients there) and beyond H
-                const double ca = readlane_f64(ab.x, d), cb = readlane_f64(ab.y, d);
-                const double nx = fma(ca * x, pc, -cb * pm);
+                to[d * kFwdLat + (gl ^ swz((d >> 1) & 3))] = pc;  // zero beyond H
+                const double nx = fma(cn[d] * x, pc, -pm);
                 pm = pc;
                 pc = nx;
             }
         }
-        if (it + 1 < nit) fetch(it + 1, pm_n, pc_n, x_n, ab_n);
+        fetch(lb + kFwdLat);
         __syncthreads();
-        if (busy) {
+        if (!busy) continue;
 #pragma unroll
-            for (int s = 0; s < kFwdLat / 16; ++s) {
+        for (int g = 0; g < G; ++g) {
+            if (g >= nrun) continue;
+#pragma unroll
+            for (int s = 0; s < kSteps; ++s) {
                 double av[4];
 #pragma unroll
-                for (int d = 0; d < 4; ++d) av[d] = Ap[8 * d * kPtPitch + 16 * s];
+                for (int d = 0; d < 4; ++d) av[d] = (s & 1 ? A1 : A0)[g * kTile + 8 * d * kFwdLat + 16 * s];
 #pragma unroll
                 for (int d = 0; d < 4; ++d)
 #pragma unroll
-                    for (int c = 0; c < NH; ++c) acc[d][c] = mfma4(av[d], bf[s][c], acc[d][c]);
+                    for (int c = 0; c < NH; ++c) acc[g][d][c] = mfma4(av[d], bf[s][c], acc[g][d][c]);
             }
         }
-        if (blk == nblk - 1) {
-            // lane 16 q + 4 bq + p holds block bq's partial D[degree q][column p]
-            // of each group; the row's four blocks are added by two exchanges
-            const int n0 = rn.n0 + kFwdDeg * g;
+    }
+    // lane 16 q + 4 bq + p holds block bq's partial D[degree q][column p] of each
+    // degree group; the row's four blocks are added by two exchanges, and lane bq
+    // keeps degree group bq
 #pragma unroll
-            for (int d = 0; d < 4; ++d)
+    for (int g = 0; g < G; ++g) {
+        double v[NH];
 #pragma unroll
-                for (int c = 0; c < NH; ++c) {
-                    double v = acc[d][c];
-                    v += __shfl_xor(v, 4);
-                    v += __shfl_xor(v, 8);
-                    acc[d][c] = 0.0;
-                    const int col = 4 * (h * NH + c) + p;
-                    const int n = n0 + 2 * (4 * d + q) + r;
-                    if (busy && bq == 0 && col < C && n <= T) {
-                        const int b = (c_off + col) >> 1, ri = (c_off + col) & 1;
-                        spec[((long long)b * ns + so + (n - m)) * 2 + ri] = v;
-                    }
-                }
+        for (int c = 0; c < NH; ++c)
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                double w = acc[g][d][c];
+                w += __shfl_xor(w, 4);
+                w += __shfl_xor(w, 8);
+                v[c] = d == 0 || bq == d ? w : v[c];
+            }
+        const int n = rn.n0 + kFwdDeg * g + 2 * (4 * bq + q) + r;
+        if (!busy || n > T || g >= nrun) continue;
+        const double sn = scale[so + (n - m)];
+#pragma unroll
+        for (int c = 0; c < NH; c += 2) {
+            const int col = column(c);
+            if (col >= C) continue;
+            double* to = spec + (((c_off + col) >> 1) * ns + so + (n - m)) * 2;
+            if (c + 1 < NH) *reinterpret_cast<double2*>(to) = make_double2(sn * v[c], sn * v[c + 1]);  // a field's re, im
+            else to[col & 1] = sn * v[c];
         }
     }
 }
@@ -432,30 +456,30 @@ __global__ void __launch_bounds__(256) k_legendre_forward(const LegRun* __restri
 // column per p = lane & 3: columns 8 h + 2 p and 8 h + 2 p + 1 of a group pair
 // (one 16-byte LDS read), 8 (NG / 2) + p of a last single group.  Result D[q][p] of
 // lane 16 q + 4 b + p is latitude 4 b + q and that column.
-// The parts are staged kInvPad doubles (and one coefficient) apart, so that the
+// The parts are staged kInvPad doubles (and two coefficients) apart, so that the
 // four a wave reads at once lie in different banks.  Degrees past the segment need
-// no checks: their recurrence coefficients, restart values and staged columns are
-// zero.
+// no checks: their staged columns are zero.
 //
 // Bound by the FP64 rate, which matrix and vector instructions share (the 4x4x4
-// shape reaches 70 of the card's 71.5 TFLOP/s, the 16x16x4 shape 48), plus three
-// recurrence instructions per two to sixteen MFMAs.  Legendre kernel / whole
-// inverse transform, against one workgroup per segment with the partial sums added
+// shape reaches 70 of the card's 71.5 TFLOP/s, the 16x16x4 shape 48), plus two
+// recurrence instructions per one to eight MFMAs.  Legendre kernel / whole
+// synthesis, against one workgroup per segment with the partial sums added
 // by the FFT (and the 16x16x4 shape above 128 northern latitudes): T1023 on 2048 x
-// 1024, 16 fields 599 -> 377 / 1093 -> 582 us; T511 on 1024 x 512, 6 fields 51 -> 28
-// / 88 -> 49; T256 on 512 x 256, 12 fields 19.1 -> 15.2 / 36.3 -> 28.4.
+// 1024, 16 fields 597 -> 369 / 1090 -> 576 us; T511 on 1024 x 512, 6 fields 51 -> 26
+// / 88 -> 48; T256 on 512 x 256, 12 fields 19.1 -> 15.2 / 36.3 -> 28.4.
 template <int NG, int R>
 __global__ void __launch_bounds__(256) k_legendre_inverse(const LegWork* __restrict__ work,
                                                           const double* __restrict__ restart,
                                                           const double* __restrict__ tail,
-                                                          const double2* __restrict__ coef,
+                                                          const double* __restrict__ coef,
+                                                          const double* __restrict__ scale,
                                                           const double* __restrict__ mu,
                                                           const double* __restrict__ spec,
                                                           double* __restrict__ Fw, int T, int nlat, int H, int Cs,
                                                           int c_off, int C) {
     constexpr int kCp = 4 * NG, kPart = kRun * kCp + kInvPad;  // pitches of a degree and of a part
     extern __shared__ double Sm[];                             // [4][kPart]
-    double2* cf = reinterpret_cast<double2*>(Sm + 4 * kPart);  // [4][kRun + 1]
+    double* cf = Sm + 4 * kPart;                               // [4][kRun + 2]: degrees 1 .. kRun of a part
     const LegWork wk = work[blockIdx.x];
     if (wk.m < 0) return;  // padding slot of the XCD-ordered list
     const int m = wk.m, L = T + 1 - m, tid = threadIdx.x;
@@ -469,14 +493,15 @@ __global__ void __launch_bounds__(256) k_legendre_inverse(const LegWork* __restr
     // one segment's inputs: double `tid` of every field's run of coefficients (all
     // coalesced), a recurrence coefficient, the lane's restart values
     double v[2 * NG], pv[R], cu[R], x[R];
-    double2 cv;
-    const int cpart = tid / (kRun + 1), cdeg = tid - cpart * (kRun + 1);
+    double cv, sv;
+    const int cpart = tid / kRun, cdeg = tid - cpart * kRun + 1;
     auto fetch = [&](int n0) {
         const int Ls = min(kInvSeg, L - n0), Lp = 8 * ((Ls + 31) / 32);
 #pragma unroll
         for (int f = 0; f < 2 * NG; ++f) v[f] = (tid < 2 * Ls && f < nb) ? sp[2 * (f * ns + n0)] : 0.0;
         const int d = cpart * Lp + cdeg;
-        cv = (cpart < 4 && d >= 1 && d < Ls) ? coef[so + n0 + d] : make_double2(0.0, 0.0);
+        cv = (cpart < 4 && d < Ls) ? coef[so + n0 + d] : 0.0;
+        sv = tid < 2 * Ls ? scale[so + n0 + (tid >> 1)] : 0.0;
         const double* rs = Ls == kInvSeg ? restart + (long long)(wk.row0 + n0 / kRun + kq) * 2 * H
                                          : tail + (long long)(m * 4 + kq) * 2 * H;
 #pragma unroll
@@ -502,9 +527,9 @@ __global__ void __launch_bounds__(256) k_legendre_inverse(const LegWork* __restr
             double* to = Sm + part * kPart + (d - part * Lp) * kCp + (tid & 1);
             if (part < 4) {
 #pragma unroll
-                for (int f = 0; f < 2 * NG; ++f) to[2 * f] = v[f];
+                for (int f = 0; f < 2 * NG; ++f) to[2 * f] = sv * v[f];
             }
-            if (cpart < 4) cf[tid] = cv;
+            if (cpart < 4) cf[cpart * (kRun + 2) + cdeg - 1] = cv;
         }
         double pa[R], ca[R];
 #pragma unroll
@@ -515,18 +540,18 @@ __global__ void __launch_bounds__(256) k_legendre_inverse(const LegWork* __restr
         if (n0 + kInvSeg < L) fetch(n0 + kInvSeg);
         __syncthreads();
         const double* B = Sm + kq * kPart;
-        const double2* c = cf + kq * (kRun + 1);
+        const double* c = cf + kq * (kRun + 2);
         for (int s0 = 0; s0 < Lp; s0 += 8) {
 #pragma unroll
             for (int u = 0; u < 8; u += 2) {
                 const int s = s0 + u;
-                const double2 c1 = c[s + 1], c2 = c[s + 2];
+                const double2 cc = *reinterpret_cast<const double2*>(c + s);  // degrees s + 1, s + 2
                 double a_e[R], a_o[R];
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     a_e[r] = ca[r];
-                    a_o[r] = fma(c1.x * x[r], ca[r], -c1.y * pa[r]);
-                    ca[r] = fma(c2.x * x[r], a_o[r], -c2.y * a_e[r]);
+                    a_o[r] = fma(cc.x * x[r], ca[r], -pa[r]);
+                    ca[r] = fma(cc.y * x[r], a_o[r], -a_e[r]);
                     pa[r] = a_o[r];
                 }
                 const double* be = B + s * kCp;
@@ -665,7 +690,7 @@ __global__ void __launch_bounds__(256) k_uv_spec_to_vd(const double2* __restrict
 
 
 size_t inverse_lds(int ng) {
-    return sizeof(double) * (4 * (size_t)(kRun * 4 * ng + kInvPad) + 2 * 4 * (size_t)(kRun + 1));
+    return sizeof(double) * (4 * (size_t)(kRun * 4 * ng + kInvPad) + 4 * (size_t)(kRun + 2));
 }
 
 }  // namespace
@@ -685,23 +710,30 @@ int leg_build(rexi_plan* pl, LegTables& t, int Tt, const std::vector<double>& no
     std::vector<int> run_base;
     std::vector<double> tail;
     std::vector<double> restart = legendre_restarts(Tt, kRun, kInvSeg, north, run_base, tail);
-    std::vector<double> lcoef = legendre_coefs(Tt);
-    // forward: one workgroup per kFwdGroup consecutive 32-degree runs of an
-    // order.  Workgroups go to the eight
+    std::vector<double> lcoef, lscale;
+    legendre_coefs(Tt, lcoef, lscale);
+    lcoef.resize(lcoef.size() + kFwdDeg + 1, 0.0);  // a forward run reads past the last order
+    // forward: one workgroup per G consecutive 32-degree runs of an order: four,
+    // which load the order's Fourier block half as often, where that leaves 16
+    // workgroups per CU (T1023: 388 us against 398 for two; T511 41.6 against 39.2,
+    // T300 18.9 against 16.5, so two there).  Workgroups go to the eight
     // XCDs round-robin by index, so slot s is filled from the queue of XCD
     // s % 8, which holds the runs of the orders m = s (mod 8), longest orders
     // first: all runs of an order share one XCD and its L2, where the order's
     // Fourier block is read from HBM once.  Queues that run out early are
     // padded with empty slots (m = -1).
     constexpr int kXcd = 8;
+    int fours = 0;
+    for (int m = 0; m <= T; ++m) fours += (Tt - m) / (4 * kFwdDeg) + 1;
+    t.fwd_g = fours >= 4096 ? 4 : 2;
     std::vector<std::vector<LegRun>> q(kXcd);
     for (int m = 0; m <= T; ++m) {
         const int nr = (Tt - m) / kFwdDeg + 1;
-        for (int r = 0; r < nr; r += kFwdGroup)
+        for (int r = 0; r < nr; r += t.fwd_g)
             q[m % kXcd].push_back(LegRun{m, m + kFwdDeg * r, run_base[m] + r * (kFwdDeg / kRun),
-                                         std::min(kFwdGroup, nr - r)});
+                                         std::min(t.fwd_g, nr - r)});
     }
-    // within a queue, two-run items before one-run items (the longest
+    // within a queue, items of more runs before those of fewer (the longest
     // orders still first among equals): the short items fill in at the end
     for (auto& v : q)
         std::stable_sort(v.begin(), v.end(), [](const LegRun& a, const LegRun& b) { return a.nrun > b.nrun; });
@@ -725,12 +757,14 @@ int leg_build(rexi_plan* pl, LegTables& t, int Tt, const std::vector<double>& no
     int rc = device_alloc((void**)&t.d_restart, restart.size() * sizeof(double));
     if (!rc) rc = device_alloc((void**)&t.d_tail, tail.size() * sizeof(double));
     if (!rc) rc = device_alloc((void**)&t.d_lcoef, lcoef.size() * sizeof(double));
+    if (!rc) rc = device_alloc((void**)&t.d_lscale, lscale.size() * sizeof(double));
     if (!rc) rc = device_alloc((void**)&t.d_tiles_f, tf.size() * sizeof(LegRun));
     if (!rc) rc = device_alloc((void**)&t.d_tiles_i, ti.size() * sizeof(LegWork));
     if (rc) return rc;
     REXI_HIP(hipMemcpy(t.d_restart, restart.data(), restart.size() * sizeof(double), hipMemcpyHostToDevice));
     REXI_HIP(hipMemcpy(t.d_tail, tail.data(), tail.size() * sizeof(double), hipMemcpyHostToDevice));
     REXI_HIP(hipMemcpy(t.d_lcoef, lcoef.data(), lcoef.size() * sizeof(double), hipMemcpyHostToDevice));
+    REXI_HIP(hipMemcpy(t.d_lscale, lscale.data(), lscale.size() * sizeof(double), hipMemcpyHostToDevice));
     REXI_HIP(hipMemcpy(t.d_tiles_f, tf.data(), tf.size() * sizeof(LegRun), hipMemcpyHostToDevice));
     REXI_HIP(hipMemcpy(t.d_tiles_i, ti.data(), ti.size() * sizeof(LegWork), hipMemcpyHostToDevice));
     t.ntiles_f = (int)tf.size();
@@ -739,7 +773,7 @@ int leg_build(rexi_plan* pl, LegTables& t, int Tt, const std::vector<double>& no
 }
 
 void leg_release(LegTables& t) {
-    void* ptrs[] = {t.d_restart, t.d_tail, t.d_lcoef, t.d_tiles_f, t.d_tiles_i};
+    void* ptrs[] = {t.d_restart, t.d_tail, t.d_lcoef, t.d_lscale, t.d_tiles_f, t.d_tiles_i};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     t = LegTables{};
@@ -778,24 +812,21 @@ int fft_inverse(rexi_plan* pl, double* grid, int nf, const double* rs, hipStream
     return REXI_OK;
 }
 
+template <int NH>
+void launch_forward(rexi_plan* pl, const LegTables& t, double* spec, int C, int c0, int w, hipStream_t s) {
+    const auto k = t.fwd_g == 4 ? k_legendre_forward<NH, 4> : k_legendre_forward<NH, 2>;
+    hipLaunchKernelGGL(k, dim3(t.ntiles_f), dim3(256), 0, s, (const LegRun*)t.d_tiles_f, t.d_restart, t.d_lcoef,
+                       t.d_lscale, pl->d_mu, pl->d_four, spec, t.T, pl->nhalf, C, c0, w);
+}
+
 // EO (C columns) -> spec [C/2][nspec(t.T)], in launches of at most 32 columns;
 // each wave takes half of a launch's four-column groups
 int leg_forward(rexi_plan* pl, const LegTables& t, double* spec, int C, hipStream_t s) {
-    const double2* coef = reinterpret_cast<const double2*>(t.d_lcoef);
+    using Launcher = void (*)(rexi_plan*, const LegTables&, double*, int, int, int, hipStream_t);
+    static constexpr Launcher of[4] = {launch_forward<1>, launch_forward<2>, launch_forward<3>, launch_forward<4>};
     for (int c0 = 0; c0 < C; c0 += 32) {
         const int w = std::min(32, C - c0);
-        const int nh = ((w + 3) / 4 + 1) / 2;  // column groups per wave, 1..4
-        const dim3 g(t.ntiles_f), b(256);
-        const LegRun* rl = (const LegRun*)t.d_tiles_f;
-#define REXI_FWD(NH_)                                                                                           \
-    if (nh == NH_)                                                                                              \
-    hipLaunchKernelGGL(k_legendre_forward<NH_>, g, b, 0, s, rl, t.d_restart, coef, pl->d_mu, pl->d_four, spec, \
-                       t.T, pl->nhalf, C, c0, w)
-        REXI_FWD(1);
-        REXI_FWD(2);
-        REXI_FWD(3);
-        REXI_FWD(4);
-#undef REXI_FWD
+        of[((w + 3) / 4 + 1) / 2 - 1](pl, t, spec, C, c0, w, s);
         REXI_HIP(hipGetLastError());
     }
     return REXI_OK;
@@ -805,7 +836,7 @@ template <int NG>
 void launch_inverse(rexi_plan* pl, const LegTables& t, const double* spec, int C, int c0, int w, hipStream_t s) {
     const auto k = t.inv_r == 2 ? k_legendre_inverse<NG, 2> : k_legendre_inverse<NG, 1>;
     hipLaunchKernelGGL(k, dim3(t.ntiles_i), dim3(256), inverse_lds(NG), s, (const LegWork*)t.d_tiles_i, t.d_restart,
-                       t.d_tail, reinterpret_cast<const double2*>(t.d_lcoef), pl->d_mu, spec, pl->d_four, t.T,
+                       t.d_tail, t.d_lcoef, t.d_lscale, pl->d_mu, spec, pl->d_four, t.T,
                        pl->nlat, pl->nhalf, C, c0, w);
 }
 

@@ -46,30 +46,44 @@ void gauss_legendre(int nlat, std::vector<double>& mu, std::vector<double>& w) {
 
 // Orthonormal associated Legendre functions by the three-term recurrence in n:
 //   P_m^m = (1/sqrt2) prod_{k=1}^{m} sqrt((2k+1)/(2k)) (1-mu^2)^{m/2},
-//   P_n^m = (mu P_{n-1}^m - e_{n-1} P_{n-2}^m) / e_n,  e_n = sqrt((n^2-m^2)/(4n^2-1)),
-// i.e. P_n = a_n mu P_{n-1} - b_n P_{n-2} with a_n = 1/e_n, b_n = e_{n-1}/e_n
-// (e_m = 0).  The device runs this recurrence itself; the host supplies the
-// coefficients and, every `run` degrees, exact restart values.
-
-// (a_n, b_n) for n > m in spectral order, [nspec][2] (zeros at n = m).
-std::vector<double> legendre_coefs(int T) {
-    std::vector<double> out(2 * (size_t)nspec_of(T), 0.0);
-    for (int m = 0; m <= T; ++m) {
-        const size_t base = (size_t)spec_offset(T, m);
-        for (int n = m + 1; n <= T; ++n) {
-            const long double en = sqrtl((long double)(n * n - m * m) / (4.0L * n * n - 1));
-            const long double en1 =
-                (n - 1 > m) ? sqrtl((long double)((n - 1) * (n - 1) - m * m) / (4.0L * (n - 1) * (n - 1) - 1)) : 0.0L;
-            out[2 * (base + n - m)] = (double)(1.0L / en);
-            out[2 * (base + n - m) + 1] = (double)(en1 / en);
-        }
+//   P_n^m = (mu P_{n-1}^m - e_{n-1} P_{n-2}^m) / e_n,  e_n = sqrt((n^2-m^2)/(4n^2-1))
+// (e_m = 0).  With P_n = s_n Q_n, s_m = s_{m+1} = 1 and s_n = (e_{n-1} / e_n) s_{n-2}
+// it has one coefficient,
+//   Q_n = c_n mu Q_{n-1} - Q_{n-2},  c_n = s_{n-1} / (e_n s_n),
+// two operations per value instead of three (s_n falls from 1 to about 0.2 over
+// 1024 degrees).  The device runs this recurrence itself; the host supplies c_n, s_n
+// and, every `run` degrees, exact restart values of Q.
+namespace {
+// c_n (0 at n = m) and s_n of order m, index n - m
+void order_coefs(int T, int m, std::vector<long double>& c, std::vector<long double>& s) {
+    c.assign(T + 1 - m, 0.0L);
+    s.assign(T + 1 - m, 1.0L);
+    long double before = 0;  // e_{n-1}
+    for (int n = m + 1; n <= T; ++n) {
+        const long double e = sqrtl((long double)(n * n - m * m) / (4.0L * n * n - 1));
+        const int k = n - m;
+        if (k > 1) s[k] = before / e * s[k - 2];
+        c[k] = s[k - 1] / (e * s[k]);
+        before = e;
     }
-    return out;
+}
+}  // namespace
+
+// c_n and s_n in spectral order, [nspec] each.
+void legendre_coefs(int T, std::vector<double>& coef, std::vector<double>& scale) {
+    coef.clear();
+    scale.clear();
+    std::vector<long double> c, s;
+    for (int m = 0; m <= T; ++m) {
+        order_coefs(T, m, c, s);
+        coef.insert(coef.end(), c.begin(), c.end());
+        scale.insert(scale.end(), s.begin(), s.end());
+    }
 }
 
 // Restart rows for runs of `run` degrees: for every order m and run r with
-// n0 = m + run r <= T, row (run_base[m] + r) holds P_{n0-1}(mu_j) (0 at n0 = m)
-// and P_{n0}(mu_j), layout [row][2][nmu].  Long double (its exponent range
+// n0 = m + run r <= T, row (run_base[m] + r) holds Q_{n0-1}(mu_j) (0 at n0 = m)
+// and Q_{n0}(mu_j), layout [row][2][nmu].  Long double (its exponent range
 // holds the seeds down to the Gaussian latitude nearest a pole at T = 1023);
 // values below 1e-300 are stored as 0.  tail: the same at the four parts of an
 // order's last segment of `seg` degrees where that one is not whole, layout
@@ -87,32 +101,31 @@ std::vector<double> legendre_restarts(int T, int run, int seg, const std::vector
         if (fabs(d) < 1e-300) d = 0.0;
         to[((size_t)row * 2 + which) * nmu + j] = d;
     };
-    for (int j = 0; j < nmu; ++j) {
-        const long double x = mu[j];
-        const long double s = sqrtl(fmaxl(0.0L, 1 - x * x));
-        long double pmm = 1.0L / sqrtl(2.0L);
-        for (int m = 0; m <= T; ++m) {
-            if (m > 0) pmm *= sqrtl((2.0L * m + 1) / (2.0L * m)) * s;
-            const int L = T + 1 - m, t0 = L / seg * seg, part = 8 * ((L - t0 + 31) / 32);  // tail from m + t0
-            long double pm2 = 0, pm1 = pmm;  // P_{n-1}, P_n at n = m
-            for (int n = m;; ++n) {
-                if ((n - m) % run == 0) {
-                    const int row = run_base[m] + (n - m) / run;
-                    put(out, row, 0, j, pm2);
-                    put(out, row, 1, j, pm1);
+    std::vector<long double> pmm(nmu, 1.0L / sqrtl(2.0L)), cosine(nmu), c, s;
+    for (int j = 0; j < nmu; ++j) cosine[j] = sqrtl(fmaxl(0.0L, 1 - (long double)mu[j] * mu[j]));
+    for (int m = 0; m <= T; ++m) {
+        order_coefs(T, m, c, s);
+        const long double up = m > 0 ? sqrtl((2.0L * m + 1) / (2.0L * m)) : 1.0L;
+        const int L = T + 1 - m, t0 = L / seg * seg, part = 8 * ((L - t0 + 31) / 32);  // tail from m + t0
+        for (int j = 0; j < nmu; ++j) {
+            if (m > 0) pmm[j] *= up * cosine[j];
+            const long double x = mu[j];
+            long double q2 = 0, q1 = pmm[j];  // Q_{n-1}, Q_n at n = m
+            for (int k = 0;; ++k) {
+                if (k % run == 0) {
+                    const int row = run_base[m] + k / run;
+                    put(out, row, 0, j, q2);
+                    put(out, row, 1, j, q1);
                 }
-                if (n - m >= t0 && (n - m - t0) % part == 0) {
-                    const int row = m * 4 + (n - m - t0) / part;
-                    put(tail, row, 0, j, pm2);
-                    put(tail, row, 1, j, pm1);
+                if (k >= t0 && (k - t0) % part == 0) {
+                    const int row = m * 4 + (k - t0) / part;
+                    put(tail, row, 0, j, q2);
+                    put(tail, row, 1, j, q1);
                 }
-                if (n == T) break;
-                const int n1 = n + 1;
-                const long double en = sqrtl((long double)(n1 * n1 - m * m) / (4.0L * n1 * n1 - 1));
-                const long double en1 = (n > m) ? sqrtl((long double)(n * n - m * m) / (4.0L * n * n - 1)) : 0.0L;
-                const long double pn = (x * pm1 - en1 * pm2) / en;
-                pm2 = pm1;
-                pm1 = pn;
+                if (k == L - 1) break;
+                const long double q = c[k + 1] * x * q1 - q2;
+                q2 = q1;
+                q1 = q;
             }
         }
     }
