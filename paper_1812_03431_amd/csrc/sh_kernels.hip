@@ -5,8 +5,7 @@
 // (the m = 0 term uses Re(xi_n^0)).
 //
 // Longitude: one workgroup per pair of grid rows j, j' = nlat-1-j runs one
-// complex FFT of length nlon (radix-2 stages taken in pairs) in LDS for both
-// rows.  Latitude: per
+// complex FFT of length nlon in registers for both rows.  Latitude: per
 // zonal order m the Legendre sum is a small dense contraction (T+1-m degrees
 // x nlat/2 latitudes x 2B real columns) and runs on FP64 MFMA
 // (v_mfma_f64_16x16x4f64).  Gauss latitudes are symmetric about the equator
@@ -22,6 +21,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "internal.hpp"
 
@@ -30,8 +30,6 @@ namespace {
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
-
-__device__ __forceinline__ int bitrev(int x, int bits) { return (int)(__brev((unsigned)x) >> (32 - bits)); }
 
 // Plane strides of the Fourier workspace, in doubles: an EO plane [j][c] of one
 // (order, parity) and an order's plane [row][c] are padded by kFourPad so that
@@ -43,68 +41,149 @@ __host__ __device__ __forceinline__ long long fw_plane(int nlat, int C) { return
 __device__ __forceinline__ double2 cmul(double2 w, double2 v) {
     return make_double2(fma(w.x, v.x, -w.y * v.y), fma(w.x, v.y, w.y * v.x));
 }
+__device__ __forceinline__ double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
+__device__ __forceinline__ double2 csub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
 
-__device__ __forceinline__ double2 twiddle(const double2* tw, int k, bool inverse) {
-    double2 w = tw[k];
-    if (inverse) w.y = -w.y;
-    return w;
-}
+// FFT of 2^BITS points, kE of them per thread in registers: radix-8, -4 and -2
+// passes in self-sorting (Stockham) order.  Before pass p, of radix r, after passes
+// of product L, thread t holds x[t + kT i], i < kE; its butterfly b takes j = t + kT b,
+// u = j mod L, the inputs x[j + k n / r] with twiddles exp(-2 pi i u k / (L r)),
+// k < r, and its outputs go to y[(j - u) r + u + k L].  So the first pass's inputs and
+// the last pass's outputs are in natural order, a wave's part contiguous, and the
+// data cross the LDS once between two passes (n = 512: two times, n = 2048: three),
+// one FFT per wave or less up to n = 512, where no barrier is needed.
+template <int BITS>
+struct Fft {
+    static constexpr int kN = 1 << BITS;
+    static constexpr int kE = kN < 8 ? kN : 8;             // points per thread
+    static constexpr int kT = kN / kE;                     // threads per FFT
+    // threads per workgroup: at least two fields, whose orders are then 32 bytes, up to
+    // n = 2048 (there 512 / 256 threads: 510 / 532 us an analysis of 16 fields at
+    // T1023), and not more than that needs (n = 512, 12 fields at T256: 256 / 512 /
+    // 1024 threads 24.9 / 25.1 / 28.1 us)
+    static constexpr int kBlock = kT > 128 ? 512 : 256;
+    static constexpr int kF = kBlock / kT;                 // FFTs per workgroup
+    static constexpr int kPasses = (BITS + 2) / 3;
+    // one point of padding every eight: neither the strided writes nor the reads meet in a bank
+    static constexpr int kPitch = kN + (kN + 7) / 8;
+    static __device__ __forceinline__ int at(int i) { return i + (i >> 3); }
+    static constexpr int radix_bits(int pass) { return BITS / kPasses + (pass < BITS % kPasses); }
+    static constexpr int before_bits(int pass) {
+        int b = 0;
+        for (int p = 0; p < pass; ++p) b += radix_bits(p);
+        return b;
+    }
 
-// In-place decimation-in-time FFTs of nb arrays X + f n, f < nb, in LDS (input
-// already in bit-reversed order); n = 2^bits.  tw[k] = exp(-2 pi i k / n),
-// k < n/2; conj for the inverse direction.  Two radix-2 stages at a time: the
-// butterflies of half-lengths h and 2h over the four elements pos + {0, h, 2h,
-// 3h} of a block of 4h are one radix-4 step with the same arithmetic and
-// twiddles, so a stage pair needs one barrier instead of two.  An odd number of
-// stages starts with one radix-2 stage.  The FFTs are bound by the latency of
-// their barrier-separated stages (11 -> 6 barriers at n = 2048).
-__device__ void fft_lds(double2* X, const double2* tw, int bits, int nb, bool inverse) {
-    const int n = 1 << bits, hb = bits - 1;
-    int lh = 0;  // half-length 2^lh of the next radix-2 stage
-    if (bits & 1) {
-        const double2 w = twiddle(tw, 0, inverse);
-        for (int t = threadIdx.x; t < (nb << hb); t += blockDim.x) {
-            const int i = 2 * t, j = i + 1;
-            const double2 u = X[i], v = cmul(w, X[j]);
-            X[i] = make_double2(u.x + v.x, u.y + v.y);
-            X[j] = make_double2(u.x - v.x, u.y - v.y);
+    // orders the LDS accesses of an FFT's threads
+    static __device__ __forceinline__ void sync() {
+        if constexpr (kT > 64) {
+            __syncthreads();
+        } else {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
-        __syncthreads();
-        lh = 1;
     }
-    for (; lh + 2 <= bits; lh += 2) {
-        const int h = 1 << lh, q = hb - 1;  // n/4 = 2^q radix-4 steps per array
-        for (int t = threadIdx.x; t < (nb << q); t += blockDim.x) {
-            const int f = t >> q, tt = t & ((1 << q) - 1);
-            const int grp = tt >> lh, pos = tt & (h - 1);
-            const int i0 = f * n + (grp << (lh + 2)) + pos, i1 = i0 + h, i2 = i1 + h, i3 = i2 + h;
-            const double2 w1 = twiddle(tw, pos << (hb - lh), inverse);
-            const double2 w2 = twiddle(tw, pos << (q - lh), inverse);
-            const double2 w3 = twiddle(tw, (pos + h) << (q - lh), inverse);
-            const double2 a0 = X[i0], a2 = X[i2];
-            const double2 t1 = cmul(w1, X[i1]), t3 = cmul(w1, X[i3]);
-            const double2 c0 = make_double2(a0.x + t1.x, a0.y + t1.y), c1 = make_double2(a0.x - t1.x, a0.y - t1.y);
-            const double2 c2 = make_double2(a2.x + t3.x, a2.y + t3.y), c3 = make_double2(a2.x - t3.x, a2.y - t3.y);
-            const double2 u = cmul(w2, c2), v = cmul(w3, c3);
-            X[i0] = make_double2(c0.x + u.x, c0.y + u.y);
-            X[i2] = make_double2(c0.x - u.x, c0.y - u.y);
-            X[i1] = make_double2(c1.x + v.x, c1.y + v.y);
-            X[i3] = make_double2(c1.x - v.x, c1.y - v.y);
+
+    // -i v (forward) or i v
+    template <bool INV>
+    static __device__ __forceinline__ double2 quarter(double2 v) {
+        return INV ? make_double2(-v.y, v.x) : make_double2(v.y, -v.x);
+    }
+
+    template <bool INV, int R, int S>
+    static __device__ __forceinline__ void dft(double2 (&x)[kE], int b) {  // of x[b + S k], k < R
+        if constexpr (R == 2) {
+            const double2 a = x[b], c = x[b + S];
+            x[b] = cadd(a, c);
+            x[b + S] = csub(a, c);
+        } else if constexpr (R == 4) {
+            const double2 a = cadd(x[b], x[b + 2 * S]), c = csub(x[b], x[b + 2 * S]);
+            const double2 d = cadd(x[b + S], x[b + 3 * S]), e = quarter<INV>(csub(x[b + S], x[b + 3 * S]));
+            x[b] = cadd(a, d);
+            x[b + S] = cadd(c, e);
+            x[b + 2 * S] = csub(a, d);
+            x[b + 3 * S] = csub(c, e);
+        } else {
+            // two radix-4 butterflies of the even and odd inputs, then radix 2
+            dft<INV, 4, 2 * S>(x, b);
+            dft<INV, 4, 2 * S>(x, b + S);
+            const double h = 0.70710678118654752440;
+            const double2 o1 = x[b + 3 * S], o3 = x[b + 7 * S];
+            const double2 q1 = quarter<INV>(o1), q3 = quarter<INV>(o3);
+            const double2 w0 = x[b + S], w1 = make_double2(h * (o1.x + q1.x), h * (o1.y + q1.y));
+            const double2 w2 = quarter<INV>(x[b + 5 * S]), w3 = make_double2(h * (q3.x - o3.x), h * (q3.y - o3.y));
+            const double2 e0 = x[b], e1 = x[b + 2 * S], e2 = x[b + 4 * S], e3 = x[b + 6 * S];
+            x[b] = cadd(e0, w0);
+            x[b + S] = cadd(e1, w1);
+            x[b + 2 * S] = cadd(e2, w2);
+            x[b + 3 * S] = cadd(e3, w3);
+            x[b + 4 * S] = csub(e0, w0);
+            x[b + 5 * S] = csub(e1, w1);
+            x[b + 6 * S] = csub(e2, w2);
+            x[b + 7 * S] = csub(e3, w3);
         }
-        __syncthreads();
     }
-}
+
+    static __device__ __forceinline__ void read(double2 (&x)[kE], const double2* X, int t) {
+#pragma unroll
+        for (int i = 0; i < kE; ++i) x[i] = X[at(t + kT * i)];
+    }
+    static __device__ __forceinline__ void write(const double2 (&x)[kE], double2* X, int t) {
+#pragma unroll
+        for (int i = 0; i < kE; ++i) X[at(t + kT * i)] = x[i];
+    }
+
+    // pass PASS and those after it, from and to registers; X: the FFT's kPitch points of LDS
+    template <bool INV, int PASS>
+    static __device__ __forceinline__ void passes(double2 (&x)[kE], double2* X, const double2* __restrict__ tw, int t) {
+        constexpr int rb = radix_bits(PASS), R = 1 << rb, lb = before_bits(PASS), L = 1 << lb, NB = kE / R;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            if constexpr (PASS > 0) {
+                const int u = ((t + kT * b) & (L - 1)) << (BITS - lb - rb);
+                double2 w[R];
+#pragma unroll
+                for (int k = 1; k < R; k *= 2) {
+                    w[k] = tw[k * u];
+                    if (INV) w[k].y = -w[k].y;
+                }
+                if constexpr (R >= 4) w[3] = cmul(w[1], w[2]);
+                if constexpr (R >= 8) {
+                    w[5] = cmul(w[1], w[4]);
+                    w[6] = cmul(w[2], w[4]);
+                    w[7] = cmul(w[3], w[4]);
+                }
+#pragma unroll
+                for (int k = 1; k < R; ++k) x[b + NB * k] = cmul(w[k], x[b + NB * k]);
+            }
+            dft<INV, R, NB>(x, b);
+        }
+        if constexpr (PASS + 1 < kPasses) {
+            if constexpr (PASS > 0) sync();  // the points read before this pass
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const int j = t + kT * b, u = j & (L - 1), base = ((j - u) << rb) + u;
+#pragma unroll
+                for (int k = 0; k < R; ++k) X[at(base + k * L)] = x[b + NB * k];
+            }
+            sync();
+            read(x, X, t);
+            passes<INV, PASS + 1>(x, X, tw, t);
+        }
+    }
+};
 
 // Two real rows share one complex FFT: with z = x + i y,
 //   X_m = (Z_m + conj(Z_{N-m})) / 2,  Y_m = (Z_m - conj(Z_{N-m})) / (2 i),
 // and for the inverse, Z = X + i Y of two Hermitian spectra transforms back to
 // x + i y.  Rows j and j' = nlat-1-j of a field are the pair in both
 // directions, which is also what the Legendre kernels' equatorial symmetry
-// needs.  A workgroup takes the pair for a group of up to nb fields, so that
-// the per-order outputs (forward) and inputs (inverse) of the group are
+// needs.  A workgroup takes the pair for kF consecutive fields (four at n = 512), so
+// that the per-order outputs (forward) and inputs (inverse) of the group are
 // contiguous.
 
-// Rows j and j' (j < nlat/2) of fields b0 .. b0+nbr-1 -> the Gauss-weighted
+// Rows j and j' (j < nlat/2) of fields b0 .. -> the Gauss-weighted
 // even and odd parts of their Fourier coefficients, for m <= T (T < nlon):
 //   EO[m][0][j][c] = w_j s_j (F_j + F_j')_m,  EO[m][1][j][c] = w_j s_j (F_j - F_j')_m,
 // F = (1/nlon) DFT, c = 2b + {0: re, 1: im}, s_j = rs[j] (rs may be NULL; it
@@ -113,7 +192,7 @@ __device__ void fft_lds(double2* X, const double2* tw, int bits, int nb, bool in
 // Block b of a launch over G field groups x H row pairs -> (g, j). Blocks are
 // dispatched to the eight XCDs in turn (b mod 8), so when H is a multiple of 8
 // all G groups of row pair j get consecutive blocks of XCD j mod 8: the groups
-// read (inverse) or write (forward) disjoint 16-byte pieces of the same
+// read (inverse) or write (forward) disjoint pieces of the same
 // spectral-side lines, which then meet in that XCD's L2 instead of being
 // fetched or written back once per group. Otherwise the plain g-major split.
 __device__ inline void fft_block(int b, int G, int H, int& g, int& j) {
@@ -127,128 +206,118 @@ __device__ inline void fft_block(int b, int G, int H, int& g, int& j) {
     }
 }
 
-__global__ void __launch_bounds__(256) k_fft_forward(const double* __restrict__ grid, double* __restrict__ EO,
-                                                     const double2* __restrict__ tw, const double* __restrict__ wts,
-                                                     const double* __restrict__ rs, int nlat, int nlon, int bits,
-                                                     int T, int C, int nb) {
-    extern __shared__ double2 X[];  // [nb][nlon] data, then [nlon/2] twiddles
-    const int H = nlat >> 1, nf = C >> 1;
+// Both kernels are bound by the memory traffic of rows and orders, the orders in
+// pieces of 16 kF bytes; where the launch is one round of workgroups, by the latency
+// of loads, passes and stores.  Against radix-2 stage pairs in the LDS with a barrier
+// each: whole analysis / synthesis at T1023 on 2048 x 1024, 16 fields 569 -> 510 / 576
+// -> 510 us (536 MB in the FFT, 120 us at 4.5 TB/s), T256 on 512 x 256, 12 fields 29.4
+// -> 24.9 / 28.6 -> 22.9.
+template <int BITS>
+__global__ void __launch_bounds__(Fft<BITS>::kBlock) k_fft_forward(const double* __restrict__ grid,
+                                                                   double* __restrict__ EO,
+                                                                   const double2* __restrict__ tw,
+                                                                   const double* __restrict__ wts,
+                                                                   const double* __restrict__ rs, int nlat, int T,
+                                                                   int C) {
+    using F = Fft<BITS>;
+    extern __shared__ double2 X[];  // [kF][kPitch]
+    const int H = nlat >> 1, nf = C >> 1, tid = threadIdx.x;
     int g, j;
-    fft_block(blockIdx.x, (nf + nb - 1) / nb, H, g, j);
-    const int b0 = g * nb, nbr = min(nb, nf - b0);
-    double2* tws = X + nb * nlon;
-    for (int k = threadIdx.x; k < nlon / 2; k += blockDim.x) tws[k] = tw[k];
-    constexpr int kU = 8;  // all loads of a thread issued before its stores
-    const int tot = nbr * nlon;
-    for (int k0 = 0; k0 < tot; k0 += kU * 256) {
-        double vx[kU], vy[kU];
+    fft_block(blockIdx.x, (nf + F::kF - 1) / F::kF, H, g, j);
+    const int b0 = g * F::kF, f = tid / F::kT, t = tid - f * F::kT;
+    double2 x[F::kE];
+    {
+        const long long fi = min(b0 + f, nf - 1);  // fields past the last one repeat it and store nothing
+        const double *north = grid + (fi * nlat + j) * F::kN + t, *south = grid + (fi * nlat + (nlat - 1 - j)) * F::kN + t;
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const int e = min(k0 + u * 256 + threadIdx.x, tot - 1);
-            const int f = e >> bits, k = e & (nlon - 1);
-            vx[u] = grid[((long long)(b0 + f) * nlat + j) * nlon + k];
-            vy[u] = grid[((long long)(b0 + f) * nlat + (nlat - 1 - j)) * nlon + k];
-        }
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const int e = k0 + u * 256 + threadIdx.x;
-            if (e < tot) {
-                const int f = e >> bits, k = e & (nlon - 1);
-                X[f * nlon + bitrev(k, bits)] = make_double2(vx[u], vy[u]);
-            }
-        }
+        for (int i = 0; i < F::kE; ++i) x[i] = make_double2(north[F::kT * i], south[F::kT * i]);
     }
+    double2* Xf = X + f * F::kPitch;
+    F::template passes<false, 0>(x, Xf, tw, t);
+    F::sync();
+    F::write(x, Xf, t);
     __syncthreads();
-    fft_lds(X, tws, bits, nbr, false);
-    const double sc = 0.5 * wts[j] * (rs ? rs[j] : 1.0) / nlon;
-    for (int m = threadIdx.x; m <= T; m += blockDim.x) {
-        double* e = EO + (long long)(m * 2) * eo_plane(H, C) + (long long)j * C + 2 * b0;
-        double* o = e + eo_plane(H, C);
-        for (int f = 0; f < nbr; ++f) {
-            const double2 z = X[f * nlon + m], w = X[f * nlon + (nlon - m) % nlon];
-            // 2 X_m = z + conj(w), 2 Y_m = -i (z - conj(w))
-            const double xr2 = z.x + w.x, xi2 = z.y - w.y;
-            const double yr2 = z.y + w.y, yi2 = w.x - z.x;
-            e[2 * f] = sc * (xr2 + yr2);
-            e[2 * f + 1] = sc * (xi2 + yi2);
-            o[2 * f] = sc * (xr2 - yr2);
-            o[2 * f + 1] = sc * (xi2 - yi2);
-        }
+    const double sc = 0.5 * wts[j] * (rs ? rs[j] : 1.0) / F::kN;
+    for (int e = tid; e < (T + 1) * F::kF; e += F::kBlock) {
+        const int m = e / F::kF, h = e - m * F::kF;
+        if (b0 + h >= nf) continue;
+        const double2 z = X[h * F::kPitch + F::at(m)], w = X[h * F::kPitch + F::at((F::kN - m) & (F::kN - 1))];
+        // 2 X_m = z + conj(w), 2 Y_m = -i (z - conj(w))
+        const double xr2 = z.x + w.x, xi2 = z.y - w.y;
+        const double yr2 = z.y + w.y, yi2 = w.x - z.x;
+        double* to = EO + (long long)(m * 2) * eo_plane(H, C) + (long long)j * C + 2 * (b0 + h);
+        *reinterpret_cast<double2*>(to) = make_double2(sc * (xr2 + yr2), sc * (xi2 + yi2));
+        *reinterpret_cast<double2*>(to + eo_plane(H, C)) = make_double2(sc * (xr2 - yr2), sc * (xi2 - yi2));
     }
 }
 
-// Fw -> rows j and j' = nlat-1-j (j < nlat/2) of fields b0 .. b0+nbr-1 of the
-// grid [B][nlat][nlon], scaled by rs[j] (rs may be NULL); orders m <= T < 1024.
-__global__ void __launch_bounds__(256) k_fft_inverse(const double* __restrict__ Fw, double* __restrict__ grid, const double2* __restrict__ tw,
-                                                     const double* __restrict__ rs, int nlat, int nlon, int bits,
-                                                     int T, int C, int nb) {
-    extern __shared__ double2 X[];  // [nb][nlon] data, then [nlon/2] twiddles
-    const int H = nlat >> 1, nf = C >> 1;
+// Fw -> rows j and j' = nlat-1-j (j < nlat/2) of fields b0 .. of the
+// grid [B][nlat][nlon], scaled by rs[j] (rs may be NULL); orders m <= T < nlon.
+// Bin k of the FFT is A_k + B_{N-k} with A_m = F_m + i G_m, B_m = conj(F_m) + i
+// conj(G_m) (m >= 1) of the rows' coefficients F and G (orders past N/2 alias).
+template <int BITS>
+__global__ void __launch_bounds__(Fft<BITS>::kBlock) k_fft_inverse(const double* __restrict__ Fw,
+                                                                   double* __restrict__ grid,
+                                                                   const double2* __restrict__ tw,
+                                                                   const double* __restrict__ rs, int nlat, int T,
+                                                                   int C) {
+    using F = Fft<BITS>;
+    extern __shared__ double2 X[];  // [kF][kPitch]
+    const int H = nlat >> 1, nf = C >> 1, tid = threadIdx.x;
     int g, j;
-    fft_block(blockIdx.x, (nf + nb - 1) / nb, H, g, j);
-    const int j2 = nlat - 1 - j;
-    const int b0 = g * nb, nbr = min(nb, nf - b0);
-    double2* tws = X + nb * nlon;
-    for (int k = threadIdx.x; k < nb * nlon; k += blockDim.x) X[k] = make_double2(0.0, 0.0);
-    for (int k = threadIdx.x; k < nlon / 2; k += blockDim.x) tws[k] = tw[k];
-    __syncthreads();
-    for (int f = 0; f < nbr; ++f) {
-        double2* Xf = X + f * nlon;
-        const int cb = 2 * (b0 + f);
-        constexpr int kM = 4;  // orders per thread: m = tid + 256 k
-        double2 fv[kM], gv[kM];  // coefficients of rows j and j'
+    fft_block(blockIdx.x, (nf + F::kF - 1) / F::kF, H, g, j);
+    const int j2 = nlat - 1 - j, b0 = g * F::kF;
+    // bins k and N - k of field h, k <= N/2: kE/2 (and one for N/2) per thread
+    constexpr int kI = F::kE / 2 + 1;
+    double2 fv[kI], gv[kI];
 #pragma unroll
-        for (int k = 0; k < kM; ++k) {
-            const int m = threadIdx.x + 256 * k;
-            double2 v = make_double2(0.0, 0.0), w = v;
-            if (m <= T) {
-                const double* p = Fw + m * fw_plane(nlat, C) + cb;
-                v = make_double2(p[(long long)j * C], p[(long long)j * C + 1]);
-                w = make_double2(p[(long long)j2 * C], p[(long long)j2 * C + 1]);
-                if (m == 0) v.y = w.y = 0.0;  // real fields: Re F_0
-            }
-            fv[k] = v;
-            gv[k] = w;
-        }
-        // Z = X + i Y with X[m] = F_m, X[N-m] = conj(F_m) (and Y alike from G):
-        // Z[m] += F_m + i G_m, Z[N-m] += conj(F_m) + i conj(G_m); two passes, as
-        // orders past N/2 alias onto the same bins
-#pragma unroll
-        for (int k = 0; k < kM; ++k) {
-            const int m = threadIdx.x + 256 * k;
-            if (m <= T) Xf[m % nlon] = make_double2(fv[k].x - gv[k].y, fv[k].y + gv[k].x);
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < kM; ++k) {
-            const int m = threadIdx.x + 256 * k;
-            if (m >= 1 && m <= T) {
-                const int q = (nlon - m % nlon) % nlon;
-                Xf[q] = make_double2(Xf[q].x + fv[k].x + gv[k].y, Xf[q].y - fv[k].y + gv[k].x);
-            }
-        }
-        __syncthreads();
+    for (int q = 0; q < kI; ++q) {
+        const int e = tid + q * F::kBlock, k = e / F::kF, h = e - k * F::kF;
+        const bool ok = k <= F::kN / 2 && k <= T && b0 + h < nf;
+        const double* p = Fw + k * fw_plane(nlat, C) + 2 * (b0 + h);
+        fv[q] = ok ? *reinterpret_cast<const double2*>(p + (long long)j * C) : make_double2(0.0, 0.0);
+        gv[q] = ok ? *reinterpret_cast<const double2*>(p + (long long)j2 * C) : make_double2(0.0, 0.0);
     }
-    // bit-reverse permutation in place
-    for (int e = threadIdx.x; e < nbr * nlon; e += blockDim.x) {
-        const int f = e >> bits, k = e & (nlon - 1);
-        const int r = bitrev(k, bits);
-        if (r > k) {
-            const double2 t = X[f * nlon + k];
-            X[f * nlon + k] = X[f * nlon + r];
-            X[f * nlon + r] = t;
+#pragma unroll
+    for (int q = 0; q < kI; ++q) {
+        const int e = tid + q * F::kBlock, k = e / F::kF, h = e - k * F::kF;
+        if (k > F::kN / 2) continue;
+        double2 v = fv[q], w = gv[q];
+        if (k == 0) v.y = w.y = 0.0;  // real fields: Re F_0
+        double2 lo = make_double2(v.x - w.y, v.y + w.x), hi = make_double2(v.x + w.y, w.x - v.y);  // A_k, B_k
+        if (k == 0) hi = make_double2(0.0, 0.0);
+        const int k2 = F::kN - k;
+        if (k2 != k && k2 <= T && b0 + h < nf) {  // k >= 1: T < nlon
+            const double* p = Fw + k2 * fw_plane(nlat, C) + 2 * (b0 + h);
+            v = *reinterpret_cast<const double2*>(p + (long long)j * C);
+            w = *reinterpret_cast<const double2*>(p + (long long)j2 * C);
+            lo = cadd(lo, make_double2(v.x + w.y, w.x - v.y));
+            hi = cadd(hi, make_double2(v.x - w.y, v.y + w.x));
+        }
+        double2* Xh = X + h * F::kPitch;
+        if (k == 0 || k2 == k) Xh[F::at(k)] = cadd(lo, hi);
+        else {
+            Xh[F::at(k)] = lo;
+            Xh[F::at(k2)] = hi;
         }
     }
     __syncthreads();
-    fft_lds(X, tws, bits, nbr, true);
+    const int f = tid / F::kT, t = tid - f * F::kT;
+    double2 x[F::kE];
+    double2* Xf = X + f * F::kPitch;
+    F::read(x, Xf, t);
+    if constexpr (F::kPasses > 1) F::sync();
+    F::template passes<true, 0>(x, Xf, tw, t);
+    if (b0 + f >= nf) return;
     const double sc = rs ? rs[j] : 1.0;
     // streaming stores for the contiguous output rows (measured 22.3 -> 20.5 us
     // at T256, 12 fields; scattered outputs elsewhere measured slower with them)
-    for (int e = threadIdx.x; e < nbr * nlon; e += blockDim.x) {
-        const int f = e >> bits, k = e & (nlon - 1);
-        const double2 z = X[e];
-        __builtin_nontemporal_store(z.x * sc, grid + ((long long)(b0 + f) * nlat + j) * nlon + k);
-        __builtin_nontemporal_store(z.y * sc, grid + ((long long)(b0 + f) * nlat + j2) * nlon + k);
+    double *north = grid + ((long long)(b0 + f) * nlat + j) * F::kN + t,
+           *south = grid + ((long long)(b0 + f) * nlat + j2) * F::kN + t;
+#pragma unroll
+    for (int i = 0; i < F::kE; ++i) {
+        __builtin_nontemporal_store(x[i].x * sc, north + F::kT * i);
+        __builtin_nontemporal_store(x[i].y * sc, south + F::kT * i);
     }
 }
 
@@ -779,37 +848,44 @@ void leg_release(LegTables& t) {
     t = LegTables{};
 }
 
-constexpr size_t kFftLds = 96 * 1024;  // LDS allowance of the FFT kernels (nlon = 4096 needs 96 KB)
-
-int fft_bits(int nlon) {
-    int bits = 0;
-    while ((1 << bits) < nlon) ++bits;
-    return bits;
+// One instantiation per length; f(Fft<bits>) for the plan's.
+template <class Fn, int BITS = 2>
+int with_fft(int nlon, Fn f) {
+    if constexpr (BITS > 12) {
+        return fail(REXI_EINVAL, "nlon must be a power of two in [4, 4096]");
+    } else {
+        return nlon == 1 << BITS ? f(std::integral_constant<int, BITS>()) : with_fft<Fn, BITS + 1>(nlon, f);
+    }
 }
 
-// grid rows [nf][nlat][nlon] -> Fw (C = 2 nf columns), row scale rs or NULL
-// Fields per FFT workgroup.  One: the FFTs are latency-bound per workgroup,
-// and four fields per workgroup (contiguous per-order writes, a quarter of the
-// workgroups) measured slower at T256, 12 fields (22.4 / 30.7 us against
-// 16.5 / 20.9 us forward / inverse).
-int fft_group(const rexi_plan*, int) { return 1; }
+template <int BITS>
+constexpr size_t fft_lds() {
+    return (size_t)Fft<BITS>::kF * Fft<BITS>::kPitch * sizeof(double2);
+}
 
+// grid rows [nf][nlat][nlon] -> EO (C = 2 nf columns), row scale rs or NULL
 int fft_forward(rexi_plan* pl, const double* grid, int nf, const double* rs, hipStream_t s) {
-    const int nb = fft_group(pl, nf);
-    const size_t lds = (size_t)(nb * pl->nlon + pl->nlon / 2) * sizeof(double2);
-    hipLaunchKernelGGL(k_fft_forward, dim3(((nf + nb - 1) / nb) * pl->nhalf), dim3(256), lds, s, grid, pl->d_four,
-                       pl->d_twiddle, pl->d_wts, rs, pl->nlat, pl->nlon, fft_bits(pl->nlon), pl->T, 2 * nf, nb);
-    REXI_HIP(hipGetLastError());
-    return REXI_OK;
+    return with_fft(pl->nlon, [&](auto bits) -> int {
+        constexpr int kBits = decltype(bits)::value;
+        using F = Fft<kBits>;
+        hipLaunchKernelGGL(k_fft_forward<kBits>, dim3((nf + F::kF - 1) / F::kF * pl->nhalf), dim3(F::kBlock),
+                           fft_lds<kBits>(), s, grid, pl->d_four, pl->d_twiddle, pl->d_wts, rs, pl->nlat, pl->T,
+                           2 * nf);
+        REXI_HIP(hipGetLastError());
+        return REXI_OK;
+    });
 }
 
+// Fw (C = 2 nf columns) -> grid rows, row scale rs or NULL
 int fft_inverse(rexi_plan* pl, double* grid, int nf, const double* rs, hipStream_t s) {
-    const int nb = fft_group(pl, nf);
-    const size_t lds = (size_t)(nb * pl->nlon + pl->nlon / 2) * sizeof(double2);
-    hipLaunchKernelGGL(k_fft_inverse, dim3(((nf + nb - 1) / nb) * pl->nhalf), dim3(256), lds, s, pl->d_four,
-                       grid, pl->d_twiddle, rs, pl->nlat, pl->nlon, fft_bits(pl->nlon), pl->T, 2 * nf, nb);
-    REXI_HIP(hipGetLastError());
-    return REXI_OK;
+    return with_fft(pl->nlon, [&](auto bits) -> int {
+        constexpr int kBits = decltype(bits)::value;
+        using F = Fft<kBits>;
+        hipLaunchKernelGGL(k_fft_inverse<kBits>, dim3((nf + F::kF - 1) / F::kF * pl->nhalf), dim3(F::kBlock),
+                           fft_lds<kBits>(), s, pl->d_four, grid, pl->d_twiddle, rs, pl->nlat, pl->T, 2 * nf);
+        REXI_HIP(hipGetLastError());
+        return REXI_OK;
+    });
 }
 
 template <int NH>
@@ -896,9 +972,10 @@ int sh_setup(rexi_plan* pl) {
     REXI_HIP(hipMemcpy(pl->d_rcos, rcos.data(), rcos.size() * sizeof(double), hipMemcpyHostToDevice));
     REXI_HIP(hipMemcpy(pl->d_twiddle, tw.data(), tw.size() * sizeof(double2), hipMemcpyHostToDevice));
     // dynamic LDS above 64 KB per workgroup
-    REXI_HIP(hipFuncSetAttribute((const void*)k_fft_forward, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFftLds));
-    REXI_HIP(hipFuncSetAttribute((const void*)k_fft_inverse, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFftLds));
-
+    static_assert(fft_lds<11>() == fft_lds<12>());
+    for (const void* f : {(const void*)k_fft_forward<11>, (const void*)k_fft_inverse<11>,
+                          (const void*)k_fft_forward<12>, (const void*)k_fft_inverse<12>})
+        REXI_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)fft_lds<12>()));
     return REXI_OK;
 }
 

@@ -40,3 +40,29 @@ def test_flat_spectra_match_oracle(T, nlat, nlon, B):
     got = plan.sh_forward(torch.from_numpy(grid).to("cuda:0")).cpu().numpy()
     err = np.max(np.abs(got - want)) / np.max(np.abs(want))
     assert err < TOL, f"sh_forward rel max err {err}"
+
+
+# every FFT length (4 .. 4096: one to four register passes, several FFTs per wave up
+# to one on eight waves), orders on both sides of nlon / 2 (where bins alias), and
+# field counts that leave a group of FFTs incomplete
+@pytest.mark.parametrize("bits", range(2, 13))
+@pytest.mark.parametrize("aliased", [False, True])
+def test_fft_lengths_match_oracle(bits, aliased):
+    import torch
+    import paper_1812_03431_amd as rexi
+    nlon = 1 << bits
+    T = min(nlon - 1 if aliased else nlon // 2 - 1, 40)
+    nlat, B = 2 * ((T + 2) // 2) + 2, 3
+    print(f"\n[gpu] fft nlon={nlon} T={T} nlat={nlat} B={B}", flush=True)
+    w = synth.Workload("sh", T=T, nlat=nlat, nlon=nlon, dt=3600.0, M=8, states=1)
+    plan = rexi.plan_for(w, max_fields=B)
+    rng = np.random.default_rng(bits)
+    spec = rng.standard_normal((B, plan.nspec)) + 1j * rng.standard_normal((B, plan.nspec))
+    spec[:, :T + 1] = spec[:, :T + 1].real
+    want = osh.synthesis(spec, T, nlat, nlon)
+    got = plan.sh_inverse(torch.from_numpy(spec).to("cuda:0")).cpu().numpy()
+    assert np.max(np.abs(got - want)) / np.max(np.abs(want)) < TOL
+    grid = rng.standard_normal((B, nlat, nlon))
+    want = osh.analysis(grid, T)
+    got = plan.sh_forward(torch.from_numpy(grid).to("cuda:0")).cpu().numpy()
+    assert np.max(np.abs(got - want)) / np.max(np.abs(want)) < TOL
