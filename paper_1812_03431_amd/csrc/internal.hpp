@@ -130,7 +130,7 @@ struct SweepItem {                // a wave's work: pairs of one chain, states [
 };
 struct SweepChain { int pair0, npair; };
 struct SweepTile { int tile, pos, nst; };               // of a state: its tile, place there, states of the tile
-struct SweepGroup { long long part_off; int nr, pad; };  // of a (chain, tile): its nr consecutive items' partials
+struct SweepGroup { long long part_off; int nr, npair; };  // of a (pair, tile): its first partial (double2), of nr items, pairs of the chain
 struct SweepTables {
     bool built = false, usable = false;
     int npairs = 0;
@@ -143,8 +143,6 @@ struct SweepTables {
     int2* d_idx = nullptr;           // [pair] spectral index of its vorticity and divergence (-1: a dummy)
     double *d_fin[2] = {nullptr, nullptr}, *d_fout[2] = {nullptr, nullptr};  // [pair][3]
     double2* d_poles[2] = {nullptr, nullptr};                                // [N][6]
-    SweepChain* d_chains = nullptr;
-    int* d_pair_chain = nullptr;
 };
 
 constexpr int kMaxLaunches = 8;  // solve launches per step (tile classes)

@@ -332,7 +332,6 @@ int build_sweep_tables(rexi_plan* pl, bool split) {
     const size_t np = t.npairs;
     std::vector<double> cst(np * kSweepCst, 0.0), fin[2], fout[2];
     std::vector<int2> idx(np, make_int2(-1, -1));
-    std::vector<int> chain_of(np);
     for (int d = 0; d < 2; ++d) {
         fin[d].assign(np * 3, 0.0);
         fout[d].assign(np * 3, 0.0);
@@ -372,7 +371,6 @@ int build_sweep_tables(rexi_plan* pl, bool split) {
                 const size_t q = q0 + k / 2;
                 const bool div = (k & 1) != 0;
                 double* c = &cst[q * kSweepCst];
-                chain_of[q] = 2 * m + p;
                 if (slot[k] < 0) {
                     c[div ? 2 : 0] = kDummy;
                     continue;
@@ -402,8 +400,6 @@ int build_sweep_tables(rexi_plan* pl, bool split) {
     if (!ok) return REXI_OK;
     int rc = upload(&t.d_cst, cst);
     if (!rc) rc = upload(&t.d_idx, idx);
-    if (!rc) rc = upload(&t.d_chains, t.chains);
-    if (!rc) rc = upload(&t.d_pair_chain, chain_of);
     for (int d = 0; d < 2 && !rc; ++d) {
         rc = upload(&t.d_fin[d], fin[d]);
         if (!rc) rc = upload(&t.d_fout[d], fout[d]);
@@ -424,8 +420,6 @@ int build_sweep_tables(rexi_plan* pl, bool split) {
 void free_sweep_tables(SweepTables& t) {
     dev_free(t.d_cst);
     dev_free(t.d_idx);
-    dev_free(t.d_chains);
-    dev_free(t.d_pair_chain);
     for (int d = 0; d < 2; ++d) {
         dev_free(t.d_fin[d]);
         dev_free(t.d_fout[d]);
@@ -471,7 +465,7 @@ int build_sweep_schedule(rexi_plan* pl, int S, long long target_items, bool spli
         for (int k = 0; k < nt; ++k) total += cost(c.npair, s0[k + 1] - s0[k]) * nb;
     const double target = total / (double)std::max<long long>(1, target_items);
     std::vector<SweepGroup>& groups = out.sweep_groups;
-    groups.resize(t.chains.size() * nt);
+    groups.resize((size_t)t.npairs * nt);
     struct Unit { double cost; SweepItem a, b; bool two; };
     std::vector<Unit> units;
     long long off = 0;
@@ -486,8 +480,8 @@ int build_sweep_schedule(rexi_plan* pl, int S, long long target_items, bool spli
             out.sweep_nst = std::max(out.sweep_nst, nst);
             const double u = cost(two ? half.x : c.npair, nst);
             const int per = split ? 1 : std::max(1, std::min((int)std::lround(target / u), nb));  // batches per item
-            SweepGroup& gr = groups[ch * nt + k];
-            gr = {off, 0, 0};
+            const long long first = off;
+            int nr = 0;
             for (int b = 0; b < nb; b += per) {
                 const int b1 = std::min(nb, b + per), k0 = 64 * b, k1 = std::min(pl->N, 64 * b1);
                 Unit x{u * (b1 - b), {c.pair0, c.npair, c.npair, s0[k], nst, k0, k1, -1, 0, 0, off, 0}, {}, two};
@@ -503,8 +497,10 @@ int build_sweep_schedule(rexi_plan* pl, int S, long long target_items, bool spli
                 }
                 units.push_back(x);
                 off += (long long)nst * c.npair * kSweepRec;
-                ++gr.nr;
+                ++nr;
             }
+            for (int q = 0; q < c.npair; ++q)
+                groups[(size_t)(c.pair0 + q) * nt + k] = {first / 2 + 3LL * q, nr, c.npair};
         }
     }
     // pairs of halves first (they start at even indices), each kind longest first

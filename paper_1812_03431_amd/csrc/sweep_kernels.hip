@@ -964,104 +964,95 @@ k_sweep_short(const SweepArgs A, int* counter) {
 }
 
 // Physical state [S][3][nspec] -> records; fin[pair][3]: factors into scaled
-// energy variables of vorticity, divergence and Phi.
-__global__ void k_sweep_prep(const double2* __restrict__ u, double* __restrict__ rec, const int2* __restrict__ idx,
-                             const double* __restrict__ fin, int npairs, int S, long long nspec) {
-    const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const int s = (int)(gid / (npairs + 1)), q = (int)(gid - (long long)s * (npairs + 1));
-    if (s >= S) return;
-    const double2* us = u + (long long)s * 3 * nspec;
-    double* r = rec + gid * kSweepRec;
-    if (q == npairs) {  // (n, m) = (0, 0)
-        for (int v = 0; v < 3; ++v) {
-            r[2 * v] = us[v * nspec].x;
-            r[2 * v + 1] = us[v * nspec].y;
-        }
+// energy variables of vorticity, divergence and Phi.  One thread per (pair, variable),
+// block row y per state.
+__global__ void k_sweep_prep(const double2* __restrict__ u, double2* __restrict__ rec, const int2* __restrict__ idx,
+                             const double* __restrict__ fin, int npairs, long long nspec) {
+    const int e = blockIdx.x * blockDim.x + threadIdx.x, q = e / 3, v = e - 3 * q;
+    if (q > npairs) return;
+    const long long s = blockIdx.y;
+    const double2* us = u + (s * 3 + (v < 2 ? v + 1 : 0)) * nspec;  // zeta, delta, Phi
+    double2* r = rec + (s * (npairs + 1) + q) * 3 + v;
+    if (q == npairs) {  // (n, m) = (0, 0), in the order Phi, zeta, delta
+        *r = u[(s * 3 + v) * nspec];
         return;
     }
     const int2 ix = idx[q];
-    const double* f = fin + 3 * q;
-    double v[kSweepRec] = {0, 0, 0, 0, 0, 0};
-    if (ix.x >= 0) {  // zeta' = -i zeta
-        const double2 z = us[nspec + ix.x];
-        v[0] = z.y * f[0];
-        v[1] = -z.x * f[0];
-    }
-    if (ix.y >= 0) {  // delta, psi = om Phi', Phi' = -i Phi
-        const double2 d = us[2 * nspec + ix.y], p = us[ix.y];
-        v[2] = d.x * f[1];
-        v[3] = d.y * f[1];
-        v[4] = p.y * f[2];
-        v[5] = -p.x * f[2];
-    }
-    for (int k = 0; k < kSweepRec; ++k) r[k] = v[k];
+    const int i = v == 0 ? ix.x : ix.y;
+    double2 x = us[max(i, 0)];
+    const double f = i >= 0 ? fin[e] : 0.0;
+    // zeta' = -i zeta; delta; psi = om Phi', Phi' = -i Phi
+    if (v != 1) x = make_double2(x.y, -x.x);
+    *r = i >= 0 ? make_double2(x.x * f, x.y * f) : make_double2(0.0, 0.0);
 }
 
 struct SweepReduceArgs {
-    const SweepChain* chains;
-    const int* pair_chain;
     const SweepTile* tiles;      // per state
-    const SweepGroup* groups;    // [chain][tiles]
+    const SweepGroup* groups;    // [pair][tiles]
     const int2* idx;
     const double* cst;
     const double* fout;          // [pair][3]: factors back to physical variables
-    const double* part;
-    const double* rec_in;
-    double* rec_out;             // next records, or null
+    const double2* part;
+    const double2* rec_in;
+    double2* rec_out;            // next records, or null
     double2* u_out;              // physical state, or null
-    int npairs, S, ntiles;
+    int npairs, ntiles;
     long long nspec;
     cd g00, gphi;
 };
 
-// Sum an item group's partials in order and finish Phi; write the next records
-// or the physical state.  One thread per (pair, state).
-__global__ void k_sweep_reduce(const SweepReduceArgs R) {
-    const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const int s = (int)(gid / (R.npairs + 1)), q = (int)(gid - (long long)s * (R.npairs + 1));
-    if (s >= R.S) return;
-    const double* ri = R.rec_in + gid * kSweepRec;
+// Sum a pair's partials in order and finish Phi; write the next records or the
+// physical state.  One thread per (pair, variable), block row y per state, so that
+// a wave reads consecutive 16-byte values; kReduce partials are in flight at once.
+// Bound by the partials' bytes where there are many (T256, four states: 113 MB,
+// 35 us), by the latency of three dependent loads where there are few.  One thread
+// per pair, with all six values of one partial after the other, took 38 us there,
+// 26 at T127 with 8215 poles and one state, and 5 to 6 for the smallest steps.
+constexpr int kReduce = 8;
+__global__ void __launch_bounds__(256) k_sweep_reduce(const SweepReduceArgs R) {
+    const int e = blockIdx.x * blockDim.x + threadIdx.x, q = e / 3, v = e - 3 * q;
+    if (q > R.npairs) return;
+    const long long s = blockIdx.y;
+    const long long at = (s * (R.npairs + 1) + q) * 3 + v;
     if (q == R.npairs) {  // the operator is zero at (0, 0)
-        for (int v = 0; v < 3; ++v) {
-            const cd y = cmul(R.g00, mk(ri[2 * v], ri[2 * v + 1]));
-            if (R.u_out) R.u_out[((long long)s * 3 + v) * R.nspec] = make_double2(y.r, y.i);
-            else {
-                R.rec_out[gid * kSweepRec + 2 * v] = y.r;
-                R.rec_out[gid * kSweepRec + 2 * v + 1] = y.i;
-            }
-        }
+        const double2 x = R.rec_in[at];
+        const cd y = cmul(R.g00, cd{x.x, x.y});
+        (R.u_out ? R.u_out[(s * 3 + v) * R.nspec] : R.rec_out[at]) = make_double2(y.r, y.i);
         return;
     }
-    const int ch = R.pair_chain[q];
-    const SweepChain c = R.chains[ch];
     const SweepTile tl = R.tiles[s];
-    const SweepGroup gr = R.groups[(long long)ch * R.ntiles + tl.tile];
-    const long long step = (long long)tl.nst * c.npair * kSweepRec;
-    const double* p = R.part + gr.part_off + ((long long)tl.pos * c.npair + (q - c.pair0)) * kSweepRec;
-    double v[kSweepRec] = {0, 0, 0, 0, 0, 0};
-    for (int r = 0; r < gr.nr; ++r, p += step)
-        for (int k = 0; k < kSweepRec; ++k) v[k] += p[k];
-    const double* cs = R.cst + (long long)q * kSweepCst;
-    const cd psi = cmul(R.gphi, mk(ri[4], ri[5]));
-    const double pr = fma(cs[4], v[4], psi.r), pi = fma(cs[4], v[5], psi.i);
+    const SweepGroup gr = R.groups[(long long)q * R.ntiles + tl.tile];
     const int2 ix = R.idx[q];
-    if (R.u_out) {
-        double2* us = R.u_out + (long long)s * 3 * R.nspec;
-        const double* f = R.fout + 3 * q;
-        if (ix.x >= 0) us[R.nspec + ix.x] = make_double2(-v[1] * f[0], v[0] * f[0]);
-        if (ix.y >= 0) {
-            us[2 * R.nspec + ix.y] = make_double2(v[2] * f[1], v[3] * f[1]);
-            us[ix.y] = make_double2(-pi * f[2], pr * f[2]);
+    const int i = v == 0 ? ix.x : ix.y;
+    double2 psi = make_double2(0.0, 0.0);
+    if (v == 2) psi = R.rec_in[at];
+    const double c = R.cst[(long long)q * kSweepCst + 2 * v];  // D2, D2, om2'
+    const double f = R.u_out ? R.fout[e] : c;
+    const long long step = 3LL * tl.nst * gr.npair;
+    const double2* p = R.part + gr.part_off + 3LL * tl.pos * gr.npair + v;
+    double sr = 0.0, si = 0.0;
+    for (int r = 0; r < gr.nr; r += kReduce) {
+        double2 t[kReduce];
+#pragma unroll
+        for (int k = 0; k < kReduce; ++k) t[k] = p[min(r + k, gr.nr - 1) * step];
+#pragma unroll
+        for (int k = 0; k < kReduce; ++k) {
+            sr += r + k < gr.nr ? t[k].x : 0.0;
+            si += r + k < gr.nr ? t[k].y : 0.0;
         }
+    }
+    if (v == 2) {
+        const cd y = cmul(R.gphi, cd{psi.x, psi.y});
+        sr = fma(c, sr, y.r);
+        si = fma(c, si, y.i);
+    }
+    if (R.u_out) {
+        if (i < 0) return;
+        double2* us = R.u_out + (s * 3 + (v < 2 ? v + 1 : 0)) * R.nspec + i;
+        *us = v == 1 ? make_double2(sr * f, si * f) : make_double2(-si * f, sr * f);
     } else {
-        double* o = R.rec_out + gid * kSweepRec;
-        const bool z = ix.x >= 0, d = ix.y >= 0;
-        o[0] = z ? cs[0] * v[0] : 0.0;
-        o[1] = z ? cs[0] * v[1] : 0.0;
-        o[2] = d ? cs[2] * v[2] : 0.0;
-        o[3] = d ? cs[2] * v[3] : 0.0;
-        o[4] = d ? pr : 0.0;
-        o[5] = d ? pi : 0.0;
+        const double g = v == 2 ? 1.0 : f;
+        R.rec_out[at] = i >= 0 ? make_double2(sr * g, si * g) : make_double2(0.0, 0.0);
     }
 }
 
@@ -1070,9 +1061,8 @@ __global__ void k_sweep_reduce(const SweepReduceArgs R) {
 hipError_t enqueue_sweep_prep(rexi_plan* pl, const Workspace& ws, const Schedule& sc, const void* u, int buf, int S,
                               int adjoint, hipStream_t s) {
     const SweepTables& t = pl->sweep[sc.split];
-    const long long n = (long long)S * (t.npairs + 1);
-    hipLaunchKernelGGL(k_sweep_prep, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, (const double2*)u,
-                       ws.rec[buf], t.d_idx, t.d_fin[adjoint], t.npairs, S, pl->nspec);
+    hipLaunchKernelGGL(k_sweep_prep, dim3((3 * (t.npairs + 1) + 255) / 256, S), dim3(256), 0, s, (const double2*)u,
+                       (double2*)ws.rec[buf], t.d_idx, t.d_fin[adjoint], t.npairs, pl->nspec);
     return hipGetLastError();
 }
 
@@ -1119,27 +1109,23 @@ hipError_t enqueue_sweep_reduce(rexi_plan* pl, const Workspace& ws, const Schedu
                                 void* u_out, int S, int adjoint, hipStream_t s) {
     const SweepTables& t = pl->sweep[sc.split];
     SweepReduceArgs r;
-    r.chains = t.d_chains;
-    r.pair_chain = t.d_pair_chain;
     r.tiles = sc.d_sweep_tiles;
     r.groups = sc.d_sweep_groups;
     r.idx = t.d_idx;
     r.cst = t.d_cst;
     r.fout = t.d_fout[adjoint];
-    r.part = reinterpret_cast<const double*>(ws.part);
-    r.rec_in = ws.rec[buf_in];
-    r.rec_out = u_out ? nullptr : ws.rec[buf_out];
+    r.part = ws.part;
+    r.rec_in = (const double2*)ws.rec[buf_in];
+    r.rec_out = u_out ? nullptr : (double2*)ws.rec[buf_out];
     r.u_out = (double2*)u_out;
     r.npairs = t.npairs;
-    r.S = S;
     r.ntiles = sc.sweep_ntiles;
     r.nspec = pl->nspec;
     const std::complex<double> g00 = adjoint ? pl->g00_adj : pl->g00_fwd;
     const std::complex<double> gp = adjoint ? pl->gphi_adj : pl->gphi_fwd;
     r.g00 = cd{g00.real(), g00.imag()};
     r.gphi = cd{gp.real(), gp.imag()};
-    const long long n = (long long)S * (t.npairs + 1);
-    hipLaunchKernelGGL(k_sweep_reduce, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, r);
+    hipLaunchKernelGGL(k_sweep_reduce, dim3((3 * (t.npairs + 1) + 255) / 256, S), dim3(256), 0, s, r);
     return hipGetLastError();
 }
 
