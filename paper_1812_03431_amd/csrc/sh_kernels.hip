@@ -374,7 +374,7 @@ __device__ __forceinline__ double mfma4(double a, double b, double c) {
 // each run by eight-byte loads, and bank conflicts in the operand reads: T1023 on
 // 2048 x 1024, 16 fields 579 -> 385 / 761 -> 569 us; T511 on 1024 x 512, 6 fields 46
 // -> 39 / 66 -> 59; T256 on 512 x 256, 12 fields 16.9 -> 16.0 / 30.8 -> 29.4.
-// Columns [c_off, c_off + C) of EO (row stride Cs), C <= 32.
+// Block row y takes columns [y cw, y cw + cw) of the Cs columns, cw <= 32.
 template <int NH, int G>
 __global__ void __launch_bounds__(256) k_legendre_forward(const LegRun* __restrict__ runs,
                                                           const double* __restrict__ restart,
@@ -382,11 +382,12 @@ __global__ void __launch_bounds__(256) k_legendre_forward(const LegRun* __restri
                                                           const double* __restrict__ scale,
                                                           const double* __restrict__ mu,
                                                           const double* __restrict__ EO, double* __restrict__ spec,
-                                                          int T, int H, int Cs, int c_off, int C) {
+                                                          int T, int H, int Cs, int cw) {
     constexpr int kTile = kFwdDeg * kFwdLat, kSteps = kFwdLat / 16;
     __shared__ double Pt[G * kTile];
     const LegRun rn = runs[blockIdx.x];
     if (rn.m < 0) return;  // padding slot of the XCD-ordered list
+    const int c_off = blockIdx.y * cw, C = min(cw, Cs - c_off);
     const int m = rn.m, nrun = rn.nrun;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
@@ -545,12 +546,13 @@ __global__ void __launch_bounds__(256) k_legendre_inverse(const LegWork* __restr
                                                           const double* __restrict__ mu,
                                                           const double* __restrict__ spec,
                                                           double* __restrict__ Fw, int T, int nlat, int H, int Cs,
-                                                          int c_off, int C) {
+                                                          int cw) {
     constexpr int kCp = 4 * NG, kPart = kRun * kCp + kInvPad;  // pitches of a degree and of a part
     extern __shared__ double Sm[];                             // [4][kPart]
     double* cf = Sm + 4 * kPart;                               // [4][kRun + 2]: degrees 1 .. kRun of a part
     const LegWork wk = work[blockIdx.x];
     if (wk.m < 0) return;  // padding slot of the XCD-ordered list
+    const int c_off = blockIdx.y * cw, C = min(cw, Cs - c_off);
     const int m = wk.m, L = T + 1 - m, tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int i = lane & 15, kq = lane >> 4, p = lane & 3;
@@ -811,7 +813,6 @@ int leg_build(rexi_plan* pl, LegTables& t, int Tt, const std::vector<double>& no
     std::vector<LegRun> tf;
     for (size_t k = 0; k < qmax; ++k)
         for (int x = 0; x < kXcd; ++x) tf.push_back(k < q[x].size() ? q[x][k] : LegRun{-1, 0, 0, 0});
-    while (!tf.empty() && tf.back().m < 0) tf.pop_back();
     // inverse: 4 R latitude tiles of one order per workgroup; the groups of an order
     // read the same spectral coefficients and go to one XCD, longest orders first.
     // R = 2 reads each staged value for two tiles (the LDS then serves the matrix
@@ -888,45 +889,52 @@ int fft_inverse(rexi_plan* pl, double* grid, int nf, const double* rs, hipStream
     });
 }
 
-template <int NH>
-void launch_forward(rexi_plan* pl, const LegTables& t, double* spec, int C, int c0, int w, hipStream_t s) {
-    const auto k = t.fwd_g == 4 ? k_legendre_forward<NH, 4> : k_legendre_forward<NH, 2>;
-    hipLaunchKernelGGL(k, dim3(t.ntiles_f), dim3(256), 0, s, (const LegRun*)t.d_tiles_f, t.d_restart, t.d_lcoef,
-                       t.d_lscale, pl->d_mu, pl->d_four, spec, t.T, pl->nhalf, C, c0, w);
+// Columns per workgroup: C split evenly into `parts` of whole groups of four, at most 32.
+int column_chunk(int C, int parts) {
+    const int groups = (C + 3) / 4;
+    parts = std::max(parts, (groups + 7) / 8);
+    return 4 * ((groups + parts - 1) / parts);
 }
 
-// EO (C columns) -> spec [C/2][nspec(t.T)], in launches of at most 32 columns;
-// each wave takes half of a launch's four-column groups
+template <int NH>
+void launch_forward(rexi_plan* pl, const LegTables& t, double* spec, int C, int cw, hipStream_t s) {
+    const auto k = t.fwd_g == 4 ? k_legendre_forward<NH, 4> : k_legendre_forward<NH, 2>;
+    hipLaunchKernelGGL(k, dim3(t.ntiles_f, (C + cw - 1) / cw), dim3(256), 0, s, (const LegRun*)t.d_tiles_f,
+                       t.d_restart, t.d_lcoef, t.d_lscale, pl->d_mu, pl->d_four, spec, t.T, pl->nhalf, C, cw);
+}
+
+// EO (C columns) -> spec [C/2][nspec(t.T)]; each wave takes half of a workgroup's
+// four-column groups
 int leg_forward(rexi_plan* pl, const LegTables& t, double* spec, int C, hipStream_t s) {
-    using Launcher = void (*)(rexi_plan*, const LegTables&, double*, int, int, int, hipStream_t);
+    using Launcher = void (*)(rexi_plan*, const LegTables&, double*, int, int, hipStream_t);
     static constexpr Launcher of[4] = {launch_forward<1>, launch_forward<2>, launch_forward<3>, launch_forward<4>};
-    for (int c0 = 0; c0 < C; c0 += 32) {
-        const int w = std::min(32, C - c0);
-        of[((w + 3) / 4 + 1) / 2 - 1](pl, t, spec, C, c0, w, s);
-        REXI_HIP(hipGetLastError());
-    }
+    const int cw = column_chunk(C, 1);
+    of[(cw / 4 + 1) / 2 - 1](pl, t, spec, C, cw, s);
+    REXI_HIP(hipGetLastError());
     return REXI_OK;
 }
 
 template <int NG>
-void launch_inverse(rexi_plan* pl, const LegTables& t, const double* spec, int C, int c0, int w, hipStream_t s) {
+void launch_inverse(rexi_plan* pl, const LegTables& t, const double* spec, int C, int cw, hipStream_t s) {
     const auto k = t.inv_r == 2 ? k_legendre_inverse<NG, 2> : k_legendre_inverse<NG, 1>;
-    hipLaunchKernelGGL(k, dim3(t.ntiles_i), dim3(256), inverse_lds(NG), s, (const LegWork*)t.d_tiles_i, t.d_restart,
-                       t.d_tail, t.d_lcoef, t.d_lscale, pl->d_mu, spec, pl->d_four, t.T,
-                       pl->nlat, pl->nhalf, C, c0, w);
+    hipLaunchKernelGGL(k, dim3(t.ntiles_i, (C + cw - 1) / cw), dim3(256), inverse_lds(NG), s,
+                       (const LegWork*)t.d_tiles_i, t.d_restart, t.d_tail, t.d_lcoef, t.d_lscale, pl->d_mu, spec,
+                       pl->d_four, t.T, pl->nlat, pl->nhalf, C, cw);
 }
 
-// spec [C/2][nspec(t.T)] -> Fw (C columns), in launches of at most 32 columns
-// (up to eight four-column groups)
+// spec [C/2][nspec(t.T)] -> Fw (C columns).  Where one latitude tile per wave leaves
+// the chip few workgroups, each takes two column groups instead of all, if they pair
+// up evenly (T256 on 512 x 256: 12 fields 15.5 -> 13.6 us, 8 fields 13.4 -> 11.3; T127,
+// 12 fields 9.3 -> 7.5; T341, 8 fields 22.4 -> 21.1; but T511 with two tiles per wave
+// 32 -> 36, and T300 with three groups 13.0 -> 16.3).
 int leg_inverse(rexi_plan* pl, const LegTables& t, const double* spec, int C, hipStream_t s) {
-    using Launcher = void (*)(rexi_plan*, const LegTables&, const double*, int, int, int, hipStream_t);
+    using Launcher = void (*)(rexi_plan*, const LegTables&, const double*, int, int, hipStream_t);
     static constexpr Launcher of[8] = {launch_inverse<1>, launch_inverse<2>, launch_inverse<3>, launch_inverse<4>,
                                        launch_inverse<5>, launch_inverse<6>, launch_inverse<7>, launch_inverse<8>};
-    for (int c0 = 0; c0 < C; c0 += 32) {
-        const int w = std::min(32, C - c0);
-        of[(w + 3) / 4 - 1](pl, t, spec, C, c0, w, s);
-        REXI_HIP(hipGetLastError());
-    }
+    const int groups = (C + 3) / 4;
+    const int cw = column_chunk(C, t.inv_r == 1 && groups % 2 == 0 ? groups / 2 : 1);
+    of[cw / 4 - 1](pl, t, spec, C, cw, s);
+    REXI_HIP(hipGetLastError());
     return REXI_OK;
 }
 
