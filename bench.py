@@ -98,9 +98,11 @@ def legendre_large_run(rexi, synth, torch, dev, reps=5):
 
 
 def kernel_source_digest():
+    """Of the solve kernels: the tiled ones and those with one pole per lane."""
     h = hashlib.sha256()
-    with open(os.path.join(ROOT, "paper_1812_03431_amd", "csrc", "rexi_kernels.hip"), "rb") as f:
-        h.update(f.read())
+    for name in ("rexi_kernels.hip", "sweep_kernels.hip"):
+        with open(os.path.join(ROOT, "paper_1812_03431_amd", "csrc", name), "rb") as f:
+            h.update(f.read())
     return h.hexdigest()[:16]
 
 
@@ -357,9 +359,10 @@ def main():
     for _ in range(args.warmup):
         job()
     torch.cuda.synchronize()
-    # the timed region runs the product path (captured step graphs); the plan
-    # brackets each step's graph replay and each Legendre launch with a HIP
-    # event pair on the launch stream
+    # the timed region runs the product path (a tiled schedule's captured step
+    # graphs, a pole-per-lane schedule's two launches); the plan brackets each
+    # step's solve and reduction and each Legendre launch with a HIP event pair
+    # on the launch stream
     plan.set_graphs(True)
     plan.set_timing(True)
     t0 = time.perf_counter()
@@ -450,17 +453,19 @@ def main():
         "schedule": chosen,
         "schedule_name": sched_name,
         "schedule_classes": [list(c) for c in sched_classes],
-        "timed_path": "step graphs on; HIP events around each step graph and Legendre launch",
+        "timed_path": "step graphs on (pole-per-lane schedules launch directly); HIP events around each step's "
+                      "solve and reduction and each Legendre launch",
         "rexi_step_ms": avg_solve_s * 1e3,
         "fwd_plus_adjoint_step_ms": 2 * avg_solve_s * 1e3,
         "batched_step_ms": batched_ms,
         "per_term_step_ms": per_term_ms,
         "batched_vs_per_term": per_term_ms / batched_ms,
         "roofline": {"bound": "alu", "achieved": achieved, "peak": FP64_VECTOR_PEAK, "unit": "TFLOP/s",
-                     "frac": achieved / FP64_VECTOR_PEAK, "traffic": traffic, "kernel": "k_solve",
+                     "frac": achieved / FP64_VECTOR_PEAK, "traffic": traffic,
+                     "kernel": "k_sweep" if "sweep" in sched_name else "k_solve",
                      "flops_per_launch": fl, "flop_count": "nspec N (40 + 156 S) per forward step",
                      "avg_launch_ms": avg_solve_s * 1e3, "launches": solve_n,
-                     "launch": "one step: the captured graph of the solve class launches and the reduction",
+                     "launch": "one step: the solve launches and the reduction",
                      "thomas_flops_per_launch": fl_thomas, "thomas_achieved": fl_thomas / avg_solve_s / 1e12,
                      "thomas_frac": fl_thomas / avg_solve_s / 1e12 / FP64_VECTOR_PEAK,
                      "algorithmic_bytes_per_launch": state_bytes,

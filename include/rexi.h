@@ -195,7 +195,8 @@ int rexi_step_adjoint(rexi_plan *plan, const void *g1, void *g0, int S, int nste
 /* rexi_step for callers that cannot allocate device memory (code under HIP
  * graph capture, tight serving loops, harnesses that forbid allocation): the
  * same kernels and the plan's current schedule for S, with the workspace
- * (states in chain layout, partial sums, work counters) in one fixed 64 MiB
+ * (states in chain layout or records, partial sums, block-boundary values, work
+ * counters) in one fixed 64 MiB
  * device array of the library instead of the plan's allocations; kernels
  * launched one by one, no graph, no event.  Calls no hipMalloc, hipFree or
  * other allocating routine.
@@ -226,7 +227,10 @@ int rexi_plan_autotune(rexi_plan *plan, int S, void *stream, int *chosen);
 
 /* Select schedule candidate `index` (as reported by rexi_plan_autotune) for
  * S states; REXI_EINVAL if out of range.  *count (may be NULL) receives the
- * number of candidates. */
+ * number of candidates.  The first step of S states builds its default schedule
+ * alone; the candidate list is built by the first call that asks for it (this
+ * one, rexi_plan_autotune or a query), and a schedule's device tables when it is
+ * selected or timed. */
 int rexi_plan_set_schedule(rexi_plan *plan, int S, int index, int *count);
 
 /* *index receives the schedule candidate that steps with S states use now
@@ -262,10 +266,12 @@ int rexi_plan_schedule_classes(rexi_plan *plan, int S, int index, int capacity, 
  * to fit); REXI_EINVAL for a NULL buf or capacity < 1. */
 int rexi_plan_schedule_name(rexi_plan *plan, int S, int index, char *buf, int capacity);
 
-/* Step graphs.  By default every step is replayed as a captured HIP graph
- * (solve launches + reduction), built on first use per (S, direction, buffer)
- * and rebuilt after a schedule change; enable = 0 makes the plan launch the
- * kernels one by one instead.  Results are identical either way. */
+/* Step graphs.  By default every step of a tiled schedule is replayed as a
+ * captured HIP graph (solve launches + reduction), built on first use per (S,
+ * direction, buffer) and rebuilt after a schedule change; enable = 0 makes the
+ * plan launch the kernels one by one instead.  A pole-per-lane ("sweep")
+ * schedule has two launches per step and always launches them.  Results are
+ * identical either way. */
 int rexi_plan_set_graphs(rexi_plan *plan, int enable);
 
 /* Tile-class launches.  A step launches one solve kernel per tile class; by
@@ -278,9 +284,8 @@ int rexi_plan_set_streams(rexi_plan *plan, int enable);
 /* Kernel timing for measurement.  rexi_plan_set_timing(plan, 1) makes the plan
  * bracket every later launch of the timed kernels with a HIP event pair on the
  * launch stream; 0 stops recording.  A solve timing covers one step: with step
- * graphs on (the default) the replay of the step's graph, i.e. the solve
- * launches and the reduction of their partial sums; with graphs off the solve
- * launches alone.  rexi_plan_kernel_time synchronises on the recorded events
+ * graphs on (the default) the solve launches and the reduction of their partial
+ * sums; with graphs off the solve launches alone.  rexi_plan_kernel_time synchronises on the recorded events
  * and returns the summed elapsed time (ms) and the number of launches of one
  * kernel since the last query, then forgets them.
  *   kernel  REXI_KERNEL_SOLVE (fused banded solve), REXI_KERNEL_LEGENDRE_FWD,

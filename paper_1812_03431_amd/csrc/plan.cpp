@@ -576,7 +576,7 @@ int grow(rexi_plan* pl, T** p, long long* capacity, long long n, bool keep) {
 // records of S states and its scratch, one slot per workgroup, at most
 // kSweepScratch bytes of them (workgroups beyond take several items in turn).
 constexpr long long kSweepScratch = 1LL << 30;
-struct Sizes { long long part = 0, rec = 0, scratch = 0; };
+struct Sizes { long long part = 0, rec = 0, scratch = 0, slot = 0; };
 
 void add_sizes(const rexi_plan* pl, const Schedule& sc, Sizes& z) {
     z.part = std::max(z.part, sc.part_size);
@@ -585,6 +585,7 @@ void add_sizes(const rexi_plan* pl, const Schedule& sc, Sizes& z) {
     if (sc.sweep_stride == 0) return;
     const long long most = std::max(1LL, kSweepScratch / 16 / kSweepWaves / sc.sweep_stride);
     const long long wgs = ((long long)sc.sweep_items.size() + kSweepWaves - 1) / kSweepWaves;
+    z.slot = std::max(z.slot, kSweepWaves * sc.sweep_stride);
     z.scratch = std::max(z.scratch, std::min(wgs, most) * kSweepWaves * sc.sweep_stride);
 }
 
@@ -592,6 +593,12 @@ int ensure_sizes(rexi_plan* pl, const Sizes& z, bool keep) {
     int rc = grow(pl, &pl->d_part, &pl->part_capacity, z.part, keep);
     for (int d = 0; d < 2 && !rc; ++d) rc = grow(pl, &pl->d_rec[d], &pl->rec_capacity[d], z.rec, keep);
     if (!rc) rc = grow(pl, &pl->d_sweep_scratch, &pl->sweep_scratch_capacity, z.scratch, keep);
+    // where memory is short, fewer slots do: their workgroups take more items in turn
+    for (long long n = z.scratch; rc == REXI_ENOMEM && n > z.slot;) {
+        (void)hipGetLastError();
+        n = std::max(z.slot, n / 2);
+        rc = grow(pl, &pl->d_sweep_scratch, &pl->sweep_scratch_capacity, n, keep);
+    }
     return rc;
 }
 

@@ -1,4 +1,6 @@
-// Fused T-REXI step kernels for gfx950.
+// Fused T-REXI step kernels for gfx950: tiled chains (the schedules that
+// measurement may choose, the default where there is no Coriolis force, and the
+// per-term form; sweep_kernels.hip has the default), and the f-sphere.
 //
 // One step (Section 4.2; Algorithm 1's sum over terms and its reduction) is
 //   u1 = D^{-1} [ sum_k beta+_k (alpha_k + dt L^)^{-1} + sum_k beta-_k (alpha_k - dt L^)^{-1} ] D u0

@@ -1,9 +1,9 @@
 // The fused T-REXI step with one pole per lane (gfx950).
 //
-// Same sum over poles as rexi_kernels.hip, for problems with enough (pole
-// batch, chain) pairs to fill the chip: a lane solves a whole tridiagonal
+// Same sum over poles as rexi_kernels.hip: a lane solves a whole tridiagonal
 // chain for its pole by plain elimination (no partitioning, no cross-lane
-// reduction of interface unknowns), 64 poles per wave.
+// reduction of interface unknowns), 64 poles per wave.  A step is k_sweep (or
+// k_sweep_short) and k_sweep_reduce.
 //
 // Real form.  With zeta = i zeta', Phi = i Phi' the shifted operator of a chain
 // is alpha + i dt H with H real symmetric: off-diagonals i c_t, diagonal
@@ -38,6 +38,21 @@
 // registers and substitutes back.  Pass 1 needs the block-end values alone, a sum
 // of products of the (real, uniform) right-hand sides with per-pole coefficients
 // that all states share.
+//
+// What bounds it.  FP64 issue: a pair of elements takes 140 FP64 instructions and
+// four reciprocals with one state, some 720 cycles of a SIMD.  At T127 with 8215
+// poles that is 75% of the time (482 us; 478 without the scalar loads' misses, 446
+// without the LDS).  With four states at T256 and 2071 poles the instructions alone
+// take 0.98 of 1.53 ms; the rest is waits that two waves per SIMD do not cover: the
+// block-boundary loads (0.1 ms), LDS reads (0.1), scalar loads (0.06).  256 registers
+// are needed for a block of six pairs (four or eight pairs, or one wave per SIMD, took
+// 1.9 to 2.4 ms).  Few poles or short chains leave latency: one item alone takes
+// 0.6 us a pair, and 5 us to start and end.
+//
+// A step, with the tiled schedules and the partial sums' reduction before / with one
+// pole per lane: T256, 2071 poles, four states 2468 / 1537 us; T301, 1245 poles, three
+// states 2457 / 983; T128, 535 poles, eight states 341 / 228; T128, 407 poles, one
+// state 80 / 47; T63, 151 poles, one state 37 / 13 in a run of 24.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -772,8 +787,11 @@ k_sweep(const SweepArgs A, int* counter) {
 // Where every part has at most kShort pairs (whole chains, or halves of split
 // ones) and one wave per SIMD is enough, nothing has to be repeated or stored:
 // pivots and forward values of the whole part stay in registers (512 per lane).
-// One batch of poles per item.  The time is the latency of one wave: its scalar
-// lines are requested at once, beside the poles.
+// One batch of poles per item.  The time is the latency of one wave, about 10 us
+// with up to 16 pairs and one state, half of it before the first pivot and after the
+// last sum: its scalar lines are requested at once, beside the poles.  T63, 151 poles,
+// one state: 15.5 us a step against 21 with split chains in blocks and 27 with whole
+// ones.
 constexpr int kShort = kSweepShort;
 
 // scalar lines of [p, p + 8 n): requested here, waited for at warm_done

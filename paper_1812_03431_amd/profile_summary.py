@@ -36,10 +36,15 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SOLVE = re.compile(r"k_solve<(\d+), (true|false), (\d), (\d), (\d)>")
 
 
+SWEEP = re.compile(r"k_sweep(_short)?(<[^>]*>)?\(")
+REDUCE = ("k_reduce", "k_sweep_reduce")
+
+
 def source_digest():
     h = hashlib.sha256()
-    with open(os.path.join(ROOT, "paper_1812_03431_amd", "csrc", "rexi_kernels.hip"), "rb") as f:
-        h.update(f.read())
+    for name in ("rexi_kernels.hip", "sweep_kernels.hip"):
+        with open(os.path.join(ROOT, "paper_1812_03431_amd", "csrc", name), "rb") as f:
+            h.update(f.read())
     return h.hexdigest()[:16]
 
 
@@ -65,8 +70,12 @@ def class_of(name):
     if m:
         se, pt, kind, w, rot = m.groups()
         return ("per_term" if pt == "true" else "batched", f"k_solve<{se}, {pt}, {kind}, {w}, {rot}>")
-    if "k_reduce" in name:
-        return ("batched", "k_reduce")
+    m = SWEEP.search(name)
+    if m:
+        return ("batched", m.group(0)[:-1])
+    for r in REDUCE:
+        if r in name:
+            return ("batched", r)
     return (None, None)
 
 
@@ -93,11 +102,11 @@ def earlier_readings(path):
     if "traffic_bytes_per_launch" in old:
         runs.append({"kernel_source_sha256_16": old.get("kernel_source_sha256_16"), "schedule": old.get("schedule"),
                      "MB_per_step": round(old["traffic_bytes_per_launch"] / 1e6, 2),
-                     "what": "k_solve class launches and k_reduce of one step"})
+                     "what": "solve launches and reduction of one step"})
         if "k_solve_classes_bytes_per_launch" in old:
             runs.append({"kernel_source_sha256_16": old.get("kernel_source_sha256_16"), "schedule": old.get("schedule"),
                          "MB_per_step": round(old["k_solve_classes_bytes_per_launch"] / 1e6, 2),
-                         "what": "k_solve class launches only (no reduction)"})
+                         "what": "solve launches only (no reduction)"})
     return runs
 
 
@@ -114,6 +123,8 @@ def traffic(fetch_csv, write_csv, schedule, workload, commands, earlier=(), sche
                 if k == kind:
                     cls[c][key].append(v)
         out[kind] = cls
+    if any("k_sweep" in c for c in out["batched"]):  # then k_reduce ends the per-term step
+        out["batched"].pop("k_reduce", None)
     per_class = {}
     step = solve_only = 0.0
     for c, v in out["batched"].items():
@@ -121,7 +132,7 @@ def traffic(fetch_csv, write_csv, schedule, workload, commands, earlier=(), sche
         w = sum(v["write_kib"]) / max(1, len(v["write_kib"]))
         per_class[c] = {"fetch_kib_mean": f, "write_kib_mean": w, "dispatches": len(v["fetch_kib"])}
         step += (f * fscale + w * wscale) * 1024.0
-        if c != "k_reduce":
+        if c not in REDUCE:
             solve_only += (f * fscale + w * wscale) * 1024.0
     pt_f = sum(sum(v["fetch_kib"]) for v in out["per_term"].values())
     pt_w = sum(sum(v["write_kib"]) for v in out["per_term"].values())
@@ -130,7 +141,7 @@ def traffic(fetch_csv, write_csv, schedule, workload, commands, earlier=(), sche
     cal = {"kernel": "torch.mul(a, 1.0, out=b) on 2^27 doubles: reads 1 GiB, writes 1 GiB",
            "fetch_kib": fcal, "write_kib": wcal, "fetch_scale": fscale, "write_scale": wscale,
            "dispatch": "the largest reading among the run's torch multiply dispatches"}
-    solve = {"kernel": "k_solve (fused REXI solve) class launches and k_reduce of one step",
+    solve = {"kernel": "solve launches (fused REXI solve) and reduction of one step",
              "workload": workload, "schedule": schedule, "schedule_name": schedule_name,
              "kernel_source_sha256_16": digest,
              "commands": commands, "calibration": cal, "per_class": per_class,
@@ -168,6 +179,8 @@ def counters(csv_paths, schedule, workload, commands, steps_note, clock_ghz=2.4,
             if k != "batched":
                 continue
             per[c][(r["Counter_Name"], run, r["Dispatch_Id"])].append(float(r["Counter_Value"]))
+    if any("k_sweep" in c for c in per):  # then k_reduce ends the per-term step
+        per.pop("k_reduce", None)
     per_class = {}
     step = collections.Counter()
     for c, d in per.items():
@@ -180,7 +193,7 @@ def counters(csv_paths, schedule, workload, commands, steps_note, clock_ghz=2.4,
         for name, v in mean.items():
             if name != "dispatches":
                 step[name] += v
-    out = {"kernel": "k_solve class launches and k_reduce of one step", "workload": workload,
+    out = {"kernel": "solve launches and reduction of one step", "workload": workload,
            "schedule": schedule, "schedule_name": schedule_name, "kernel_source_sha256_16": source_digest(),
            "commands": commands,
            "per_class_mean_per_dispatch": per_class, "per_step": dict(step), "note": steps_note}
@@ -210,7 +223,8 @@ def stats(stats_csv, trace_csv, schedule, workload, command, events_ms, schedule
     sched = f"schedule {schedule}" + (f" ({schedule_name})" if schedule_name else "")
     lines = [f"# rocprofv3 kernel statistics: {workload} benchmark job (bench.py), {sched}",
              "# command (on one MI355X, from /tmp with TMPDIR=/tmp):", f"#   {command}",
-             "# one REXI step = one captured graph: a k_solve launch per tile class "
+             "# one REXI step = k_sweep<split chains, one state> or k_sweep_short and k_sweep_reduce or, with a tiled "
+             "schedule, one captured graph: a k_solve launch per tile class "
              "(template <elements per lane, per-term, move kind, waves, states per item>) and k_reduce;",
              "# k_solve<.., true, .., 1, 1> are the per-term comparison launches (one per pole and class).",
              f"# kernel source sha256[:16] = {source_digest()}"]
@@ -218,10 +232,10 @@ def stats(stats_csv, trace_csv, schedule, workload, command, events_ms, schedule
     for r in sorted(rows(trace_csv), key=lambda r: int(r["Start_Timestamp"])):
         n = r["Kernel_Name"]
         k, c = class_of(n)
-        if k == "batched" and c != "k_reduce":
+        if k == "batched" and c not in REDUCE:
             if start is None:
                 start = int(r["Start_Timestamp"])
-        elif c == "k_reduce" and start is not None:
+        elif c in REDUCE and start is not None:
             spans.append((int(r["End_Timestamp"]) - start) / 1e3)
             start = None
     if spans:
@@ -242,7 +256,7 @@ def stats(stats_csv, trace_csv, schedule, workload, command, events_ms, schedule
 
 # flops of one MFMA wave-instruction of each Legendre kernel:
 # v_mfma_f64_4x4x4f64 (four blocks of 4 x 4 x 4 multiply-adds) or, in the
-# inverse for grids of more than 128 northern latitudes, v_mfma_f64_16x16x4f64
+# sequential inverse that earlier summaries hold, v_mfma_f64_16x16x4f64
 MFMA_FLOPS = {"k_legendre_forward": 4 * 4 * 4 * 4 * 2, "k_legendre_inverse": 4 * 4 * 4 * 4 * 2,
               "k_legendre_inverse_seq": 16 * 16 * 4 * 2}
 SH_KERNELS = ("k_fft_forward", "k_legendre_forward", "k_legendre_inverse_seq", "k_legendre_inverse", "k_fft_inverse")
@@ -272,7 +286,7 @@ def sh(stats_csv, pmc_csv, title, commands, T, nlat, fields, peak=78.6):
     lines += [f"# algorithmic Legendre flops per launch 2 (nlat/2) (2B) nspec = {alg:.4g} (folded: the kernels use the "
               f"equatorial symmetry; unfolded, 2 nlat (2B) nspec, twice that: frac x 2); FP64 matrix peak {peak} TFLOP/s",
               "# MFMA pipe busy = SQ_VALU_MFMA_BUSY_CYCLES / (1024 SIMDs x GRBM_GUI_ACTIVE / 8 XCDs); executed = "
-              "SQ_INSTS_MFMA x 512 flop (v_mfma_f64_4x4x4f64) or x 2048 (v_mfma_f64_16x16x4f64, k_legendre_inverse_seq)",
+              "SQ_INSTS_MFMA x 512 flop (v_mfma_f64_4x4x4f64)",
               "# summary: python -m paper_1812_03431_amd.profile_summary sh (this file's arguments)", "",
               f"{'kernel':24s} {'calls':>5s} {'avg_us':>8s} {'min_us':>8s} {'max_us':>8s} {'alg_TF':>7s} {'frac':>6s} "
               f"{'exec_MFLOP':>10s} {'mfma_busy':>9s} {'waves':>6s} {'valu/wave':>9s} {'lds_conf':>9s}"]
