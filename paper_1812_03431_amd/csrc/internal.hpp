@@ -117,6 +117,7 @@ constexpr int kSweepRec = 6;      // doubles of data per pair and state
 constexpr int kSweepPad = 2 * kSweepBlock * kSweepRec;  // doubles past the end of constants and data that a block may read
 constexpr int kSweepStates = 4;   // most states per work item
 constexpr int kSweepWaves = 4;    // waves of a workgroup
+constexpr int kSweepGroups = 512; // workgroups that the chip holds, two per CU
 constexpr int kSweepSplit = 24;   // shortest chain that is split between two waves
 constexpr int kSweepShort = 16;   // most pairs of a chain (or half) that a wave holds in registers
 constexpr int kSweepKind = 3;     // its kind in a schedule's classes (no moves between lanes)
@@ -322,6 +323,17 @@ int check_state_call(rexi_plan* pl, const void* in, const void* out, int S, int 
 // The no-allocation step's fixed device array: its address on the current
 // device, looked up once per device (noalloc.hip).
 int scratch_setup(void** ptr, size_t* bytes);
+
+// Whole-chain schedules whose workgroups' block-boundary values, one slot each,
+// exceed the 256 MB memory-side cache run as a resident grid that takes the items
+// from a counter, so that kSweepGroups slots (0.4 GB) are written and read again and
+// again.  T301, three states (1.5 GB otherwise) 993 -> 969 us a step; T256, four
+// states (1.8 GB) 1542 -> 1534; within 0.5% at T128, eight states (0.42 GB) and T127,
+// one state (0.29 GB).  Split and register-resident schedules are smaller.
+inline bool sweep_resident(const Schedule& sc) {
+    const long long wgs = ((long long)sc.sweep_items.size() + kSweepWaves - 1) / kSweepWaves;
+    return !sc.split && wgs > kSweepGroups && wgs * kSweepWaves * sc.sweep_stride * 16 > (256LL << 20);
+}
 
 // The plan's own workspace.
 inline Workspace plan_workspace(const rexi_plan* pl, const Schedule& sc) {

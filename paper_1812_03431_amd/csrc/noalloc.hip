@@ -63,22 +63,21 @@ struct Carver {
     }
 };
 
-// Of a pole-per-lane schedule: records, partial sums and counters, then the
-// workgroups' slots.  Fewer workgroups than fill the chip (two per CU) would run
+// Of a pole-per-lane schedule: records, partial sums, then the workgroups' slots (no
+// counter: the workgroups take their items in turn).  Fewer workgroups than fill the chip (two per CU) would run
 // much slower than the tiled schedule, which then takes the call.
-struct SweepPieces { size_t rec[2], part, counters, slots; long long groups; };
+struct SweepPieces { size_t rec[2], part, slots; long long groups; };
 
 bool carve(const rexi_plan* pl, const Schedule& sc, SweepPieces& w) {
     Carver c;
     const size_t rec = ((size_t)(pl->sweep[sc.split].npairs + 1) * sc.S * kSweepRec + kSweepPad) * sizeof(double);
     for (size_t& o : w.rec) o = c.take(rec);
     w.part = c.take((size_t)sc.part_size * 16);
-    w.counters = c.take(kMaxLaunches * sizeof(int));
     w.slots = c.off;
     const size_t slot = (size_t)sc.sweep_stride * 16 * kSweepWaves;
     const long long wgs = ((long long)sc.sweep_items.size() + kSweepWaves - 1) / kSweepWaves;
     w.groups = c.off > pl->scratch_bytes ? 0 : slot ? (long long)((pl->scratch_bytes - c.off) / slot) : wgs;
-    return w.groups >= std::min(wgs, 512LL);
+    return w.groups >= std::min(wgs, (long long)kSweepGroups);
 }
 }  // namespace
 
@@ -113,7 +112,6 @@ extern "C" int rexi_step_noalloc(rexi_plan* plan, const void* u0, void* u1, int 
             char* base = static_cast<char*>(plan->scratch);
             Workspace ws{};
             ws.part = reinterpret_cast<double2*>(base + w.part);
-            ws.counters = reinterpret_cast<int*>(base + w.counters);
             for (int d = 0; d < 2; ++d) ws.rec[d] = reinterpret_cast<double*>(base + w.rec[d]);
             ws.sweep_scratch = reinterpret_cast<double2*>(base + w.slots);
             ws.sweep_groups = (int)std::min(w.groups, 1LL << 20);

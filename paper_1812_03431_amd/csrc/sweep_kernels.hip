@@ -1108,6 +1108,12 @@ hipError_t enqueue_sweep_solve(rexi_plan* pl, const Workspace& ws, const Schedul
     const size_t lds = sizeof(double2) * kSweepWaves *
                        ((sc.short_chains ? 64 : 0) + 128 * (size_t)sc.sweep_nst + kRedDoubles / 2);
     int* counter = nullptr;
+    if (!sc.persistent && ws.counters && sweep_resident(sc)) {
+        grid = std::min(grid, kSweepGroups);
+        counter = ws.counters;
+        const hipError_t e = enqueue_reset_counters(counter, 1, s);
+        if (e != hipSuccess) return e;
+    }
     if (sc.persistent) {
         int dev = 0, ncu = 0, per_cu = 0;
         hipError_t e = hipGetDevice(&dev);
