@@ -222,7 +222,7 @@ int rexi_step_per_term(rexi_plan *plan, const void *u0, void *u1, int S, void *s
 
 /* Time the candidate tile/wave schedules for S states on `stream` (runs
  * steps on internal buffers) and keep the fastest for later calls with S (a
- * persistent one only where it is faster by more than 1%).
+ * persistent one only where it is faster by more than 3%).
  * *chosen (may be NULL) receives the index of the chosen candidate. */
 int rexi_plan_autotune(rexi_plan *plan, int S, void *stream, int *chosen);
 
