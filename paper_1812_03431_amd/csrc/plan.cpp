@@ -53,6 +53,7 @@ int dev_alloc(T** p, size_t count) {
     hipError_t e = hipMalloc((void**)p, count * sizeof(T));
     if (e != hipSuccess) {
         *p = nullptr;
+        (void)hipGetLastError();  // reported here; a later launch's check would find it again
         return fail(REXI_ENOMEM, std::string("hipMalloc of ") + std::to_string(count * sizeof(T)) +
                                      " bytes failed: " + hipGetErrorString(e));
     }
@@ -595,7 +596,6 @@ int ensure_sizes(rexi_plan* pl, const Sizes& z, bool keep) {
     if (!rc) rc = grow(pl, &pl->d_sweep_scratch, &pl->sweep_scratch_capacity, z.scratch, keep);
     // where memory is short, fewer slots do: their workgroups take more items in turn
     for (long long n = z.scratch; rc == REXI_ENOMEM && n > z.slot;) {
-        (void)hipGetLastError();
         n = std::max(z.slot, n / 2);
         rc = grow(pl, &pl->d_sweep_scratch, &pl->sweep_scratch_capacity, n, keep);
     }
@@ -1271,9 +1271,13 @@ int rexi_plan_autotune(rexi_plan* plan, int S, void* stream, int* chosen) {
     hipStream_t s = (hipStream_t)stream;
     const size_t bytes = (size_t)S * 3 * plan->nspec * 16;
     void *u0 = nullptr, *u1 = nullptr;
-    REXI_HIP(hipMalloc(&u0, bytes));
-    hipError_t e = hipMalloc(&u1, bytes);
-    if (e != hipSuccess) { (void)hipFree(u0); return hip_fail(e, "hipMalloc"); }
+    hipError_t e = hipMalloc(&u0, bytes);
+    if (e == hipSuccess) e = hipMalloc(&u1, bytes);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        (void)hipFree(u0);
+        return hip_fail(e, "hipMalloc");
+    }
     hipEvent_t a = nullptr, b = nullptr;
     int best = -1;
     float best_ms = 0;

@@ -770,7 +770,10 @@ namespace {
 
 int device_alloc(void** p, size_t bytes) {
     hipError_t e = hipMalloc(p, bytes ? bytes : 1);
-    if (e != hipSuccess) return fail(REXI_ENOMEM, std::string("hipMalloc failed: ") + hipGetErrorString(e));
+    if (e != hipSuccess) {
+        (void)hipGetLastError();  // reported here; a later launch's check would find it again
+        return fail(REXI_ENOMEM, std::string("hipMalloc failed: ") + hipGetErrorString(e));
+    }
     return REXI_OK;
 }
 

@@ -1,0 +1,335 @@
+// The plan and its step entry points (plan.cpp, noalloc.hip) on the CPU: a stub HIP
+// runtime whose device memory is host memory with a register of live allocations, and
+// stub launchers that check every pointer and size that the kernels would be given.
+// usage: plan_host SCENARIO; exit status 0 where it passes.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <functional>
+#include <map>
+#include <new>
+#include <set>
+#include <string>
+#include <vector>
+
+#include "internal.hpp"
+
+using namespace rexi;
+
+// ------------------------------------------------------------------ stub runtime
+namespace {
+
+std::map<char*, size_t> live;
+std::set<void*> held;          // workspace that launches under a caller's capture were given
+int bad = 0, mallocs = 0, events_made = 0;
+int fail_at = 0;               // the fail_at-th hipMalloc from now fails ...
+bool fail_on = false;          // ... and those after it
+size_t budget = ~size_t(0), used = 0;
+bool capturing = false;
+hipError_t last_error = hipSuccess;
+double now_ms = 0;             // what the launches so far took
+std::function<double(const Schedule&)> cost;  // of one step, ms
+
+void complain(const std::string& what) {
+    std::fprintf(stderr, "  %s\n", what.c_str());
+    ++bad;
+}
+
+// [p, p + bytes) is device memory
+void need(const void* p, size_t bytes, const char* what, const void* array = nullptr, size_t array_bytes = 0) {
+    const char* c = static_cast<const char*>(p);
+    const char* a = static_cast<const char*>(array);
+    if (a && c >= a && c + bytes <= a + array_bytes) return;
+    auto it = live.upper_bound(const_cast<char*>(c));
+    if (p && it != live.begin()) {
+        --it;
+        if (c >= it->first && c + bytes <= it->first + it->second) {
+            if (capturing) held.insert(it->first);
+            return;
+        }
+    }
+    complain(std::string(what) + (p ? ": not within a live allocation" : ": NULL"));
+}
+
+void expect(bool ok, const std::string& what) {
+    if (!ok) complain("expected: " + what);
+}
+
+}  // namespace
+
+extern "C" {
+hipError_t hipMalloc(void** p, size_t n) {
+    ++mallocs;
+    const bool fails = (fail_at > 0 && --fail_at == 0) || used + n > budget;
+    if (fails) {
+        if (fail_on) fail_at = 1;
+        *p = nullptr;
+        return last_error = hipErrorOutOfMemory;
+    }
+    if (capturing) complain("allocation under a caller's capture");
+    *p = std::malloc(n);
+    live[static_cast<char*>(*p)] = n;
+    used += n;
+    return hipSuccess;
+}
+hipError_t hipFree(void* p) {
+    if (!p) return hipSuccess;
+    auto it = live.find(static_cast<char*>(p));
+    if (it == live.end()) {
+        complain("hipFree of something else");
+        return hipErrorInvalidValue;
+    }
+    if (held.count(p)) complain("workspace of a captured step freed");
+    used -= it->second;
+    live.erase(it);
+    std::free(p);
+    return hipSuccess;
+}
+hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) {
+    need(d, n, "hipMemcpy");
+    std::memcpy(d, s, n);
+    return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind, hipStream_t) { return hipSuccess; }
+hipError_t hipMemset(void*, int, size_t) { return hipSuccess; }
+hipError_t hipMemsetAsync(void*, int, size_t, hipStream_t) { return hipSuccess; }
+hipError_t hipGetLastError() {
+    const hipError_t e = last_error;
+    last_error = hipSuccess;
+    return e;
+}
+const char* hipGetErrorString(hipError_t) { return "stub"; }
+hipError_t hipGetDevice(int* d) {
+    *d = 0;
+    return hipSuccess;
+}
+hipError_t hipGetSymbolAddress(void** p, const void* s) {
+    *p = const_cast<void*>(s);
+    return hipSuccess;
+}
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
+    *s = reinterpret_cast<hipStream_t>(8);
+    return hipSuccess;
+}
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipSuccess; }
+hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t* g) {
+    *g = reinterpret_cast<hipGraph_t>(8);
+    return hipSuccess;
+}
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* st) {
+    *st = capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+hipError_t hipGraphInstantiate(hipGraphExec_t* e, hipGraph_t, hipGraphNode_t*, char*, size_t) {
+    *e = reinterpret_cast<hipGraphExec_t>(8);
+    return hipSuccess;
+}
+hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
+hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
+hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t* e) {
+    ++events_made;
+    *e = reinterpret_cast<hipEvent_t>(new double(0));
+    return hipSuccess;
+}
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
+hipError_t hipEventDestroy(hipEvent_t e) {
+    delete reinterpret_cast<double*>(e);
+    return hipSuccess;
+}
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t) {
+    *reinterpret_cast<double*>(e) = now_ms;
+    return hipSuccess;
+}
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b) {
+    *ms = (float)(*reinterpret_cast<double*>(b) - *reinterpret_cast<double*>(a));
+    return hipSuccess;
+}
+}  // extern "C"
+
+// ------------------------------------------------------------------ stub launchers
+namespace rexi {
+
+bool solve_variant_supported(int SE, int kind, int rot, bool) {
+    return kind == 0 ? SE == 16 && rot == 1 : kind == 2 ? (SE == 4 || SE == 8) && rot <= 2 : SE <= 16;
+}
+int solve_waves_per_item() { return 4; }
+int solve_variant_list(bool, int*, int*, int*, int) { return 0; }
+
+static void need_ws(rexi_plan* pl, const void* p, size_t bytes, const char* what) {
+    need(p, bytes, what, pl->scratch, pl->scratch_bytes);
+}
+static void need_chains(rexi_plan* pl, const Workspace& ws, int buf, int S) {
+    need_ws(pl, ws.ch_var[buf], (size_t)S * (pl->nslots + 2) * 16, "ch_var");
+    need_ws(pl, ws.ch_phi[buf], (size_t)S * pl->nspec * 16, "ch_phi");
+}
+hipError_t enqueue_prep(rexi_plan* pl, const Workspace& ws, const void*, int buf, int S, int, const MInfo* layout,
+                        hipStream_t) {
+    need_chains(pl, ws, buf, S);
+    need(layout, sizeof(MInfo) * (pl->T + 1), "layout");
+    return hipGetLastError();
+}
+hipError_t enqueue_solve(rexi_plan* pl, const Workspace& ws, const Schedule& sc, int buf, int S, int adjoint,
+                         hipStream_t) {
+    need_chains(pl, ws, buf, S);
+    need(sc.d_items, sc.items.size() * sizeof(Item), "items");
+    need(sc.d_minfo, sc.minfo.size() * sizeof(MInfo), "minfo");
+    need(pl->d_poles[adjoint], (size_t)pl->N * 96, "poles");
+    need_ws(pl, ws.part, (size_t)sc.part_size * 16, "part");
+    if (sc.persistent) need_ws(pl, ws.counters, kMaxLaunches * sizeof(int), "counters");
+    if (cost) now_ms += cost(sc);
+    return hipGetLastError();
+}
+hipError_t enqueue_reduce(rexi_plan* pl, const Workspace& ws, const Schedule& sc, const double2* part, int buf_in,
+                          int buf_out, void*, int S, int, const int*, hipStream_t) {
+    need_chains(pl, ws, buf_in, S);
+    need_chains(pl, ws, buf_out, S);
+    need(sc.d_groups, sc.groups.size() * sizeof(Group), "groups");
+    need_ws(pl, part, (size_t)sc.part_size * 16, "part");
+    return hipGetLastError();
+}
+hipError_t enqueue_zero(double2* p, long long n, hipStream_t) {
+    need(p, (size_t)n * 16, "zeroed");
+    return hipGetLastError();
+}
+hipError_t enqueue_finish(rexi_plan* pl, const Workspace& ws, int buf, void*, int S, int, const MInfo*, hipStream_t) {
+    need_chains(pl, ws, buf, S);
+    return hipGetLastError();
+}
+hipError_t enqueue_per_term_pole(rexi_plan* pl, const Workspace& ws, const Schedule& sc, int, int buf, int S,
+                                 hipStream_t) {
+    need_chains(pl, ws, buf, S);
+    need(sc.d_items, sc.items.size() * sizeof(Item), "items");
+    need(pl->d_acc, (size_t)sc.part_size * 16, "acc");
+    return hipGetLastError();
+}
+hipError_t enqueue_fsphere_steps(rexi_plan*, const void*, void*, int, int, int, hipStream_t) { return hipGetLastError(); }
+
+static void need_records(rexi_plan* pl, const Workspace& ws, const Schedule& sc, int buf) {
+    need_ws(pl, ws.rec[buf], ((size_t)(pl->sweep[sc.split].npairs + 1) * sc.S * kSweepRec + kSweepPad) * 8, "records");
+}
+hipError_t enqueue_sweep_prep(rexi_plan* pl, const Workspace& ws, const Schedule& sc, const void*, int buf, int,
+                              int adjoint, hipStream_t) {
+    const SweepTables& t = pl->sweep[sc.split];
+    need_records(pl, ws, sc, buf);
+    need(t.d_idx, (size_t)t.npairs * sizeof(int2), "idx");
+    need(t.d_fin[adjoint], (size_t)t.npairs * 24, "fin");
+    return hipGetLastError();
+}
+hipError_t enqueue_sweep_solve(rexi_plan* pl, const Workspace& ws, const Schedule& sc, int buf, int, int adjoint,
+                               hipStream_t) {
+    const SweepTables& t = pl->sweep[sc.split];
+    need_records(pl, ws, sc, buf);
+    need(sc.d_sweep_items, sc.sweep_items.size() * sizeof(SweepItem), "sweep items");
+    need(t.d_cst, ((size_t)t.npairs * kSweepCst + kSweepPad) * 8, "cst");
+    need(t.d_poles[adjoint], (size_t)pl->N * 96, "sweep poles");
+    need_ws(pl, ws.part, (size_t)sc.part_size * 16, "part");
+    const int wgs = ((int)sc.sweep_items.size() + kSweepWaves - 1) / kSweepWaves;
+    int grid = std::min(wgs, ws.sweep_groups);
+    if (grid < 1) return hipErrorInvalidValue;
+    if (sc.persistent || (ws.counters && sweep_resident(sc))) {
+        need_ws(pl, ws.counters, sizeof(int), "counters");
+        grid = std::min(grid, kSweepGroups);
+    }
+    if (sc.sweep_stride > 0)
+        need_ws(pl, ws.sweep_scratch, (size_t)grid * kSweepWaves * sc.sweep_stride * 16, "boundary values");
+    // register-resident chains take one group of items per workgroup
+    if (sc.short_chains && !sc.persistent) expect(grid == wgs, "a workgroup for every group of items");
+    if (cost) now_ms += cost(sc);
+    return hipGetLastError();
+}
+hipError_t enqueue_sweep_reduce(rexi_plan* pl, const Workspace& ws, const Schedule& sc, int buf_in, int buf_out,
+                                void* u_out, int, int adjoint, hipStream_t) {
+    const SweepTables& t = pl->sweep[sc.split];
+    need_records(pl, ws, sc, buf_in);
+    if (!u_out) need_records(pl, ws, sc, buf_out);
+    need(sc.d_sweep_tiles, sc.sweep_tiles.size() * sizeof(SweepTile), "tiles");
+    need(sc.d_sweep_groups, sc.sweep_groups.size() * sizeof(SweepGroup), "sweep groups");
+    need(t.d_fout[adjoint], (size_t)t.npairs * 24, "fout");
+    need_ws(pl, ws.part, (size_t)sc.part_size * 16, "part");
+    return hipGetLastError();
+}
+int sh_setup(rexi_plan*) { return REXI_OK; }
+void sh_release(rexi_plan*) {}
+int sh_run(rexi_plan*, const void*, void*, int, bool, hipStream_t) { return REXI_OK; }
+int sh_vec_run(rexi_plan*, const void*, void*, long long, int, bool, hipStream_t) { return REXI_OK; }
+
+}  // namespace rexi
+
+// ------------------------------------------------------------------ scenarios
+namespace {
+
+// States are only passed on; their addresses have to be apart.
+char* const kIn = reinterpret_cast<char*>(size_t(1) << 44);
+char* const kOut = reinterpret_cast<char*>(size_t(1) << 45);
+
+rexi_plan* make_plan(int T, int M, int max_states) {
+    rexi_params p{};
+    p.T = T;
+    p.radius = 6.37122e6;
+    p.omega = 7.292e-5;
+    p.gravity = 9.80616;
+    p.mean_depth = 1e4;
+    p.dt = 3600;
+    p.M = M;
+    p.h = 0.2;
+    p.L = 11;
+    p.normalize = 1;
+    p.max_states = max_states;
+    p.max_fields = 1;
+    rexi_plan* pl = nullptr;
+    const int rc = rexi_plan_create(&p, &pl);
+    if (rc) {
+        std::fprintf(stderr, "rexi_plan_create: %d %s\n", rc, rexi_last_error());
+        std::exit(2);
+    }
+    return pl;
+}
+
+int step(rexi_plan* pl, int S) { return rexi_step(pl, kIn, kOut, S, 2, nullptr); }
+
+void destroy(rexi_plan* pl) {
+    held.clear();
+    rexi_plan_destroy(pl);
+    expect(live.empty(), "all device memory given back");
+    for (auto& a : live) std::free(a.first);
+    live.clear();
+    used = 0;
+}
+
+// An allocation failure that a call has reported is not reported again by the next.
+int handled_failure() {
+    rexi_plan* pl = make_plan(31, 20, 8);
+    expect(step(pl, 2) == REXI_OK, "a step");
+    fail_at = 1;
+    expect(rexi_step_per_term(pl, kIn, kOut, 2, nullptr) == REXI_ENOMEM, "REXI_ENOMEM where an allocation fails");
+    expect(step(pl, 2) == REXI_OK, "the step after it");
+    for (int n = 1; n <= 2; ++n) {  // (the schedules are uploaded before its two states)
+        int index = 0;
+        expect(rexi_plan_autotune(pl, 2, nullptr, &index) == REXI_OK, "the schedules timed");
+        fail_at = n;
+        expect(rexi_plan_autotune(pl, 2, nullptr, &index) != REXI_OK, "an error where a state's allocation fails");
+        expect(step(pl, 2) == REXI_OK, "the step after it");
+    }
+    expect(last_error == hipSuccess, "no error left behind");
+    destroy(pl);
+    return bad;
+}
+
+const std::map<std::string, int (*)()> kScenarios = {
+    {"handled_failure", handled_failure},
+};
+
+}  // namespace
+
+int main(int argc, char** argv) {
+    const auto it = kScenarios.find(argc > 1 ? argv[1] : "");
+    if (it == kScenarios.end()) return 2;
+    return it->second() ? 1 : 0;
+}
