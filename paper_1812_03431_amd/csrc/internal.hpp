@@ -254,6 +254,7 @@ struct rexi_plan {
     double* d_rec[2] = {nullptr, nullptr};
     double2* d_sweep_scratch = nullptr;
     long long rec_capacity[2] = {0, 0}, sweep_scratch_capacity = 0;
+    long long scratch_refused = 1LL << 62;  // scratch that could not be had (double2)
     // captured step graphs: key (S, adjoint, input buffer), valid for `graph_gen`
     struct StepGraph {
         const rexi::Schedule* sched;

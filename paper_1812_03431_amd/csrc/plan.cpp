@@ -555,19 +555,21 @@ void drop_graphs(rexi_plan* pl) {
 
 // A buffer of at least n entries.  The smaller one is kept until the plan is
 // destroyed where `keep` says that a caller's captured graph may hold it, else
-// freed.
+// freed, before the new one is there only where both do not fit.
 template <class T>
 int grow(rexi_plan* pl, T** p, long long* capacity, long long n, bool keep) {
     if (n <= *capacity) return REXI_OK;
     drop_graphs(pl);
     T* q = nullptr;
-    if (!keep) dev_free(*p);
     int rc = dev_alloc(&q, (size_t)n);
-    if (rc) {
-        if (!keep) *capacity = 0;
-        return rc;
+    if (rc && !keep && *p) {
+        dev_free(*p);
+        *capacity = 0;
+        rc = dev_alloc(&q, (size_t)n);
     }
-    if (*p) pl->retired.push_back(*p);
+    if (rc) return rc;
+    if (keep && *p) pl->retired.push_back(*p);
+    else dev_free(*p);
     *p = q;
     *capacity = n;
     return REXI_OK;
@@ -590,11 +592,17 @@ void add_sizes(const rexi_plan* pl, const Schedule& sc, Sizes& z) {
     z.scratch = std::max(z.scratch, std::min(wgs, most) * kSweepWaves * sc.sweep_stride);
 }
 
-int ensure_sizes(rexi_plan* pl, const Sizes& z, bool keep) {
+// Every step checks its schedule's sizes here: the buffers are shared by all
+// schedules, and a growth that failed may have left smaller ones.  Where memory is
+// short, fewer slots of scratch do (their workgroups take more items in turn); what
+// failed once is then tried again only by a call that selects a schedule (`retry`).
+int ensure_sizes(rexi_plan* pl, const Sizes& z, bool keep, bool retry) {
     int rc = grow(pl, &pl->d_part, &pl->part_capacity, z.part, keep);
     for (int d = 0; d < 2 && !rc; ++d) rc = grow(pl, &pl->d_rec[d], &pl->rec_capacity[d], z.rec, keep);
-    if (!rc) rc = grow(pl, &pl->d_sweep_scratch, &pl->sweep_scratch_capacity, z.scratch, keep);
-    // where memory is short, fewer slots do: their workgroups take more items in turn
+    if (rc) return rc;
+    if (!retry && pl->sweep_scratch_capacity >= z.slot && z.scratch >= pl->scratch_refused) return REXI_OK;
+    rc = grow(pl, &pl->d_sweep_scratch, &pl->sweep_scratch_capacity, z.scratch, keep);
+    if (rc == REXI_ENOMEM) pl->scratch_refused = z.scratch;
     for (long long n = z.scratch; rc == REXI_ENOMEM && n > z.slot;) {
         n = std::max(z.slot, n / 2);
         rc = grow(pl, &pl->d_sweep_scratch, &pl->sweep_scratch_capacity, n, keep);
@@ -643,10 +651,10 @@ long long sweep_waves(const rexi_plan* pl, int S) {
 constexpr long long kSweepTarget = 8192;
 
 // Uploads schedule `sc` and, where the no-allocation step's array does not hold
-// it, the tiled schedule that takes that step in its place.
+// it, before it the tiled schedule that takes that step in its place.
 int upload_with_tiled(rexi_plan* pl, Schedule& sc, Schedule* tiled) {
-    int rc = upload_schedule(pl, sc);
-    if (!rc && tiled && !noalloc_takes(pl, sc)) rc = upload_schedule(pl, *tiled);
+    int rc = tiled && !noalloc_takes(pl, sc) ? upload_schedule(pl, *tiled) : REXI_OK;
+    if (!rc) rc = upload_schedule(pl, sc);
     return rc;
 }
 
@@ -661,7 +669,11 @@ int first_schedule(rexi_plan* pl, int S) {
         pl->first_tiled.resize(S + 1);
     }
     Schedule &sc = pl->first[S], &t = pl->first_tiled[S];
-    if (sc.on_device) return REXI_OK;
+    Sizes z;
+    if (sc.on_device) {
+        add_sizes(pl, sc, z);
+        return ensure_sizes(pl, z, false, false);
+    }
     const bool split = sweep_waves(pl, S) <= kSplitWaves;
     int rc = build_sweep_tables(pl, split);
     if (rc) return rc;
@@ -675,11 +687,10 @@ int first_schedule(rexi_plan* pl, int S) {
         t = Schedule();  // the no-allocation step refuses then
         tiled = false;
     }
-    Sizes z;
-    add_sizes(pl, sc, z);
-    rc = ensure_sizes(pl, z, false);
-    if (!rc) rc = upload_with_tiled(pl, sc, tiled ? &t : nullptr);
-    return rc;
+    rc = upload_with_tiled(pl, sc, tiled ? &t : nullptr);
+    if (rc) return rc;
+    add_sizes(pl, sc, z);  // last: the scratch takes what memory there is
+    return ensure_sizes(pl, z, false, false);
 }
 
 // Candidate schedules for S states (built on first use, on the host only; those
@@ -754,11 +765,12 @@ int schedules_for(rexi_plan* pl, int S, bool all, std::vector<Schedule>** out) {
         pl->chosen[S] = dflt >= 0 ? dflt : 0;
     }
     *out = &c;
+    const int rc = upload_with_tiled(pl, c[pl->chosen[S]], pl->tiled[S] >= 0 ? &c[pl->tiled[S]] : nullptr);
+    if (rc) return rc;
     Sizes z;
     for (int i = 0; i < (int)c.size(); ++i)
         if (all || i == pl->chosen[S]) add_sizes(pl, c[i], z);
-    const int rc = ensure_sizes(pl, z, stepped);
-    return rc ? rc : upload_with_tiled(pl, c[pl->chosen[S]], pl->tiled[S] >= 0 ? &c[pl->tiled[S]] : nullptr);
+    return ensure_sizes(pl, z, stepped, all);
 }
 
 bool overlaps(const void* a, size_t na, const void* b, size_t nb) {

@@ -322,8 +322,77 @@ int handled_failure() {
     return bad;
 }
 
+void disarm() {
+    fail_at = 0;
+    fail_on = false;
+}
+
+// `first` succeeds; then the n-th allocation of `second` fails (alone, or with all
+// after it), for every n that there is; then both succeed again, on sound buffers.
+void fail_every(const char* what, int T, int M, std::function<int(rexi_plan*)> first,
+                std::function<int(rexi_plan*)> second) {
+    for (int all = 0; all < 2; ++all)
+        for (int n = 1;; ++n) {
+            rexi_plan* pl = make_plan(T, M, 8);
+            expect(first(pl) == REXI_OK, std::string(what) + ": the first call succeeds");
+            fail_at = n;
+            fail_on = all != 0;
+            const int before = mallocs, rc = second(pl);
+            const bool hit = mallocs - before >= n;
+            disarm();
+            const std::string at = std::string(what) + ", allocation " + std::to_string(n) + (all ? " on" : "");
+            expect(rc == REXI_OK || (hit && rc == REXI_ENOMEM), at + ": succeeds or reports REXI_ENOMEM");
+            expect(first(pl) == REXI_OK, at + ": the first call again");
+            expect(second(pl) == REXI_OK, at + ": the failed call again");
+            expect(first(pl) == REXI_OK, at + ": the first call at last");
+            destroy(pl);
+            if (!hit || bad > 20) break;
+        }
+}
+
+// Steps of more states than before, whose allocations fail one after another (with
+// the tables of both there: T 63, chains in registers, without boundary values; T 100,
+// split chains; T 200, whole ones).
+int failed_growth() {
+    for (int T : {63, 100, 200})
+        for (int S : {1, 4})
+            fail_every("more states", T, T == 200 ? 150 : 21,
+                       [S](rexi_plan* p) { return step(p, S); }, [](rexi_plan* p) { return step(p, 8); });
+    return bad;
+}
+
+// Where memory is short a schedule runs with fewer slots for boundary values, and its
+// next steps allocate nothing.
+int shortage() {
+    for (int listed = 0; listed < 2; ++listed) {
+        auto use = [&](rexi_plan* pl) {
+            int n = 0;
+            if (listed) expect(rexi_plan_set_schedule(pl, 8, -1, &n) == REXI_OK, "the schedules listed");
+            expect(step(pl, 8) == REXI_OK, "a step");
+        };
+        rexi_plan* pl = make_plan(200, 150, 8);
+        use(pl);
+        const long long full = pl->sweep_scratch_capacity;
+        const size_t all = used;
+        destroy(pl);
+        pl = make_plan(200, 150, 8);
+        budget = all - (size_t)full * 16 * 5 / 8;
+        use(pl);
+        expect(pl->sweep_scratch_capacity > 0 && pl->sweep_scratch_capacity < full, "fewer slots");
+        const int before = mallocs;
+        for (int k = 0; k < 3; ++k) expect(step(pl, 8) == REXI_OK, "a further step");
+        expect(mallocs == before, "no further allocation");
+        expect(step(pl, 1) == REXI_OK && step(pl, 8) == REXI_OK, "steps of other states between them");
+        budget = ~size_t(0);
+        destroy(pl);
+    }
+    return bad;
+}
+
 const std::map<std::string, int (*)()> kScenarios = {
     {"handled_failure", handled_failure},
+    {"failed_growth", failed_growth},
+    {"shortage", shortage},
 };
 
 }  // namespace
