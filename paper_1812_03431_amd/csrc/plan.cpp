@@ -317,6 +317,16 @@ void sweep_layout(rexi_plan* pl, bool split) {
         }
 }
 
+void free_sweep_tables(SweepTables& t) {
+    dev_free(t.d_cst);
+    dev_free(t.d_idx);
+    for (int d = 0; d < 2; ++d) {
+        dev_free(t.d_fin[d]);
+        dev_free(t.d_fout[d]);
+        dev_free(t.d_poles[d]);
+    }
+}
+
 // Tables of the pole-per-lane solve (see sweep_kernels.hip), built with the
 // first schedule that reads them.  Not usable without a Coriolis force (the scaling
 // divides by the couplings) or where the scaled constants leave a comfortable FP64
@@ -396,9 +406,11 @@ int build_sweep_tables(rexi_plan* pl, bool split) {
         }
     }
     cst.resize(cst.size() + kSweepPad, 0.0);
-    t.usable = ok;
-    t.built = true;
-    if (!ok) return REXI_OK;
+    if (!ok) {
+        t.built = true;
+        return REXI_OK;
+    }
+    free_sweep_tables(t);  // of a build that did not end
     int rc = upload(&t.d_cst, cst);
     if (!rc) rc = upload(&t.d_idx, idx);
     for (int d = 0; d < 2 && !rc; ++d) {
@@ -415,17 +427,12 @@ int build_sweep_tables(rexi_plan* pl, bool split) {
         }
         if (!rc) rc = upload(&t.d_poles[d], pd);
     }
-    return rc;
-}
-
-void free_sweep_tables(SweepTables& t) {
-    dev_free(t.d_cst);
-    dev_free(t.d_idx);
-    for (int d = 0; d < 2; ++d) {
-        dev_free(t.d_fin[d]);
-        dev_free(t.d_fout[d]);
-        dev_free(t.d_poles[d]);
+    if (rc) {
+        free_sweep_tables(t);
+        return rc;
     }
+    t.usable = t.built = true;
+    return REXI_OK;
 }
 
 // Where the chip is not filled, a long chain's time is what counts: with at most

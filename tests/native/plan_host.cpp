@@ -389,9 +389,18 @@ int shortage() {
     return bad;
 }
 
+// The first step of a plan, whose allocations fail one after another.
+int failed_tables() {
+    for (int T : {63, 100})
+        for (int S : {1, 8})
+            fail_every("a first step", T, 150, [](rexi_plan*) { return REXI_OK; }, [S](rexi_plan* p) { return step(p, S); });
+    return bad;
+}
+
 const std::map<std::string, int (*)()> kScenarios = {
     {"handled_failure", handled_failure},
     {"failed_growth", failed_growth},
+    {"failed_tables", failed_tables},
     {"shortage", shortage},
 };
 
