@@ -183,7 +183,10 @@ int sh_uv_to_vortdiv(rexi_plan *plan, const double *uv, void *vd, long long stri
  * states: u1 = R^nsteps u0 with
  *   R = sum_k beta+_k (alpha_k + dt L)^{-1} + sum_k beta-_k (alpha_k - dt L)^{-1}.
  *   u0, u1  device complex128 [S][3][nspec] (must not overlap)
- *   1 <= S <= max_states, nsteps >= 0 (0 copies u0 to u1). */
+ *   1 <= S <= max_states, nsteps >= 0 (0 copies u0 to u1).
+ * Once a first call with S has allocated, a step of a pole-per-lane schedule (see
+ * rexi_plan_schedule_name) may be captured into a caller's graph; the workspace that
+ * the graph holds then stays until the plan is destroyed. */
 int rexi_step(rexi_plan *plan, const void *u0, void *u1, int S, int nsteps, void *stream);
 
 /* Adjoint of rexi_step: g0 = (R^H)^nsteps g1, the conjugate-transposed

@@ -226,7 +226,8 @@ struct rexi_plan {
     // until the candidates of S are asked for: the default alone, and the tiled one
     // that takes its no-allocation steps (see schedules_for)
     std::vector<rexi::Schedule> first, first_tiled;
-    std::vector<void*> retired;  // workspace that a caller's graph may still hold
+    bool captured = false;       // a caller has captured a step
+    std::vector<void*> retired;  // smaller workspace that its graph may hold
     std::vector<rexi::Schedule> per_term;             // [S]
     long long acc_capacity = 0;
 

@@ -560,22 +560,30 @@ void drop_graphs(rexi_plan* pl) {
     ++pl->graph_gen;
 }
 
-// A buffer of at least n entries.  The smaller one is kept until the plan is
-// destroyed where `keep` says that a caller's captured graph may hold it, else
-// freed, before the new one is there only where both do not fit.
+// A step enqueued on a capturing stream: the caller's graph holds the workspace.
+void note_capture(rexi_plan* pl, hipStream_t s) {
+    if (pl->captured) return;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) (void)hipGetLastError();
+    else pl->captured = st != hipStreamCaptureStatusNone;
+}
+
+// A buffer of at least n entries.  The buffers are shared by all state counts: once
+// a caller has captured a step, smaller ones are kept until the plan is destroyed;
+// else they are freed, before the new one is there only where both do not fit.
 template <class T>
-int grow(rexi_plan* pl, T** p, long long* capacity, long long n, bool keep) {
+int grow(rexi_plan* pl, T** p, long long* capacity, long long n) {
     if (n <= *capacity) return REXI_OK;
     drop_graphs(pl);
     T* q = nullptr;
     int rc = dev_alloc(&q, (size_t)n);
-    if (rc && !keep && *p) {
+    if (rc && !pl->captured && *p) {
         dev_free(*p);
         *capacity = 0;
         rc = dev_alloc(&q, (size_t)n);
     }
     if (rc) return rc;
-    if (keep && *p) pl->retired.push_back(*p);
+    if (pl->captured && *p) pl->retired.push_back(*p);
     else dev_free(*p);
     *p = q;
     *capacity = n;
@@ -603,16 +611,16 @@ void add_sizes(const rexi_plan* pl, const Schedule& sc, Sizes& z) {
 // schedules, and a growth that failed may have left smaller ones.  Where memory is
 // short, fewer slots of scratch do (their workgroups take more items in turn); what
 // failed once is then tried again only by a call that selects a schedule (`retry`).
-int ensure_sizes(rexi_plan* pl, const Sizes& z, bool keep, bool retry) {
-    int rc = grow(pl, &pl->d_part, &pl->part_capacity, z.part, keep);
-    for (int d = 0; d < 2 && !rc; ++d) rc = grow(pl, &pl->d_rec[d], &pl->rec_capacity[d], z.rec, keep);
+int ensure_sizes(rexi_plan* pl, const Sizes& z, bool retry) {
+    int rc = grow(pl, &pl->d_part, &pl->part_capacity, z.part);
+    for (int d = 0; d < 2 && !rc; ++d) rc = grow(pl, &pl->d_rec[d], &pl->rec_capacity[d], z.rec);
     if (rc) return rc;
     if (!retry && pl->sweep_scratch_capacity >= z.slot && z.scratch >= pl->scratch_refused) return REXI_OK;
-    rc = grow(pl, &pl->d_sweep_scratch, &pl->sweep_scratch_capacity, z.scratch, keep);
+    rc = grow(pl, &pl->d_sweep_scratch, &pl->sweep_scratch_capacity, z.scratch);
     if (rc == REXI_ENOMEM) pl->scratch_refused = z.scratch;
     for (long long n = z.scratch; rc == REXI_ENOMEM && n > z.slot;) {
         n = std::max(z.slot, n / 2);
-        rc = grow(pl, &pl->d_sweep_scratch, &pl->sweep_scratch_capacity, n, keep);
+        rc = grow(pl, &pl->d_sweep_scratch, &pl->sweep_scratch_capacity, n);
     }
     return rc;
 }
@@ -679,7 +687,7 @@ int first_schedule(rexi_plan* pl, int S) {
     Sizes z;
     if (sc.on_device) {
         add_sizes(pl, sc, z);
-        return ensure_sizes(pl, z, false, false);
+        return ensure_sizes(pl, z, false);
     }
     const bool split = sweep_waves(pl, S) <= kSplitWaves;
     int rc = build_sweep_tables(pl, split);
@@ -697,7 +705,7 @@ int first_schedule(rexi_plan* pl, int S) {
     rc = upload_with_tiled(pl, sc, tiled ? &t : nullptr);
     if (rc) return rc;
     add_sizes(pl, sc, z);  // last: the scratch takes what memory there is
-    return ensure_sizes(pl, z, false, false);
+    return ensure_sizes(pl, z, false);
 }
 
 // Candidate schedules for S states (built on first use, on the host only; those
@@ -709,8 +717,6 @@ int schedules_for(rexi_plan* pl, int S, bool all, std::vector<Schedule>** out) {
         pl->tiled.resize(S + 1, -1);
     }
     std::vector<Schedule>& c = pl->sched[S];
-    // buffers that an earlier step of S states used outlive a growth here
-    const bool stepped = !c.empty() || ((int)pl->first.size() > S && pl->first[S].on_device);
     if (c.empty()) {
         const long long tg[] = {2048, kTiledTarget, 4096, 8192};
         // states per item (see build_schedule): one (each state factorises
@@ -777,7 +783,7 @@ int schedules_for(rexi_plan* pl, int S, bool all, std::vector<Schedule>** out) {
     Sizes z;
     for (int i = 0; i < (int)c.size(); ++i)
         if (all || i == pl->chosen[S]) add_sizes(pl, c[i], z);
-    return ensure_sizes(pl, z, stepped, all);
+    return ensure_sizes(pl, z, all);
 }
 
 bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
@@ -916,6 +922,7 @@ int do_step(rexi_plan* pl, const void* u0, void* u1, int S, int nsteps, int adjo
     int rc = check_state_call(pl, u0, u1, S, nsteps);
     if (rc) return rc;
     if (pl->prm.fsphere) return run_fsphere(pl, u0, u1, S, nsteps, adjoint, (hipStream_t)stream);
+    note_capture(pl, (hipStream_t)stream);
     const Schedule* sc = nullptr;
     if ((int)pl->sched.size() <= S || pl->sched[S].empty()) {
         rc = first_schedule(pl, S);
@@ -1232,14 +1239,10 @@ int rexi_step_per_term(rexi_plan* plan, const void* u0, void* u1, int S, void* s
             if (!rc) rc = upload_schedule(plan, sc);
             if (rc) { free_schedule(sc); sc = Schedule(); return rc; }
         }
-        if (sc.part_size > plan->acc_capacity) {
-            dev_free(plan->d_acc);
-            plan->acc_capacity = 0;
-            rc = dev_alloc(&plan->d_acc, (size_t)sc.part_size);
-            if (rc) return rc;
-            plan->acc_capacity = sc.part_size;
-        }
         hipStream_t s = (hipStream_t)stream;
+        note_capture(plan, s);
+        rc = grow(plan, &plan->d_acc, &plan->acc_capacity, sc.part_size);
+        if (rc) return rc;
         const Workspace ws = plan_workspace(plan, sc);
         REXI_HIP(enqueue_prep(plan, ws, u0, 0, S, 0, plan->sched_layout, s));
         REXI_HIP(enqueue_zero(plan->d_acc, sc.part_size, s));

@@ -397,11 +397,38 @@ int failed_tables() {
     return bad;
 }
 
+// The workspace that a caller's captured step was given is there until the plan is
+// destroyed, whatever state counts and schedules come after it.
+int captured_buffers() {
+    for (int T : {63, 100, 200}) {
+        rexi_plan* pl = make_plan(T, T == 200 ? 150 : 21, 8);
+        int n = 0;
+        expect(step(pl, 1) == REXI_OK && rexi_step_per_term(pl, kIn, kOut, 1, nullptr) == REXI_OK, "steps of one state");
+        capturing = true;
+        expect(step(pl, 1) == REXI_OK && rexi_step_per_term(pl, kIn, kOut, 1, nullptr) == REXI_OK, "captured steps");
+        capturing = false;
+        expect(!held.empty(), "workspace in use");
+        for (int S : {2, 4, 8}) {
+            expect(step(pl, S) == REXI_OK && rexi_step_per_term(pl, kIn, kOut, S, nullptr) == REXI_OK, "steps of more states");
+            expect(rexi_plan_set_schedule(pl, S, -1, &n) == REXI_OK && n > 0, "their schedules");
+            expect(rexi_plan_set_schedule(pl, S, n - 1, nullptr) == REXI_OK && step(pl, S) == REXI_OK, "another one");
+        }
+        destroy(pl);
+    }
+    // without a capture nothing is kept: the buffers are one schedule's after the growth
+    rexi_plan* pl = make_plan(63, 21, 8);
+    for (int S : {1, 2, 4, 8}) expect(step(pl, S) == REXI_OK, "steps of more and more states");
+    expect(pl->retired.empty(), "no smaller buffer kept");
+    destroy(pl);
+    return bad;
+}
+
 const std::map<std::string, int (*)()> kScenarios = {
     {"handled_failure", handled_failure},
     {"failed_growth", failed_growth},
     {"failed_tables", failed_tables},
     {"shortage", shortage},
+    {"captured_buffers", captured_buffers},
 };
 
 }  // namespace
