@@ -311,9 +311,10 @@ hipError_t enqueue_sweep_solve(rexi_plan* pl, const Workspace& ws, const Schedul
                                hipStream_t s);
 hipError_t enqueue_sweep_reduce(rexi_plan* pl, const Workspace& ws, const Schedule& sc, int buf_in, int buf_out,
                                 void* u_out, int S, int adjoint, hipStream_t s);
-// nsteps steps of a pole-per-lane schedule, launched one by one (plan.cpp).
+// nsteps steps of a pole-per-lane schedule, launched one by one (plan.cpp); timed:
+// between events where the plan's timing is on.
 int run_sweep_steps(rexi_plan* pl, const Workspace& ws, const Schedule& sc, const void* u0, void* u1, int S,
-                    int nsteps, int adjoint, hipStream_t s);
+                    int nsteps, int adjoint, bool timed, hipStream_t s);
 int sh_setup(rexi_plan* pl);
 void sh_release(rexi_plan* pl);
 int sh_run(rexi_plan* pl, const void* in, void* out, int B, bool forward, hipStream_t s);

@@ -120,7 +120,7 @@ extern "C" int rexi_step_noalloc(rexi_plan* plan, const void* u0, void* u1, int 
                                         (hipStream_t)stream));
                 return REXI_OK;
             }
-            return run_sweep_steps(plan, ws, *psc, u0, u1, S, nsteps, 0, (hipStream_t)stream);
+            return run_sweep_steps(plan, ws, *psc, u0, u1, S, nsteps, 0, false, (hipStream_t)stream);
         }
         psc = !listed ? &plan->first_tiled[S] : plan->tiled[S] >= 0 ? &plan->sched[S][plan->tiled[S]] : nullptr;
         if (!psc || !psc->on_device) return fail(REXI_EUNSUPPORTED, "no schedule fits the no-allocation limit");

@@ -833,16 +833,16 @@ int step_graph(rexi_plan* pl, const Schedule& sc, int S, int adjoint, int buf, h
 }  // namespace
 
 int run_sweep_steps(rexi_plan* pl, const Workspace& ws, const Schedule& sc, const void* u0, void* u1, int S,
-                    int nsteps, int adjoint, hipStream_t s) {
+                    int nsteps, int adjoint, bool timed, hipStream_t s) {
     REXI_HIP(enqueue_sweep_prep(pl, ws, sc, u0, 0, S, adjoint, s));
     int cur = 0;
     for (int k = 0; k < nsteps; ++k) {
         const bool last = (k == nsteps - 1);
-        REXI_HIP(timed_begin(pl, REXI_KERNEL_SOLVE, s));
+        if (timed) REXI_HIP(timed_begin(pl, REXI_KERNEL_SOLVE, s));
         REXI_HIP(enqueue_sweep_solve(pl, ws, sc, cur, S, adjoint, s));
-        if (!pl->use_graphs) REXI_HIP(timed_end(pl, REXI_KERNEL_SOLVE, s));
+        if (timed && !pl->use_graphs) REXI_HIP(timed_end(pl, REXI_KERNEL_SOLVE, s));
         REXI_HIP(enqueue_sweep_reduce(pl, ws, sc, cur, cur ^ 1, last ? u1 : nullptr, S, adjoint, s));
-        if (pl->use_graphs) REXI_HIP(timed_end(pl, REXI_KERNEL_SOLVE, s));
+        if (timed && pl->use_graphs) REXI_HIP(timed_end(pl, REXI_KERNEL_SOLVE, s));
         cur ^= 1;
     }
     return REXI_OK;
@@ -858,7 +858,7 @@ int run_steps(rexi_plan* pl, const Schedule& sc, const void* u0, void* u1, int S
         return REXI_OK;
     }
     const Workspace ws = plan_workspace(pl, sc);
-    if (sc.sweep) return run_sweep_steps(pl, ws, sc, u0, u1, S, nsteps, adjoint, s);
+    if (sc.sweep) return run_sweep_steps(pl, ws, sc, u0, u1, S, nsteps, adjoint, true, s);
     REXI_HIP(enqueue_prep(pl, ws, u0, 0, S, adjoint, pl->sched_layout, s));
     int cur = 0;
     if (pl->use_graphs) {

@@ -423,12 +423,32 @@ int captured_buffers() {
     return bad;
 }
 
+// The no-allocation step makes no events and is not timed, also where timing is on.
+int noalloc_untimed() {
+    for (int T : {31, 100}) {
+        rexi_plan* pl = make_plan(T, 20, 8);
+        expect(step(pl, 2) == REXI_OK, "a step");
+        rexi_plan_set_timing(pl, 1);
+        const int e = events_made, m = mallocs;
+        expect(rexi_step_noalloc(pl, kIn, kOut, 2, 3, nullptr) == REXI_OK, "a no-allocation step");
+        expect(events_made == e && mallocs == m, "no event and no allocation");
+        double ms = 0;
+        long long n = -1;
+        expect(rexi_plan_kernel_time(pl, REXI_KERNEL_SOLVE, &ms, &n) == REXI_OK && n == 0, "nothing timed");
+        expect(step(pl, 2) == REXI_OK, "a step");
+        expect(rexi_plan_kernel_time(pl, REXI_KERNEL_SOLVE, &ms, &n) == REXI_OK && n == 2, "its two launches timed");
+        destroy(pl);
+    }
+    return bad;
+}
+
 const std::map<std::string, int (*)()> kScenarios = {
     {"handled_failure", handled_failure},
     {"failed_growth", failed_growth},
     {"failed_tables", failed_tables},
     {"shortage", shortage},
     {"captured_buffers", captured_buffers},
+    {"noalloc_untimed", noalloc_untimed},
 };
 
 }  // namespace
