@@ -17,6 +17,7 @@ using cld = std::complex<long double>;
 // ---------------------------------------------------------------- errors
 int fail(int code, const std::string& msg);
 int hip_fail(hipError_t e, const char* what);
+int caught() noexcept;  // of a C entry whose body threw: the host's memory ran out
 #define REXI_HIP(call)                                            \
     do {                                                          \
         hipError_t e_ = (call);                                   \

@@ -90,7 +90,7 @@ bool noalloc_takes(const rexi_plan* pl, const Schedule& sc) {
 
 using namespace rexi;
 
-extern "C" int rexi_step_noalloc(rexi_plan* plan, const void* u0, void* u1, int S, int nsteps, void* stream) {
+extern "C" int rexi_step_noalloc(rexi_plan* plan, const void* u0, void* u1, int S, int nsteps, void* stream) try {
     int rc = check_state_call(plan, u0, u1, S, nsteps);
     if (rc) return rc;
     if (plan->prm.fsphere) return fail(REXI_EUNSUPPORTED, "the no-allocation step is built for the rotating sphere only");
@@ -157,4 +157,6 @@ extern "C" int rexi_step_noalloc(rexi_plan* plan, const void* u0, void* u1, int 
         cur ^= 1;
     }
     return REXI_OK;
+} catch (...) {
+    return caught();
 }

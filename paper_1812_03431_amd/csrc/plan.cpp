@@ -8,7 +8,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
-#include <new>
+#include <memory>
 #include <string>
 
 #include "internal.hpp"
@@ -25,12 +25,22 @@ int fail(int code, const std::string& msg) {
     return code;
 }
 
+int caught() noexcept {
+    try {
+        return fail(REXI_ENOMEM, "host allocation failed");
+    } catch (...) {
+        g_err.clear();
+        return REXI_ENOMEM;
+    }
+}
+
 int hip_fail(hipError_t e, const char* what) {
     return fail(REXI_EHIP, std::string(what) + ": " + hipGetErrorString(e));
 }
 
 hipError_t timed_begin(rexi_plan* pl, int kind, hipStream_t s) {
     if (!pl->timing) return hipSuccess;
+    pl->events[kind].reserve(pl->events[kind].size() + 1);
     hipEvent_t a = nullptr, b = nullptr;
     hipError_t e = hipEventCreate(&a);
     if (e != hipSuccess) return e;
@@ -307,14 +317,20 @@ std::vector<int> sweep_slots(int T, int m, int p, bool split, int2* half) {
 void sweep_layout(rexi_plan* pl, bool split) {
     SweepTables& t = pl->sweep[split];
     if (!t.chains.empty()) return;
+    std::vector<SweepChain> chains;
+    std::vector<int2> halves;
+    int npairs = 0;
     for (int m = 0; m <= pl->T; ++m)
         for (int p = 0; p < 2; ++p) {
             int2 half;
             const int np = (int)sweep_slots(pl->T, m, p, split, &half).size() / 2;
-            t.chains.push_back({t.npairs, np});
-            t.halves.push_back(half);
-            t.npairs += np;
+            chains.push_back({npairs, np});
+            halves.push_back(half);
+            npairs += np;
         }
+    t.chains = std::move(chains);
+    t.halves = std::move(halves);
+    t.npairs = npairs;
 }
 
 void free_sweep_tables(SweepTables& t) {
@@ -574,6 +590,7 @@ void note_capture(rexi_plan* pl, hipStream_t s) {
 template <class T>
 int grow(rexi_plan* pl, T** p, long long* capacity, long long n) {
     if (n <= *capacity) return REXI_OK;
+    pl->retired.reserve(pl->retired.size() + 1);
     drop_graphs(pl);
     T* q = nullptr;
     int rc = dev_alloc(&q, (size_t)n);
@@ -583,7 +600,7 @@ int grow(rexi_plan* pl, T** p, long long* capacity, long long n) {
         rc = dev_alloc(&q, (size_t)n);
     }
     if (rc) return rc;
-    if (pl->captured && *p) pl->retired.push_back(*p);
+    if (pl->captured && *p) pl->retired.push_back(*p);  // (room reserved)
     else dev_free(*p);
     *p = q;
     *capacity = n;
@@ -673,16 +690,25 @@ int upload_with_tiled(rexi_plan* pl, Schedule& sc, Schedule* tiled) {
     return rc;
 }
 
+// Entries of S states in the plan's lists; sched, by whose size the entries are
+// looked up, last.
+void room_for(rexi_plan* pl, int S) {
+    const size_t n = (size_t)S + 1;
+    if (pl->sched.size() >= n) return;
+    pl->first.resize(n);
+    pl->first_tiled.resize(n);
+    pl->chosen.resize(n, -1);
+    pl->tiled.resize(n, -1);
+    pl->sched.resize(n);
+}
+
 // The default schedule of S states alone, for the first step; the candidate list,
 // of which it is a part, is built by the first call that asks for it.  A new
 // plan's first step, with all of the list built and uploaded in it / the default
 // alone: T301, three states, 21 / 4 ms; T256, four states, 39 / 5 ms; T15, two
 // states, 7.9 / 0.4 ms.  REXI_EUNSUPPORTED: the default is a tiled schedule.
 int first_schedule(rexi_plan* pl, int S) {
-    if ((int)pl->first.size() <= S) {
-        pl->first.resize(S + 1);
-        pl->first_tiled.resize(S + 1);
-    }
+    room_for(pl, S);
     Schedule &sc = pl->first[S], &t = pl->first_tiled[S];
     Sizes z;
     if (sc.on_device) {
@@ -711,11 +737,7 @@ int first_schedule(rexi_plan* pl, int S) {
 // Candidate schedules for S states (built on first use, on the host only; those
 // that run are uploaded).  all: the workspace holds any of them afterwards.
 int schedules_for(rexi_plan* pl, int S, bool all, std::vector<Schedule>** out) {
-    if ((int)pl->sched.size() <= S) {
-        pl->sched.resize(S + 1);
-        pl->chosen.resize(S + 1, -1);
-        pl->tiled.resize(S + 1, -1);
-    }
+    room_for(pl, S);
     std::vector<Schedule>& c = pl->sched[S];
     if (c.empty()) {
         const long long tg[] = {2048, kTiledTarget, 4096, 8192};
@@ -730,10 +752,6 @@ int schedules_for(rexi_plan* pl, int S, bool all, std::vector<Schedule>** out) {
         const bool few = sweep_waves(pl, S) <= kSplitWaves;
         int rc = build_sweep_tables(pl, few);
         if (rc) return rc;
-        if ((int)pl->first.size() <= S) {
-            pl->first.resize(S + 1);
-            pl->first_tiled.resize(S + 1);
-        }
         std::vector<Schedule> list;
         int tiled = -1, dflt = -1, from_first = -1, from_tiled = -1;
         for (int rot : rots)
@@ -803,6 +821,7 @@ int step_graph(rexi_plan* pl, const Schedule& sc, int S, int adjoint, int buf, h
             *done = g.done;
             return REXI_OK;
         }
+    pl->graphs.reserve(pl->graphs.size() + 1);
     hipGraph_t graph = nullptr;
     REXI_HIP(hipStreamBeginCapture(pl->cap_stream, hipStreamCaptureModeThreadLocal));
     const Workspace ws = plan_workspace(pl, sc);
@@ -998,10 +1017,18 @@ std::vector<double2> to_d2(const std::vector<std::complex<double>>& v) {
     return o;
 }
 
+struct Destroy {
+    void operator()(rexi_plan* pl) const {
+        release(pl);
+        delete pl;
+    }
+};
+
 int create(const rexi_params* p, rexi_plan** out) {
     int rc = check_params(p);
     if (rc) return rc;
-    rexi_plan* pl = new rexi_plan();
+    std::unique_ptr<rexi_plan, Destroy> own(new rexi_plan());
+    rexi_plan* const pl = own.get();
     pl->prm = *p;
     const int T = p->T;
     pl->T = T;
@@ -1130,12 +1157,8 @@ int create(const rexi_params* p, rexi_plan** out) {
     // the no-allocation step's workspace on this device (looked up once per device)
     if (!rc) rc = scratch_setup(&pl->scratch, &pl->scratch_bytes);
     if (!rc && p->nlat > 0) rc = sh_setup(pl);
-    if (rc) {
-        release(pl);
-        delete pl;
-        return rc;
-    }
-    *out = pl;
+    if (rc) return rc;
+    *out = own.release();
     return REXI_OK;
 }
 
@@ -1146,59 +1169,59 @@ extern "C" {
 const char* rexi_last_error(void) { return g_err.c_str(); }
 
 int rexi_coeffs(int M, double h, int L, int normalize, int capacity, double* alpha, double* beta_plus,
-                double* beta_minus, int* n_poles) {
-    try {
-        g_err.clear();
-        if (M < 1 || M > 1 << 20) return fail(REXI_EINVAL, "M must be in [1, 2^20]");
-        if (!(h > 0) || !std::isfinite(h)) return fail(REXI_EINVAL, "h must be positive");
-        if (L < 1 || L > 32) return fail(REXI_EINVAL, "L must be in [1, 32]");
-        if (capacity < 0) return fail(REXI_EINVAL, "capacity must be >= 0");
-        const int N = 2 * (M + L) + 1;
-        if (n_poles) *n_poles = N;
-        if (capacity == 0) return REXI_OK;
-        if (capacity < N) return fail(REXI_EINVAL, "capacity below the number of poles");
-        if (!alpha || !beta_plus || !beta_minus) return fail(REXI_EINVAL, "output array is NULL");
-        const Poles P = make_poles(M, h, L, normalize);
-        for (int k = 0; k < N; ++k) {
-            alpha[2 * k] = P.alpha[k].real();
-            alpha[2 * k + 1] = P.alpha[k].imag();
-            beta_plus[2 * k] = P.beta_plus[k].real();
-            beta_plus[2 * k + 1] = P.beta_plus[k].imag();
-            beta_minus[2 * k] = P.beta_minus[k].real();
-            beta_minus[2 * k + 1] = P.beta_minus[k].imag();
-        }
-        return REXI_OK;
-    } catch (const std::bad_alloc&) {
-        return fail(REXI_ENOMEM, "host allocation failed");
+                double* beta_minus, int* n_poles) try {
+    g_err.clear();
+    if (M < 1 || M > 1 << 20) return fail(REXI_EINVAL, "M must be in [1, 2^20]");
+    if (!(h > 0) || !std::isfinite(h)) return fail(REXI_EINVAL, "h must be positive");
+    if (L < 1 || L > 32) return fail(REXI_EINVAL, "L must be in [1, 32]");
+    if (capacity < 0) return fail(REXI_EINVAL, "capacity must be >= 0");
+    const int N = 2 * (M + L) + 1;
+    if (n_poles) *n_poles = N;
+    if (capacity == 0) return REXI_OK;
+    if (capacity < N) return fail(REXI_EINVAL, "capacity below the number of poles");
+    if (!alpha || !beta_plus || !beta_minus) return fail(REXI_EINVAL, "output array is NULL");
+    const Poles P = make_poles(M, h, L, normalize);
+    for (int k = 0; k < N; ++k) {
+        alpha[2 * k] = P.alpha[k].real();
+        alpha[2 * k + 1] = P.alpha[k].imag();
+        beta_plus[2 * k] = P.beta_plus[k].real();
+        beta_plus[2 * k + 1] = P.beta_plus[k].imag();
+        beta_minus[2 * k] = P.beta_minus[k].real();
+        beta_minus[2 * k + 1] = P.beta_minus[k].imag();
     }
+    return REXI_OK;
+} catch (...) {
+    return caught();
 }
 
-int rexi_plan_create(const rexi_params* p, rexi_plan** out) {
+int rexi_plan_create(const rexi_params* p, rexi_plan** out) try {
     if (!out) return fail(REXI_EINVAL, "out is NULL");
     *out = nullptr;
-    try {
-        return create(p, out);
-    } catch (const std::bad_alloc&) {
-        return fail(REXI_ENOMEM, "host allocation failed");
-    }
+    return create(p, out);
+} catch (...) {
+    return caught();
 }
 
-int rexi_plan_destroy(rexi_plan* plan) {
+int rexi_plan_destroy(rexi_plan* plan) try {
     if (!plan) return fail(REXI_EINVAL, "plan is NULL");
     release(plan);
     delete plan;
     return REXI_OK;
+} catch (...) {
+    return caught();
 }
 
-int rexi_plan_info(const rexi_plan* plan, int* n_poles, int* nspec, long long* blocks) {
+int rexi_plan_info(const rexi_plan* plan, int* n_poles, int* nspec, long long* blocks) try {
     if (!plan) return fail(REXI_EINVAL, "plan is NULL");
     if (n_poles) *n_poles = plan->N;
     if (nspec) *nspec = (int)plan->nspec;
     if (blocks) *blocks = (long long)plan->N * (plan->T + 1);
     return REXI_OK;
+} catch (...) {
+    return caught();
 }
 
-int rexi_plan_coeffs(const rexi_plan* plan, double* alpha, double* beta_plus, double* beta_minus) {
+int rexi_plan_coeffs(const rexi_plan* plan, double* alpha, double* beta_plus, double* beta_minus) try {
     if (!plan || !alpha || !beta_plus || !beta_minus) return fail(REXI_EINVAL, "NULL argument");
     for (int k = 0; k < plan->N; ++k) {
         alpha[2 * k] = plan->poles.alpha[k].real();
@@ -1209,52 +1232,48 @@ int rexi_plan_coeffs(const rexi_plan* plan, double* alpha, double* beta_plus, do
         beta_minus[2 * k + 1] = plan->poles.beta_minus[k].imag();
     }
     return REXI_OK;
+} catch (...) {
+    return caught();
 }
 
-int rexi_step(rexi_plan* plan, const void* u0, void* u1, int S, int nsteps, void* stream) {
-    try {
-        return do_step(plan, u0, u1, S, nsteps, 0, stream);
-    } catch (const std::bad_alloc&) {
-        return fail(REXI_ENOMEM, "host allocation failed");
-    }
+int rexi_step(rexi_plan* plan, const void* u0, void* u1, int S, int nsteps, void* stream) try {
+    return do_step(plan, u0, u1, S, nsteps, 0, stream);
+} catch (...) {
+    return caught();
 }
 
-int rexi_step_adjoint(rexi_plan* plan, const void* g1, void* g0, int S, int nsteps, void* stream) {
-    try {
-        return do_step(plan, g1, g0, S, nsteps, 1, stream);
-    } catch (const std::bad_alloc&) {
-        return fail(REXI_ENOMEM, "host allocation failed");
-    }
+int rexi_step_adjoint(rexi_plan* plan, const void* g1, void* g0, int S, int nsteps, void* stream) try {
+    return do_step(plan, g1, g0, S, nsteps, 1, stream);
+} catch (...) {
+    return caught();
 }
 
-int rexi_step_per_term(rexi_plan* plan, const void* u0, void* u1, int S, void* stream) {
+int rexi_step_per_term(rexi_plan* plan, const void* u0, void* u1, int S, void* stream) try {
     int rc = check_state_call(plan, u0, u1, S, 1);
     if (rc) return rc;
     if (plan->prm.fsphere) return fail(REXI_EUNSUPPORTED, "the per-term form is not built for f-sphere plans");
-    try {
-        if ((int)plan->per_term.size() <= S) plan->per_term.resize(S + 1);
-        Schedule& sc = plan->per_term[S];
-        if (sc.items.empty()) {
-            rc = build_schedule(plan, S, 0, 0, true, 0, sc);  // 8 elements per lane, one wave per chain
-            if (!rc) rc = upload_schedule(plan, sc);
-            if (rc) { free_schedule(sc); sc = Schedule(); return rc; }
-        }
-        hipStream_t s = (hipStream_t)stream;
-        note_capture(plan, s);
-        rc = grow(plan, &plan->d_acc, &plan->acc_capacity, sc.part_size);
+    if ((int)plan->per_term.size() <= S) plan->per_term.resize(S + 1);
+    Schedule& sc = plan->per_term[S];
+    if (!sc.on_device) {
+        rc = build_schedule(plan, S, 0, 0, true, 0, sc);  // 8 elements per lane, one wave per chain
+        if (!rc) rc = upload_schedule(plan, sc);
         if (rc) return rc;
-        const Workspace ws = plan_workspace(plan, sc);
-        REXI_HIP(enqueue_prep(plan, ws, u0, 0, S, 0, plan->sched_layout, s));
-        REXI_HIP(enqueue_zero(plan->d_acc, sc.part_size, s));
-        for (int k = 0; k < plan->N; ++k) REXI_HIP(enqueue_per_term_pole(plan, ws, sc, k, 0, S, s));
-        REXI_HIP(enqueue_reduce(plan, ws, sc, plan->d_acc, 0, 1, u1, S, 0, plan->d_slot_m, s));
-        return REXI_OK;
-    } catch (const std::bad_alloc&) {
-        return fail(REXI_ENOMEM, "host allocation failed");
     }
+    hipStream_t s = (hipStream_t)stream;
+    note_capture(plan, s);
+    rc = grow(plan, &plan->d_acc, &plan->acc_capacity, sc.part_size);
+    if (rc) return rc;
+    const Workspace ws = plan_workspace(plan, sc);
+    REXI_HIP(enqueue_prep(plan, ws, u0, 0, S, 0, plan->sched_layout, s));
+    REXI_HIP(enqueue_zero(plan->d_acc, sc.part_size, s));
+    for (int k = 0; k < plan->N; ++k) REXI_HIP(enqueue_per_term_pole(plan, ws, sc, k, 0, S, s));
+    REXI_HIP(enqueue_reduce(plan, ws, sc, plan->d_acc, 0, 1, u1, S, 0, plan->d_slot_m, s));
+    return REXI_OK;
+} catch (...) {
+    return caught();
 }
 
-int rexi_plan_set_schedule(rexi_plan* plan, int S, int index, int* count) {
+int rexi_plan_set_schedule(rexi_plan* plan, int S, int index, int* count) try {
     if (!plan) return fail(REXI_EINVAL, "plan is NULL");
     if (plan->prm.fsphere) return fail(REXI_EUNSUPPORTED, "f-sphere plans have no schedules");
     if (S < 1 || S > plan->prm.max_states) return fail(REXI_EINVAL, "S out of range");
@@ -1270,9 +1289,11 @@ int rexi_plan_set_schedule(rexi_plan* plan, int S, int index, int* count) {
     rc = schedules_for(plan, S, true, &c);
     if (rc) plan->chosen[S] = was;
     return rc;
+} catch (...) {
+    return caught();
 }
 
-int rexi_plan_get_schedule(rexi_plan* plan, int S, int* index) {
+int rexi_plan_get_schedule(rexi_plan* plan, int S, int* index) try {
     if (!plan || !index) return fail(REXI_EINVAL, "NULL argument");
     if (plan->prm.fsphere) return fail(REXI_EUNSUPPORTED, "f-sphere plans have no schedules");
     if (S < 1 || S > plan->prm.max_states) return fail(REXI_EINVAL, "S out of range");
@@ -1281,26 +1302,39 @@ int rexi_plan_get_schedule(rexi_plan* plan, int S, int* index) {
     if (rc) return rc;
     *index = plan->chosen[S];
     return REXI_OK;
+} catch (...) {
+    return caught();
 }
 
-int rexi_plan_autotune(rexi_plan* plan, int S, void* stream, int* chosen) {
+int rexi_plan_autotune(rexi_plan* plan, int S, void* stream, int* chosen) try {
     if (!plan) return fail(REXI_EINVAL, "plan is NULL");
     if (plan->prm.fsphere) return fail(REXI_EUNSUPPORTED, "f-sphere plans have no schedules");
     if (S < 1 || S > plan->prm.max_states) return fail(REXI_EINVAL, "S out of range");
     std::vector<Schedule>* c = nullptr;
     int rc = schedules_for(plan, S, true, &c);
     if (rc) return rc;
-    hipStream_t s = (hipStream_t)stream;
+    struct Held {
+        hipStream_t s;
+        void *u0 = nullptr, *u1 = nullptr;
+        hipEvent_t a = nullptr, b = nullptr;
+        ~Held() {
+            if (a) (void)hipEventDestroy(a);
+            if (b) (void)hipEventDestroy(b);
+            (void)hipStreamSynchronize(s);
+            (void)hipFree(u0);
+            (void)hipFree(u1);
+        }
+    } held{(hipStream_t)stream};
+    hipStream_t& s = held.s;
+    void *&u0 = held.u0, *&u1 = held.u1;
+    hipEvent_t &a = held.a, &b = held.b;
     const size_t bytes = (size_t)S * 3 * plan->nspec * 16;
-    void *u0 = nullptr, *u1 = nullptr;
     hipError_t e = hipMalloc(&u0, bytes);
     if (e == hipSuccess) e = hipMalloc(&u1, bytes);
     if (e != hipSuccess) {
         (void)hipGetLastError();
-        (void)hipFree(u0);
         return hip_fail(e, "hipMalloc");
     }
-    hipEvent_t a = nullptr, b = nullptr;
     int best = -1;
     float best_ms = 0;
     rc = REXI_OK;
@@ -1329,34 +1363,33 @@ int rexi_plan_autotune(rexi_plan* plan, int S, void* stream, int* chosen) {
             if (best < 0 || ms < best_ms * (resident ? 0.97f : 1.0f)) { best = i; best_ms = ms; }
         }
     } while (0);
-    if (a) (void)hipEventDestroy(a);
-    if (b) (void)hipEventDestroy(b);
-    (void)hipStreamSynchronize(s);
-    (void)hipFree(u0);
-    (void)hipFree(u1);
     if (rc) return rc;
     if (plan->chosen[S] != best) drop_graphs(plan);
     plan->chosen[S] = best;
     if (chosen) *chosen = best;
     return schedules_for(plan, S, true, &c);  // what the no-allocation step needs with it
+} catch (...) {
+    return caught();
 }
 
-int rexi_solve_variants(int per_term, int capacity, int* se, int* kind, int* states_per_item, int* count) {
+int rexi_solve_variants(int per_term, int capacity, int* se, int* kind, int* states_per_item, int* count) try {
     if (capacity < 0) return fail(REXI_EINVAL, "capacity must be >= 0");
     const int n = solve_variant_list(per_term != 0, se, kind, states_per_item, capacity);
     if (count) *count = n;
     return REXI_OK;
+} catch (...) {
+    return caught();
 }
 
 int rexi_plan_schedule_classes(rexi_plan* plan, int S, int index, int capacity, int* se, int* kind,
-                               int* states_per_item, int* count) {
+                               int* states_per_item, int* count) try {
     if (!plan) return fail(REXI_EINVAL, "plan is NULL");
     if (plan->prm.fsphere) return fail(REXI_EUNSUPPORTED, "f-sphere plans have no schedules");
     if (S < 1 || S > plan->prm.max_states) return fail(REXI_EINVAL, "S out of range");
     if (capacity < 0) return fail(REXI_EINVAL, "capacity must be >= 0");
     const Schedule* sc = nullptr;
     if (index == -1) {
-        if ((int)plan->per_term.size() <= S || plan->per_term[S].items.empty())
+        if ((int)plan->per_term.size() <= S || !plan->per_term[S].on_device)
             return fail(REXI_EINVAL, "the per-term schedule for S is built by the first rexi_step_per_term call");
         sc = &plan->per_term[S];
     } else {
@@ -1374,9 +1407,11 @@ int rexi_plan_schedule_classes(rexi_plan* plan, int S, int index, int capacity, 
     }
     if (count) *count = n;
     return REXI_OK;
+} catch (...) {
+    return caught();
 }
 
-int rexi_plan_schedule_name(rexi_plan* plan, int S, int index, char* buf, int capacity) {
+int rexi_plan_schedule_name(rexi_plan* plan, int S, int index, char* buf, int capacity) try {
     if (!plan) return fail(REXI_EINVAL, "plan is NULL");
     if (!buf || capacity < 1) return fail(REXI_EINVAL, "buf is NULL or capacity < 1");
     buf[0] = 0;
@@ -1384,7 +1419,7 @@ int rexi_plan_schedule_name(rexi_plan* plan, int S, int index, char* buf, int ca
     if (S < 1 || S > plan->prm.max_states) return fail(REXI_EINVAL, "S out of range");
     const Schedule* sc = nullptr;
     if (index == -1) {
-        if ((int)plan->per_term.size() <= S || plan->per_term[S].items.empty())
+        if ((int)plan->per_term.size() <= S || !plan->per_term[S].on_device)
             return fail(REXI_EINVAL, "the per-term schedule for S is built by the first rexi_step_per_term call");
         sc = &plan->per_term[S];
     } else {
@@ -1396,29 +1431,37 @@ int rexi_plan_schedule_name(rexi_plan* plan, int S, int index, char* buf, int ca
     }
     std::snprintf(buf, (size_t)capacity, "%s", sc->name.c_str());
     return REXI_OK;
+} catch (...) {
+    return caught();
 }
 
-int rexi_plan_set_streams(rexi_plan* plan, int enable) {
+int rexi_plan_set_streams(rexi_plan* plan, int enable) try {
     if (!plan) return fail(REXI_EINVAL, "plan is NULL");
     const bool on = enable != 0;
     if (on != plan->concurrent) drop_graphs(plan);
     plan->concurrent = on;
     return REXI_OK;
+} catch (...) {
+    return caught();
 }
 
-int rexi_plan_set_graphs(rexi_plan* plan, int enable) {
+int rexi_plan_set_graphs(rexi_plan* plan, int enable) try {
     if (!plan) return fail(REXI_EINVAL, "plan is NULL");
     plan->use_graphs = enable != 0;
     return REXI_OK;
+} catch (...) {
+    return caught();
 }
 
-int rexi_plan_set_timing(rexi_plan* plan, int enable) {
+int rexi_plan_set_timing(rexi_plan* plan, int enable) try {
     if (!plan) return fail(REXI_EINVAL, "plan is NULL");
     plan->timing = enable != 0;
     return REXI_OK;
+} catch (...) {
+    return caught();
 }
 
-int rexi_plan_kernel_time(rexi_plan* plan, int kernel, double* total_ms, long long* launches) {
+int rexi_plan_kernel_time(rexi_plan* plan, int kernel, double* total_ms, long long* launches) try {
     if (!plan) return fail(REXI_EINVAL, "plan is NULL");
     if (kernel < 0 || kernel > 2) return fail(REXI_EINVAL, "unknown kernel");
     double tot = 0;
@@ -1436,26 +1479,36 @@ int rexi_plan_kernel_time(rexi_plan* plan, int kernel, double* total_ms, long lo
     if (total_ms) *total_ms = tot;
     if (launches) *launches = n;
     return REXI_OK;
+} catch (...) {
+    return caught();
 }
 
-int sh_forward(rexi_plan* plan, const double* grid, void* spec, int B, void* stream) {
+int sh_forward(rexi_plan* plan, const double* grid, void* spec, int B, void* stream) try {
     if (!plan) return fail(REXI_EINVAL, "plan is NULL");
     return sh_run(plan, grid, spec, B, true, (hipStream_t)stream);
+} catch (...) {
+    return caught();
 }
 
-int sh_inverse(rexi_plan* plan, const void* spec, double* grid, int B, void* stream) {
+int sh_inverse(rexi_plan* plan, const void* spec, double* grid, int B, void* stream) try {
     if (!plan) return fail(REXI_EINVAL, "plan is NULL");
     return sh_run(plan, spec, grid, B, false, (hipStream_t)stream);
+} catch (...) {
+    return caught();
 }
 
-int sh_vortdiv_to_uv(rexi_plan* plan, const void* vd, long long stride, double* uv, int B, void* stream) {
+int sh_vortdiv_to_uv(rexi_plan* plan, const void* vd, long long stride, double* uv, int B, void* stream) try {
     if (!plan) return fail(REXI_EINVAL, "plan is NULL");
     return sh_vec_run(plan, vd, uv, stride, B, true, (hipStream_t)stream);
+} catch (...) {
+    return caught();
 }
 
-int sh_uv_to_vortdiv(rexi_plan* plan, const double* uv, void* vd, long long stride, int B, void* stream) {
+int sh_uv_to_vortdiv(rexi_plan* plan, const double* uv, void* vd, long long stride, int B, void* stream) try {
     if (!plan) return fail(REXI_EINVAL, "plan is NULL");
     return sh_vec_run(plan, uv, vd, stride, B, false, (hipStream_t)stream);
+} catch (...) {
+    return caught();
 }
 
 }  // extern "C"

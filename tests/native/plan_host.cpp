@@ -24,14 +24,22 @@ namespace {
 
 std::map<char*, size_t> live;
 std::set<void*> held;          // workspace that launches under a caller's capture were given
-int bad = 0, mallocs = 0, events_made = 0;
+int bad = 0, mallocs = 0, events_made = 0, events_live = 0;
 int fail_at = 0;               // the fail_at-th hipMalloc from now fails ...
 bool fail_on = false;          // ... and those after it
 size_t budget = ~size_t(0), used = 0;
 bool capturing = false;
 hipError_t last_error = hipSuccess;
+long long new_at = 0;          // the new_at-th allocation of the host from now fails
 double now_ms = 0;             // what the launches so far took
 std::function<double(const Schedule&)> cost;  // of one step, ms
+
+// The stub's own allocations do not fail.
+struct Quiet {
+    long long was = new_at;
+    Quiet() { new_at = 0; }
+    ~Quiet() { new_at = was; }
+};
 
 void complain(const std::string& what) {
     std::fprintf(stderr, "  %s\n", what.c_str());
@@ -40,6 +48,7 @@ void complain(const std::string& what) {
 
 // [p, p + bytes) is device memory
 void need(const void* p, size_t bytes, const char* what, const void* array = nullptr, size_t array_bytes = 0) {
+    Quiet quiet;
     const char* c = static_cast<const char*>(p);
     const char* a = static_cast<const char*>(array);
     if (a && c >= a && c + bytes <= a + array_bytes) return;
@@ -60,8 +69,17 @@ void expect(bool ok, const std::string& what) {
 
 }  // namespace
 
+void* operator new(size_t n) {
+    if (new_at > 0 && --new_at == 0) throw std::bad_alloc();
+    if (void* p = std::malloc(n ? n : 1)) return p;
+    throw std::bad_alloc();
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
+
 extern "C" {
 hipError_t hipMalloc(void** p, size_t n) {
+    Quiet quiet;
     ++mallocs;
     const bool fails = (fail_at > 0 && --fail_at == 0) || used + n > budget;
     if (fails) {
@@ -133,12 +151,15 @@ hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
 hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
 hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipSuccess; }
 hipError_t hipEventCreate(hipEvent_t* e) {
+    Quiet quiet;
     ++events_made;
+    ++events_live;
     *e = reinterpret_cast<hipEvent_t>(new double(0));
     return hipSuccess;
 }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
 hipError_t hipEventDestroy(hipEvent_t e) {
+    --events_live;
     delete reinterpret_cast<double*>(e);
     return hipSuccess;
 }
@@ -269,7 +290,7 @@ namespace {
 char* const kIn = reinterpret_cast<char*>(size_t(1) << 44);
 char* const kOut = reinterpret_cast<char*>(size_t(1) << 45);
 
-rexi_plan* make_plan(int T, int M, int max_states) {
+rexi_params make_plan_params(int T, int M, int max_states) {
     rexi_params p{};
     p.T = T;
     p.radius = 6.37122e6;
@@ -283,6 +304,11 @@ rexi_plan* make_plan(int T, int M, int max_states) {
     p.normalize = 1;
     p.max_states = max_states;
     p.max_fields = 1;
+    return p;
+}
+
+rexi_plan* make_plan(int T, int M, int max_states) {
+    const rexi_params p = make_plan_params(T, M, max_states);
     rexi_plan* pl = nullptr;
     const int rc = rexi_plan_create(&p, &pl);
     if (rc) {
@@ -298,6 +324,7 @@ void destroy(rexi_plan* pl) {
     held.clear();
     rexi_plan_destroy(pl);
     expect(live.empty(), "all device memory given back");
+    expect(events_live == 0, "all events given back");
     for (auto& a : live) std::free(a.first);
     live.clear();
     used = 0;
@@ -442,6 +469,81 @@ int noalloc_untimed() {
     return bad;
 }
 
+// Host allocations that fail end in REXI_ENOMEM, not in an exception that leaves the
+// C interface, and nothing half built is used afterwards.
+int host_allocations() {
+    auto names = [](rexi_plan* pl, int S) {
+        std::string all;
+        int n = 0;
+        expect(rexi_plan_set_schedule(pl, S, -1, &n) == REXI_OK, "the schedules");
+        for (int i = 0; i < n; ++i) {
+            char buf[128];
+            expect(rexi_plan_schedule_name(pl, S, i, buf, sizeof buf) == REXI_OK, "a name");
+            all += std::string(buf) + " ";
+        }
+        return all;
+    };
+    const int T = 26, S = 3;
+    struct Call {
+        const char* what;
+        std::function<int(rexi_plan*)> f;
+    };
+    const Call calls[] = {
+        {"rexi_step", [](rexi_plan* p) { return step(p, S); }},
+        {"rexi_step_per_term", [](rexi_plan* p) { return rexi_step_per_term(p, kIn, kOut, S, nullptr); }},
+        {"rexi_plan_set_schedule", [](rexi_plan* p) { return rexi_plan_set_schedule(p, S, 3, nullptr); }},
+        {"rexi_plan_get_schedule", [](rexi_plan* p) { int i; return rexi_plan_get_schedule(p, S, &i); }},
+        {"rexi_plan_schedule_name", [](rexi_plan* p) { char b[128]; return rexi_plan_schedule_name(p, S, 0, b, 128); }},
+        {"rexi_plan_schedule_classes",
+         [](rexi_plan* p) { int n; return rexi_plan_schedule_classes(p, S, 0, 0, nullptr, nullptr, nullptr, &n); }},
+        {"rexi_plan_autotune", [](rexi_plan* p) { int i; return rexi_plan_autotune(p, S, nullptr, &i); }},
+    };
+    rexi_plan* ref = make_plan(T, 20, 8);
+    expect(step(ref, S) == REXI_OK, "a step");
+    const std::string want = names(ref, S);
+    destroy(ref);
+    for (const Call& c : calls)
+        for (long long n = 1;; n += 1 + n / 25) {
+            rexi_plan* pl = make_plan(T, 20, 8);
+            rexi_plan_set_timing(pl, 1);
+            new_at = n;
+            int rc = -99;
+            try {
+                rc = c.f(pl);
+            } catch (...) {
+            }
+            const bool hit = new_at == 0;
+            new_at = 0;
+            const std::string at = std::string(c.what) + ", host allocation " + std::to_string(n);
+            expect(hit ? rc == REXI_ENOMEM || rc == REXI_OK : rc == REXI_OK, at + ": REXI_ENOMEM, got " + std::to_string(rc));
+            expect(c.f(pl) == REXI_OK, at + ": the call again");
+            expect(step(pl, S) == REXI_OK, at + ": a step");
+            expect(names(pl, S) == want, at + ": the schedules as ever");
+            destroy(pl);
+            if (!hit || bad > 20) break;
+        }
+    for (long long n = 1;; n += 1 + n / 25) {  // a plan that is not made leaves nothing
+        rexi_params p = make_plan_params(T, 20, 8);
+        rexi_plan* pl = nullptr;
+        new_at = n;
+        int rc = -99;
+        try {
+            rc = rexi_plan_create(&p, &pl);
+        } catch (...) {
+        }
+        const bool hit = new_at == 0;
+        new_at = 0;
+        expect(hit ? rc == REXI_ENOMEM && !pl : rc == REXI_OK, "rexi_plan_create: REXI_ENOMEM");
+        if (!hit) {
+            destroy(pl);
+            break;
+        }
+        expect(live.empty(), "rexi_plan_create, host allocation " + std::to_string(n) + ": nothing left");
+        if (bad > 20) break;
+    }
+    return bad;
+}
+
 const std::map<std::string, int (*)()> kScenarios = {
     {"handled_failure", handled_failure},
     {"failed_growth", failed_growth},
@@ -449,6 +551,7 @@ const std::map<std::string, int (*)()> kScenarios = {
     {"shortage", shortage},
     {"captured_buffers", captured_buffers},
     {"noalloc_untimed", noalloc_untimed},
+    {"host_allocations", host_allocations},
 };
 
 }  // namespace
