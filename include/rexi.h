@@ -198,19 +198,21 @@ int rexi_step_adjoint(rexi_plan *plan, const void *g1, void *g0, int S, int nste
 /* rexi_step for callers that cannot allocate device memory (code under HIP
  * graph capture, tight serving loops, harnesses that forbid allocation): the
  * same kernels and the plan's current schedule for S, with the workspace
- * (states in chain layout or records, partial sums, block-boundary values, work
- * counters) in one fixed 64 MiB
- * device array of the library instead of the plan's allocations; kernels
- * launched one by one, no graph, no event.  Calls no hipMalloc, hipFree or
- * other allocating routine.
+ * (states in chain layout or records, partial sums, block-boundary values,
+ * work counters) in one fixed 64 MiB device array of the library instead of
+ * the plan's allocations; kernels launched one by one, no graph, no event.
+ * Calls no hipMalloc, hipFree or other allocating routine.
  *   Arguments as rexi_step.  The schedules for S must exist: one earlier
  *   rexi_step, rexi_plan_set_schedule or rexi_plan_autotune call with S
  *   builds them (and allocates); otherwise REXI_EINVAL.  A step whose
  *   workspace exceeds 64 MiB returns REXI_EUNSUPPORTED (a schedule with fewer
  *   work items, rexi_plan_set_schedule, needs less; T256 with 4 states fits
  *   with about 2048 items).  A pole-per-lane schedule whose workspace for a
- *   full chip exceeds it is replaced by the default tiled schedule for S.  Persistent schedules (a resident grid taking
- *   items from a counter) return REXI_EUNSUPPORTED.
+ *   full chip exceeds it is replaced by the default tiled schedule for S where
+ *   the plan chose it itself (the default, or rexi_plan_autotune's choice);
+ *   another one, selected by rexi_plan_set_schedule, returns REXI_EUNSUPPORTED.
+ *   Persistent schedules (a resident grid taking items from a counter) return
+ *   REXI_EUNSUPPORTED.
  *   The array is per GPU and lives until the process ends; every call on a
  *   GPU uses it, so calls that overlap on one GPU (on different streams or
  *   from different threads) race. */

@@ -223,6 +223,7 @@ struct rexi_plan {
     // schedules: candidates per S, chosen index per S; per-term form per S
     std::vector<std::vector<rexi::Schedule>> sched;  // [S] -> candidates
     std::vector<int> chosen;
+    std::vector<int> own;    // what the plan chose itself, the default or autotune's, [S]
     std::vector<int> tiled;  // the default among the tiled schedules, [S]
     // until the candidates of S are asked for: the default alone, and the tiled one
     // that takes its no-allocation steps (see schedules_for)

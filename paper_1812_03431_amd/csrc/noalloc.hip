@@ -122,6 +122,9 @@ extern "C" int rexi_step_noalloc(rexi_plan* plan, const void* u0, void* u1, int 
             }
             return run_sweep_steps(plan, ws, *psc, u0, u1, S, nsteps, 0, false, (hipStream_t)stream);
         }
+        if (listed && plan->chosen[S] != plan->own[S])
+            return fail(REXI_EUNSUPPORTED, "the selected schedule needs more workspace than the no-allocation limit of " +
+                                               std::to_string(plan->scratch_bytes) + " bytes");
         psc = !listed ? &plan->first_tiled[S] : plan->tiled[S] >= 0 ? &plan->sched[S][plan->tiled[S]] : nullptr;
         if (!psc || !psc->on_device) return fail(REXI_EUNSUPPORTED, "no schedule fits the no-allocation limit");
     }

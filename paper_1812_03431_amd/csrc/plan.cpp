@@ -698,6 +698,7 @@ void room_for(rexi_plan* pl, int S) {
     pl->first.resize(n);
     pl->first_tiled.resize(n);
     pl->chosen.resize(n, -1);
+    pl->own.resize(n, -1);
     pl->tiled.resize(n, -1);
     pl->sched.resize(n);
 }
@@ -793,7 +794,7 @@ int schedules_for(rexi_plan* pl, int S, bool all, std::vector<Schedule>** out) {
         if (from_tiled >= 0) list[from_tiled] = std::exchange(pl->first_tiled[S], Schedule());
         c = std::move(list);
         pl->tiled[S] = tiled;
-        pl->chosen[S] = dflt >= 0 ? dflt : 0;
+        pl->chosen[S] = pl->own[S] = dflt >= 0 ? dflt : 0;
     }
     *out = &c;
     const int rc = upload_with_tiled(pl, c[pl->chosen[S]], pl->tiled[S] >= 0 ? &c[pl->tiled[S]] : nullptr);
@@ -1365,7 +1366,7 @@ int rexi_plan_autotune(rexi_plan* plan, int S, void* stream, int* chosen) try {
     } while (0);
     if (rc) return rc;
     if (plan->chosen[S] != best) drop_graphs(plan);
-    plan->chosen[S] = best;
+    plan->chosen[S] = plan->own[S] = best;
     if (chosen) *chosen = best;
     return schedules_for(plan, S, true, &c);  // what the no-allocation step needs with it
 } catch (...) {

@@ -31,7 +31,7 @@ size_t budget = ~size_t(0), used = 0;
 bool capturing = false;
 hipError_t last_error = hipSuccess;
 long long new_at = 0;          // the new_at-th allocation of the host from now fails
-double now_ms = 0;             // what the launches so far took
+double now_ms = 0, begin_ms = 0, graph_ms = 0;  // what the launches so far took
 std::function<double(const Schedule&)> cost;  // of one step, ms
 
 // The stub's own allocations do not fail.
@@ -134,9 +134,15 @@ hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
 }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
-hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipSuccess; }
+// (the plan's own graphs: an instance holds what its launches take)
+hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) {
+    begin_ms = now_ms;
+    return hipSuccess;
+}
 hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t* g) {
     *g = reinterpret_cast<hipGraph_t>(8);
+    graph_ms = now_ms - begin_ms;
+    now_ms = begin_ms;
     return hipSuccess;
 }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* st) {
@@ -144,12 +150,19 @@ hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* st) {
     return hipSuccess;
 }
 hipError_t hipGraphInstantiate(hipGraphExec_t* e, hipGraph_t, hipGraphNode_t*, char*, size_t) {
-    *e = reinterpret_cast<hipGraphExec_t>(8);
+    Quiet quiet;
+    *e = reinterpret_cast<hipGraphExec_t>(new double(graph_ms));
     return hipSuccess;
 }
 hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
-hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
-hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipSuccess; }
+hipError_t hipGraphExecDestroy(hipGraphExec_t e) {
+    delete reinterpret_cast<double*>(e);
+    return hipSuccess;
+}
+hipError_t hipGraphLaunch(hipGraphExec_t e, hipStream_t) {
+    now_ms += *reinterpret_cast<double*>(e);
+    return hipSuccess;
+}
 hipError_t hipEventCreate(hipEvent_t* e) {
     Quiet quiet;
     ++events_made;
@@ -544,6 +557,42 @@ int host_allocations() {
     return bad;
 }
 
+// A pole-per-lane schedule that the no-allocation step's array does not hold is
+// replaced where the plan chose it, and refused where the caller did.
+int noalloc_selection() {
+    rexi_plan* pl = make_plan(60, 500, 8);
+    const int S = 4;
+    auto noalloc = [&] { return rexi_step_noalloc(pl, kIn, kOut, S, 1, nullptr); };
+    int n = 0, own = -1;
+    expect(step(pl, S) == REXI_OK && noalloc() == REXI_OK, "the default, unlisted");
+    expect(rexi_plan_get_schedule(pl, S, &own) == REXI_OK && noalloc() == REXI_OK, "the default, listed");
+    expect(rexi_plan_set_schedule(pl, S, -1, &n) == REXI_OK, "the schedules");
+    int refused = 0, ran = 0;
+    for (int i = 0; i < n; ++i) {
+        char name[128];
+        expect(rexi_plan_set_schedule(pl, S, i, nullptr) == REXI_OK, "a selection");
+        expect(rexi_plan_schedule_name(pl, S, i, name, sizeof name) == REXI_OK, "a name");
+        if (std::string(name).find("sweep") != 0) continue;
+        const int rc = noalloc();
+        if (i == own) expect(rc == REXI_OK, "the plan's own choice, selected again");
+        else expect(rc == REXI_EUNSUPPORTED, std::string(name) + " refused"), ++refused;
+    }
+    expect(refused > 0, "another pole-per-lane schedule");
+    cost = [](const Schedule& sc) { return sc.sweep && !sc.persistent && sc.sweep_items.size() < 2000 ? 1.0 : 2.0; };
+    int best = -1;
+    expect(rexi_plan_autotune(pl, S, nullptr, &best) == REXI_OK && pl->sched[S][best].sweep, "the autotuner's choice");
+    expect(noalloc() == REXI_OK, "the autotuner's choice");
+    cost = nullptr;
+    for (int i = 0; i < n; ++i)  // tiled schedules run or are refused as selected
+        if (!pl->sched[S][i].sweep && !pl->sched[S][i].persistent) {
+            expect(rexi_plan_set_schedule(pl, S, i, nullptr) == REXI_OK, "a selection");
+            ran += noalloc() == REXI_OK;
+        }
+    expect(ran > 0, "tiled schedules that fit");
+    destroy(pl);
+    return bad;
+}
+
 const std::map<std::string, int (*)()> kScenarios = {
     {"handled_failure", handled_failure},
     {"failed_growth", failed_growth},
@@ -552,6 +601,7 @@ const std::map<std::string, int (*)()> kScenarios = {
     {"captured_buffers", captured_buffers},
     {"noalloc_untimed", noalloc_untimed},
     {"host_allocations", host_allocations},
+    {"noalloc_selection", noalloc_selection},
 };
 
 }  // namespace
