@@ -32,6 +32,7 @@ bool capturing = false;
 hipError_t last_error = hipSuccess;
 long long new_at = 0;          // the new_at-th allocation of the host from now fails
 double now_ms = 0, begin_ms = 0, graph_ms = 0;  // what the launches so far took
+int last_wgs = 0, last_grid = 0;  // of the last pole-per-lane solve (0: a tiled one)
 std::function<double(const Schedule&)> cost;  // of one step, ms
 
 // The stub's own allocations do not fail.
@@ -217,6 +218,7 @@ hipError_t enqueue_solve(rexi_plan* pl, const Workspace& ws, const Schedule& sc,
     need(pl->d_poles[adjoint], (size_t)pl->N * 96, "poles");
     need_ws(pl, ws.part, (size_t)sc.part_size * 16, "part");
     if (sc.persistent) need_ws(pl, ws.counters, kMaxLaunches * sizeof(int), "counters");
+    last_wgs = last_grid = 0;
     if (cost) now_ms += cost(sc);
     return hipGetLastError();
 }
@@ -273,6 +275,8 @@ hipError_t enqueue_sweep_solve(rexi_plan* pl, const Workspace& ws, const Schedul
     }
     if (sc.sweep_stride > 0)
         need_ws(pl, ws.sweep_scratch, (size_t)grid * kSweepWaves * sc.sweep_stride * 16, "boundary values");
+    last_wgs = wgs;
+    last_grid = grid;
     // register-resident chains take one group of items per workgroup
     if (sc.short_chains && !sc.persistent) expect(grid == wgs, "a workgroup for every group of items");
     if (cost) now_ms += cost(sc);
@@ -593,6 +597,28 @@ int noalloc_selection() {
     return bad;
 }
 
+// Which way the no-allocation step takes at the sizes that test_zz_no_alloc_paths.py
+// runs on a GPU.
+int noalloc_routes() {
+    struct Case {
+        int T, S, M;
+        char route;  // 'a' a slot for every workgroup, 's' several items in turn, 't' the tiled schedule
+    };
+    for (const Case& c : {Case{100, 1, 250, 'a'}, Case{60, 1, 500, 'a'}, Case{100, 1, 500, 's'}, Case{31, 8, 1000, 's'},
+                          Case{60, 4, 500, 't'}, Case{150, 1, 250, 't'}}) {
+        rexi_plan* pl = make_plan(c.T, c.M, 8);
+        expect(step(pl, c.S) == REXI_OK && last_wgs > 0, "a pole-per-lane step");
+        expect(pl->first[c.S].sweep_stride > 0, "with boundary values");
+        expect(rexi_step_noalloc(pl, kIn, kOut, c.S, 2, nullptr) == REXI_OK, "a no-allocation step");
+        const char r = last_wgs == 0 ? 't' : last_grid == last_wgs ? 'a' : 's';
+        expect(r == c.route, "T" + std::to_string(c.T) + " S" + std::to_string(c.S) + " M" + std::to_string(c.M) +
+                                 ": route " + c.route + ", got " + r);
+        if (c.route == 's') expect(last_grid >= kSweepGroups, "workgroups that fill the chip");
+        destroy(pl);
+    }
+    return bad;
+}
+
 const std::map<std::string, int (*)()> kScenarios = {
     {"handled_failure", handled_failure},
     {"failed_growth", failed_growth},
@@ -602,6 +628,7 @@ const std::map<std::string, int (*)()> kScenarios = {
     {"noalloc_untimed", noalloc_untimed},
     {"host_allocations", host_allocations},
     {"noalloc_selection", noalloc_selection},
+    {"noalloc_routes", noalloc_routes},
 };
 
 }  // namespace
