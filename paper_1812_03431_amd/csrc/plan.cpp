@@ -461,20 +461,32 @@ int build_sweep_tables(rexi_plan* pl, bool split) {
 // rounds (2100 waves 28 -> 26 us).
 constexpr long long kSplitWaves = 1900, kShortWaves = 1100;
 
-// A pole-per-lane schedule: the states in tiles of up to kSweepStates, split
+// A pole-per-lane schedule: the states in tiles of up to `most`, split
 // evenly; items are (chain, tile, range of 64-pole batches), as many per
 // (chain, tile) as its share of target_items, longest first.  split: one batch per
 // item, and the two halves of a split chain are consecutive items from an even
 // index on (waves of one workgroup).
-int build_sweep_schedule(rexi_plan* pl, int S, long long target_items, bool split, bool short_chains, Schedule& out) {
+int build_sweep_schedule(rexi_plan* pl, int S, int most, long long target_items, bool split, bool short_chains,
+                         Schedule& out) {
     sweep_layout(pl, split);
     const SweepTables& t = pl->sweep[split];
+    const int nt = (S + most - 1) / most, nb = (pl->N + 63) / 64;
+    if (short_chains) {
+        long long waves = 0;
+        int npmax = 0;
+        for (size_t ch = 0; ch < t.chains.size(); ++ch) {
+            const int2 half = t.halves[ch];
+            waves += (half.x > 0 ? 2LL : 1LL) * nt * nb;
+            npmax = std::max(npmax, half.x > 0 ? std::max(half.x, half.y) : t.chains[ch].npair);
+        }
+        if (npmax > kSweepShort || waves > kShortWaves * (S == nt ? 2 : 1))
+            return fail(REXI_EUNSUPPORTED, "chains too long or too many for registers");
+    }
     out = Schedule();
     out.sweep = true;
     out.split = split;
     out.short_chains = short_chains;
     out.S = S;
-    const int nt = (S + kSweepStates - 1) / kSweepStates, nb = (pl->N + 63) / 64;
     out.sweep_ntiles = nt;
     std::vector<SweepTile>& tiles = out.sweep_tiles;
     tiles.resize(S);
@@ -538,11 +550,7 @@ int build_sweep_schedule(rexi_plan* pl, int S, long long target_items, bool spli
     out.part_size = (off + 1) / 2;
     out.sweep_stride = (long long)((npmax + kSweepBlock - 1) / kSweepBlock) * (1 + 2 * out.sweep_nst) * 64;
     out.rot_max = out.sweep_nst;
-    if (short_chains) {
-        if (npmax > kSweepShort || (long long)out.sweep_items.size() > kShortWaves * (out.sweep_nst == 1 ? 2 : 1))
-            return fail(REXI_EUNSUPPORTED, "chains too long or too many for registers");
-        out.sweep_stride = 0;
-    }
+    if (short_chains) out.sweep_stride = 0;
     out.launches.push_back({2 * kSweepBlock, kSweepKind, 0, (int)out.sweep_items.size(), 1, out.sweep_nst});
     char buf[96];
     std::snprintf(buf, sizeof buf, "%s_items%lld%s", short_chains ? "sweep_short" : split ? "sweep2" : "sweep", (long long)out.sweep_items.size(),
@@ -673,14 +681,40 @@ constexpr long long kTiledTarget = 2816;
 int tiled_rot(int S) { return S % 2 == 0 ? 2 : 0; }
 
 // The pole-per-lane solve's default: one pole per lane wherever the operator
-// allows it, which at every size and state count measured (T63 to T301, 1 to 8
-// states) beats the tiled schedules (see sweep_kernels.hip).  ~8192 items (four per
+// allows it, which with the states of an item chosen as below beats the tiled
+// schedules at every size, state count and number of poles measured (T15 to T1023, 1
+// to 64 states, 25 to 8215 poles; the least gains are 8 to 11%, at T127 with four
+// states and 129 poles and at T256 with 16 states and 39 poles).  ~8192 items (four per
 // wave slot of the chip) against ~4096 at T256 with four states: 1527 / 1570 us per
 // step; within 1% of each other elsewhere.
-long long sweep_waves(const rexi_plan* pl, int S) {
-    return 2LL * (pl->T + 1) * ((S + kSweepStates - 1) / kSweepStates) * ((pl->N + 63) / 64);
+long long sweep_waves(const rexi_plan* pl, int S, int most) {
+    return 2LL * (pl->T + 1) * ((S + most - 1) / most) * ((pl->N + 63) / 64);
 }
 constexpr long long kSweepTarget = 8192;
+
+// States of an item: up to kSweepStates share a pole's pivots, but one after the
+// other.  Where few poles or short chains leave the chip idle, an item's time is what
+// counts (T127, 25 poles, by states of an item 1 / 2 / 4: 30 / 42 / 70 us a step, the
+// tiled schedule 51), so an item takes one state, or else two, where the waves are at
+// most kTileWaves, or where registers hold the chains so that kShortWaves is the
+// limit.  Four states, 1 / 2 / 4 of them an item: T127, 25 poles 33 / 44 / 70; T256, 25
+// poles 92 (2056 waves) / 90 (1028) / 141; six states, T100, 151 poles 53 (3636) / 58
+// (1818) / 54 (1212, three an item).
+constexpr long long kTileWaves = 1500;
+
+int default_sweep_schedule(rexi_plan* pl, int S, Schedule& out) {
+    const bool split = sweep_waves(pl, S, kSweepStates) <= kSplitWaves;
+    if (split) {
+        for (int most : {1, 2, kSweepStates})
+            if (sweep_waves(pl, S, most) <= kSplitWaves) {
+                const int rc = build_sweep_schedule(pl, S, most, 0, true, true, out);
+                if (rc != REXI_EUNSUPPORTED) return rc;
+            }
+        for (int most : {1, 2})
+            if (sweep_waves(pl, S, most) <= kTileWaves) return build_sweep_schedule(pl, S, most, 0, true, false, out);
+    }
+    return build_sweep_schedule(pl, S, kSweepStates, split ? 0 : kSweepTarget, split, false, out);
+}
 
 // Uploads schedule `sc` and, where the no-allocation step's array does not hold
 // it, before it the tiled schedule that takes that step in its place.
@@ -716,12 +750,11 @@ int first_schedule(rexi_plan* pl, int S) {
         add_sizes(pl, sc, z);
         return ensure_sizes(pl, z, false);
     }
-    const bool split = sweep_waves(pl, S) <= kSplitWaves;
+    const bool split = sweep_waves(pl, S, kSweepStates) <= kSplitWaves;
     int rc = build_sweep_tables(pl, split);
     if (rc) return rc;
     if (!pl->sweep[split].usable) return REXI_EUNSUPPORTED;
-    rc = split ? build_sweep_schedule(pl, S, 0, true, true, sc) : REXI_EUNSUPPORTED;
-    if (rc == REXI_EUNSUPPORTED) rc = build_sweep_schedule(pl, S, split ? 0 : kSweepTarget, split, false, sc);
+    rc = default_sweep_schedule(pl, S, sc);
     if (rc) return rc;
     bool tiled = !t.on_device && !noalloc_takes(pl, sc);
     if (tiled && (build_schedule(pl, S, kTiledPolicy, kTiledTarget, false, tiled_rot(S), t) != REXI_OK ||
@@ -750,9 +783,11 @@ int schedules_for(rexi_plan* pl, int S, bool all, std::vector<Schedule>** out) {
             rots.push_back(1);
             rots.push_back(2);
         }
-        const bool few = sweep_waves(pl, S) <= kSplitWaves;
+        const bool few = sweep_waves(pl, S, kSweepStates) <= kSplitWaves;
         int rc = build_sweep_tables(pl, few);
         if (rc) return rc;
+        Schedule own;  // the pole-per-lane default, for its name
+        if (pl->sweep[few].usable && (rc = default_sweep_schedule(pl, S, own))) return rc;
         std::vector<Schedule> list;
         int tiled = -1, dflt = -1, from_first = -1, from_tiled = -1;
         for (int rot : rots)
@@ -774,19 +809,22 @@ int schedules_for(rexi_plan* pl, int S, bool all, std::vector<Schedule>** out) {
                 }
         dflt = tiled;
         for (int persistent = 0; pl->sweep[few].usable && persistent < 2; ++persistent)
-            for (long long t : {4096LL, kSweepTarget, 0LL, -1LL}) {  // 0: split chains, -1: split and in registers
-                Schedule sc;
-                if (t <= 0 && !few) continue;
-                rc = build_sweep_schedule(pl, S, t, t <= 0, t < 0, sc);
-                if (rc == REXI_EUNSUPPORTED) continue;
-                if (rc) return rc;
-                sc.persistent = persistent != 0;
-                if (sc.persistent) sc.name = "persistent_" + sc.name;
-                if (!persistent && t != 4096) {
-                    dflt = (int)list.size();
-                    if (pl->first[S].on_device && pl->first[S].name == sc.name) from_first = dflt;
+            for (int most : {kSweepStates, 2, 1}) {
+                if (most < kSweepStates && (S <= most || sweep_waves(pl, S, most) > kSplitWaves)) continue;
+                for (long long t : {4096LL, kSweepTarget, 0LL, -1LL}) {  // 0: split chains, -1: split and in registers
+                    Schedule sc;
+                    if (t <= 0 ? !few : most < kSweepStates) continue;
+                    rc = build_sweep_schedule(pl, S, most, t, t <= 0, t < 0, sc);
+                    if (rc == REXI_EUNSUPPORTED) continue;
+                    if (rc) return rc;
+                    sc.persistent = persistent != 0;
+                    if (sc.persistent) sc.name = "persistent_" + sc.name;
+                    if (t != 4096 && sc.name == own.name) {
+                        dflt = (int)list.size();
+                        if (pl->first[S].on_device) from_first = dflt;
+                    }
+                    list.push_back(std::move(sc));
                 }
-                list.push_back(std::move(sc));
             }
         if (list.empty()) return fail(REXI_EUNSUPPORTED, "no schedule fits this truncation");
         // the device copies of the first step's schedules move with them

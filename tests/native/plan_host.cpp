@@ -619,6 +619,33 @@ int noalloc_routes() {
     return bad;
 }
 
+// States of an item of the default schedule: one or two where that leaves few waves;
+// the default is among the candidates, by its name, once.
+int few_poles() {
+    struct Case {
+        int T, S, M, most;
+    };
+    for (const Case& c : {Case{127, 4, 1, 1}, Case{127, 8, 1, 2}, Case{100, 6, 53, 3}, Case{63, 4, 1, 1}, Case{63, 6, 21, 3},
+                          Case{256, 4, 1, 2}, Case{256, 1, 1, 1}, Case{200, 8, 150, 4}, Case{31, 3, 500, 3}}) {
+        const std::string at = "T" + std::to_string(c.T) + " S" + std::to_string(c.S) + " M" + std::to_string(c.M);
+        rexi_plan* pl = make_plan(c.T, c.M, 8);
+        expect(step(pl, c.S) == REXI_OK, at + ": a step");
+        expect(pl->first[c.S].sweep_nst == c.most, at + ": " + std::to_string(c.most) + " states an item, got " +
+                                                      std::to_string(pl->first[c.S].sweep_nst));
+        const std::string name = pl->first[c.S].name;
+        int index = -1;
+        expect(rexi_plan_get_schedule(pl, c.S, &index) == REXI_OK && pl->sched[c.S][index].name == name, at + ": listed");
+        std::set<std::string> names;
+        for (const Schedule& x : pl->sched[c.S])
+            if (x.sweep && x.split) expect(names.insert(x.name).second, at + ": " + x.name + " once");
+        for (int i = 0; i < (int)pl->sched[c.S].size(); ++i)
+            if (pl->sched[c.S][i].sweep)
+                expect(rexi_plan_set_schedule(pl, c.S, i, nullptr) == REXI_OK && step(pl, c.S) == REXI_OK, at + ": a step of each");
+        destroy(pl);
+    }
+    return bad;
+}
+
 const std::map<std::string, int (*)()> kScenarios = {
     {"handled_failure", handled_failure},
     {"failed_growth", failed_growth},
@@ -629,6 +656,7 @@ const std::map<std::string, int (*)()> kScenarios = {
     {"host_allocations", host_allocations},
     {"noalloc_selection", noalloc_selection},
     {"noalloc_routes", noalloc_routes},
+    {"few_poles", few_poles},
 };
 
 }  // namespace
