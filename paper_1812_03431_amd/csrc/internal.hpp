@@ -64,6 +64,30 @@ struct LegTables {
     int inv_r = 1;                // latitude tiles per wave of the inverse
 };
 
+// Columns per workgroup: C split evenly into `parts` of whole groups of four, at most 32.
+inline int column_chunk(int C, int parts) {
+    const int groups = (C + 3) / 4;
+    parts = std::max(parts, (groups + 7) / 8);
+    return 4 * ((groups + parts - 1) / parts);
+}
+
+// Columns per workgroup of the inverse of C columns, `tiles` workgroups to a chunk of
+// them.  With one latitude tile per wave and at most 850 workgroups of as many columns
+// as fit, each takes two column groups instead, if they pair up evenly: whole
+// syntheses, all / two groups, T256 on 512 x 256, 12 fields (528 workgroups) 21.6 /
+// 19.8 us, 16 fields 25.9 / 23.6; T127, 24 fields (256) 12.8 / 12.0, 96 fields (768)
+// 25.7 / 24.9; T279 on 1024 x 280, 8 fields (840) 25.3 / 24.6.  Beyond that the
+// recurrences, repeated for every eight columns, cost more than the waiting that the
+// further workgroups cover: T300, 12 fields (912) 35.3 / 37.7; T256, 24 fields (1056)
+// 31.1 / 32.5, 512 fields 518 / 563; T127, 1024 fields 220 / 249.  Three groups at
+// T300 took 16.3 us of kernel against 13.0, and two tiles per wave at T511 36 against
+// 32.
+inline int inverse_columns(int C, int tiles_per_wave, int tiles) {
+    const int groups = (C + 3) / 4, all = column_chunk(C, 1);
+    if (tiles_per_wave > 1 || groups % 2 || tiles * ((C + all - 1) / all) > 850) return all;
+    return column_chunk(C, groups / 2);
+}
+
 __host__ __device__ inline long long spec_offset(int T, int m) {
     return (long long)m * (T + 1) - (long long)m * (m - 1) / 2;
 }

@@ -892,13 +892,6 @@ int fft_inverse(rexi_plan* pl, double* grid, int nf, const double* rs, hipStream
     });
 }
 
-// Columns per workgroup: C split evenly into `parts` of whole groups of four, at most 32.
-int column_chunk(int C, int parts) {
-    const int groups = (C + 3) / 4;
-    parts = std::max(parts, (groups + 7) / 8);
-    return 4 * ((groups + parts - 1) / parts);
-}
-
 template <int NH>
 void launch_forward(rexi_plan* pl, const LegTables& t, double* spec, int C, int cw, hipStream_t s) {
     const auto k = t.fwd_g == 4 ? k_legendre_forward<NH, 4> : k_legendre_forward<NH, 2>;
@@ -925,17 +918,12 @@ void launch_inverse(rexi_plan* pl, const LegTables& t, const double* spec, int C
                        pl->d_four, t.T, pl->nlat, pl->nhalf, C, cw);
 }
 
-// spec [C/2][nspec(t.T)] -> Fw (C columns).  Where one latitude tile per wave leaves
-// the chip few workgroups, each takes two column groups instead of all, if they pair
-// up evenly (T256 on 512 x 256: 12 fields 15.5 -> 13.6 us, 8 fields 13.4 -> 11.3; T127,
-// 12 fields 9.3 -> 7.5; T341, 8 fields 22.4 -> 21.1; but T511 with two tiles per wave
-// 32 -> 36, and T300 with three groups 13.0 -> 16.3).
+// spec [C/2][nspec(t.T)] -> Fw (C columns)
 int leg_inverse(rexi_plan* pl, const LegTables& t, const double* spec, int C, hipStream_t s) {
     using Launcher = void (*)(rexi_plan*, const LegTables&, const double*, int, int, hipStream_t);
     static constexpr Launcher of[8] = {launch_inverse<1>, launch_inverse<2>, launch_inverse<3>, launch_inverse<4>,
                                        launch_inverse<5>, launch_inverse<6>, launch_inverse<7>, launch_inverse<8>};
-    const int groups = (C + 3) / 4;
-    const int cw = column_chunk(C, t.inv_r == 1 && groups % 2 == 0 ? groups / 2 : 1);
+    const int cw = inverse_columns(C, t.inv_r, t.ntiles_i);
     of[cw / 4 - 1](pl, t, spec, C, cw, s);
     REXI_HIP(hipGetLastError());
     return REXI_OK;

@@ -646,6 +646,29 @@ int few_poles() {
     return bad;
 }
 
+// Column chunks of the inverse transform: two groups of four where there are few
+// workgroups, else as many columns as fit; every chunk is compiled (up to 32 columns).
+int inverse_chunks() {
+    struct Case {
+        int B, per_wave, tiles, columns;
+    };
+    for (const Case& c : {Case{12, 1, 528, 8}, Case{16, 1, 528, 8}, Case{24, 1, 528, 24}, Case{32, 1, 528, 32},
+                          Case{512, 1, 528, 32}, Case{8, 1, 840, 8}, Case{8, 1, 912, 16}, Case{12, 1, 912, 24},
+                          Case{96, 1, 128, 8}, Case{1024, 1, 128, 32}, Case{5, 1, 264, 12}, Case{1, 1, 16, 4},
+                          Case{16, 2, 4096, 32}, Case{17, 2, 4096, 20}}) {
+        const int got = inverse_columns(2 * c.B, c.per_wave, c.tiles);
+        expect(got == c.columns, std::to_string(c.B) + " fields, " + std::to_string(c.tiles) + " tiles: " +
+                                     std::to_string(c.columns) + " columns, got " + std::to_string(got));
+    }
+    for (int B = 1; B <= 1024; ++B)
+        for (int tiles : {8, 400, 2000})
+            for (int per_wave : {1, 2}) {
+                const int cw = inverse_columns(2 * B, per_wave, tiles);
+                expect(cw >= 4 && cw <= 32 && cw % 4 == 0, "a compiled chunk");
+            }
+    return bad;
+}
+
 const std::map<std::string, int (*)()> kScenarios = {
     {"handled_failure", handled_failure},
     {"failed_growth", failed_growth},
@@ -657,6 +680,7 @@ const std::map<std::string, int (*)()> kScenarios = {
     {"noalloc_selection", noalloc_selection},
     {"noalloc_routes", noalloc_routes},
     {"few_poles", few_poles},
+    {"inverse_chunks", inverse_chunks},
 };
 
 }  // namespace
