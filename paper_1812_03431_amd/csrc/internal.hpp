@@ -235,7 +235,7 @@ struct rexi_plan {
     // per pole, forward [0] and adjoint [1]: alpha, 1/alpha, wx, wy, wx/alpha,
     // wy/alpha (6 complex, see rexi_kernels.hip)
     double2* d_poles[2] = {nullptr, nullptr};
-    // workspace (sized for max_states)
+    // states of the tiled solve, for max_states, where it runs
     double2 *d_ch_var[2] = {nullptr, nullptr};  // [S][nslots + 2]
     double2 *d_ch_phi[2] = {nullptr, nullptr};  // [S][nspec]
     double2 *d_part = nullptr;

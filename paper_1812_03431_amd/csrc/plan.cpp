@@ -619,11 +619,17 @@ int grow(rexi_plan* pl, T** p, long long* capacity, long long n) {
 // records of S states and its scratch, one slot per workgroup, at most
 // kSweepScratch bytes of them (workgroups beyond take several items in turn).
 constexpr long long kSweepScratch = 1LL << 30;
-struct Sizes { long long part = 0, rec = 0, scratch = 0, slot = 0; };
+struct Sizes {
+    long long part = 0, rec = 0, scratch = 0, slot = 0;
+    bool chains = false;  // the tiled solve's states
+};
 
 void add_sizes(const rexi_plan* pl, const Schedule& sc, Sizes& z) {
     z.part = std::max(z.part, sc.part_size);
-    if (!sc.sweep) return;
+    if (!sc.sweep) {
+        z.chains = true;
+        return;
+    }
     z.rec = std::max(z.rec, (long long)(pl->sweep[sc.split].npairs + 1) * sc.S * kSweepRec + kSweepPad);
     if (sc.sweep_stride == 0) return;
     const long long most = std::max(1LL, kSweepScratch / 16 / kSweepWaves / sc.sweep_stride);
@@ -632,12 +638,24 @@ void add_sizes(const rexi_plan* pl, const Schedule& sc, Sizes& z) {
     z.scratch = std::max(z.scratch, std::min(wgs, most) * kSweepWaves * sc.sweep_stride);
 }
 
+// The states in chain layout, with the first tiled schedule or per-term step: the
+// pole-per-lane schedules do not read them (64 states at T1023: 3.2 GB).
+int ensure_chains(rexi_plan* pl) {
+    int rc = REXI_OK;
+    for (int d = 0; d < 2 && !rc; ++d) {
+        if (!pl->d_ch_var[d]) rc = dev_alloc(&pl->d_ch_var[d], (size_t)pl->prm.max_states * (pl->nslots + 2));
+        if (!rc && !pl->d_ch_phi[d]) rc = dev_alloc(&pl->d_ch_phi[d], (size_t)pl->prm.max_states * pl->nspec);
+    }
+    return rc;
+}
+
 // Every step checks its schedule's sizes here: the buffers are shared by all
 // schedules, and a growth that failed may have left smaller ones.  Where memory is
 // short, fewer slots of scratch do (their workgroups take more items in turn); what
 // failed once is then tried again only by a call that selects a schedule (`retry`).
 int ensure_sizes(rexi_plan* pl, const Sizes& z, bool retry) {
-    int rc = grow(pl, &pl->d_part, &pl->part_capacity, z.part);
+    int rc = z.chains ? ensure_chains(pl) : REXI_OK;
+    if (!rc) rc = grow(pl, &pl->d_part, &pl->part_capacity, z.part);
     for (int d = 0; d < 2 && !rc; ++d) rc = grow(pl, &pl->d_rec[d], &pl->rec_capacity[d], z.rec);
     if (rc) return rc;
     if (!retry && pl->sweep_scratch_capacity >= z.slot && z.scratch >= pl->scratch_refused) return REXI_OK;
@@ -1156,10 +1174,6 @@ int create(const rexi_params* p, rexi_plan** out) {
     }
     if (!rc) rc = upload(&pl->sched_layout, lay);
     if (!rc) rc = upload(&pl->d_slot_m, slot_m);
-    for (int d = 0; d < 2 && !rc; ++d) {
-        rc = dev_alloc(&pl->d_ch_var[d], (size_t)p->max_states * (pl->nslots + 2));
-        if (!rc) rc = dev_alloc(&pl->d_ch_phi[d], (size_t)p->max_states * pl->nspec);
-    }
     if (!rc && p->fsphere) {
         pl->f0dt = p->f0 * p->dt;
         std::vector<std::complex<double>> fp;
@@ -1301,6 +1315,7 @@ int rexi_step_per_term(rexi_plan* plan, const void* u0, void* u1, int S, void* s
     hipStream_t s = (hipStream_t)stream;
     note_capture(plan, s);
     rc = grow(plan, &plan->d_acc, &plan->acc_capacity, sc.part_size);
+    if (!rc) rc = ensure_chains(plan);
     if (rc) return rc;
     const Workspace ws = plan_workspace(plan, sc);
     REXI_HIP(enqueue_prep(plan, ws, u0, 0, S, 0, plan->sched_layout, s));

@@ -669,6 +669,33 @@ int inverse_chunks() {
     return bad;
 }
 
+// The tiled solve's states are allocated where a tiled schedule or the per-term form
+// runs; the default's steps have their records alone.
+int chain_states() {
+    rexi_plan* pl = make_plan(100, 21, 64);
+    const size_t states = (size_t)64 * (pl->nslots + 2) * 16;
+    expect(used < states, "a plan without states");
+    expect(step(pl, 1) == REXI_OK && step(pl, 8) == REXI_OK, "steps");
+    for (const auto& a : live) expect(a.second != states, "no states of the tiled solve");
+    expect(rexi_step_noalloc(pl, kIn, kOut, 1, 1, nullptr) == REXI_OK, "a no-allocation step");
+    expect(rexi_step_per_term(pl, kIn, kOut, 2, nullptr) == REXI_OK, "a step in the per-term form");
+    destroy(pl);
+    rexi_params p = make_plan_params(26, 20, 4);
+    p.omega = 0;  // the default is a tiled schedule
+    expect(rexi_plan_create(&p, &pl) == REXI_OK, "a plan without rotation");
+    expect(step(pl, 2) == REXI_OK && step(pl, 4) == REXI_OK, "tiled steps");
+    destroy(pl);
+    for (bool term : {true, false})
+        fail_every("tiled states", 40, 21, [](rexi_plan* q) {
+            return rexi_plan_set_schedule(q, 2, 0, nullptr) ? -99 : step(q, 1);  // (0: a tiled one)
+        }, [term](rexi_plan* q) { return term ? rexi_step_per_term(q, kIn, kOut, 2, nullptr) : step(q, 2); });
+    fail_every("a tiled schedule", 40, 21, [](rexi_plan* q) { return step(q, 2); }, [](rexi_plan* q) {
+        const int rc = rexi_plan_set_schedule(q, 2, 0, nullptr);
+        return rc ? rc : step(q, 2);
+    });
+    return bad;
+}
+
 const std::map<std::string, int (*)()> kScenarios = {
     {"handled_failure", handled_failure},
     {"failed_growth", failed_growth},
@@ -681,6 +708,7 @@ const std::map<std::string, int (*)()> kScenarios = {
     {"noalloc_routes", noalloc_routes},
     {"few_poles", few_poles},
     {"inverse_chunks", inverse_chunks},
+    {"chain_states", chain_states},
 };
 
 }  // namespace
