@@ -1389,8 +1389,8 @@ int rexi_plan_autotune(rexi_plan* plan, int S, void* stream, int* chosen) try {
         (void)hipGetLastError();
         return hip_fail(e, "hipMalloc");
     }
-    int best = -1;
-    float best_ms = 0;
+    int fastest[2] = {-1, -1};  // of the ordinary and of the persistent schedules
+    float fastest_ms[2] = {0, 0};
     rc = REXI_OK;
     do {
         if ((e = hipMemsetAsync(u0, 0, bytes, s)) != hipSuccess) { rc = hip_fail(e, "hipMemsetAsync"); break; }
@@ -1410,14 +1410,18 @@ int rexi_plan_autotune(rexi_plan* plan, int S, void* stream, int* chosen) try {
             if ((e = hipEventSynchronize(b)) != hipSuccess) { rc = hip_fail(e, "hipEventSynchronize"); break; }
             float ms = 0;
             if ((e = hipEventElapsedTime(&ms, a, b)) != hipSuccess) { rc = hip_fail(e, "hipEventElapsedTime"); break; }
-            // a persistent schedule, which the no-allocation step refuses, only where it
-            // is clearly faster: timings one after another drift by 1 to 2% with the
-            // clock, and the pole-per-lane twins run the same code where they are large
-            const bool resident = best >= 0 && sc.persistent && !(*c)[best].persistent;
-            if (best < 0 || ms < best_ms * (resident ? 0.97f : 1.0f)) { best = i; best_ms = ms; }
+            const int k = sc.persistent;
+            if (fastest[k] < 0 || ms < fastest_ms[k]) {
+                fastest[k] = i;
+                fastest_ms[k] = ms;
+            }
         }
     } while (0);
     if (rc) return rc;
+    // a persistent schedule, which the no-allocation step refuses, only where it is
+    // clearly faster: timings one after another drift by 1 to 2% with the clock, and
+    // the pole-per-lane twins run the same code where they are large
+    const int best = fastest[0] < 0 || (fastest[1] >= 0 && fastest_ms[1] < 0.97f * fastest_ms[0]) ? fastest[1] : fastest[0];
     if (plan->chosen[S] != best) drop_graphs(plan);
     plan->chosen[S] = plan->own[S] = best;
     if (chosen) *chosen = best;

@@ -696,6 +696,40 @@ int chain_states() {
     return bad;
 }
 
+// The autotuner keeps a persistent schedule only where it is faster than every other by
+// more than 3%, whatever the order of the candidates.
+int autotune_margin() {
+    struct Case {
+        double first, second, ordinary;  // ms a step: the first and the last persistent candidate, an ordinary one between them
+        int want;
+    };
+    rexi_plan* pl = make_plan(26, 20, 4);
+    const int S = 2;
+    int n = 0, index = -1;
+    expect(rexi_plan_set_schedule(pl, S, -1, &n) == REXI_OK, "the schedules");
+    const std::vector<Schedule>& list = pl->sched[S];
+    int first = -1, second = -1, ordinary = -1;
+    for (int i = 0; i < n; ++i) {
+        if (list[i].persistent && first < 0) first = i;
+        if (list[i].persistent) second = i;
+        if (!list[i].persistent && first >= 0) ordinary = i;
+    }
+    expect(first >= 0 && first < ordinary && ordinary < second, "candidates of both kinds in turn");
+    for (const Case& c : {Case{0.99, 2, 1.00, ordinary}, Case{2, 0.99, 1.00, ordinary}, Case{0.95, 2, 1.00, first},
+                          Case{2, 0.95, 1.00, second}, Case{0.96, 0.95, 1.00, second}, Case{0.95, 0.96, 1.00, first},
+                          Case{1.50, 1.60, 1.00, ordinary}}) {
+        cost = [&](const Schedule& sc) {
+            const int i = (int)(&sc - list.data());
+            return i == first ? c.first : i == second ? c.second : i == ordinary ? c.ordinary : 3.0;
+        };
+        expect(rexi_plan_autotune(pl, S, nullptr, &index) == REXI_OK && index == c.want && pl->chosen[S] == c.want,
+               "candidate " + std::to_string(c.want) + ", got " + std::to_string(index));
+    }
+    cost = nullptr;
+    destroy(pl);
+    return bad;
+}
+
 const std::map<std::string, int (*)()> kScenarios = {
     {"handled_failure", handled_failure},
     {"failed_growth", failed_growth},
@@ -709,6 +743,7 @@ const std::map<std::string, int (*)()> kScenarios = {
     {"few_poles", few_poles},
     {"inverse_chunks", inverse_chunks},
     {"chain_states", chain_states},
+    {"autotune_margin", autotune_margin},
 };
 
 }  // namespace

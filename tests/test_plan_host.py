@@ -25,7 +25,8 @@ def plan_host(tmp_path_factory):
 @pytest.mark.parametrize("scenario", ["handled_failure", "failed_growth", "failed_tables", "shortage",
                                       "captured_buffers", "noalloc_untimed", "host_allocations",
                                       "noalloc_selection", "noalloc_routes",
-                                      "few_poles", "inverse_chunks", "chain_states"])
+                                      "few_poles", "inverse_chunks", "chain_states",
+                                      "autotune_margin"])
 def test_plan_host(plan_host, scenario):
     r = subprocess.run([plan_host, scenario], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, f"{scenario} exited with {r.returncode}:\n{r.stderr[-4000:]}"
