@@ -703,30 +703,29 @@ int autotune_margin() {
         double first, second, ordinary;  // ms a step: the first and the last persistent candidate, an ordinary one between them
         int want;
     };
-    rexi_plan* pl = make_plan(26, 20, 4);
     const int S = 2;
-    int n = 0, index = -1;
-    expect(rexi_plan_set_schedule(pl, S, -1, &n) == REXI_OK, "the schedules");
-    const std::vector<Schedule>& list = pl->sched[S];
-    int first = -1, second = -1, ordinary = -1;
-    for (int i = 0; i < n; ++i) {
-        if (list[i].persistent && first < 0) first = i;
-        if (list[i].persistent) second = i;
-        if (!list[i].persistent && first >= 0) ordinary = i;
-    }
-    expect(first >= 0 && first < ordinary && ordinary < second, "candidates of both kinds in turn");
-    for (const Case& c : {Case{0.99, 2, 1.00, ordinary}, Case{2, 0.99, 1.00, ordinary}, Case{0.95, 2, 1.00, first},
-                          Case{2, 0.95, 1.00, second}, Case{0.96, 0.95, 1.00, second}, Case{0.95, 0.96, 1.00, first},
-                          Case{1.50, 1.60, 1.00, ordinary}}) {
+    // (want: 0 the first, 1 the second, 2 the ordinary one)
+    for (const Case& c : {Case{0.99, 2, 1.00, 2}, Case{2, 0.99, 1.00, 2}, Case{0.95, 2, 1.00, 0}, Case{2, 0.95, 1.00, 1},
+                          Case{0.96, 0.95, 1.00, 1}, Case{0.95, 0.96, 1.00, 0}, Case{1.50, 1.60, 1.00, 2}}) {
+        rexi_plan* pl = make_plan(26, 20, 4);  // (a plan's graphs hold their times)
+        int n = 0, index = -1, at[3] = {-1, -1, -1};
+        expect(rexi_plan_set_schedule(pl, S, -1, &n) == REXI_OK, "the schedules");
+        const std::vector<Schedule>& list = pl->sched[S];
+        for (int i = 0; i < n; ++i) {
+            if (list[i].persistent && at[0] < 0) at[0] = i;
+            if (list[i].persistent) at[1] = i;
+            else if (at[0] >= 0) at[2] = i;
+        }
+        expect(at[0] >= 0 && at[0] < at[2] && at[2] < at[1], "candidates of both kinds in turn");
         cost = [&](const Schedule& sc) {
             const int i = (int)(&sc - list.data());
-            return i == first ? c.first : i == second ? c.second : i == ordinary ? c.ordinary : 3.0;
+            return i == at[0] ? c.first : i == at[1] ? c.second : i == at[2] ? c.ordinary : 3.0;
         };
-        expect(rexi_plan_autotune(pl, S, nullptr, &index) == REXI_OK && index == c.want && pl->chosen[S] == c.want,
-               "candidate " + std::to_string(c.want) + ", got " + std::to_string(index));
+        expect(rexi_plan_autotune(pl, S, nullptr, &index) == REXI_OK && index == at[c.want] && pl->chosen[S] == index,
+               "candidate " + std::to_string(at[c.want]) + ", got " + std::to_string(index));
+        cost = nullptr;
+        destroy(pl);
     }
-    cost = nullptr;
-    destroy(pl);
     return bad;
 }
 
