@@ -42,9 +42,10 @@ Poles make_poles(int M, double h, int L, int normalize);
 // Gauss-Legendre nodes (descending, north to south) and weights.
 void gauss_legendre(int nlat, std::vector<double>& mu, std::vector<double>& w);
 
-// Recurrence coefficients (a_n, b_n) of the orthonormal P_n^m, [nspec][2], and
-// exact restart rows (P_{n0-1}, P_{n0}) at n0 = m + run r, [row][2][nmu] with
-// row = run_base[m] + r (run_base has T + 2 entries).
+// Orthonormal P_n^m = s_n Q_n with Q_n = c_n mu Q_{n-1} - Q_{n-2}: c_n and s_n in
+// spectral order, [nspec] each, and exact restart rows (Q_{n0-1}, Q_{n0}) at n0 = m +
+// run r, [row][2][nmu] with row = run_base[m] + r (run_base has T + 2 entries); tail:
+// the same at the parts of an order's last segment (see tables.cpp).
 void legendre_coefs(int T, std::vector<double>& coef, std::vector<double>& scale);
 std::vector<double> legendre_restarts(int T, int run, int seg, const std::vector<double>& mu,
                                       std::vector<int>& run_base, std::vector<double>& tail);
@@ -150,7 +151,7 @@ struct SweepItem {                // a wave's work: pairs of one chain, states [
     int pair0, npair;
     int pstride;                  // pairs of the whole chain (a split chain: both halves and the middle)
     int s0, nst, k0, k1;
-    int mid, half, pad;           // a half of a split chain: its middle pair and which half, else mid = -1
+    int mid, half;                // a half of a split chain: its middle pair and which half, else mid = -1
     long long part_off;           // doubles; layout [nst][pstride][kSweepRec], from this item's first pair
     long long mid_off;            // the same from the middle pair
 };
@@ -207,7 +208,7 @@ struct Schedule {
     bool split = false;                   // long chains split between two waves
     bool short_chains = false;            // every part of a chain in registers
     int sweep_nst = 0, sweep_ntiles = 0;  // most states of an item, state tiles
-    long long sweep_stride = 0;           // scratch of one workgroup (double2)
+    long long sweep_stride = 0;           // scratch of one wave (double2)
     std::vector<SweepItem> sweep_items;
     std::vector<SweepTile> sweep_tiles;
     std::vector<SweepGroup> sweep_groups;

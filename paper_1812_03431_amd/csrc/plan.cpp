@@ -520,7 +520,7 @@ int build_sweep_schedule(rexi_plan* pl, int S, int most, long long target_items,
             int nr = 0;
             for (int b = 0; b < nb; b += per) {
                 const int b1 = std::min(nb, b + per), k0 = 64 * b, k1 = std::min(pl->N, 64 * b1);
-                Unit x{u * (b1 - b), {c.pair0, c.npair, c.npair, s0[k], nst, k0, k1, -1, 0, 0, off, 0}, {}, two};
+                Unit x{u * (b1 - b), {c.pair0, c.npair, c.npair, s0[k], nst, k0, k1, -1, 0, off, 0}, {}, two};
                 if (two) {
                     x.a.npair = half.x;
                     x.a.mid = c.pair0 + half.x;
@@ -570,7 +570,7 @@ void free_schedule(Schedule& s) {
 }
 
 // Each graph is destroyed only after its last launch has completed (its
-// buffers may be freed or reused right after: ensure_part, schedule and
+// buffers may be freed or reused right after: grow, schedule and
 // stream changes).
 void drop_graphs(rexi_plan* pl) {
     for (auto& g : pl->graphs) {

@@ -4,11 +4,11 @@
 // Synthesis: xi(mu_j, lam_k) = sum_m c_m Re( sum_n xi_n^m P_n^m(mu_j) e^{i m lam_k} ), c_0 = 1, c_m = 2
 // (the m = 0 term uses Re(xi_n^0)).
 //
-// Longitude: one workgroup per pair of grid rows j, j' = nlat-1-j runs one
-// complex FFT of length nlon in registers for both rows.  Latitude: per
-// zonal order m the Legendre sum is a small dense contraction (T+1-m degrees
-// x nlat/2 latitudes x 2B real columns) and runs on FP64 MFMA
-// (v_mfma_f64_16x16x4f64).  Gauss latitudes are symmetric about the equator
+// Longitude: one complex FFT of length nlon in registers per field and pair of
+// grid rows j, j' = nlat-1-j, a workgroup taking the pair's FFTs of several
+// fields.  Latitude: per zonal order m the Legendre sum is a small dense
+// contraction (T+1-m degrees x nlat/2 latitudes x 2B real columns) and runs on
+// FP64 MFMA (v_mfma_f64_4x4x4f64, four blocks).  Gauss latitudes are symmetric about the equator
 // and P_n^m(-mu) = (-1)^{n-m} P_n^m(mu), so only northern latitudes are used
 // and each sum splits into an even part (F_j + F_{j'}) and an odd part
 // (F_j - F_{j'}).
@@ -27,9 +27,6 @@
 
 namespace rexi {
 namespace {
-
-typedef double v4d __attribute__((ext_vector_type(4)));
-
 
 // Plane strides of the Fourier workspace, in doubles: an EO plane [j][c] of one
 // (order, parity) and an order's plane [row][c] are padded by kFourPad so that
@@ -527,7 +524,9 @@ __global__ void __launch_bounds__(256) k_legendre_forward(const LegRun* __restri
 // (one 16-byte LDS read), 8 (NG / 2) + p of a last single group.  Result D[q][p] of
 // lane 16 q + 4 b + p is latitude 4 b + q and that column.
 // The parts are staged kInvPad doubles (and two coefficients) apart, so that the
-// four a wave reads at once lie in different banks.  Degrees past the segment need
+// four a wave reads at once lie in different banks (the stores that stage a segment
+// do meet: with eight groups all degrees of a wave's store lie in one bank, with two
+// in four; 3.0e7 conflict cycles a launch at T1023, 16 fields).  Degrees past the segment need
 // no checks: their staged columns are zero.
 //
 // Bound by the FP64 rate, which matrix and vector instructions share (the 4x4x4
@@ -677,12 +676,6 @@ __global__ void __launch_bounds__(256) k_legendre_inverse(const LegWork* __restr
         }
     }
 }
-
-// Vector transforms (Eq. (1): V = k x grad(psi) + grad(chi), lap psi = zeta,
-// lap chi = delta; Section 3's scaled winds U = u cos(lat), V = v cos(lat)).
-// On degree n, lap = -n(n+1)/a^2, and with eps_n = sqrt((n^2 - m^2)/(4n^2 - 1))
-// the latitude derivative of the orthonormal P_n^m obeys
-//   (1 - mu^2) dP_n^m/dmu = (n + 1) eps_n P_{n-1}^m - n eps_{n+1} P_{n+1}^m,
 
 // Vector transforms (Eq. (1): V = k x grad(psi) + grad(chi), lap psi = zeta,
 // lap chi = delta; Section 3's scaled winds U = u cos(lat), V = v cos(lat)).

@@ -51,7 +51,7 @@
 //
 // A step, with the tiled schedules and the partial sums' reduction before / with one
 // pole per lane: T256, 2071 poles, four states 2468 / 1537 us; T301, 1245 poles, three
-// states 2457 / 983; T128, 535 poles, eight states 341 / 228; T128, 407 poles, one
+// states 2457 / 969; T128, 535 poles, eight states 341 / 228; T128, 407 poles, one
 // state 80 / 47; T63, 151 poles, one state 37 / 13 in a run of 24.
 #include <hip/hip_runtime.h>
 
@@ -771,8 +771,8 @@ k_sweep(const SweepArgs A, int* counter) {
         if (i * kSweepWaves + wave < A.nitems) {
             typedef const SweepItem __attribute__((address_space(4)))* iptr;
             const iptr p = (iptr)(unsigned long long)(A.items + (i * kSweepWaves + wave));
-            const SweepItem it{p->pair0, p->npair, p->pstride, p->s0, p->nst, p->k0, p->k1, p->mid, p->half, p->pad,
-                               p->part_off, p->mid_off};
+            const SweepItem it{p->pair0, p->npair, p->pstride, p->s0, p->nst, p->k0, p->k1, p->mid, p->half, p->part_off,
+                               p->mid_off};
             sweep_wave<SPLIT, ONE>(A, it, scr, red, car, lds_q, wave, lane, car_stride);
         } else if (SPLIT) {  // the barriers of meet
             __syncthreads();
@@ -971,8 +971,8 @@ k_sweep_short(const SweepArgs A, int* counter) {
         if (i * kSweepWaves + wave < A.nitems) {
             typedef const SweepItem __attribute__((address_space(4)))* iptr;
             const iptr p = (iptr)(unsigned long long)(A.items + (i * kSweepWaves + wave));
-            const SweepItem it{p->pair0, p->npair, p->pstride, p->s0, p->nst, p->k0, p->k1, p->mid, p->half, p->pad,
-                               p->part_off, p->mid_off};
+            const SweepItem it{p->pair0, p->npair, p->pstride, p->s0, p->nst, p->k0, p->k1, p->mid, p->half, p->part_off,
+                               p->mid_off};
             short_item(A, it, red, lds, wave, lane);
         } else {
             for (int s = 0; s < A.nst; ++s) __syncthreads();
