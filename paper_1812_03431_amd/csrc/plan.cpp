@@ -40,13 +40,14 @@ int hip_fail(hipError_t e, const char* what) {
 
 hipError_t timed_begin(rexi_plan* pl, int kind, hipStream_t s) {
     if (!pl->timing) return hipSuccess;
-    pl->events[kind].reserve(pl->events[kind].size() + 1);
+    auto& v = pl->events[kind];
+    if (v.size() == v.capacity()) v.reserve(2 * v.size() + 16);  // before the events, which a throw would leak
     hipEvent_t a = nullptr, b = nullptr;
     hipError_t e = hipEventCreate(&a);
     if (e != hipSuccess) return e;
     e = hipEventCreate(&b);
     if (e != hipSuccess) { (void)hipEventDestroy(a); return e; }
-    pl->events[kind].push_back({a, b});
+    v.push_back({a, b});
     return hipEventRecord(a, s);
 }
 
